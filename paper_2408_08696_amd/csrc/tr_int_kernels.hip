@@ -96,17 +96,24 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const T *__restrict__ log
   }
 }
 
-// Two-stage variant for k <= 8, without workgroup barriers.  An element becomes one 64-bit key whose
-// unsigned order is the total order of k_topk: the float mapped to an order-preserving unsigned (with
-// -0 folded onto +0) in the high word, the complemented index in the low word; key 0 is "nothing".
-// Stage 1: every wave owns TOPK_WAVE_ELEMS consecutive elements of a row, each lane holds 16 of them in
-// registers together with their maximum, and k rounds of "wave-wide maximum, the owning lane drops it and
-// recomputes its own" write the wave's k best keys.  Stage 2, one wave per row, merges the candidates of
-// all waves of the row the same way (up to 16 per lane).
-constexpr int TOPK_EPL = 16;                     // elements per lane
-constexpr int TOPK_WAVE_ELEMS = 64 * TOPK_EPL;   // elements per stage-1 wave
-constexpr int TOPK1_THREADS = 256;
-constexpr int TOPK_MAX_WAVES_PER_ROW = 128;      // stage 2 holds 8 candidates per wave, 16 per lane
+// Threshold variant for k <= TOPK_WAVES.  A workgroup of 16 waves holds one segment (up to TOPK_SEG elements, the whole
+// row for most vocabularies) in registers.  The k-th largest of the 16 wave maxima is a value that at least k elements
+// reach, so the segment's k best are all among the elements not below it - a dozen or two on ordinary logits.  Those go
+// to LDS as 64-bit keys whose unsigned order is the total order of k_topk (the float mapped to an order-preserving
+// unsigned, with -0 folded onto +0, in the high word; the complemented index in the low word; key 0 is "nothing"), and
+// each finds its place by counting the keys above it.  Per element that is one load, one maximum and no 64-bit
+// arithmetic.  Rows whose ties put more than TOPK_LIST elements at or above the threshold are selected by k exact
+// passes over the registers instead.  A row of several segments leaves k keys per segment to k_topk_merge.
+// What bounds it: latency (launch, one load round trip, three barriers).  80 rows of 32000 bf16 logits took 12.4 + 5.8 us
+// as "every wave selects its own k best by k rounds of 64-bit maxima, a second kernel merges 32 waves per row" (the
+// rounds are ~900 clocks of vector ALU each).
+constexpr int TOPK_WAVES = 16;
+constexpr int TOPK_SEL_THREADS = TOPK_WAVES * 64;
+constexpr int TOPK_EPT = 32;                             // elements a thread holds
+constexpr int TOPK_SEG = TOPK_SEL_THREADS * TOPK_EPT;
+constexpr int TOPK_LIST = 1024;                          // candidates kept in LDS
+constexpr int TOPK_MAX_SEGS = 64;
+constexpr int TOPK_ROW_SLOTS = TOPK_MAX_SEGS * TOPK_WAVES; // scratch keys per row
 
 __device__ inline uint64_t topk_key(float v, int32_t idx) {
   uint32_t u = __float_as_uint(v + 0.0f); // -0 + 0 = +0
@@ -117,98 +124,173 @@ __device__ inline uint64_t topk_key(float v, int32_t idx) {
 // mirror inside 8 lanes, mirror inside the row of 16) leave every lane with its row's maximum, and the
 // four row maxima are read out as scalars.  All 64 lanes must be active.
 template <int CTRL>
-__device__ inline uint64_t dpp_u64(uint64_t x) {
-  const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-  const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, 0xF, 0xF, false);
-  const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, CTRL, 0xF, 0xF, false);
-  return ((uint64_t)h2 << 32) | l2;
+__device__ inline float dpp_f32(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
-__device__ inline uint64_t readlane_u64(uint64_t x, int lane) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
-  return ((uint64_t)hi << 32) | lo;
+__device__ inline float wave_max_f32(float x) {
+  x = fmaxf(x, dpp_f32<0xB1>(x));  // quad_perm [1,0,3,2]
+  x = fmaxf(x, dpp_f32<0x4E>(x));  // quad_perm [2,3,0,1]
+  x = fmaxf(x, dpp_f32<0x141>(x)); // row_half_mirror
+  x = fmaxf(x, dpp_f32<0x140>(x)); // row_mirror
+  auto lane = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
+  return fmaxf(fmaxf(lane(0), lane(16)), fmaxf(lane(32), lane(48)));
 }
-__device__ inline uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
-__device__ inline uint64_t wave_max_u64(uint64_t x) {
-  x = max_u64(x, dpp_u64<0xB1>(x));  // quad_perm [1,0,3,2]
-  x = max_u64(x, dpp_u64<0x4E>(x));  // quad_perm [2,3,0,1]
-  x = max_u64(x, dpp_u64<0x141>(x)); // row_half_mirror
-  x = max_u64(x, dpp_u64<0x140>(x)); // row_mirror
-  return max_u64(max_u64(readlane_u64(x, 0), readlane_u64(x, 16)), max_u64(readlane_u64(x, 32), readlane_u64(x, 48)));
-}
-// k rounds of maximum-with-replacement over the keys every lane holds; lane 0 writes the winners
-__device__ inline void wave_select(uint64_t (&key)[TOPK_EPL], int32_t k, uint64_t *__restrict__ out) {
-  uint64_t m = 0;
+
+// VEC: 16-byte loads (base and row pitch 16-byte aligned, at least one full vector per thread of the workgroup, so
+// that every wave has elements); otherwise one element per load.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__restrict__ logits, int32_t V, int32_t k,
+                                                                  int32_t seg_len, int32_t *__restrict__ out,
+                                                                  uint64_t *__restrict__ cand) {
+  constexpr int E = VEC ? 16 / (int)sizeof(T) : 1; // elements per load
+  __shared__ float wmax[TOPK_WAVES];
+  __shared__ uint64_t list[TOPK_LIST];
+  __shared__ uint64_t wbest[TOPK_WAVES];
+  __shared__ int32_t count;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blockIdx.y, seg = blockIdx.x, lo = seg * seg_len;
+  const int cnt = V - lo < seg_len ? V - lo : seg_len;
+  const T *src = logits + (size_t)row * V + lo;
+  auto index_of = [&](int i) { return ((i / E) * TOPK_SEL_THREADS + tid) * E + i % E; }; // of register i, in the segment
+  float v[TOPK_EPT];
 #pragma unroll
-  for (int b = 0; b < TOPK_EPL; ++b) m = key[b] > m ? key[b] : m;
-  for (int p = 0; p < k; ++p) {
-    const uint64_t best = wave_max_u64(m);
-    if ((threadIdx.x & 63) == 0) out[p] = best;
-    if (m == best && best != 0) { // keys are unique (the index is part of them): one lane owns the winner
-      m = 0;
+  for (int c = 0; c < TOPK_EPT / E; ++c) {
+    const int j = (c * TOPK_SEL_THREADS + tid) * E;
+    if constexpr (VEC) {
+      uint4 w = uint4{0u, 0u, 0u, 0u};
+      const bool on = j < cnt; // a vector is inside or outside as a whole (V and seg_len are multiples of E)
+      if (on) w = *reinterpret_cast<const uint4 *>(src + j);
+      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-      for (int b = 0; b < TOPK_EPL; ++b) {
-        if (key[b] == best) key[b] = 0;
-        m = key[b] > m ? key[b] : m;
+      for (int e = 0; e < E; ++e) {
+        const float x = sizeof(T) == 2 ? bf16_to_f32((bf16_t)(ww[e / 2] >> (16 * (e & 1)))) : __uint_as_float(ww[e % 4]);
+        v[c * E + e] = on ? x : -__builtin_inff();
+      }
+    } else {
+      v[c] = j < cnt ? to_f32<T>(src[j]) : -__builtin_inff();
+    }
+  }
+  if (tid == 0) count = 0;
+  float m = v[0];
+#pragma unroll
+  for (int i = 1; i < TOPK_EPT; ++i) m = fmaxf(m, v[i]);
+  const float wm = wave_max_f32(m);
+  if (lane == 0) wmax[wave] = wm;
+  __syncthreads();
+  // threshold: the wave maximum of rank k - 1 (waves without elements count as -inf, which admits every element)
+  float thr;
+  {
+    const float mine = wmax[lane & (TOPK_WAVES - 1)];
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < TOPK_WAVES; ++j) {
+      const float o = wmax[j];
+      rank += (o > mine || (o == mine && j < (lane & (TOPK_WAVES - 1)))) ? 1 : 0;
+    }
+    const uint64_t at = __ballot(rank == k - 1);
+    thr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_ctzll(at)));
+  }
+  if (m >= thr) {
+#pragma unroll
+    for (int i = 0; i < TOPK_EPT; ++i) {
+      const int j = index_of(i);
+      if (v[i] >= thr && j < cnt) {
+        const int p = atomicAdd(&count, 1);
+        if (p < TOPK_LIST) list[p] = topk_key(v[i], lo + j);
       }
     }
+  }
+  __syncthreads();
+  const int n = count;
+  auto emit = [&](int rank, uint64_t key) {
+    if (cand != nullptr) cand[((size_t)row * gridDim.x + seg) * k + rank] = key;
+    else out[(size_t)row * k + rank] = (int32_t)~(uint32_t)key;
+  };
+  if (cand != nullptr && tid >= cnt && tid < k) emit(tid, 0); // a last segment shorter than k
+  if (n <= TOPK_LIST) {
+    if (tid < n) {
+      const uint64_t key = list[tid];
+      int rank = 0;
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) rank += list[j] > key ? 1 : 0; // keys are unique: the index is part of them
+      if (rank < k) emit(rank, key);
+    }
+    return;
+  }
+  uint64_t prev = ~0ull; // n is uniform over the workgroup
+  for (int p = 0; p < k; ++p) {
+    uint64_t best = 0;
+#pragma unroll
+    for (int i = 0; i < TOPK_EPT; ++i) {
+      const int j = index_of(i);
+      const uint64_t key = j < cnt ? topk_key(v[i], lo + j) : 0;
+      if (key < prev && key > best) best = key;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      const uint64_t o = __shfl_xor(best, off);
+      best = o > best ? o : best;
+    }
+    if (lane == 0) wbest[wave] = best;
+    __syncthreads();
+    best = wbest[0];
+    for (int w = 1; w < TOPK_WAVES; ++w) best = wbest[w] > best ? wbest[w] : best;
+    if (tid == 0) emit(p, best);
+    prev = best;
+    __syncthreads();
+  }
+}
+
+// one workgroup per row: the k best of n_cand keys by counting the keys above each
+__global__ __launch_bounds__(256) void k_topk_merge(const uint64_t *__restrict__ cand, int32_t n_cand, int32_t k,
+                                                    int32_t *__restrict__ out) {
+  __shared__ uint64_t list[TOPK_ROW_SLOTS];
+  const int row = blockIdx.x;
+  for (int c = threadIdx.x; c < n_cand; c += 256) list[c] = cand[(size_t)row * n_cand + c];
+  __syncthreads();
+  for (int c = threadIdx.x; c < n_cand; c += 256) {
+    const uint64_t key = list[c];
+    if (key == 0) continue;
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < n_cand; ++j) rank += list[j] > key ? 1 : 0;
+    if (rank < k) out[(size_t)row * k + rank] = (int32_t)~(uint32_t)key;
   }
 }
 
 template <typename T>
-__global__ __launch_bounds__(TOPK1_THREADS) void k_topk_stage1(const T *__restrict__ logits, int32_t V, int32_t k,
-                                                                int32_t waves_per_row, uint64_t *__restrict__ cand) {
-  const int rowi = blockIdx.y, lane = threadIdx.x & 63;
-  const int w = blockIdx.x * (TOPK1_THREADS / 64) + (threadIdx.x >> 6); // wave index inside the row
-  if (w >= waves_per_row) return;
-  const T *row = logits + (size_t)rowi * V;
-  const int lo = w * TOPK_WAVE_ELEMS;
-  uint64_t key[TOPK_EPL];
-#pragma unroll
-  for (int b = 0; b < TOPK_EPL; ++b) {
-    const int j = lo + b * 64 + lane;
-    key[b] = j < V ? topk_key(to_f32<T>(row[j]), j) : 0;
-  }
-  wave_select(key, k, cand + ((size_t)rowi * waves_per_row + w) * 8);
-}
-
-__global__ __launch_bounds__(64) void k_topk_stage2(const uint64_t *__restrict__ cand, int32_t k, int32_t waves_per_row,
-                                                    int32_t *__restrict__ out) {
-  const int rowi = blockIdx.x, lane = threadIdx.x;
-  const int n_cand = waves_per_row * 8; // slot c: wave c / 8, rank c % 8; ranks >= k were not written
-  uint64_t key[TOPK_EPL];
-#pragma unroll
-  for (int b = 0; b < TOPK_EPL; ++b) {
-    const int c = b * 64 + lane;
-    key[b] = (c < n_cand && (c & 7) < k) ? cand[(size_t)rowi * n_cand + c] : 0;
-  }
-  __shared__ uint64_t win[8];
-  wave_select(key, k, win);
-  __syncthreads();
-  if (lane < k) out[(size_t)rowi * k + lane] = (int32_t)~(uint32_t)win[lane];
+static hipError_t topk_select(const T *logits, int32_t rows, int32_t V, int32_t k, int32_t segs, int32_t *out,
+                              uint64_t *cand, KernelTimer tm, hipStream_t st) {
+  constexpr int E = 16 / (int)sizeof(T);
+  const int seg_len = segs == 1 ? V : ((V + segs - 1) / segs + 7) / 8 * 8; // <= TOPK_SEG, which is a multiple of 8
+  // vectors only where each thread gets one: on shorter rows they would leave waves empty and with them no threshold
+  if (V % E == 0 && (uintptr_t)logits % 16 == 0 && seg_len >= TOPK_SEL_THREADS * E)
+    return launch(k_topk_select<T, true>, dim3(segs, rows), dim3(TOPK_SEL_THREADS), 0, st, tm, logits, V, k, seg_len, out,
+                  cand);
+  return launch(k_topk_select<T, false>, dim3(segs, rows), dim3(TOPK_SEL_THREADS), 0, st, tm, logits, V, k, seg_len, out,
+                cand);
 }
 
 hipError_t launch_topk(const void *logits, int32_t dtype, int32_t rows, int32_t V, int32_t k, int32_t *d_topk,
                        void *d_cand, Profiler *prof, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   const size_t esz = dtype_size(dtype);
-  const int wpr = (V + TOPK_WAVE_ELEMS - 1) / TOPK_WAVE_ELEMS;
-  if (k <= 8 && V >= 8 && wpr <= TOPK_MAX_WAVES_PER_ROW && d_cand != nullptr) {
-    const int wg_per_row = (wpr + TOPK1_THREADS / 64 - 1) / (TOPK1_THREADS / 64);
-    for (int r0 = 0; r0 < rows; r0 += TR_MAX_NODES) { // the candidate scratch holds TR_MAX_NODES rows
-      const int nr = rows - r0 < TR_MAX_NODES ? rows - r0 : TR_MAX_NODES;
+  const int segs = (V + TOPK_SEG - 1) / TOPK_SEG;
+  if (k <= TOPK_WAVES && segs <= TOPK_MAX_SEGS && (segs == 1 || d_cand != nullptr)) {
+    const int step = segs == 1 ? 65535 : TR_MAX_NODES; // the candidate scratch holds TR_MAX_NODES rows
+    for (int r0 = 0; r0 < rows; r0 += step) {
+      const int nr = rows - r0 < step ? rows - r0 : step;
       const char *src = (const char *)logits + (size_t)r0 * V * esz;
-      hipError_t e;
-      if (dtype == TR_BF16)
-        e = launch(k_topk_stage1<bf16_t>, dim3(wg_per_row, nr), dim3(TOPK1_THREADS), 0, st, prof_next(prof, PC_TOPK),
-                   (const bf16_t *)src, V, k, wpr, (uint64_t *)d_cand);
-      else
-        e = launch(k_topk_stage1<float>, dim3(wg_per_row, nr), dim3(TOPK1_THREADS), 0, st, prof_next(prof, PC_TOPK),
-                   (const float *)src, V, k, wpr, (uint64_t *)d_cand);
+      int32_t *dst = d_topk + (size_t)r0 * k;
+      uint64_t *cand = segs == 1 ? nullptr : (uint64_t *)d_cand;
+      const KernelTimer tm = prof_next(prof, PC_TOPK);
+      hipError_t e = dtype == TR_BF16 ? topk_select<bf16_t>((const bf16_t *)src, nr, V, k, segs, dst, cand, tm, st)
+                                      : topk_select<float>((const float *)src, nr, V, k, segs, dst, cand, tm, st);
       if (e != hipSuccess) return e;
-      e = launch(k_topk_stage2, dim3(nr), dim3(64), 0, st, prof_next(prof, PC_TOPK_MERGE), (const uint64_t *)d_cand, k,
-                 wpr, d_topk + (size_t)r0 * k);
-      if (e != hipSuccess) return e;
+      if (segs > 1) {
+        e = launch(k_topk_merge, dim3(nr), dim3(256), 0, st, prof_next(prof, PC_TOPK_MERGE), (const uint64_t *)d_cand,
+                   segs * k, k, dst);
+        if (e != hipSuccess) return e;
+      }
     }
     return hipSuccess;
   }
@@ -219,15 +301,16 @@ hipError_t launch_topk(const void *logits, int32_t dtype, int32_t rows, int32_t 
                 k, d_topk);
 }
 
-size_t topk_scratch_bytes() { return (size_t)TR_MAX_NODES * TOPK_MAX_WAVES_PER_ROW * 8 * sizeof(uint64_t); }
+size_t topk_scratch_bytes() { return (size_t)TR_MAX_NODES * TOPK_ROW_SLOTS * sizeof(uint64_t); }
 
 // ---------------------------------------------------------------------------------------------
-// argtopk without any allocation: the candidate scratch of the two-stage kernels is a file-scope device
+// argtopk without any allocation: the candidate scratch of rows of several segments is a file-scope device
 // array (one copy per GPU, held until the process ends) instead of memory a context allocated.  In host
 // code the array's name is only a stand-in: the address the kernels get comes from hipGetSymbolAddress,
 // asked once per device with that device current.
 // ---------------------------------------------------------------------------------------------
-constexpr size_t TOPK_STATIC_BYTES = (size_t)TR_MAX_NODES * TOPK_MAX_WAVES_PER_ROW * 8 * sizeof(uint64_t); // 1 MiB
+constexpr size_t TOPK_STATIC_BYTES = (size_t)TR_MAX_NODES * TOPK_ROW_SLOTS * sizeof(uint64_t); // 1 MiB
+constexpr int TOPK_STATIC_MAX_V = 131072;
 static __device__ __align__(256) unsigned char scratch[TOPK_STATIC_BYTES];
 
 constexpr int MAX_DEVICES = 64;
@@ -257,8 +340,7 @@ static void *static_scratch(hipError_t *err) {
 }
 
 bool topk_static_fits(int32_t rows, int32_t V, int32_t k) {
-  const int wpr = (V + TOPK_WAVE_ELEMS - 1) / TOPK_WAVE_ELEMS;
-  return rows >= 0 && rows <= TR_MAX_NODES && V >= 8 && wpr <= TOPK_MAX_WAVES_PER_ROW && k >= 1 && k <= 8;
+  return rows >= 0 && rows <= TR_MAX_NODES && V >= 8 && V <= TOPK_STATIC_MAX_V && k >= 1 && k <= 8;
 }
 
 hipError_t launch_topk_static(const void *logits, int32_t dtype, int32_t rows, int32_t V, int32_t k, int32_t *d_topk,
@@ -267,8 +349,8 @@ hipError_t launch_topk_static(const void *logits, int32_t dtype, int32_t rows, i
   hipError_t e = hipSuccess;
   void *cand = static_scratch(&e);
   if (cand == nullptr) return e;
-  // every candidate slot stage 2 reads is written by stage 1 of the same call, so nothing of the
-  // previous call's contents needs clearing
+  // every candidate slot the merge reads is written by the same call, so nothing of the previous call's
+  // contents needs clearing
   return launch_topk(logits, dtype, rows, V, k, d_topk, cand, nullptr, st);
 }
 

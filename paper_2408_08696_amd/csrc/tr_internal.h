@@ -140,7 +140,7 @@ struct tr_ctx {
   tr::TreeDev chain;     // chain of TR_MAX_NODES nodes (prefill chunks)
   void *d_tree_blob;     // backing store of both trees
   int32_t *d_step_L;     // committed length at the start of the current accept/update
-  void *d_topk_cand;     // per-segment top-k candidates (two-stage top-k)
+  void *d_topk_cand;     // top-k candidates of rows longer than one segment
   int32_t update_mode;   // tr_update_mode bits
   tr::Profiler prof;
 };
@@ -149,11 +149,11 @@ namespace tr {
 
 // --- integer kernels (tr_int_kernels.hip) -------------------------------------------------------
 hipError_t launch_build_tree(tr_ctx *c, const int32_t *d_root, int32_t *d_S, hipStream_t s);
-// d_cand: scratch of topk_scratch_bytes() owned by the context (may be NULL: slower one-kernel path)
+// d_cand: scratch of topk_scratch_bytes() owned by the context, for rows longer than one segment (NULL: slower kernel)
 hipError_t launch_topk(const void *logits, int32_t dtype, int32_t rows, int32_t V, int32_t k,
                        int32_t *d_topk, void *d_cand, Profiler *prof, hipStream_t s);
 size_t topk_scratch_bytes();
-// the same two-stage kernels on the library's static device scratch (no allocation anywhere)
+// the same kernels on the library's static device scratch (no allocation anywhere)
 bool topk_static_fits(int32_t rows, int32_t V, int32_t k);
 hipError_t launch_topk_static(const void *logits, int32_t dtype, int32_t rows, int32_t V, int32_t k,
                               int32_t *d_topk, hipStream_t s);

@@ -111,6 +111,31 @@ def test_topk_vocabulary_edges(V):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V,k", [(449, 8), (4095, 8), (4096, 8), (8191, 16), (8192, 16), (8200, 1), (20003, 17),
+                                 (32767, 8), (32768, 9), (32769, 8), (65536, 16), (65544, 8), (98312, 8)])
+def test_topk_segment_edges(dtype, V, k):
+    """Rows around the selection kernel's units: 16 waves with and without elements, the first row lengths taken with
+    16-byte loads, one segment against several, a last segment that is shorter than the others, the largest k it takes
+    and the one beyond; more ties at the threshold than its list holds, and a row that does not start on 16 bytes."""
+    require_gpu()
+    rows = 3
+    x = synth.normal_tensor((rows, V), 3.0, seed=V, dtype=dtype)
+    x[1, :] = x[1].max()                        # every element ties
+    x[2, V // 3:V // 3 + 1100] = x[2].max() + 1  # more than the candidate list, inside one or two segments
+    ctx = _ctx(synth.single(), V, k)
+    say("topk segments", dtype, V, k)
+    for shift in (0, 1):
+        buf = torch.zeros(rows * V + 8, dtype=dtype, device="cuda")
+        buf[shift:shift + rows * V] = x.reshape(-1).cuda()
+        d_topk = torch.full((rows, k), -1, dtype=torch.int32, device="cuda")
+        ctx.op_topk(buf[shift:shift + rows * V].view(rows, V), d_topk)
+        got = d_topk.cpu().numpy()
+        for r in range(rows):
+            assert got[r].tolist() == O.topk_ids(x[r].float().numpy(), k).tolist(), (V, k, shift, r)
+    ctx.close()
+
+
 @pytest.mark.parametrize("name", ["tree80", "wide128", "tree15"])
 def test_matrix_update_last_wins(name):
     require_gpu()
