@@ -19,18 +19,16 @@ static bool packed_supported(const tr_model &m);
 
 Workspace plan_workspace(const tr_model &m) {
   Workspace w;
-  const bool generic = !packed_supported(m); // the packed path keeps neither raw Q/K/V nor gate/up outputs
+  const bool generic = !packed_supported(m);
   const size_t esz = dtype_size(m.dtype);
-  const size_t hq = (size_t)m.n_heads * m.head_dim, hk = (size_t)m.n_kv_heads * m.head_dim;
+  const size_t hq = (size_t)m.n_heads * m.head_dim;
   const size_t R = generic ? NP : NPW; // rows of the activation buffers
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
   w.x = take(R * m.d_model * 4);
   w.xn = take(R * m.d_model * esz);
-  w.qkv = take(generic ? (size_t)NP * (hq + 2 * hk) * 4 : 0);
   w.q = take(R * hq * esz);
   w.attn = take(R * hq * esz);
-  w.gu = take(generic ? (size_t)NP * 2 * m.d_ffn * 4 : 0);
   w.h = take(R * m.d_ffn * esz);
   w.rope = take(R * m.head_dim * 4);
   w.logits = take((size_t)NP * m.vocab * 4);
@@ -70,152 +68,12 @@ __global__ __launch_bounds__(256) void k_embed_rope(const T *__restrict__ E, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// RMSNorm: out[n,:] = T(x[n,:] * rsqrt(mean(x^2) + eps) * g)
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_rmsnorm(const float *__restrict__ x, const T *__restrict__ g, int32_t d,
-                                                 float eps, T *__restrict__ out) {
-  __shared__ float red[4];
-  const int n = blockIdx.x;
-  const float *row = x + (size_t)n * d;
-  float ss = 0.f;
-  for (int j = threadIdx.x; j < d; j += 256) {
-    const float v = row[j];
-    ss += v * v;
-  }
-  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const float tot = (red[0] + red[1]) + (red[2] + red[3]);
-  const float r = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int j = threadIdx.x; j < d; j += 256) out[(size_t)n * d + j] = from_f32<T>(row[j] * r * to_f32<T>(g[j]));
-}
-
-// ---------------------------------------------------------------------------------------------
-// Generic linear: y[n,o] (+)= sum_k a[n,k] * w[o,k].  One wave per output feature and group of 16
-// rows; lanes stride over k.  mode 0 = store, 1 = accumulate into y (residual add).
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_linear_generic(const T *__restrict__ a, const T *__restrict__ w, int32_t n,
-                                                        int32_t K, int32_t O, float *__restrict__ y, int32_t ldy,
-                                                        int32_t mode) {
-  const int lane = threadIdx.x & 63;
-  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int n0 = blockIdx.y * 16;
-  if (o >= O) return;
-  float acc[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-  const T *wr = w + (size_t)o * K;
-  for (int kk = lane; kk < K; kk += 64) {
-    const float wv = to_f32<T>(wr[kk]);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int r = n0 + j;
-      const float av = r < n ? to_f32<T>(a[(size_t)r * K + kk]) : 0.f;
-      acc[j] += wv * av;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    float v = acc[j];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    acc[j] = v;
-  }
-  if (lane < 16 && n0 + lane < n) {
-    float v = 0.f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if (j == lane) v = acc[j];
-    float *dst = y + (size_t)(n0 + lane) * ldy + o;
-    *dst = mode ? (*dst + v) : v;
-  }
-}
-
-template <typename T>
-static hipError_t linear_generic(const void *a, const void *w, int32_t n, int32_t K, int32_t O, float *y, int32_t ldy,
-                                 int32_t mode, hipStream_t st, KernelTimer tm = KernelTimer{}) {
-  return launch(k_linear_generic<T>, dim3((O + 3) / 4, (n + 15) / 16), dim3(256), 0, st, tm, (const T *)a, (const T *)w, n,
-                K, O, y, ldy, mode);
-}
-
-// h[n,f] = T(silu(g) * u) with gu = [gate | up], each F wide
-template <typename T>
-__global__ __launch_bounds__(256) void k_swiglu(const float *__restrict__ gu, int32_t F, T *__restrict__ h) {
-  const int n = blockIdx.y;
-  const int f = blockIdx.x * 256 + threadIdx.x;
-  if (f >= F) return;
-  const float g = gu[(size_t)n * 2 * F + f], u = gu[(size_t)n * 2 * F + F + f];
-  h[(size_t)n * F + f] = from_f32<T>(g / (1.0f + expf(-g)) * u);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Rotary embedding + KV write.  Block (n, head) over the concatenated [q heads | k heads | v heads].
-// Rotated q -> q[n, h, :]; rotated k -> K[layer][h][L+n][:]; v -> V[layer][h][:][L+n].
-// ---------------------------------------------------------------------------------------------
-constexpr int ROPE_HPB = 8; // heads per block
-template <typename T>
-__global__ __launch_bounds__(256) void k_rope_kv(const float *__restrict__ qkv, int32_t n_part, size_t part_stride,
-                                                 const float *__restrict__ rope, int32_t H, int32_t Hkv, int32_t hd,
-                                                 int32_t cap,
-                                                 const int32_t *__restrict__ d_len, T *__restrict__ q,
-                                                 T *__restrict__ Kl, T *__restrict__ Vl, int32_t tiled) {
-  const int n = blockIdx.x;
-  const int half = hd / 2;
-  const int heads = H + 2 * Hkv;
-  const int width = heads * hd;
-  const int pos = *d_len + n;
-  const float *row = qkv + (size_t)n * width;
-  // work item = (head, i): elements i and i + hd/2 of that head (a rotation pair for q and k heads)
-  const int items = ROPE_HPB * half;
-  for (int it = threadIdx.x; it < items; it += 256) {
-    const int hh = blockIdx.y * ROPE_HPB + it / half, i = it % half;
-    if (hh >= heads) break;
-    const float *src = row + (size_t)hh * hd;
-    // the projection may arrive as n_part K-split partial sums, added here in split order
-    float a = src[i], b = src[i + half];
-    for (int s = 1; s < n_part; ++s) {
-      a += src[(size_t)s * part_stride + i];
-      b += src[(size_t)s * part_stride + i + half];
-    }
-    if (hh < H + Hkv) {
-      const float c = rope[(size_t)n * hd + i], sn = rope[(size_t)n * hd + half + i];
-      const float ra = a * c - b * sn, rb = b * c + a * sn;
-      a = ra;
-      b = rb;
-    }
-    const T ta = from_f32<T>(a), tb = from_f32<T>(b);
-    if (hh < H) {
-      T *dst = q + ((size_t)n * H + hh) * hd;
-      dst[i] = ta;
-      dst[i + half] = tb;
-    } else if (hh < H + Hkv) {
-      if (tiled) {
-        T *dst = Kl + (size_t)(hh - H) * cap * hd;
-        dst[kv_k_index(pos, i)] = ta;
-        dst[kv_k_index(pos, i + half)] = tb;
-      } else {
-        T *dst = Kl + ((size_t)(hh - H) * cap + pos) * hd;
-        dst[i] = ta;
-        dst[i + half] = tb;
-      }
-    } else {
-      T *dst = Vl + (size_t)(hh - H - Hkv) * hd * cap;
-      if (tiled) {
-        dst[kv_v_index(pos, i)] = ta;
-        dst[kv_v_index(pos, i + half)] = tb;
-      } else {
-        dst[(size_t)i * cap + pos] = ta;
-        dst[(size_t)(i + half) * cap + pos] = tb;
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Generic tree attention (Section 2.2 "Tree Attention"): block (node n, head h).  Keys are the
+// Generic tree attention (Section 2.2 "Tree Attention"), plain cache layout: block (node n, head h).  Keys are the
 // committed positions 0..L-1 and the tree nodes j whose bit is set in anc[n] (cache position L+j);
-// everything else is skipped exactly.  Online softmax over chunks of 256 keys.
+// everything else is skipped exactly.  Online softmax over chunks of 256 keys: a thread scores one key (its row of K
+// in 16-byte loads), then the value contraction splits the chunk's keys over 256 / hd groups of hd threads (one
+// feature each, V is position-contiguous) that meet in LDS once at the end.  With one group, hd of the 256 threads
+// walked all keys one by one and the launch took 15.5 us on the tiny model's 100 to 150 positions.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void k_attn_generic(const T *__restrict__ q, const T *__restrict__ Kl,
@@ -223,9 +81,10 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T *__restrict__ q, c
                                                       int32_t cap, int32_t n_nodes, const uint64_t *__restrict__ anc,
                                                       const int32_t *__restrict__ d_len, T *__restrict__ out,
                                                       int32_t out_row_tiles) {
+  constexpr int E = 16 / (int)sizeof(T);
   __shared__ float sq[256];
-  __shared__ float sp[256];
-  __shared__ float red[4];
+  __shared__ __align__(16) float sp[256];
+  __shared__ float red[4], red2[4];
   const int n = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
   const int hk = h / (H / Hkv);
   const int L = *d_len;
@@ -235,7 +94,9 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T *__restrict__ q, c
   if (tid < hd) sq[tid] = to_f32<T>(q[((size_t)n * H + h) * hd + tid]);
   __syncthreads();
   const float scale = 1.0f / sqrtf((float)hd);
-  float m = -1e30f, l = 0.f, acc = 0.f; // acc: output element tid (< hd)
+  const int groups = 256 / hd, grp = tid / hd, dd = tid - grp * hd; // threads past groups * hd hold no feature
+  const int span = ((256 + groups - 1) / groups + 3) & ~3;          // keys of a chunk per group
+  float m = -1e30f, l = 0.f, acc = 0.f; // acc: feature dd, keys of this thread's group
   const int total = L + n_nodes;
   for (int base = 0; base < total; base += 256) {
     const int j = base + tid;
@@ -248,7 +109,14 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T *__restrict__ q, c
     if (vis) {
       const T *kr = Kh + (size_t)j * hd;
       float dot = 0.f;
-      for (int e = 0; e < hd; ++e) dot += sq[e] * to_f32<T>(kr[e]);
+      int e = 0;
+      for (; e + E <= hd; e += E) {
+        T kv[E];
+        __builtin_memcpy(kv, kr + e, 16);
+#pragma unroll
+        for (int i = 0; i < E; ++i) dot += sq[e + i] * to_f32<T>(kv[i]);
+      }
+      for (; e < hd; ++e) dot += sq[e] * to_f32<T>(kr[e]);
       s = dot * scale;
     }
     float cm = s;
@@ -261,28 +129,36 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T *__restrict__ q, c
     sp[tid] = p;
     float ps = p;
     for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-    __syncthreads(); // red (max) consumed by everyone, sp complete
-    if ((tid & 63) == 0) red[tid >> 6] = ps;
+    if ((tid & 63) == 0) red2[tid >> 6] = ps;
     __syncthreads();
     const float corr = expf(m - m_new);
-    l = l * corr + ((red[0] + red[1]) + (red[2] + red[3]));
+    l = l * corr + ((red2[0] + red2[1]) + (red2[2] + red2[3]));
     m = m_new;
-    if (tid < hd) {
-      acc *= corr;
-      const T *vr = Vh + (size_t)tid * cap + base;
+    acc *= corr;
+    if (grp < groups) {
+      const T *vr = Vh + (size_t)dd * cap + base;
       const int cnt = total - base < 256 ? total - base : 256;
-      for (int e = 0; e < cnt; ++e) {
-        const float pe = sp[e];
-        if (pe != 0.f) acc += pe * to_f32<T>(vr[e]);
+      int e = grp * span;
+      const int e1 = e + span < cnt ? e + span : cnt;
+      for (; e + 4 <= e1; e += 4) { // weights of keys nobody sees are exact zeros and the cache holds finite values
+        T vv[4];
+        __builtin_memcpy(vv, vr + e, 4 * sizeof(T));
+        const float4 pe = *reinterpret_cast<const float4 *>(sp + e);
+        acc += pe.x * to_f32<T>(vv[0]) + pe.y * to_f32<T>(vv[1]) + pe.z * to_f32<T>(vv[2]) + pe.w * to_f32<T>(vv[3]);
       }
+      for (; e < e1; ++e) acc += sp[e] * to_f32<T>(vr[e]);
     }
     __syncthreads();
   }
+  sp[tid] = acc;
+  __syncthreads();
   if (tid < hd) {
+    float o = sp[tid];
+    for (int i = 1; i < groups; ++i) o += sp[i * hd + tid];
     // row-major [n, H*hd], or fragment order for the o-projection when out_row_tiles > 0
     const size_t idx = out_row_tiles > 0 ? act_frag_index(n, h * hd + tid, out_row_tiles)
                                          : ((size_t)n * H + h) * hd + tid;
-    out[idx] = from_f32<T>(acc / l);
+    out[idx] = from_f32<T>(o / l);
   }
 }
 
@@ -320,43 +196,45 @@ static hipError_t forward_generic(const tr_model &m, const tr_kv &kv, const Tree
                                   hipStream_t st) {
   const Workspace w = plan_workspace(m);
   const int d = m.d_model, H = m.n_heads, Hkv = m.n_kv_heads, hd = m.head_dim, F = m.d_ffn;
-  const int hq = H * hd, hk = Hkv * hd, wq = hq + 2 * hk;
+  const int hq = H * hd;
   float *x = (float *)(ws + w.x);
-  T *xn = (T *)(ws + w.xn);
-  float *qkv = (float *)(ws + w.qkv);
   T *q = (T *)(ws + w.q);
   T *attn = (T *)(ws + w.attn);
-  float *gu = (float *)(ws + w.gu);
   T *hbuf = (T *)(ws + w.h);
   float *rope = (float *)(ws + w.rope);
   const size_t lsz = (size_t)Hkv * kv.capacity * hd;
+  auto normed = [&](const void *gain, int epilogue) { // norm(x) as the input
+    RowsArgs p{};
+    p.a = x; p.gain = gain; p.eps = m.rms_eps; p.n = n; p.K = d; p.epilogue = epilogue;
+    return p;
+  };
+  auto residual = [&](const void *a, int K, const void *wt) { // x += a * wt^T
+    RowsArgs p{};
+    p.a = a; p.w[0] = wt; p.n = n; p.K = K; p.O = d; p.epilogue = ROWS_ADD; p.y = x; p.ldy = d;
+    return p;
+  };
 
   TR_TRY(launch(k_embed_rope<T>, dim3(n), dim3(256), 0, st, prof_next(prof, PC_EMBED), (const T *)m.embed, m.vocab, d, tok,
                 tree.depth, kv.d_len, hd, m.rope_theta, x, rope));
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
-    TR_TRY(launch(k_rmsnorm<T>, dim3(n), dim3(256), 0, st, prof_next(prof, PC_NORM), x, (const T *)lw.attn_norm, d,
-                  m.rms_eps, xn));
-    TR_TRY(linear_generic<T>(xn, lw.wq, n, d, hq, qkv, wq, 0, st, prof_next(prof, PC_QKV)));
-    TR_TRY(linear_generic<T>(xn, lw.wk, n, d, hk, qkv + hq, wq, 0, st, prof_next(prof, PC_QKV)));
-    TR_TRY(linear_generic<T>(xn, lw.wv, n, d, hk, qkv + hq + hk, wq, 0, st, prof_next(prof, PC_QKV)));
-    TR_TRY(launch(k_rope_kv<T>, dim3(n, (H + 2 * Hkv + ROPE_HPB - 1) / ROPE_HPB), dim3(256), 0, st,
-                  prof_next(prof, PC_ROPE), qkv, 1, (size_t)0, rope, H, Hkv, hd, kv.capacity, kv.d_len, q,
-                  (T *)kv.k + (size_t)l * lsz, (T *)kv.v + (size_t)l * lsz, kv.layout));
+    RowsArgs p = normed(lw.attn_norm, ROWS_ROPE);
+    p.w[0] = lw.wq; p.w[1] = lw.wk; p.w[2] = lw.wv; p.O = (H + 2 * Hkv) * hd;
+    p.q = q; p.k_layer = (T *)kv.k + (size_t)l * lsz; p.v_layer = (T *)kv.v + (size_t)l * lsz;
+    p.rope = rope; p.d_len = kv.d_len; p.H = H; p.Hkv = Hkv; p.hd = hd; p.cap = kv.capacity; p.tiled = kv.layout;
+    TR_TRY(launch_rows(p, m.dtype, st, prof_next(prof, PC_QKV)));
     TR_TRY(attention_dispatch<T>(kv, l, H, tree, n, q, attn, 0, (float *)(ws + w.part_ml), (float *)(ws + w.part_acc),
                                  prof, st));
-    TR_TRY(linear_generic<T>(attn, lw.wo, n, hq, d, x, d, 1, st, prof_next(prof, PC_OPROJ)));
-    TR_TRY(launch(k_rmsnorm<T>, dim3(n), dim3(256), 0, st, prof_next(prof, PC_NORM), x, (const T *)lw.ffn_norm, d,
-                  m.rms_eps, xn));
-    TR_TRY(linear_generic<T>(xn, lw.w_gate, n, d, F, gu, 2 * F, 0, st, prof_next(prof, PC_GATEUP)));
-    TR_TRY(linear_generic<T>(xn, lw.w_up, n, d, F, gu + F, 2 * F, 0, st, prof_next(prof, PC_GATEUP)));
-    TR_TRY(launch(k_swiglu<T>, dim3((F + 255) / 256, n), dim3(256), 0, st, prof_next(prof, PC_GATEUP), gu, F, hbuf));
-    TR_TRY(linear_generic<T>(hbuf, lw.w_down, n, F, d, x, d, 1, st, prof_next(prof, PC_DOWN)));
+    TR_TRY(launch_rows(residual(attn, hq, lw.wo), m.dtype, st, prof_next(prof, PC_OPROJ)));
+    p = normed(lw.ffn_norm, ROWS_SWIGLU);
+    p.w[0] = lw.w_gate; p.w[1] = lw.w_up; p.O = F; p.h = hbuf;
+    TR_TRY(launch_rows(p, m.dtype, st, prof_next(prof, PC_GATEUP)));
+    TR_TRY(launch_rows(residual(hbuf, F, lw.w_down), m.dtype, st, prof_next(prof, PC_DOWN)));
   }
   if (logits_out != nullptr) {
-    TR_TRY(launch(k_rmsnorm<T>, dim3(n), dim3(256), 0, st, prof_next(prof, PC_NORM), x, (const T *)m.final_norm, d,
-                  m.rms_eps, xn));
-    TR_TRY(linear_generic<T>(xn, m.lm_head, n, d, m.vocab, logits_out, m.vocab, 0, st, prof_next(prof, PC_LMHEAD)));
+    RowsArgs p = normed(m.final_norm, ROWS_STORE);
+    p.w[0] = m.lm_head; p.O = m.vocab; p.y = logits_out; p.ldy = m.vocab;
+    TR_TRY(launch_rows(p, m.dtype, st, prof_next(prof, PC_LMHEAD)));
   }
   return hipSuccess;
 }
@@ -681,8 +559,9 @@ hipError_t run_linear(const void *x, const void *w, int32_t dtype, int32_t layou
     }
     return hipSuccess;
   }
-  if (dtype == TR_BF16) return linear_generic<bf16_t>(x, w, n, in_f, out_f, y, out_f, 0, st);
-  return linear_generic<float>(x, w, n, in_f, out_f, y, out_f, 0, st);
+  RowsArgs p{};
+  p.a = x; p.w[0] = w; p.n = n; p.K = in_f; p.O = out_f; p.epilogue = ROWS_STORE; p.y = y; p.ldy = out_f;
+  return launch_rows(p, dtype, st);
 }
 
 } // namespace tr

@@ -68,11 +68,9 @@ struct TreeDev {
 // hold NPW rows, which is what one prompt-ingestion pass takes.
 struct Workspace {
   size_t x;        // float  [NP, d]            residual stream
-  size_t xn;       // T      [NP, d]            normalised activations
-  size_t qkv;      // float  [NP, (H+2Hkv)*hd]  (generic path only)
+  size_t xn;       // T      [NP, d]            normalised activations (packed path)
   size_t q;        // T      [NP, H*hd]         rotated queries
   size_t attn;     // T      [NP, H*hd]         attention output
-  size_t gu;       // float  [NP, 2F]           gate | up (generic path only)
   size_t h;        // T      [NP, F]            silu(gate)*up
   size_t rope;     // float  [NP, hd]           cos[hd/2] | sin[hd/2] per row
   size_t logits;   // float  [NP, V]            used when the caller passes no logits buffer

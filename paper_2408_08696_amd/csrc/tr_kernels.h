@@ -94,6 +94,30 @@ hipError_t launch_gemm_wide(const GemmArgs &g, int32_t max_splits, int32_t *out_
                             KernelTimer tm = KernelTimer{});
 hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t K, int32_t rope_hd, hipStream_t st);
 
+// Shape-generic projections on row-major weights with their prologue and epilogue (tr_rows.hip).
+enum RowsEpilogue {
+  ROWS_STORE = 0,  // y[row * ldy + o] = v
+  ROWS_ADD = 1,    // y[row * ldy + o] += v (residual stream)
+  ROWS_SWIGLU = 2, // h[row * O + f] = T(silu(gate) * up); w[0] = gate, w[1] = up, O = features of one of them
+  ROWS_ROPE = 3    // Q/K/V: rotate, write queries and this layer's cache entries; w = {q, k, v}, O = all outputs
+};
+struct RowsArgs {
+  const void *a;    // gain != nullptr: float [n, K], the residual stream to normalise; else T [n, K]
+  const void *gain; // T [K] or nullptr
+  float eps;
+  const void *w[3]; // T, row-major [.., K]
+  int32_t n, K, O;
+  int32_t epilogue;
+  float *y;
+  int32_t ldy;
+  void *h;
+  void *q, *k_layer, *v_layer; // ROWS_ROPE
+  const float *rope;
+  const int32_t *d_len;
+  int32_t H, Hkv, hd, cap, tiled;
+};
+hipError_t launch_rows(const RowsArgs &p, int32_t dtype, hipStream_t st, KernelTimer tm = KernelTimer{});
+
 // Tree attention for head_dim 128, bf16 K/V/Q, split over the key axis with a merge pass.
 // len_bound: host upper bound of L + n (sizes the split count only).
 // Query heads one workgroup of launch_attn_mfma serves (they share a K/V head), and the key-axis splits it

@@ -435,3 +435,23 @@ def test_pack_rejects_bad_sizes():
     with pytest.raises(tr.TRError) as e:
         tr.pack_weight(w)                                      # 48 is not a multiple of 32
     assert e.value.status == tr.TR_EINVAL
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,K,O", [(1, 1, 1), (15, 128, 1024), (16, 344, 17), (17, 385, 33), (33, 31, 16), (64, 500, 20),
+                                   (65, 1027, 15), (128, 192, 130)])
+def test_row_major_linear_edges(dtype, n, K, O):
+    """Row-major projections around the kernel's units (16 outputs, 1 / 2 / 4 row tiles per workgroup, k-steps of 64
+    bytes dealt to four waves, 16-byte chunks that end inside or straddle a row's end, rows that start off 16 bytes)."""
+    require_gpu()
+    say("row-major linear", dtype, n, K, O)
+    x = synth.normal_tensor((n, K), 1.0, seed=K, dtype=dtype)
+    w = synth.normal_tensor((O, K), 1.0, seed=O + 1, dtype=dtype)
+    ctx = tr.Context(64, 8, [-1], [-1], 1)
+    y = torch.full((n, O), float("nan"), device="cuda")
+    ctx.op_linear(x.cuda(), w.cuda(), y)
+    want = x.double() @ w.double().t()
+    # products are exact in float32 for bf16 and rounded once for float32; K - 1 sums, each off by half an ulp
+    bound = (K + 1) * 2.0 ** -24 * (x.double().abs() @ w.double().abs().t())
+    assert bool(((y.cpu().double() - want).abs() <= bound).all())
+    ctx.close()
