@@ -42,29 +42,45 @@ Workspace plan_workspace(const tr_model &m) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Embedding gather + rotary table.  Row n: x[n,:] = E[tok[n],:]; cos/sin of (L + depth[n]) * f_i
-// with f_i = theta^(-2i/hd), evaluated in double so that long positions keep float32 accuracy.
-// depth == nullptr: row n sits n positions after L (a run of consecutive prompt tokens).
+// Rotary table of one row: cos/sin of pos * f_i with f_i = theta^(-2i/hd), evaluated in double so that long positions
+// keep float32 accuracy.
 // ---------------------------------------------------------------------------------------------
+__device__ inline void rope_row(int pos, int32_t hd, float theta, float *__restrict__ rope_n) {
+  const int half = hd / 2;
+  for (int i = threadIdx.x; i < half; i += blockDim.x) {
+    const double f = pow((double)theta, -2.0 * (double)i / (double)hd);
+    double sn, cs;
+    sincos((double)pos * f, &sn, &cs);
+    rope_n[i] = (float)cs;
+    rope_n[half + i] = (float)sn;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Embedding gather + rotary table.  Row n: x[n,:] = E[tok[n],:]; cos/sin of position L + depth[n].
+// depth == nullptr: row n sits n positions after L (a run of consecutive prompt tokens).
+// Block (n, 0) writes row n of the table, block (n, 1 + c) columns 1024 c .. of x: the table's double-precision chain
+// (2 us) and the copy run side by side.
+// ---------------------------------------------------------------------------------------------
+constexpr int EMBED_CHUNK = 1024;
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_rope(const T *__restrict__ E, int32_t V, int32_t d,
                                                     const int32_t *__restrict__ tok, const int32_t *__restrict__ depth,
                                                     const int32_t *__restrict__ d_len, int32_t hd, float theta,
                                                     float *__restrict__ x, float *__restrict__ rope) {
   const int n = blockIdx.x;
+  if (blockIdx.y == 0) {
+    rope_row(*d_len + (depth != nullptr ? depth[n] : n), hd, theta, rope + (size_t)n * hd);
+    return;
+  }
   int t = tok[n];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
-  const T *src = E + (size_t)t * d;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) x[(size_t)n * d + j] = to_f32<T>(src[j]);
-  const int half = hd / 2;
-  const double pos = (double)(*d_len + (depth != nullptr ? depth[n] : n));
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    const double f = pow((double)theta, -2.0 * (double)i / (double)hd);
-    double sn, cs;
-    sincos(pos * f, &sn, &cs);
-    rope[(size_t)n * hd + i] = (float)cs;
-    rope[(size_t)n * hd + half + i] = (float)sn;
-  }
+  const int j = (blockIdx.y - 1) * EMBED_CHUNK + threadIdx.x * 4; // d is a multiple of 4
+  if (j >= d) return;
+  T v[4];
+  __builtin_memcpy(v, E + (size_t)t * d + j, 4 * sizeof(T));
+  *reinterpret_cast<float4 *>(x + (size_t)n * d + j) =
+      float4{to_f32<T>(v[0]), to_f32<T>(v[1]), to_f32<T>(v[2]), to_f32<T>(v[3])};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -214,8 +230,9 @@ static hipError_t forward_generic(const tr_model &m, const tr_kv &kv, const Tree
     return p;
   };
 
-  TR_TRY(launch(k_embed_rope<T>, dim3(n), dim3(256), 0, st, prof_next(prof, PC_EMBED), (const T *)m.embed, m.vocab, d, tok,
-                tree.depth, kv.d_len, hd, m.rope_theta, x, rope));
+  TR_TRY(launch(k_embed_rope<T>, dim3(n, 1 + (d + EMBED_CHUNK - 1) / EMBED_CHUNK), dim3(256), 0, st,
+                prof_next(prof, PC_EMBED), (const T *)m.embed, m.vocab, d, tok, tree.depth, kv.d_len, hd, m.rope_theta, x,
+                rope));
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
     RowsArgs p = normed(lw.attn_norm, ROWS_ROPE);
@@ -245,38 +262,24 @@ static hipError_t forward_generic(const tr_model &m, const tr_kv &kv, const Tree
 // which the next normalisation kernel folds into x in a fixed order.
 // ---------------------------------------------------------------------------------------------
 // Residual update and normalisation input, block (row, chunk of 1024 columns), 128 threads x 8 columns:
-//   x[row, c] += sum_s part[s][row, c]        (n_part may be 0)
+//   x[row, c] += sum_s part[s][row, c]        (in split order)
 //   xg_frag    = bf16(x * g)                   fragment order; rows n..16*row_tiles-1 are zeros
 //   ssq[row, chunk] = sum over the chunk of x^2
 // The RMS scale 1/sqrt(mean(x^2) + eps) is a per-row scalar, so the GEMM that consumes xg_frag applies
 // it to its output rows (gemm row_ssq arguments) instead of this kernel needing a whole-row reduction.
+// k_embed_frag is the same for the first layer, where x comes from the embedding table, and writes the rotary table
+// beside it (blocks of chunk n_chunks).
 constexpr int NORM_CHUNK = 1024;
 static_assert(NORM_CHUNK == 128 * 8, "one block iteration covers 128 threads x 8 columns");
-__global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const float *__restrict__ part,
-                                                  int32_t n_part, size_t part_stride, const bf16_t *__restrict__ g,
-                                                  int32_t n, int32_t d, int32_t row_tiles,
-                                                  bf16_t *__restrict__ xg_frag, float *__restrict__ ssq,
-                                                  int32_t n_chunks) {
+constexpr int NORM_MAX_PARTS = 4;
+static_assert(NORM_MAX_PARTS >= GEMM_MAX_SPLITS && NORM_MAX_PARTS >= WIDE_MAX_SPLITS, "all partial sums are read at once");
+
+__device__ inline void norm_operand(const float (&v)[8], bool live, const bf16_t *__restrict__ g, int row, int j, int32_t d,
+                                    int32_t row_tiles, bf16_t *__restrict__ xg_frag, float *__restrict__ ssq_at, bool row_on) {
   __shared__ float red[2];
-  const int row = blockIdx.x, chunk = blockIdx.y;
-  const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
-  const bool live = row < n && j < d;
   float ss = 0.f;
   uint4 pk = uint4{0u, 0u, 0u, 0u};
   if (live) {
-    float *xr = x + (size_t)row * d + j;
-    float4 a = *reinterpret_cast<const float4 *>(xr), b = *reinterpret_cast<const float4 *>(xr + 4);
-    for (int s = 0; s < n_part; ++s) {
-      const float *pr = part + (size_t)s * part_stride + (size_t)row * d + j;
-      const float4 pa = *reinterpret_cast<const float4 *>(pr), pb = *reinterpret_cast<const float4 *>(pr + 4);
-      a.x += pa.x; a.y += pa.y; a.z += pa.z; a.w += pa.w;
-      b.x += pb.x; b.y += pb.y; b.z += pb.z; b.w += pb.w;
-    }
-    if (n_part > 0) {
-      *reinterpret_cast<float4 *>(xr) = a;
-      *reinterpret_cast<float4 *>(xr + 4) = b;
-    }
-    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     const uint4 gv = *reinterpret_cast<const uint4 *>(g + j);
     const uint32_t gw[4] = {gv.x, gv.y, gv.z, gv.w};
     uint32_t o[4];
@@ -292,7 +295,68 @@ __global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const f
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
-  if (threadIdx.x == 0 && row < n) ssq[(size_t)row * n_chunks + chunk] = red[0] + red[1];
+  if (threadIdx.x == 0 && row_on) *ssq_at = red[0] + red[1];
+}
+
+__global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const float *__restrict__ part,
+                                                  int32_t n_part, size_t part_stride, const bf16_t *__restrict__ g,
+                                                  int32_t n, int32_t d, int32_t row_tiles,
+                                                  bf16_t *__restrict__ xg_frag, float *__restrict__ ssq,
+                                                  int32_t n_chunks) {
+  const int row = blockIdx.x, chunk = blockIdx.y;
+  const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
+  const bool live = row < n && j < d;
+  float v[8];
+  if (live) {
+    float *xr = x + (size_t)row * d + j;
+    const float *pr = part + (size_t)row * d + j;
+    float4 a = *reinterpret_cast<const float4 *>(xr), b = *reinterpret_cast<const float4 *>(xr + 4);
+    float4 pa[NORM_MAX_PARTS], pb[NORM_MAX_PARTS];
+#pragma unroll
+    for (int s = 0; s < NORM_MAX_PARTS; ++s)
+      if (s < n_part) {
+        pa[s] = *reinterpret_cast<const float4 *>(pr + (size_t)s * part_stride);
+        pb[s] = *reinterpret_cast<const float4 *>(pr + (size_t)s * part_stride + 4);
+      }
+#pragma unroll
+    for (int s = 0; s < NORM_MAX_PARTS; ++s)
+      if (s < n_part) {
+        a.x += pa[s].x; a.y += pa[s].y; a.z += pa[s].z; a.w += pa[s].w;
+        b.x += pb[s].x; b.y += pb[s].y; b.z += pb[s].z; b.w += pb[s].w;
+      }
+    *reinterpret_cast<float4 *>(xr) = a;
+    *reinterpret_cast<float4 *>(xr + 4) = b;
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  }
+  norm_operand(v, live, g, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
+}
+
+__global__ __launch_bounds__(128) void k_embed_frag(const bf16_t *__restrict__ E, int32_t V, const int32_t *__restrict__ tok,
+                                                    const int32_t *__restrict__ depth, const int32_t *__restrict__ d_len,
+                                                    int32_t hd, float theta, float *__restrict__ x,
+                                                    float *__restrict__ rope, const bf16_t *__restrict__ g, int32_t n,
+                                                    int32_t d, int32_t row_tiles, bf16_t *__restrict__ xg_frag,
+                                                    float *__restrict__ ssq, int32_t n_chunks) {
+  const int row = blockIdx.x, chunk = blockIdx.y;
+  if (chunk == n_chunks) {
+    if (row < n) rope_row(*d_len + (depth != nullptr ? depth[row] : row), hd, theta, rope + (size_t)row * hd);
+    return;
+  }
+  const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
+  const bool live = row < n && j < d;
+  float v[8];
+  if (live) {
+    int t = tok[row];
+    t = t < 0 ? 0 : (t >= V ? V - 1 : t);
+    bf16_t e[8];
+    __builtin_memcpy(e, E + (size_t)t * d + j, 16);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = bf16_to_f32(e[i]);
+    float *xr = x + (size_t)row * d + j;
+    *reinterpret_cast<float4 *>(xr) = float4{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<float4 *>(xr + 4) = float4{v[4], v[5], v[6], v[7]};
+  }
+  norm_operand(v, live, g, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
 }
 
 // row-major bf16 [n, K] -> fragment order (standalone linear op only)
@@ -340,8 +404,9 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
   float *ssq = (float *)(ws + w.ssq);
   const int nch = (d + NORM_CHUNK - 1) / NORM_CHUNK;
 
-  TR_TRY(launch(k_embed_rope<T>, dim3(n), dim3(256), 0, st, prof_next(prof, PC_EMBED), (const T *)m.embed, m.vocab, d, tok,
-                tree.depth, kv.d_len, hd, m.rope_theta, x, rope));
+  TR_TRY(launch(k_embed_frag, dim3(NT * 16, nch + 1), dim3(128), 0, st, prof_next(prof, PC_EMBED), (const T *)m.embed,
+                m.vocab, tok, tree.depth, kv.d_len, hd, m.rope_theta, x, rope, (const T *)m.layers[0].attn_norm, n, d, NT,
+                xn, ssq, nch));
   int pending = 0; // partial sums waiting in ypart
   auto add_norm = [&](const void *gain) {
     return launch(k_add_frag, dim3(NT * 16, nch), dim3(128), 0, st, prof_next(prof, PC_NORM), x, ypart, pending, ystride,
@@ -349,7 +414,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
-    TR_TRY(add_norm(lw.attn_norm));
+    if (l > 0) TR_TRY(add_norm(lw.attn_norm));
     {
       GemmArgs g{};
       g.a_frag = xn; g.n = n; g.K = d;
@@ -436,8 +501,9 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, const TreeDev
   const KernelTimer no_timer{};
   const size_t ystride = (size_t)NPW * d;
 
-  TR_TRY(launch(k_embed_rope<T>, dim3(n), dim3(256), 0, st, no_timer, (const T *)m.embed, m.vocab, d, tok,
-                (const int32_t *)nullptr, kv.d_len, hd, m.rope_theta, x, rope));
+  TR_TRY(launch(k_embed_frag, dim3(RT * 16, nch + 1), dim3(128), 0, st, no_timer, (const T *)m.embed, m.vocab, tok,
+                (const int32_t *)nullptr, kv.d_len, hd, m.rope_theta, x, rope, (const T *)m.layers[0].attn_norm, n, d, RT,
+                xn, ssq, nch));
   int pending = 0;
   auto add_norm = [&](const void *gain) {
     return launch(k_add_frag, dim3(RT * 16, nch), dim3(128), 0, st, no_timer, x, ypart, pending, ystride,
@@ -445,7 +511,7 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, const TreeDev
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
-    TR_TRY(add_norm(lw.attn_norm));
+    if (l > 0) TR_TRY(add_norm(lw.attn_norm));
     {
       GemmArgs g{};
       g.a_frag = xn; g.n = n; g.K = d;
