@@ -546,14 +546,21 @@ __global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__rest
 //   argmax_j ( logits[i][j] * inv_t + noise[L + depth(i) - pos0][j] ),   ties to the smallest j,
 // i.e. a draw from softmax(logits / T) when the noise is standard Gumbel.  The two float32 operations
 // are kept separate (no fused multiply-add): they decide an integer, and whoever repeats them rounds
-// the same way.  One workgroup per node.
+// the same way.  One workgroup of 16 waves per node; a thread has U vectors of both rows in flight, which is what
+// counts (every node's compute unit pulls two rows of V floats): 128 nodes x 32000 took 39 us with 4 waves and one
+// element of each row in flight, 9.3 now.  VEC: 16-byte loads (V a multiple of 4, both bases aligned).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_sample_tokens(const float *__restrict__ logits, const float *__restrict__ noise,
-                                                       int32_t V, int32_t pos0, int32_t noise_rows, float inv_t,
-                                                       const int32_t *__restrict__ depth,
-                                                       const int32_t *__restrict__ d_len, int32_t *__restrict__ tokens) {
-  __shared__ float sv[256];
-  __shared__ int32_t si[256];
+constexpr int SAMPLE_THREADS = 1024;
+template <bool VEC>
+__global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *__restrict__ logits,
+                                                                  const float *__restrict__ noise, int32_t V, int32_t pos0,
+                                                                  int32_t noise_rows, float inv_t,
+                                                                  const int32_t *__restrict__ depth,
+                                                                  const int32_t *__restrict__ d_len,
+                                                                  int32_t *__restrict__ tokens) {
+  constexpr int E = VEC ? 4 : 1, U = 4;
+  __shared__ float sv[SAMPLE_THREADS / 64];
+  __shared__ int32_t si[SAMPLE_THREADS / 64];
   const int i = blockIdx.x;
   int row = *d_len + depth[i] - pos0;
   row = row < 0 ? 0 : (row >= noise_rows ? noise_rows - 1 : row); // the host checked the range; never read outside
@@ -561,35 +568,55 @@ __global__ __launch_bounds__(256) void k_sample_tokens(const float *__restrict__
   const float *nz = noise + (size_t)row * V;
   float best = -__builtin_huge_valf();
   int bj = 0x7fffffff;
-  for (int j = threadIdx.x; j < V; j += 256) {
-    const float y = __fadd_rn(__fmul_rn(lg[j], inv_t), nz[j]);
-    if (y > best || bj == 0x7fffffff) { // j grows, so on equal values the earlier index stays
-      best = y;
-      bj = j;
+  for (int j0 = threadIdx.x * E; j0 < V; j0 += SAMPLE_THREADS * E * U) {
+    float a[U][E], b[U][E];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u * SAMPLE_THREADS * E;
+      const int jc = j < V ? j : j0; // past the end: an element seen before, skipped below
+      __builtin_memcpy(a[u], lg + jc, sizeof(a[u]));
+      __builtin_memcpy(b[u], nz + jc, sizeof(b[u]));
     }
-  }
-  sv[threadIdx.x] = best;
-  si[threadIdx.x] = bj;
-  __syncthreads();
-  for (int h = 128; h >= 1; h >>= 1) {
-    if (threadIdx.x < h) {
-      const float ov = sv[threadIdx.x + h];
-      const int oi = si[threadIdx.x + h];
-      if (oi != 0x7fffffff && (si[threadIdx.x] == 0x7fffffff || ov > sv[threadIdx.x] ||
-                               (ov == sv[threadIdx.x] && oi < si[threadIdx.x]))) {
-        sv[threadIdx.x] = ov;
-        si[threadIdx.x] = oi;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int j = j0 + u * SAMPLE_THREADS * E + e;
+        const float y = __fadd_rn(__fmul_rn(a[u][e], inv_t), b[u][e]);
+        if (j < V && (y > best || bj == 0x7fffffff)) { // j grows, so on equal values the earlier index stays
+          best = y;
+          bj = j;
+        }
       }
-    }
-    __syncthreads();
   }
-  if (threadIdx.x == 0) tokens[i] = si[0];
+  auto merge = [&](float ov, int oi) {
+    if (oi != 0x7fffffff && (bj == 0x7fffffff || ov > best || (ov == best && oi < bj))) {
+      best = ov;
+      bj = oi;
+    }
+  };
+  for (int off = 32; off > 0; off >>= 1) {
+    const float ov = __shfl_xor(best, off);
+    const int oi = __shfl_xor(bj, off);
+    merge(ov, oi);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sv[threadIdx.x >> 6] = best;
+    si[threadIdx.x >> 6] = bj;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < SAMPLE_THREADS / 64; ++w) merge(sv[w], si[w]);
+    tokens[i] = bj;
+  }
 }
 
 hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logits, const float *d_noise,
                                 int32_t pos0, int32_t noise_rows, float inv_t, int32_t *d_tokens, hipStream_t st) {
-  return launch(k_sample_tokens, dim3(c->tree.n_nodes), dim3(256), 0, st, c->prof.next(PC_SAMPLE), d_logits, d_noise, c->V,
-                pos0, noise_rows, inv_t, c->tree.depth, kv->d_len, d_tokens);
+  const bool vec = c->V % 4 == 0 && (uintptr_t)d_logits % 16 == 0 && (uintptr_t)d_noise % 16 == 0;
+  return launch(vec ? k_sample_tokens<true> : k_sample_tokens<false>, dim3(c->tree.n_nodes), dim3(SAMPLE_THREADS), 0, st,
+                c->prof.next(PC_SAMPLE), d_logits, d_noise, c->V, pos0, noise_rows, inv_t, c->tree.depth, kv->d_len,
+                d_tokens);
 }
 
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk,

@@ -313,3 +313,26 @@ def test_sample_tokens_match_oracle(V, L):
         ctx.op_sample(kv, logits.cuda(), noise[:L + 2].cuda(), 1.0, tokens)     # table too short for the tree
     with pytest.raises(tr.TRError):
         ctx.op_sample(kv, logits.cuda(), noise.cuda(), 0.0, tokens)
+
+
+@pytest.mark.parametrize("V", [8, 1023, 4097, 16384, 16388, 20003])
+def test_sample_tokens_edges(V):
+    """Draws at vocabularies around the kernel's pass (1024 threads, 4 loads of 1 or 4 elements each), with equal
+    values in different threads and at the row's ends."""
+    require_gpu()
+    say("sample edges", V)
+    t = synth.tree15()
+    ctx = tr.Context(V, 8, t.parent, t.rank, t.n_layers)
+    kv = tr.KVDesc(synth.ModelShape("s", 1, 128, 1, 1, 128, 128, V, "bf16"), 160)
+    kv.reset(3)
+    logits = synth.normal_tensor((t.n_nodes, V), 3.0, seed=V, dtype=torch.float32)
+    noise = torch.zeros(t.n_layers, V)
+    logits[0, :] = 1.0
+    logits[1, V - 1] = logits[1].max() + 1
+    logits[2, V // 2:] = logits[2].max() + 1
+    logits[3, :] = -float("inf")
+    tokens = torch.zeros(t.n_nodes, dtype=torch.int32, device="cuda")
+    ctx.op_sample(kv, logits.cuda(), noise.cuda(), 2.0, tokens, noise_pos0=3)
+    depth = O.make_tree(t.parent, t.rank, 8).depth
+    assert tokens.cpu().tolist() == O.sample_tokens(logits.numpy(), [int(d) for d in depth], 2.0, noise.numpy()).tolist()
+    ctx.close()
