@@ -1,31 +1,31 @@
 // Projection GEMM for prompt ingestion: y[n, O] = a[n, K] * w[O, K]^T with n up to WIDE_MAX_ROWS rows at once.
 //
-// The decode-step kernel (tr_gemm_mfma.hip) reads every weight byte once per 128 rows at most, so a prompt of
-// 512 tokens streams the model four times.  Here a workgroup of eight waves owns NW consecutive out-tiles and a
-// block of 8 * RTW row tiles (each wave RTW tiles of 16 rows); with RTW = 4 one workgroup spans all 512 rows and
-// the weights are read from memory exactly once per pass.  Where several row blocks share an out-tile group,
-// their workgroups have linear ids congruent modulo 8, land on one XCD, and share the group's weights through
-// that XCD's L2.
+// A workgroup of eight waves owns NW consecutive out-tiles and RB row tiles (16 x 16 tiles = 256 x 256 outputs in the
+// largest shape); its waves form a WR x WC grid over that block, so that a tile loaded once serves WC or WR of them.
+// Both operands travel memory -> LDS without passing through registers (global_load_lds, 16 bytes a lane: a fragment
+// tile is one contiguous KiB on both sides) into a ring of D k-steps, D - 1 of them under way while one is multiplied.
+// A wave reads the operands of k-step s + 1 between the MFMAs of k-step s and meets the others once per k-step; the
+// MFMAs that follow the barrier have their operands in registers already.  A wave ends with the sums over its k range
+// for its outputs: no cross-wave reduction, the epilogue runs from registers.  Projections with few out-tiles (o and
+// down) are split over k so that the launch still fills the chip; the residual kernel adds the partial sums.  Row
+// blocks of one out-tile group have linear ids congruent modulo 8, land on one XCD and share its weights in that L2.
 //
-// Weight tiles travel global -> registers -> LDS, loaded cooperatively by all eight waves 24 tiles at a time
-// (24 / NW k-steps) into a double buffer (one workgroup barrier per stage) with two further stages in flight in
-// registers.  Every wave multiplies each weight tile it reads from LDS with its RTW activation tiles (global ->
-// registers, prefetched four k-steps deep).  A wave ends with the sums over its k range for its rows: no
-// cross-wave reduction, the epilogue runs from registers.  Projections with few out-tiles (o and down) are split
-// over k so that the launch still fills the chip; the residual kernel adds the partial sums.
-//
-// What bounds it (7B gate/up projection of 511 rows, 92 Gflop): with one row tile per wave the LDS set the pace
-// (every MFMA needs a 1 KiB tile read, the LDS delivers one per 8 clocks to the whole compute unit): 109 us.
-// With two or four row tiles per wave, 86-94 us = 1.0 PFLOP/s at a shader clock of 1.85 GHz (measured during the
-// launch), the matrix pipe 68 % busy.  That time did not move with the MFMA shape, the depth of the LDS read-ahead,
-// the place of the LDS hand-over in the stage, the stage size, a second workgroup per compute unit, or weight
-// stages brought in by direct global -> LDS loads; it follows the volume of global loads a compute unit issues
-// (-33 % without the weight loads, -15 % with one activation tile for all waves), 19-24 bytes per clock against
-// 60 for a loop of nothing but loads: the waves that load are the waves that must keep the matrix pipe fed, they
-// issue in order, and a load that waits for a slot in the memory pipe holds up the MFMAs behind it.
+// What bounds it.  A compute unit takes tiles in at 47-52 GB/s when part of them comes from memory, against 100-107
+// when all are in L2 and whatever the share of the chip that is busy (96 to 256 workgroups alike): its load path
+// holds about 48 KB and returns in order, so every tile waits as long as a weight tile does.  The time of a k-step is
+// therefore its tiles over that rate, and the shapes with the most MFMAs per tile win wherever they fill the chip:
+// us per k-step (tile pairs per workgroup) 0.28-0.31 (64), 0.40-0.42 (96), 0.43-0.45 (128), 0.57-0.59 (192), 0.66-0.74
+// (256, 1.4 PFLOP/s in full rounds, the matrix pipe 73 % busy).  LDS reads are conflict-free and take a quarter of
+// that unit's time.  Measured without effect: weight tiles at other strides or in another k order per workgroup, wave
+// priorities; slower: touching lines ahead of the loads to bring them into L2 (the touches go through the same path).
+// 512 rows, us per launch, this kernel / one that took weights through registers and activations straight to the
+// operands (8 x 1 wave grid): 7B gate/up 83 / 94, o + down 80 / 103, 70B gate/up 391 / 489, o + down 276 / 360.
 //
 // Same packed weight layout, fragment-ordered activations and epilogues (plain store, RoPE + cache append,
 // SwiGLU) as the decode kernel.
+#include <type_traits>
+#include <utility>
+
 #include "tr_kernels.h"
 
 namespace tr {
@@ -33,7 +33,6 @@ namespace tr {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 __device__ inline f32x16 mfma32w(const u32x4 &a, const u32x4 &b, f32x16 c) {
@@ -41,115 +40,111 @@ __device__ inline f32x16 mfma32w(const u32x4 &a, const u32x4 &b, f32x16 c) {
 }
 
 constexpr int WIDE_WAVES = 8;
-constexpr int WIDE_TPS = 24;                    // weight tiles per LDS stage (24 KiB)
-constexpr int WIDE_TPW = WIDE_TPS / WIDE_WAVES; // tiles a wave loads per stage
-constexpr int WIDE_PA = 4;                      // k-steps of activation tiles a wave keeps in flight
 
-// NW: out-tiles per workgroup (SwiGLU: NW / 2 gate + NW / 2 up); RTW: row tiles per wave.
-template <int MODE, bool SCALED, int NW, int RTW>
+// One 1 KiB tile from memory straight into LDS: lane l's 16 bytes at gbase + voff land at lds_off + 16 l.  The
+// instruction has no destination register; what it writes becomes readable after wait_tiles() and a barrier.  (The
+// builtin for it makes the compiler wait for all such loads before every LDS read.)
+__device__ inline void tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(gbase)
+               : "memory"); // nothing the compiler emits here uses m0
+}
+// The same for lanes 0 .. 31 alone: half a tile.  (Called with all lanes active.)
+__device__ inline void half_tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, 0xffffffff\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
+               ::"s"(lds_off), "v"(voff), "s"(gbase) : "memory");
+}
+// Waits until at most `left` of this wave's tile loads are still under way and all its LDS reads have returned.
+template <int left>
+__device__ inline void wait_tiles() {
+  static_assert(left >= 0 && left < 64, "six bits of vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(left) : "memory");
+}
+__device__ inline void meet_waves() { asm volatile("s_barrier" ::: "memory"); }
+
+template <typename F, int... J>
+__device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
+  (f(std::integral_constant<int, J>{}), ...);
+}
+
+// RP2 x NP2: pairs of row tiles x pairs of out-tiles per wave; WR x WC: the workgroup's wave grid (WR * WC = 8).
+// SwiGLU: an out-tile pair is (gate tile, up tile) of the same 16 features.
+template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D>
 __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32_t row_tiles) {
-  constexpr int KS = WIDE_TPS / NW; // k-steps per stage
-  constexpr int P = MODE == GEMM_SWIGLU ? NW / 2 : NW;
-  static_assert(KS * NW == WIDE_TPS && (KS == 2 || KS == 4), "a pass over the activation registers is 1 or 2 stages");
-  __shared__ u32x4 buf[2][WIDE_TPS][64]; // 48 KiB
+  constexpr int RB = 2 * RP2 * WR, NW = 2 * NP2 * WC; // row tiles and out-tiles of the workgroup
+  constexpr int T = RB + NW;                          // tiles per k-step
+  constexpr int C = (T + WIDE_WAVES - 1) / WIDE_WAVES;      // tile loads of a wave per k-step
+  constexpr bool HALVES = T % WIDE_WAVES != 0;              // the last of them is half a tile
+  static_assert(T % WIDE_WAVES == 0 || T % WIDE_WAVES == WIDE_WAVES / 2, "whole and half tiles only");
+  static_assert(WR * WC == WIDE_WAVES && D * T <= 160 && D >= 3, "the ring is the compute unit's LDS at most");
+  extern __shared__ u32x4 ring[]; // [D][T][64]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // in a scalar register: what depends on it alone is uniform
+  const int wr = wave / WC, wc = wave % WC;
   const int KT = g.K / 32;
   // linear id -> (k-split, out-tile group, row block): ids that differ by 8 share an XCD, so the row blocks of
   // a group are 8 apart; groups are numbered (id % 8) + 8 * (id / (8 * row_blocks))
-  const int row_blocks = (row_tiles + WIDE_WAVES * RTW - 1) / (WIDE_WAVES * RTW);
+  const int row_blocks = (row_tiles + RB - 1) / RB;
   const int per_split = ((g.groups + 7) / 8) * 8 * row_blocks;
   const int split = blockIdx.x / per_split, id = blockIdx.x - split * per_split;
   const int bx = (id & 7) + 8 * (id / (8 * row_blocks));
   const int rb = (id >> 3) % row_blocks;
   if (bx >= g.groups) return; // uniform over the workgroup (group count not a multiple of 8)
-  // this split's k-steps [k0, k1): equal shares rounded up to whole stages
-  int per_k = (KT + g.splits - 1) / g.splits;
-  per_k = (per_k + KS - 1) / KS * KS;
+  const int per_k = (KT + g.splits - 1) / g.splits;
   const int k0 = split * per_k, k1 = k0 + per_k < KT ? k0 + per_k : KT;
+  const int nk = k1 - k0; // >= 1: the launch leaves no split empty
   const int tile0 = bx * g.part_q + (bx < g.part_rem ? bx : g.part_rem);
   const int n_valid = g.part_q + (bx < g.part_rem ? 1 : 0);
 
-  // the WIDE_TPW weight tiles of a stage this wave fetches: stage tile j = wave + 8 i is (k-step j / NW, tile j % NW)
-  const u32x4 *wsrc[WIDE_TPW];
-  int wk[WIDE_TPW];
+  // The tiles of a k-step this wave loads: tile j = wave + 8 i, the first RB of them row tiles, then out-tiles (with
+  // T = 8 c + 4 the last four are loaded by two waves each, half by half: every wave then has the same number of loads
+  // to wait for).  Row tiles past the last and unused out-tile slots load a neighbour again; nothing of theirs is stored.
+  uint64_t src[C];
+  uint32_t dst[C], step[C];
 #pragma unroll
-  for (int i = 0; i < WIDE_TPW; ++i) {
-    const int j = wave + WIDE_WAVES * i, u = j % NW;
-    wk[i] = j / NW;
-    const int uu = u < P ? u : u - P;   // SwiGLU: tiles P .. 2P-1 come from the up matrix
-    int t = tile0 + (uu < n_valid ? uu : 0);
-    int sidx = 0;
-    while (sidx + 1 < g.n_seg && t >= g.seg[sidx].out_tiles) {
-      t -= g.seg[sidx].out_tiles;
-      ++sidx;
+  for (int i = 0; i < C; ++i) {
+    const bool half = HALVES && i == C - 1;
+    const int j = WIDE_WAVES * i + (half ? wave >> 1 : wave);
+    if (j < RB) {
+      int rt = rb * RB + j;
+      rt = rt < row_tiles ? rt : row_tiles - 1;
+      src[i] = reinterpret_cast<uint64_t>(g.a_frag) + ((uint64_t)k0 * row_tiles + rt) * 1024;
+      step[i] = (uint32_t)row_tiles * 1024;
+    } else {
+      const int u = j - RB;
+      const int uu = MODE == GEMM_SWIGLU ? u >> 1 : u;
+      int t = tile0 + (uu < n_valid ? uu : 0);
+      int sidx = 0;
+      while (sidx + 1 < g.n_seg && t >= g.seg[sidx].out_tiles) {
+        t -= g.seg[sidx].out_tiles;
+        ++sidx;
+      }
+      const bf16_t *mat = (MODE == GEMM_SWIGLU && (u & 1)) ? g.w2 : g.seg[sidx].w;
+      src[i] = reinterpret_cast<uint64_t>(mat) + ((uint64_t)t * KT + k0) * 1024;
+      step[i] = 1024;
     }
-    const bf16_t *mat = (MODE == GEMM_SWIGLU && u >= P) ? g.w2 : g.seg[sidx].w;
-    wsrc[i] = reinterpret_cast<const u32x4 *>(mat) + (size_t)t * KT * 64 + lane;
+    dst[i] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)ring + j * 1024;
+    if (half) {
+      src[i] += (wave & 1) * 512;
+      dst[i] += (wave & 1) * 512;
+    }
   }
-  const int n_stages = (k1 - k0 + KS - 1) / KS;
-  u32x4 wreg[2][WIDE_TPW]; // two weight stages in flight in registers
-  auto load_stage = [&](int slot, int s) { // unconditional, clamped: the counts in flight stay compile-time facts
-#pragma unroll
-    for (int i = 0; i < WIDE_TPW; ++i) {
-      int kt = k0 + s * KS + wk[i];
-      kt = kt < k1 ? kt : k1 - 1;
-      wreg[slot][i] = __builtin_nontemporal_load(wsrc[i] + (size_t)kt * 64);
-    }
-  };
-  // tiles of k-steps past the end of the k range go to LDS as zeros, so the multiply loop needs no tail case
-  auto store_stage = [&](int slot, int b, int s) {
-#pragma unroll
-    for (int i = 0; i < WIDE_TPW; ++i) {
-      const bool in_range = k0 + s * KS + wk[i] < k1;
-      buf[b][wave + WIDE_WAVES * i][lane] = in_range ? wreg[slot][i] : u32x4{0u, 0u, 0u, 0u};
-    }
+  const uint32_t voff = lane * 16;
+  auto load = [&](int i, uint32_t slot_off) { // the i-th load of the next k-step, into the ring slot at this offset
+    if (HALVES && i == C - 1) half_tile_to_lds(dst[i] + slot_off, voff, src[i]);
+    else tile_to_lds(dst[i] + slot_off, voff, src[i]);
+    src[i] += step[i];
   };
 
-  // MFMA shape: v_mfma_f32_32x32x16_bf16 (same rate per flop as the 16x16x32 form, half as many instructions and
-  // LDS reads per flop).  Its operands are rebuilt from the 16x32 fragment tiles by addressing
-  // alone: for k-half h of a k-step, lane l supplies 8 k-values 16 h + 8 (l / 32) .. + 7 of item l % 32, i.e.
-  // lane slot (l % 16) + 16 (2 h + l / 32) of the first (l % 32 < 16) or second tile of a pair.  A weight pair
-  // is out-tiles (2p, 2p + 1), or for SwiGLU (gate tile p, up tile p); an activation pair is two consecutive row
-  // tiles.  The 32 x 32 result leaves lane l with row l % 32 of the row pair and, in elements 4q .. 4q + 3,
-  // features 8 q + 4 (l / 32) .. + 3 of the 32 the weight pair spans.
-  constexpr int NP2 = NW / 2, RP2 = RTW / 2;
-  static_assert(NW % 2 == 0 && RTW % 2 == 0, "tiles are consumed in pairs");
+  // MFMA shape: v_mfma_f32_32x32x16_bf16 (same rate per flop as the 16x16x32 form, half as many instructions).  Its
+  // operands are rebuilt from the 16x32 fragment tiles by addressing alone: for k-half h of a k-step, lane l supplies
+  // 8 k-values 16 h + 8 (l / 32) .. + 7 of item l % 32, i.e. lane slot (l % 16) + 16 (2 h + l / 32) of the first
+  // (l % 32 < 16) or second tile of a pair.  The 32 x 32 result leaves lane l with row l % 32 of the row pair and, in
+  // elements 4q .. 4q + 3, features 8 q + 4 (l / 32) .. + 3 of the 32 the out-tile pair spans.
   const int half_sel = (lane >> 4) & 1, hb = lane >> 5;
-  const int frag_slot = (lane & 15) + 16 * hb; // + 32 for the second k-half
+  const int frag = half_sel * 64 + (lane & 15) + 16 * hb; // in 16-byte units; + 32 for the second k-half
+  const char *abase = reinterpret_cast<const char *>(ring + wr * (2 * RP2) * 64 + frag);
+  const char *wbase = reinterpret_cast<const char *>(ring + (RB + wc * (2 * NP2)) * 64 + frag);
 
-  // this wave's row tiles rt0 .. rt0 + RTW - 1; a short last block leaves some of them, or whole waves, without
-  // rows: those multiply the last tile again and store nothing
-  const int rt0 = (rb * WIDE_WAVES + wave) * RTW;
-  const bool wave_live = rt0 < row_tiles;
-  const u32x4 *abase = reinterpret_cast<const u32x4 *>(g.a_frag);
-  int aoff[RP2];
-#pragma unroll
-  for (int j = 0; j < RP2; ++j) {
-    const int rt = rt0 + 2 * j + half_sel;
-    aoff[j] = (rt < row_tiles ? rt : row_tiles - 1) * 64 + frag_slot;
-  }
-  u32x4 aq[WIDE_PA][RP2][2];
-  auto issue_a = [&](int slot, int kt) {
-    const int kc = kt < k1 ? kt : k1 - 1;
-#pragma unroll
-    for (int j = 0; j < RP2; ++j) {
-      aq[slot][j][0] = abase[(size_t)kc * row_tiles * 64 + aoff[j]];
-      aq[slot][j][1] = abase[(size_t)kc * row_tiles * 64 + aoff[j] + 32];
-    }
-  };
-  // LDS tile of pair p that this lane reads, relative to the k-step's first tile
-  int wsel[NP2];
-#pragma unroll
-  for (int p2 = 0; p2 < NP2; ++p2) wsel[p2] = MODE == GEMM_SWIGLU ? p2 + P * half_sel : 2 * p2 + half_sel;
-
-  // register slot of stage s is s & 1; at the top of iteration s the slots hold stages s + 1 and s + 2
-  load_stage(0, 0);
-#pragma unroll
-  for (int j = 0; j < WIDE_PA; ++j) issue_a(j, k0 + j);
-  load_stage(1, 1);
-  store_stage(0, 0, 0);
-  load_stage(0, 2);
   f32x16 acc[NP2][RP2];
 #pragma unroll
   for (int u = 0; u < NP2; ++u)
@@ -157,42 +152,93 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
     for (int j = 0; j < RP2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[u][j][e] = 0.f;
-  __syncthreads();
+  u32x4 wf[2][NP2][2], af[2][RP2][2]; // operands of the current and the next k-step
 
-  for (int s0 = 0; s0 < n_stages; s0 += 2) {
-#pragma unroll
-    for (int si = 0; si < 2; ++si) { // s & 1 == si: buffer, register slots and activation registers are static
-      const int s = s0 + si;
-      // the stage's weight pairs in order (k-step, pair), both k-halves of the next pair requested from LDS before
-      // the current pair is multiplied, so that a read has the MFMAs of another pair to land behind (two pairs
-      // ahead measured no faster)
-      u32x4 wc0 = buf[si][wsel[0]][frag_slot], wc1 = buf[si][wsel[0]][frag_slot + 32];
-#pragma unroll
-      for (int t = 0; t < KS * NP2; ++t) {
-        u32x4 wn0 = wc0, wn1 = wc1;
-        if (t + 1 < KS * NP2) {
-          const int kn = (t + 1) / NP2, pn = (t + 1) % NP2;
-          wn0 = buf[si][kn * NW + wsel[pn]][frag_slot];
-          wn1 = buf[si][kn * NW + wsel[pn]][frag_slot + 32];
-        }
-        __builtin_amdgcn_sched_barrier(0); // keep this order: left alone, the scheduler bunches the reads and spills
-        const int k = t / NP2, p2 = t % NP2;
-        const int slot = (si * KS + k) % WIDE_PA;
-#pragma unroll
-        for (int j = 0; j < RP2; ++j) acc[p2][j] = mfma32w(wc0, aq[slot][j][0], acc[p2][j]);
-#pragma unroll
-        for (int j = 0; j < RP2; ++j) acc[p2][j] = mfma32w(wc1, aq[slot][j][1], acc[p2][j]);
-        if (p2 + 1 == NP2) issue_a(slot, k0 + s * KS + k + WIDE_PA); // the k-step's activation registers are free
-        __builtin_amdgcn_sched_barrier(0);
-        wc0 = wn0;
-        wc1 = wn1;
-      }
-      store_stage(si ^ 1, si ^ 1, s + 1); // that buffer was last read before the previous barrier
-      load_stage(si ^ 1, s + 3);
-      __syncthreads(); // uniform: every wave runs every stage
+  constexpr int READS = 2 * (NP2 + RP2), MFMAS = 2 * NP2 * RP2;
+  constexpr int RPM = (READS + MFMAS - 2) / (MFMAS - 1); // operand reads behind an MFMA (1 where they fit, 2 cost 1 %)
+  auto read_frag = [&](int set, int i, uint32_t at) { // i-th of the READS operand reads of the k-step in ring slot `at`
+    const int h = i / (NP2 + RP2), r = i % (NP2 + RP2);
+    if (r < RP2) af[set][r][h] = *reinterpret_cast<const u32x4 *>(abase + at + (2 * r * 64 + 32 * h) * 16);
+    else wf[set][r - RP2][h] = *reinterpret_cast<const u32x4 *>(wbase + at + (2 * (r - RP2) * 64 + 32 * h) * 16);
+  };
+  // One k-step s in ring slot `slot` (a byte offset): its operands (set SET) were read during s - 1; the tiles of s + 1
+  // must have landed for every wave, and its own slot, which every wave has read, takes k-step s + D.  Of the
+  // min(s + D, nk) k-steps requested so far, those past s + 1 may stay under way.  STEADY: s + D < nk.
+  constexpr uint32_t SLOT = T * 1024;
+  uint32_t slot = 0;
+  auto k_step = [&](auto set_c, auto steady_c, int s) {
+    constexpr int SET = decltype(set_c)::value;
+    constexpr bool STEADY = decltype(steady_c)::value;
+    if constexpr (STEADY) {
+      wait_tiles<(D - 2) * C>();
+    } else {
+      const int under_way = nk - 2 - s;
+      if (under_way >= D - 2) wait_tiles<(D - 2) * C>();
+      else
+        for_each_step([&](auto j) {
+          constexpr int J = decltype(j)::value;
+          if (under_way == J) wait_tiles<J * C>();
+        }, std::make_integer_sequence<int, D - 2>{});
     }
+    meet_waves();
+    const uint32_t next = slot + SLOT < D * SLOT ? slot + SLOT : 0;
+#pragma unroll
+    for (int i = 0; i < MFMAS; ++i) {
+      const int h = i / (NP2 * RP2), p = (i / RP2) % NP2, j = i % RP2;
+      acc[p][j] = mfma32w(wf[SET][p][h], af[SET][j][h], acc[p][j]);
+#pragma unroll
+      for (int r = 0; r < READS; ++r)
+        if (r / RPM == i) read_frag(SET ^ 1, r, next);
+      __builtin_amdgcn_sched_barrier(0); // keep this order: left alone, the scheduler bunches the reads
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (i == 1 + c * ((MFMAS - 2) / C) && (STEADY || s + D < nk)) load(c, slot);
+    }
+    slot = next;
+  };
+
+#pragma unroll
+  for (int s = 0; s < D; ++s)
+    if (s < nk) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) load(c, s * SLOT);
+    }
+  if (nk >= D) wait_tiles<(D - 1) * C>();
+  else wait_tiles<0>();
+  meet_waves();
+#pragma unroll
+  for (int r = 0; r < READS; ++r) read_frag(0, r, 0);
+  constexpr std::integral_constant<int, 0> set0{};
+  constexpr std::integral_constant<int, 1> set1{};
+  int s = 0;
+  if (nk & 1) { // one k-step ahead of the pairs
+    if (nk - 2 >= D - 2) wait_tiles<(D - 2) * C>();
+    else wait_tiles<0>();
+    meet_waves();
+#pragma unroll
+    for (int i = 0; i < MFMAS; ++i) {
+      const int h = i / (NP2 * RP2), p = (i / RP2) % NP2, j = i % RP2;
+      acc[p][j] = mfma32w(wf[0][p][h], af[0][j][h], acc[p][j]);
+    }
+    if (D < nk) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) load(c, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < READS; ++r) read_frag(0, r, SLOT);
+    slot = SLOT;
+    s = 1;
   }
-  if (!wave_live) return;
+  for (; s + 2 <= nk - D; s += 2) {
+    k_step(set0, std::true_type{}, s);
+    k_step(set1, std::true_type{}, s + 1);
+  }
+  for (; s < nk; s += 2) {
+    k_step(set0, std::false_type{}, s);
+    k_step(set1, std::false_type{}, s + 1);
+  }
+  const int rt0 = rb * RB + wr * 2 * RP2;
+  if (rt0 >= row_tiles) return;
 
   // epilogue from registers
 #pragma unroll
@@ -217,7 +263,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
       for (int q = 0; q < (MODE == GEMM_SWIGLU ? 2 : 4); ++q) {
         // STORE: elements 4q .. 4q+3 are features 8 (q & 1) + 4 hb .. + 3 of out-tile 2 p2 + q / 2
         // SWIGLU: elements 4q .. (gate) and 8 + 4q .. (up) are features 8 q + 4 hb .. + 3 of tile p2
-        const int u = MODE == GEMM_SWIGLU ? p2 : 2 * p2 + (q >> 1);
+        const int u = MODE == GEMM_SWIGLU ? wc * NP2 + p2 : 2 * (wc * NP2 + p2) + (q >> 1);
         if (u >= n_valid) continue;
         const int o = (tile0 + u) * 16 + 8 * (MODE == GEMM_SWIGLU ? q : (q & 1)) + 4 * hb;
         const f32x16 &a = acc[p2][j];
@@ -279,22 +325,33 @@ bool gemm_wide_supported(int32_t n, int32_t K, int32_t O) {
   return n >= 1 && n <= WIDE_MAX_ROWS && K % 32 == 0 && K >= 64 && O % 32 == 0;
 }
 
-template <int NW, int RTW>
+template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D>
+static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
+  constexpr int smem = D * (2 * RP2 * WR + 2 * NP2 * WC) * 1024;
+  static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
+  if (!once) return hipErrorInvalidValue;
+  return launch(k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D>, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
+}
+template <int RP2, int NP2, int WR, int WC, int D>
 static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
-  const dim3 block(WIDE_WAVES * 64);
-  if (g.mode == GEMM_SWIGLU) {
-    if (g.row_ssq != nullptr) return launch(k_gemm_wide<GEMM_SWIGLU, true, NW, RTW>, dim3(grid), block, 0, st, tm, g, row_tiles);
-    return launch(k_gemm_wide<GEMM_SWIGLU, false, NW, RTW>, dim3(grid), block, 0, st, tm, g, row_tiles);
-  }
-  if (g.row_ssq != nullptr) return launch(k_gemm_wide<GEMM_STORE, true, NW, RTW>, dim3(grid), block, 0, st, tm, g, row_tiles);
-  return launch(k_gemm_wide<GEMM_STORE, false, NW, RTW>, dim3(grid), block, 0, st, tm, g, row_tiles);
+  if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D>(g, row_tiles, grid, st, tm);
+  if (g.row_ssq != nullptr) return launch_ks<GEMM_STORE, true, RP2, NP2, WR, WC, D>(g, row_tiles, grid, st, tm);
+  return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D>(g, row_tiles, grid, st, tm);
 }
 
-// Chooses the workgroup shape, fills the tile assignment and launches.  g.n is the total row count
+// The workgroup shapes: row tiles x out-tiles, and the measured us of one k-step when every compute unit has a
+// workgroup (see the header).  The smallest leaves room for two workgroups on a compute unit.
+struct WideShape {
+  int rb, nw;
+  double step_us;
+};
+static constexpr WideShape WIDE_SHAPES[5] = {{8, 8, 0.31}, {8, 12, 0.42}, {16, 8, 0.45}, {16, 12, 0.585}, {16, 16, 0.70}};
+
+// Chooses the workgroup shape and the K-splits, fills the tile assignment and launches.  g.n is the total row count
 // (<= WIDE_MAX_ROWS); a_frag / h_frag use ceil(n / 16) row tiles; the RMS scale takes at most 8 partial sums per
-// row.  max_splits > 1 (plain store without scale only): y[s] = y + s * split_stride receives the partial sum
-// of k-range s, and *out_splits how many the launch used.
-//   Shapes: 12 out-tiles x 2 row tiles per wave, 6 x 4 (one workgroup spans 512 rows) or 6 x 2.
+// row and SwiGLU needs it.  max_splits > 1 (plain store without scale only): y[s] = y + s * split_stride receives the
+// partial sum of k-range s, and *out_splits how many the launch used.
 hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *out_splits, hipStream_t st, KernelTimer tm) {
   GemmArgs g = args;
   if (g.n < 1 || g.n > WIDE_MAX_ROWS || g.K % 32 != 0 || g.K < 64 || (g.row_ssq != nullptr && g.n_ssq > 8))
@@ -302,40 +359,32 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   int32_t total = 0;
   for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
+  if (g.mode == GEMM_SWIGLU && g.row_ssq == nullptr) return hipErrorInvalidValue;
   const bool may_split = g.mode == GEMM_STORE && g.rope.q == nullptr && g.row_ssq == nullptr && max_splits > 1;
   const int row_tiles = (g.n + 15) / 16;
   const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles
   auto groups_of = [&](int nw) { return (total + nw / unit - 1) / (nw / unit); };
-  // Shape and K-splits by a cost model of what bounds the kernel, the KiB a workgroup pulls per k-step (its row
-  // tiles and its weight tiles, 1 KiB each) times its k-steps, per round of 256 workgroups, plus a fixed cost
-  // per round (ramp and epilogue, in the same unit) and what the partial sums of a K-split cost to write and
-  // re-read.
+  // Cost in us: rounds of 256 workgroups, each its k-steps plus 8 for ramp and epilogue, plus what a partial sum costs
+  // to write (3.5 TB/s) and to read back (5 TB/s).
   const int KT = g.K / 32;
-  int nw = 12, rtw = 2, best_splits = 1;
+  int shape = 0, best_splits = 1;
   double best = 1e30;
-  static const int cand[3][2] = {{12, 2}, {6, 4}, {6, 2}};
-  for (int c = 0; c < 3; ++c) {
-    const int cnw = cand[c][0], crtw = cand[c][1], ks = WIDE_TPS / cnw;
-    if (row_tiles <= 16 && crtw == 4) continue;
-    const int rb = (row_tiles + WIDE_WAVES * crtw - 1) / (WIDE_WAVES * crtw);
-    const int rows_wg = row_tiles < WIDE_WAVES * crtw ? row_tiles : WIDE_WAVES * crtw;
+  for (int v = 0; v < 5; ++v) {
+    const int row_blocks = (row_tiles + WIDE_SHAPES[v].rb - 1) / WIDE_SHAPES[v].rb;
     for (int sp = 1; sp <= (may_split ? max_splits : 1); ++sp) {
-      int per_k = (KT + sp - 1) / sp;
-      per_k = (per_k + ks - 1) / ks * ks;
-      if (sp > 1 && (per_k < 8 * ks || (sp - 1) * per_k >= KT)) continue; // at least 8 stages, no empty share
-      const int wgs = groups_of(cnw) * rb * sp;
-      const int rounds = (wgs + 255) / 256;
-      double cost = rounds * ((double)per_k * (rows_wg + cnw) + 150.0);
-      if (sp > 1) cost += sp * 160.0 * row_tiles / 32.0;
+      const int per_k = (KT + sp - 1) / sp;
+      if (sp > 1 && (per_k < 16 || (sp - 1) * per_k >= KT)) continue; // no empty share, none that is all ramp
+      const int rounds = (groups_of(WIDE_SHAPES[v].nw) * row_blocks * sp + 255) / 256;
+      double cost = rounds * (per_k * WIDE_SHAPES[v].step_us + 8.0);
+      if (sp > 1) cost += sp * (64.0 * g.n * total) * (1 / 3.5e6 + 1 / 5e6);
       if (cost < best) {
         best = cost;
-        nw = cnw;
-        rtw = crtw;
+        shape = v;
         best_splits = sp;
       }
     }
   }
-  const int row_blocks = (row_tiles + WIDE_WAVES * rtw - 1) / (WIDE_WAVES * rtw);
+  const int nw = WIDE_SHAPES[shape].nw, row_blocks = (row_tiles + WIDE_SHAPES[shape].rb - 1) / WIDE_SHAPES[shape].rb;
   g.total_tiles = total;
   g.tiles_per_wg = nw / unit;
   g.groups = groups_of(nw);
@@ -344,9 +393,13 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   g.splits = best_splits;
   if (out_splits != nullptr) *out_splits = g.splits;
   const unsigned grid = (unsigned)(((g.groups + 7) / 8) * 8 * row_blocks * g.splits);
-  if (nw == 12) return launch_shape<12, 2>(g, row_tiles, grid, st, tm);
-  if (rtw == 2) return launch_shape<6, 2>(g, row_tiles, grid, st, tm);
-  return launch_shape<6, 4>(g, row_tiles, grid, st, tm);
+  switch (shape) {
+  case 0: return launch_shape<1, 2, 4, 2, 5>(g, row_tiles, grid, st, tm);
+  case 1: return launch_shape<1, 3, 4, 2, 7>(g, row_tiles, grid, st, tm);
+  case 2: return launch_shape<2, 2, 4, 2, 6>(g, row_tiles, grid, st, tm);
+  case 3: return launch_shape<2, 3, 4, 2, 5>(g, row_tiles, grid, st, tm);
+  }
+  return launch_shape<2, 4, 4, 2, 5>(g, row_tiles, grid, st, tm);
 }
 
 } // namespace tr

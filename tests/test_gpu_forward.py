@@ -364,6 +364,30 @@ def test_linear_bf16_packed_matches_oracle_matmul(n, K_, O_, splits):
     assert err < 2e-5 * np.sqrt(K_)                           # fp32 accumulation of K products of O(1/sqrt(K))
 
 
+@pytest.mark.parametrize("n,K_,O_,splits", [# workgroups of 8 x 8 tiles: fewer k-steps than ring slots, an odd number
+                                            (129, 64, 64, 1), (135, 96, 256, 1), (200, 160, 64, 1), (257, 1120, 8224, 2),
+                                            (512, 4096, 4096, 4),                 # 8 x 8, split over k
+                                            (511, 4096, 12288, 1), (129, 1056, 24576, 1),  # 8 x 12
+                                            (500, 96, 12320, 1), (511, 4096, 4640, 3),  # 16 x 8
+                                            (505, 1056, 16416, 1), (385, 96, 20512, 1),                        # 16 x 12
+                                            (505, 736, 28704, 1), (400, 224, 32000, 1), (512, 64, 28704, 1)])  # 16 x 16
+def test_wide_projection_edges(n, K_, O_, splits):
+    """Prompt-ingestion projection in every workgroup shape its launcher has: k ranges shorter than, equal to and past
+    the LDS ring, odd and even numbers of k-steps, last row block and last out-tile group partly empty."""
+    require_gpu()
+    say("wide projection", n, K_, O_, splits)
+    x = synth.normal_tensor((n, K_), 1.0, seed=n + K_, dtype=torch.bfloat16).cuda()
+    w = synth.uniform_tensor((O_, K_), float(np.sqrt(3.0 / K_)), seed=9, tensor_id=O_, dtype=torch.bfloat16).cuda()
+    ctx = tr.Context(16, 8, [-1], [-1], 1)
+    y = torch.full((n, O_), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(((n + 15) // 16 * 16 * K_ * 2 + 512 + splits * n * O_ * 4 + 512), dtype=torch.uint8, device="cuda")
+    ctx.op_linear(x, tr.pack_weight(w), y, ws, packed=True, splits=splits)
+    ref = x.double() @ w.double().T
+    # K products of O(1/sqrt(K)), each rounded to 2^-24 of the running sum on its way into it
+    assert float((y.double() - ref).abs().max()) < 2e-5 * np.sqrt(K_)
+    ctx.close()
+
+
 def test_linear_row_limits():
     """Packed weights take up to TR_PREFILL_ROWS rows (the prompt-ingestion kernel above TR_MAX_NODES), row-major
     ones TR_MAX_NODES; one more is TR_EINVAL, on the host, before any launch."""
