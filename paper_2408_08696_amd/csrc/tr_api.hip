@@ -231,7 +231,7 @@ tr_status tr_workspace_bytes(const tr_ctx *c, const tr_model *m, size_t *bytes) 
   if (c == nullptr || bytes == nullptr) return TR_EINVAL;
   tr_status s = check_model(m);
   if (s != TR_OK) return s;
-  *bytes = plan_workspace(*m).total;
+  *bytes = plan_workspace(*m, NPW_MOST).total;
   return TR_OK;
 }
 
@@ -302,10 +302,15 @@ tr_status tr_prefill(tr_ctx *c, const tr_model *m, tr_kv *kv, const int32_t *d_t
   if ((int64_t)kv->len_bound + n_tokens > kv->capacity) return TR_ECAPACITY;
   if (ws_bytes < plan_workspace(*m).total) return TR_ECAPACITY;
   hipStream_t st = as_stream(stream);
-  const int rows = prefill_rows(*m, *kv);
+  const int most = prefill_rows(*m, *kv, ws_bytes);
+  int rows = most;
+  if (most > NP && n_tokens > most) { // passes of about the same size: a short last one would stream all weights for a few rows
+    const int passes = (n_tokens + most - 1) / most;
+    rows = ((n_tokens + passes - 1) / passes + 255) / 256 * 256; // whole row blocks of the projection kernel
+  }
   for (int lo = 0; lo < n_tokens; lo += rows) {
     const int n = n_tokens - lo < rows ? n_tokens - lo : rows;
-    if (run_prefill_pass(*m, *kv, c->chain, n, d_tokens + lo, ws, st) != hipSuccess) return TR_EHIP;
+    if (run_prefill_pass(*m, *kv, c->chain, n, most, d_tokens + lo, ws, st) != hipSuccess) return TR_EHIP;
     if (launch_advance_len(kv->d_len, n, st) != hipSuccess) return TR_EHIP;
     kv->len_bound += n;
   }

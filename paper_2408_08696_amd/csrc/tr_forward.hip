@@ -17,12 +17,12 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static bool packed_supported(const tr_model &m);
 
-Workspace plan_workspace(const tr_model &m) {
+Workspace plan_workspace(const tr_model &m, int rows) {
   Workspace w;
   const bool generic = !packed_supported(m);
   const size_t esz = dtype_size(m.dtype);
   const size_t hq = (size_t)m.n_heads * m.head_dim;
-  const size_t R = generic ? NP : NPW; // rows of the activation buffers
+  const size_t R = generic ? NP : rows; // rows of the activation buffers
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
   w.x = take(R * m.d_model * 4);
@@ -34,8 +34,8 @@ Workspace plan_workspace(const tr_model &m) {
   w.logits = take((size_t)NP * m.vocab * 4);
   w.part_ml = take((size_t)ATTN_MAX_SPLITS * NP * m.n_heads * 2 * 4);
   w.part_acc = take((size_t)ATTN_MAX_SPLITS * NP * m.n_heads * m.head_dim * 4);
-  w.ypart = take((generic ? (size_t)GEMM_MAX_SPLITS * NP : (size_t)WIDE_MAX_SPLITS * NPW) * m.d_model * 4);
-  static_assert(WIDE_MAX_SPLITS * NPW >= GEMM_MAX_SPLITS * NP, "ypart serves both paths");
+  w.ypart = take((generic ? (size_t)GEMM_MAX_SPLITS * NP : (size_t)WIDE_PART_ROWS) * m.d_model * 4);
+  static_assert(WIDE_PART_ROWS >= GEMM_MAX_SPLITS * NP && WIDE_PART_ROWS >= NPW_MOST, "ypart serves both paths");
   w.ssq = take(R * ((m.d_model + 1023) / 1024) * 4);
   w.total = off;
   return w;
@@ -197,7 +197,7 @@ static hipError_t attention_dispatch(const tr_kv &kv, int32_t layer, int32_t H, 
   if (kv.layout == TR_KV_TILED) {
     return launch_attn_mfma((const bf16_t *)q, (const bf16_t *)Kl, (const bf16_t *)Vl, H, kv.n_kv_heads, kv.capacity,
                             n, tree.anc, kv.d_len, kv.len_bound + n, part_ml, part_acc, (bf16_t *)out, out_row_tiles,
-                            0, prof, st);
+                            prof, st);
   }
   return launch(k_attn_generic<T>, dim3(n, H), dim3(256), 0, st, prof_next(prof, PC_ATTN), q, Kl, Vl, H, kv.n_kv_heads,
                 kv.head_dim, kv.capacity, n, tree.anc, kv.d_len, out, out_row_tiles);
@@ -475,16 +475,14 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
 }
 
 // ---------------------------------------------------------------------------------------------
-// Prompt ingestion on the packed path: up to NPW rows per pass.  The projections take all rows at once
-// (tr_gemm_wide.hip: the layer's weights are read from memory once per pass instead of once per 128 rows);
-// attention runs per block of 128 rows with the chain masks, each block seeing the committed length plus the
-// rows before it as its prefix (their keys and values are in the cache by then: the Q/K/V projection of the
-// whole pass precedes it).  Same arithmetic per row as forward_packed with one K-split.
+// Prompt ingestion on the packed path: up to `most` rows per pass (what the workspace was sized for).  The projections
+// (tr_gemm_wide.hip) and the attention (tr_attn_causal.hip; the Q/K/V projection has cached the keys and values of the
+// whole pass by then) take all rows in one launch each.  Same arithmetic per row as forward_packed with one K-split.
 // ---------------------------------------------------------------------------------------------
-static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n, const int32_t *tok,
+static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, int32_t most, const int32_t *tok,
                                unsigned char *ws, hipStream_t st) {
   typedef bf16_t T;
-  const Workspace w = plan_workspace(m);
+  const Workspace w = plan_workspace(m, most);
   const int d = m.d_model, H = m.n_heads, Hkv = m.n_kv_heads, hd = m.head_dim, F = m.d_ffn;
   const int hq = H * hd, hk = Hkv * hd;
   const int RT = (n + 15) / 16;
@@ -499,7 +497,8 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, const TreeDev
   float *ssq = (float *)(ws + w.ssq);
   const int nch = (d + NORM_CHUNK - 1) / NORM_CHUNK;
   const KernelTimer no_timer{};
-  const size_t ystride = (size_t)NPW * d;
+  const size_t ystride = (size_t)RT * 16 * d; // the fewer rows a pass has, the more partial sums fit ypart
+  const int max_splits = WIDE_PART_ROWS / (RT * 16) < WIDE_MAX_SPLITS ? WIDE_PART_ROWS / (RT * 16) : WIDE_MAX_SPLITS;
 
   TR_TRY(launch(k_embed_frag, dim3(RT * 16, nch + 1), dim3(128), 0, st, no_timer, (const T *)m.embed, m.vocab, tok,
                 (const int32_t *)nullptr, kv.d_len, hd, m.rope_theta, x, rope, (const T *)m.layers[0].attn_norm, n, d, RT,
@@ -525,18 +524,14 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, const TreeDev
       TR_TRY(launch_gemm_wide(g, 1, nullptr, st));
     }
     if (l == m.n_layers - 1) break; // ingestion only needs the cache: nothing reads the last layer's output
-    for (int r0 = 0; r0 < n; r0 += NP) {
-      const int nb = n - r0 < NP ? n - r0 : NP;
-      TR_TRY(launch_attn_mfma(q + (size_t)r0 * hq, (const T *)kv.k + (size_t)l * lsz, (const T *)kv.v + (size_t)l * lsz, H,
-                              Hkv, kv.capacity, nb, chain.anc, kv.d_len, kv.len_bound + r0 + nb,
-                              (float *)(ws + w.part_ml), (float *)(ws + w.part_acc), attn, RT, r0, nullptr, st));
-    }
+    TR_TRY(launch_attn_causal(q, (const T *)kv.k + (size_t)l * lsz, (const T *)kv.v + (size_t)l * lsz, H, Hkv, kv.capacity, n,
+                              kv.d_len, attn, RT, st));
     {
       GemmArgs g{};
       g.a_frag = attn; g.n = n; g.K = hq;
       g.seg[0] = GemmSeg{(const T *)lw.wo, d / 16};
       g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      TR_TRY(launch_gemm_wide(g, WIDE_MAX_SPLITS, &pending, st));
+      TR_TRY(launch_gemm_wide(g, max_splits, &pending, st));
     }
     TR_TRY(add_norm(lw.ffn_norm));
     {
@@ -552,7 +547,7 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, const TreeDev
       g.a_frag = hbuf; g.n = n; g.K = F;
       g.seg[0] = GemmSeg{(const T *)lw.w_down, d / 16};
       g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      TR_TRY(launch_gemm_wide(g, WIDE_MAX_SPLITS, &pending, st));
+      TR_TRY(launch_gemm_wide(g, max_splits, &pending, st));
     }
   }
   return hipSuccess;
@@ -563,11 +558,14 @@ static bool wide_supported(const tr_model &m, const tr_kv &kv) {
          m.d_model >= 64 && m.d_ffn >= 64;
 }
 
-int32_t prefill_rows(const tr_model &m, const tr_kv &kv) { return wide_supported(m, kv) ? NPW : NP; }
+int32_t prefill_rows(const tr_model &m, const tr_kv &kv, size_t ws_bytes) {
+  if (!wide_supported(m, kv)) return NP;
+  return ws_bytes >= plan_workspace(m, NPW_MOST).total ? NPW_MOST : NPW;
+}
 
-hipError_t run_prefill_pass(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n, const int32_t *d_tokens,
-                            void *ws, hipStream_t st) {
-  if (n > NP && wide_supported(m, kv) && n <= NPW) return forward_wide(m, kv, chain, n, d_tokens, (unsigned char *)ws, st);
+hipError_t run_prefill_pass(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n, int32_t most,
+                            const int32_t *d_tokens, void *ws, hipStream_t st) {
+  if (n > NP && wide_supported(m, kv) && n <= most) return forward_wide(m, kv, n, most, d_tokens, (unsigned char *)ws, st);
   if (n > NP) return hipErrorInvalidValue;
   return run_forward(m, kv, chain, n, d_tokens, nullptr, ws, nullptr, st);
 }

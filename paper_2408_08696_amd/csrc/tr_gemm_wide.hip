@@ -41,26 +41,11 @@ __device__ inline f32x16 mfma32w(const u32x4 &a, const u32x4 &b, f32x16 c) {
 
 constexpr int WIDE_WAVES = 8;
 
-// One 1 KiB tile from memory straight into LDS: lane l's 16 bytes at gbase + voff land at lds_off + 16 l.  The
-// instruction has no destination register; what it writes becomes readable after wait_tiles() and a barrier.  (The
-// builtin for it makes the compiler wait for all such loads before every LDS read.)
-__device__ inline void tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(gbase)
-               : "memory"); // nothing the compiler emits here uses m0
-}
-// The same for lanes 0 .. 31 alone: half a tile.  (Called with all lanes active.)
+// tile_to_lds for lanes 0 .. 31 alone: half a tile.  (Called with all lanes active.)
 __device__ inline void half_tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
   asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, 0xffffffff\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
                ::"s"(lds_off), "v"(voff), "s"(gbase) : "memory");
 }
-// Waits until at most `left` of this wave's tile loads are still under way and all its LDS reads have returned.
-template <int left>
-__device__ inline void wait_tiles() {
-  static_assert(left >= 0 && left < 64, "six bits of vmcnt");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(left) : "memory");
-}
-__device__ inline void meet_waves() { asm volatile("s_barrier" ::: "memory"); }
-
 template <typename F, int... J>
 __device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
   (f(std::integral_constant<int, J>{}), ...);

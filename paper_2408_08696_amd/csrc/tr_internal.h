@@ -64,8 +64,10 @@ struct TreeDev {
 };
 
 // Workspace carve-up (byte offsets, all 256-aligned).  Buffers are sized for NP = TR_MAX_NODES rows; for models
-// the packed path serves, the activation buffers (x, xn, q, attn, h, rope, ssq, and ypart as one complete sum)
-// hold NPW rows, which is what one prompt-ingestion pass takes.
+// the packed path serves, the activation buffers (x, xn, q, attn, h, rope, ssq) hold the `rows` of one prompt-ingestion
+// pass and ypart WIDE_PART_ROWS.  NPW rows are what every workspace must have; tr_workspace_bytes asks for NPW_MOST,
+// enough for whole rounds of the projections' largest workgroup shape at every width (4095 tokens of 8 70B-wide layers:
+// 50.7 ms in passes of 512 rows, 40.8 in passes of 2048 with their attention in one launch), and a pass takes as many rows as its workspace was sized for.
 struct Workspace {
   size_t x;        // float  [NP, d]            residual stream
   size_t xn;       // T      [NP, d]            normalised activations (packed path)
@@ -82,10 +84,12 @@ struct Workspace {
 };
 constexpr int NP = TR_MAX_NODES;
 constexpr int NPW = TR_PREFILL_ROWS;
+constexpr int NPW_MOST = 2048;
+constexpr int WIDE_PART_ROWS = 2048; // a pass of n rows keeps up to WIDE_PART_ROWS / n partial sums
 constexpr int ATTN_MAX_SPLITS = 16;
 constexpr int GEMM_MAX_SPLITS = 4;
 
-Workspace plan_workspace(const tr_model &m);
+Workspace plan_workspace(const tr_model &m, int rows = NPW);
 
 // ---------------------------------------------------------------------------------------------
 // optional per-kernel timing.  While enabled, every kernel of the step is launched with a start and a
@@ -168,11 +172,11 @@ hipError_t launch_stream(const void *src, void *dst, size_t bytes, hipStream_t s
 // Runs rows `tokens` through the model.  `write_logits` may be NULL (no LM head).
 hipError_t run_forward(const tr_model &m, const tr_kv &kv, const TreeDev &tree, int32_t n,
                        const int32_t *d_tokens, float *write_logits, void *ws, Profiler *prof, hipStream_t s);
-// Prompt ingestion: rows one pass may take for this model and cache (NPW on the packed path with a tiled cache,
-// else NP), and the pass itself: n consecutive prompt tokens, causal, keys / values appended at the committed
-// length (which the caller advances afterwards), no logits.
-int32_t prefill_rows(const tr_model &m, const tr_kv &kv);
-hipError_t run_prefill_pass(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n,
+// Prompt ingestion: rows one pass may take for this model, cache and workspace size (NPW_MOST or NPW on the packed path
+// with a tiled cache, else NP), and the pass itself: n <= `most` consecutive prompt tokens, causal, keys / values appended
+// at the committed length (which the caller advances afterwards), no logits.
+int32_t prefill_rows(const tr_model &m, const tr_kv &kv, size_t ws_bytes);
+hipError_t run_prefill_pass(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n, int32_t most,
                             const int32_t *d_tokens, void *ws, hipStream_t s);
 hipError_t run_tree_attention(const tr_kv &kv, int32_t layer, int32_t H, const TreeDev &tree,
                               const void *d_q, void *d_out, void *ws, hipStream_t s);

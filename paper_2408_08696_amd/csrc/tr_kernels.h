@@ -23,6 +23,21 @@ __host__ __device__ inline size_t act_frag_index(int r, int k, int row_tiles) {
   return ((((size_t)(k >> 5) * row_tiles + (r >> 4)) * 64) + (r & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
 }
 
+// One 1 KiB tile from memory straight into LDS: lane l's 16 bytes at gbase + voff land at lds_off + 16 l.  The
+// instruction has no destination register; what it writes becomes readable after wait_tiles() and a barrier.  (The
+// builtin for it makes the compiler wait for all such loads before every LDS read.)
+__device__ inline void tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(gbase)
+               : "memory"); // nothing the compiler emits here uses m0
+}
+// Waits until at most `left` of this wave's tile loads are still under way and all its LDS reads have returned.
+template <int left>
+__device__ inline void wait_tiles() {
+  static_assert(left >= 0 && left < 64, "six bits of vmcnt");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(left) : "memory");
+}
+__device__ inline void meet_waves() { asm volatile("s_barrier" ::: "memory"); }
+
 struct GemmSeg {
   const bf16_t *w;   // packed weight matrix
   int32_t out_tiles; // its out_features / 16
@@ -87,7 +102,7 @@ hipError_t launch_gemm_mfma(const GemmArgs &g, hipStream_t st, KernelTimer tm = 
 // Prompt ingestion: the same contraction and epilogues for up to WIDE_MAX_ROWS rows per launch (tr_gemm_wide.hip);
 // a_frag / h_frag span ceil(n / 16) row tiles, rope rows are indexed by row; a plain store may be split over k
 // into up to max_splits partial sums split_stride floats apart (*out_splits receives the count used).
-constexpr int WIDE_MAX_ROWS = NPW;
+constexpr int WIDE_MAX_ROWS = NPW_MOST;
 constexpr int WIDE_MAX_SPLITS = 4;
 bool gemm_wide_supported(int32_t n, int32_t K, int32_t O);
 hipError_t launch_gemm_wide(const GemmArgs &g, int32_t max_splits, int32_t *out_splits, hipStream_t st,
@@ -126,11 +141,13 @@ int attn_heads_per_wg(int32_t H, int32_t Hkv, int32_t n);
 int attn_choose_splits(int32_t head_groups, int32_t len_bound);
 // true: one launch without key splits or merge pass (short sequences); then the two values above do not apply
 bool attn_one_launch(int32_t H, int32_t Hkv, int32_t len_bound);
-// row0 (prompt ingestion in blocks of rows): the rows are rows row0 .. row0 + n - 1 of a longer pass whose
-// keys and values are already cached; they see the committed length plus row0 positions as prefix, node j of
-// this launch sits at that prefix length + j, and with out_row_tiles > 0 the output lands at row row0 + j.
 hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
                             int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
-                            float *part_acc, bf16_t *out, int32_t out_row_tiles, int32_t row0, Profiler *prof, hipStream_t st);
+                            float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st);
+
+// Prompt ingestion (tr_attn_causal.hip): n consecutive rows behind the committed length, row r sees the positions up to
+// its own; the keys and values of all of them are cached already.  out in fragment order over out_row_tiles row tiles.
+hipError_t launch_attn_causal(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
+                              int32_t n, const int32_t *d_len, bf16_t *out, int32_t out_row_tiles, hipStream_t st);
 
 } // namespace tr
