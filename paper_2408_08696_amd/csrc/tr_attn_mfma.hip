@@ -400,29 +400,31 @@ __global__ __launch_bounds__(ATT1_WAVES * 64) void k_attn_tile(const bf16_t *__r
 // out[node, h, :] = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - max m), o_s the split's normalised
 // output; splits without visible keys (l_s == 0) contribute nothing.  Block (8 nodes, head), 32 threads x
 // 4 features per node; all loads of a thread are issued before any arithmetic.
+template <int MOST>
 __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part_ml, const float *__restrict__ part_acc,
-                                                    int32_t H, int32_t n, int32_t nsplit, bf16_t *__restrict__ out,
+                                                    int32_t part_rows, int32_t H, int32_t n, int32_t nsplit,
+                                                    bf16_t *__restrict__ out,
                                                     int32_t out_row_tiles) {
   const int node = blockIdx.x * 8 + (threadIdx.x >> 5), h = blockIdx.y, d = (threadIdx.x & 31) * 4;
   if (node >= n) return;
-  float2 ml[ATTN_MAX_SPLITS];
-  f16x4 av[ATTN_MAX_SPLITS];
+  float2 ml[MOST];
+  f16x4 av[MOST];
 #pragma unroll
-  for (int s = 0; s < ATTN_MAX_SPLITS; ++s) {
+  for (int s = 0; s < MOST; ++s) {
     if (s < nsplit) {
-      const size_t row = ((size_t)s * H + h) * NP + node;
+      const size_t row = ((size_t)s * H + h) * part_rows + node;
       ml[s] = *reinterpret_cast<const float2 *>(part_ml + row * 2);
       av[s] = reinterpret_cast<const f16x4 *>(part_acc)[row * 32 + (d >> 2)];
     }
   }
   float M = NEG_BIG;
 #pragma unroll
-  for (int s = 0; s < ATTN_MAX_SPLITS; ++s)
+  for (int s = 0; s < MOST; ++s)
     if (s < nsplit && ml[s].y > 0.f) M = fmaxf(M, ml[s].x);
   float den = 0.f;
   float4 num = float4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < ATTN_MAX_SPLITS; ++s) {
+  for (int s = 0; s < MOST; ++s) {
     if (s < nsplit && ml[s].y > 0.f) {
       const float w = exp2f(ml[s].x - M) * ml[s].y;
       den += w;
@@ -437,6 +439,17 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
   const size_t idx = out_row_tiles > 0 ? act_frag_index(node, h * 128 + d, out_row_tiles)
                                        : ((size_t)node * H + h) * 128 + d;
   store_stream(out + idx, o);
+}
+
+// part_rows: rows reserved per (split, head)
+hipError_t launch_attn_merge(const float *part_ml, const float *part_acc, int32_t part_rows, int32_t H, int32_t n, int32_t nsplit,
+                             bf16_t *out, int32_t out_row_tiles, KernelTimer tm, hipStream_t st) {
+  const dim3 grid((n + 7) / 8, H);
+  if (nsplit > ATTN_MAX_SPLITS)
+    return launch(k_attn_merge<2 * ATTN_MAX_SPLITS>, grid, dim3(256), 0, st, tm, part_ml, part_acc, part_rows, H, n, nsplit, out, out_row_tiles);
+  if (nsplit <= ATTN_MAX_SPLITS / 2)
+    return launch(k_attn_merge<ATTN_MAX_SPLITS / 2>, grid, dim3(256), 0, st, tm, part_ml, part_acc, part_rows, H, n, nsplit, out, out_row_tiles);
+  return launch(k_attn_merge<ATTN_MAX_SPLITS>, grid, dim3(256), 0, st, tm, part_ml, part_acc, part_rows, H, n, nsplit, out, out_row_tiles);
 }
 
 int attn_heads_per_wg(int32_t H, int32_t Hkv, int32_t n) {
@@ -487,6 +500,8 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
                             int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
                             float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st) {
   if (Hkv < 1 || H % Hkv != 0) return hipErrorInvalidValue;
+  if (attn_rows_better(H, Hkv, n, len_bound))
+    return launch_attn_rows(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, part_ml, part_acc, out, out_row_tiles, prof, st);
   const KernelTimer tm = prof_next(prof, PC_ATTN);
   if (attn_one_launch(H, Hkv, len_bound)) {
     const int NT = (n + 15) / 16;
@@ -510,8 +525,7 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
   case 8: e = launch_attn_nt<8>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
   }
   if (e != hipSuccess || nsplit == 1) return e;
-  return launch(k_attn_merge, dim3((n + 7) / 8, H), dim3(256), 0, st, prof_next(prof, PC_ATTN_MERGE), part_ml, part_acc, H,
-                n, nsplit, out, out_row_tiles);
+  return launch_attn_merge(part_ml, part_acc, NP, H, n, nsplit, out, out_row_tiles, prof_next(prof, PC_ATTN_MERGE), st);
 }
 
 } // namespace tr

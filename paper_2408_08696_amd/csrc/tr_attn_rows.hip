@@ -1,0 +1,259 @@
+// Tree attention for few query rows per K/V head (up to 128 pairs of node and query head): every K/V byte is read once.
+//
+// The queries that share a K/V head are the rows of one operand, row = node * group + head of the group, so that a group's
+// heads share each K/V tile in a workgroup's LDS instead of re-reading it from L2 one workgroup after another.  A workgroup
+// owns one K/V head and one of nsplit shares of the keys; its waves form a grid of RW tiles of 32 rows x KS key groups.  A
+// key group takes a 32-key tile per step (16 KiB, loaded straight from memory into a ring of D slots, D - 1 under way) and
+// its RW waves multiply it (v_mfma_f32_32x32x16_bf16, operands and lanes as in tr_attn_causal.hip); with one row tile a
+// wave's ring is its own and the loop has no barrier.  At the end the key groups meet in LDS, and the workgroup writes the
+// result (one share) or (maximum, sum, normalised output in half precision) for k_attn_merge.
+#include "tr_kernels.h"
+
+namespace tr {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+
+__device__ inline f32x16 mfma32r(const u32x4 &a, const u32x4 &b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+constexpr size_t rows_lds_bytes(int rw, int ks, int d) { // the rings; at the end the accumulators and (maximum, sum)
+  const size_t ring = (size_t)ks * d * 16384, meet = (size_t)ks * rw * 32 * (512 + 8);
+  return ring > meet ? ring : meet;
+}
+
+template <int RW, int KS, int D>
+__global__ __launch_bounds__(RW * KS * 64) void k_attn_rows(const bf16_t *__restrict__ q, const bf16_t *__restrict__ Kl,
+                                                            const bf16_t *__restrict__ Vl, int32_t H, int32_t Hkv,
+                                                            int32_t cap, int32_t n, const uint64_t *__restrict__ anc,
+                                                            const int32_t *__restrict__ d_len, int32_t nsplit,
+                                                            float *__restrict__ part_ml, float *__restrict__ part_acc,
+                                                            int32_t part_rows, bf16_t *__restrict__ out,
+                                                            int32_t out_row_tiles) {
+  constexpr int LOADS = (16 + RW - 1) / RW; // tile loads of a wave per step
+  extern __shared__ u32x4 lds[];            // [KS][D][K 8 tiles | V 8 tiles][64]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = wave % RW, ks = wave / RW;
+  const int half_sel = (lane >> 4) & 1, hb = lane >> 5;
+  const int hk = blockIdx.x, split = blockIdx.y, G = H / Hkv, R = n * G;
+  const int row = rw * 32 + (lane & 31), rc = row < R ? row : R - 1;
+  const int node = rc / G, h = hk * G + (rc - node * G);
+
+  const uint64_t kbase = reinterpret_cast<uint64_t>(Kl + (size_t)hk * cap * 128);
+  const uint64_t vbase = reinterpret_cast<uint64_t>(Vl + (size_t)hk * cap * 128);
+  const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds + ks * (D * 16384);
+  const uint32_t voff = lane * 16;
+  auto tile_of = [&](int step) { return (step * nsplit + split) * KS + ks; };
+  auto load_step = [&](int slot, int t) { // 32-key tile t into ring slot `slot`
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      int j = rw + RW * i;
+      j = j < 16 ? j : 15; // three waves: two of the 18 loads repeat the last tile
+      tile_to_lds(ring0 + slot * 16384 + j * 1024, voff, (j < 8 ? kbase : vbase) + ((uint64_t)t * 8 + (j & 7)) * 1024);
+    }
+  };
+  // the first tiles are asked for before the committed length is known: inside the cache even if beyond the sequence
+  const int cap_tiles = cap / 32;
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s) {
+    const int t = tile_of(s);
+    load_step(s, t < cap_tiles ? t : cap_tiles - 1);
+  }
+  // Q^T operand: contraction step c, half s: Q[row][32 c + 16 s + 8 hb .. + 7]; rows past the last repeat it
+  u32x4 qf[4][2];
+  {
+    const u32x4 *qp = reinterpret_cast<const u32x4 *>(q + ((size_t)node * H + h) * 128 + 8 * hb);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      qf[c][0] = qp[c * 4];
+      qf[c][1] = qp[c * 4 + 2];
+    }
+  }
+  const uint64_t a0 = anc[2 * node], a1 = anc[2 * node + 1];
+  const int L = *d_len, total = L + n, n_tiles = (total + 31) >> 5;
+
+  f32x16 acc[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[d][e] = 0.f;
+  float m = -1e30f, l = 0.f; // running maximum of the row (base 2), this lane's share of its sum
+  const float sc = 0.08838834764831845f * 1.4426950408889634f; // 1/sqrt(128) * log2(e)
+  const int frag = half_sel * 64 + (lane & 15) + 16 * hb;      // a pair of neighbouring tiles; + 32 for the second half
+  const int kfrag = half_sel * 256 + (lane & 15) + 16 * hb;    // K: the pair is 4 tiles apart
+  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
+
+  int slot = 0;
+  for (int step = 0; (step * nsplit + split) * KS < n_tiles; ++step) { // uniform over the workgroup
+    wait_tiles<(D - 2) * LOADS>();
+    if (RW > 1) meet_waves(); // this step's tiles are there for the group, and it has read the slot that is refilled next
+    {
+      int t = tile_of(step + D - 1);
+      t = t < n_tiles ? t : n_tiles - 1; // past the end: again the last one, so that the counts under way stay constant
+      load_step(slot == 0 ? D - 1 : slot - 1, t);
+    }
+    const u32x4 *kt = lds + (ks * D + slot) * 1024, *vt = kt + 512;
+    slot = slot + 1 < D ? slot + 1 : 0;
+    const int key0 = tile_of(step) * 32;
+    if (key0 >= total) continue; // uniform over the wave
+
+    f32x16 s, s2; // two chains of four products
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = s2[e] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      s = mfma32r(kt[c * 64 + kfrag], qf[c][0], s);
+      s2 = mfma32r(kt[c * 64 + kfrag + 32], qf[c][1], s2);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] += s2[e];
+    if (key0 + 32 > L) { // some keys are tree nodes, or past the last
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int p = key0 + 8 * (e >> 2) + 4 * hb + (e & 3), j = p - L;
+        const bool vis = j < 0 || (j < n && (((j < 64 ? a0 >> j : a1 >> (j - 64)) & 1ull) != 0));
+        s[e] = vis ? s[e] : -INFINITY;
+      }
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx * sc);
+    if (__any(m_new > m)) {
+      const float corr = __builtin_amdgcn_exp2f(m - m_new);
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[d][e] *= corr;
+      l *= corr;
+      m = m_new;
+    }
+    // m is finite, so an invisible key's probability is exactly 0, also in a row that has seen no key of this wave's yet
+    u32x4 pf[2];
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], sc, -m));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], sc, -m));
+      const bf16x2 p = __builtin_convertvector(f32x2{p0, p1}, bf16x2);
+      l = __builtin_amdgcn_fdot2_f32_bf16(p, ones, l, false); // the sum of the rounded probabilities
+      pf[(e >> 2) & 1][(e >> 3) * 2 + ((e & 3) >> 1)] = __builtin_bit_cast(uint32_t, p);
+    }
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) acc[d] = mfma32r(vt[d * 128 + frag + 32 * hh], pf[hh], acc[d]);
+  }
+  l += __shfl_xor(l, 32);
+
+  // the key groups meet: accumulators as rows of 32 chunks of 4 features, chunk c of a row in place c ^ (row % 32) so that
+  // the 32 rows a wave stores at once hit distinct banks
+  wait_tiles<0>(); // the repeated loads past the end have landed
+  __syncthreads(); // and everyone has read the last tiles
+  f32x4 *xa = reinterpret_cast<f32x4 *>(lds);                        // [KS][RW * 32][32]
+  float2 *xm = reinterpret_cast<float2 *>(xa + KS * RW * 32 * 32);   // [KS][RW * 32]
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd)
+      xa[(ks * RW * 32 + row) * 32 + ((8 * d + 2 * qd + hb) ^ (row & 31))] =
+          f32x4{acc[d][4 * qd], acc[d][4 * qd + 1], acc[d][4 * qd + 2], acc[d][4 * qd + 3]};
+  if (hb == 0) xm[ks * RW * 32 + row] = float2{m, l};
+  __syncthreads();
+  for (int i = tid; i < R * 32; i += RW * KS * 64) {
+    const int r = i >> 5, c = i & 31;
+    float top = -1e30f, den = 0.f;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) top = fmaxf(top, xm[k * RW * 32 + r].x);
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const float2 ml = xm[k * RW * 32 + r];
+      const float w = __builtin_amdgcn_exp2f(ml.x - top);
+      den += ml.y * w;
+      v += xa[(k * RW * 32 + r) * 32 + (c ^ (r & 31))] * w;
+    }
+    v *= den > 0.f ? 1.0f / den : 0.f;
+    const int nd = r / G, hh = hk * G + (r - nd * G);
+    if (nsplit == 1) {
+      const ushort4 o = ushort4{f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};
+      const size_t idx = out_row_tiles > 0 ? act_frag_index(nd, hh * 128 + 4 * c, out_row_tiles) : ((size_t)nd * H + hh) * 128 + 4 * c;
+      store_stream(out + idx, o);
+    } else {
+      const size_t prow = ((size_t)split * H + hh) * part_rows + nd;
+      if (c == 0) *reinterpret_cast<float2 *>(part_ml + prow * 2) = float2{top, den};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fminf(fmaxf(v[e], -65504.0f), 65504.0f); // saturate, as in k_attn_mfma
+      reinterpret_cast<f16x4 *>(part_acc)[prow * 32 + c] = __builtin_convertvector(v, f16x4);
+    }
+  }
+}
+
+template <int RW, int KS, int D>
+static hipError_t launch_grid(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
+                              int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t nsplit, float *part_ml,
+                              float *part_acc, int32_t part_rows, bf16_t *out, int32_t out_row_tiles, hipStream_t st,
+                              KernelTimer tm) {
+  constexpr int smem = (int)rows_lds_bytes(RW, KS, D);
+  static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_rows<RW, KS, D>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
+  if (!once) return hipErrorInvalidValue;
+  return launch(k_attn_rows<RW, KS, D>, dim3(Hkv, nsplit), dim3(RW * KS * 64), smem, st, tm, q, Kl, Vl, H, Hkv, cap, n, anc,
+                d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles);
+}
+
+static int key_groups(int rows) { return rows <= 64 ? 4 : 2; }
+
+// Where this form is the faster one, by rows per K/V head, group size G and bound on the sequence.  The split form of
+// tr_attn_mfma.hip reads K and V once per two heads of a group, in tiles that one to four waves of a workgroup fetch one at
+// a time; this one pays about 2 us more at its end for every 32 rows beyond the first.  Measured, us per layer, split form /
+// this: 64 heads on 8: 1 node 24.4 / 14.0 at 4096 positions and 71 / 22 at 16000, 8 nodes 13.7 / 13.0 at 1400, 15 nodes
+// 25.1 / 21.1 at 4096 and 72 / 29 at 16000 but 16.9 / 19.4 at 2048; 32 on 8: 16 nodes 20.6 / 18.8 at 6000, 32 nodes 24.2 /
+// 23.4 at 8192; 32 on 16: 8 nodes 15.2 / 13.6 at 3072, never with more than 32 rows; 32 on 32: 1 node 17.2 / 14.2 at 2048
+// and 82 / 51 at 16000, 64 nodes 38.7 / 37.1 at 8192 but 24.3 / 25.8 at 4096.
+bool attn_rows_better(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
+  const int G = H / Hkv, rows = n * G;
+  if (rows > 128 || attn_one_launch(H, Hkv, len_bound)) return false;
+  if (rows <= 32) return G != 2 || len_bound >= 3072;
+  if (rows <= 64) return G == 2 ? false : len_bound >= (G >= 8 ? 1400 : G >= 3 ? 5120 : 7168);
+  return G >= 8 ? len_bound >= 3072 : G >= 3 && len_bound >= 8192;
+}
+
+// Key shares: one, without a merge launch (4.8 us), up to six steps; else all compute units, at least a step each.
+static int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
+  const int steps = ((len_bound + 31) / 32 + key_groups(n * (H / Hkv)) - 1) / key_groups(n * (H / Hkv));
+  if (steps <= 6) return 1;
+  int s = 256 / Hkv;
+  const int most = n <= 64 ? 2 * ATTN_MAX_SPLITS : ATTN_MAX_SPLITS; // what the partial buffers hold
+  if (s > most) s = most;
+  if (s > steps) s = steps;
+  return s < 1 ? 1 : s;
+}
+
+hipError_t launch_attn_rows(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
+                            int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
+                            float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st) {
+  if (Hkv < 1 || H % Hkv != 0 || n < 1 || n * (H / Hkv) > 128) return hipErrorInvalidValue;
+  const int rows = n * (H / Hkv), nsplit = attn_rows_splits(H, Hkv, n, len_bound), part_rows = n <= 64 ? 64 : NP;
+  const KernelTimer tm = prof_next(prof, PC_ATTN);
+  hipError_t e;
+  if (rows <= 32)
+    e = launch_grid<1, 4, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+  else if (rows <= 64)
+    e = launch_grid<2, 4, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+  else if (rows <= 96)
+    e = launch_grid<3, 2, 4>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+  else
+    e = launch_grid<4, 2, 4>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+  if (e != hipSuccess || nsplit == 1) return e;
+  return launch_attn_merge(part_ml, part_acc, part_rows, H, n, nsplit, out, out_row_tiles, prof_next(prof, PC_ATTN_MERGE), st);
+}
+
+} // namespace tr

@@ -370,6 +370,17 @@ def test_tree_attention_matches_per_path_attention(tmpl_name, H, Hkv, L, tiled):
     say("worst relative error", worst)
 
 
+@pytest.mark.parametrize("tmpl_name,H,Hkv,L", [("single", 16, 2, 0), ("single", 16, 2, 40), ("single", 64, 8, 800), ("prefix3", 64, 8, 3001),
+                                               ("prefix20", 8, 8, 900), ("prefix32", 4, 4, 1201),               # one tile of 32 rows
+                                               ("prefix8", 64, 8, 1500), ("prefix40", 2, 2, 7190),              # two
+                                               ("prefix12", 64, 8, 3100), ("prefix24", 16, 4, 8200),            # three
+                                               ("tree15", 64, 8, 3333), ("prefix16", 8, 1, 5001)])              # four
+def test_few_rows_attention(tmpl_name, H, Hkv, L):
+    """The form for few (node, head) rows per K/V head, every row-tile count of it: sequences shorter than its first step,
+    one key share and many, last tiles partly tree, partly past the end."""
+    test_tree_attention_matches_per_path_attention(tmpl_name, H, Hkv, L, True)
+
+
 @pytest.mark.parametrize("n,K_,O_,splits", [(80, 4096, 4096, 2), (80, 11008, 4096, 2), (81, 4096, 1024, 4),
                                             (1, 4096, 512, 1), (128, 512, 2048, 1), (16, 256, 64, 1),
                                             (80, 1024, 32000, 1), (80, 4096, 12288, 1), (37, 96, 32, 3),
