@@ -148,6 +148,7 @@ tr_status tr_create(int32_t V, int32_t k, const tr_tree_template *t, tr_ctx **ou
   if (e == hipSuccess) e = hipMemset(c->d_M, 0, (size_t)V * k * sizeof(int32_t));
   if (e == hipSuccess) e = hipMalloc(&c->d_tree_blob, blob);
   if (e == hipSuccess) e = hipMemcpy(c->d_tree_blob, h, blob, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&c->h_step), sizeof(tr_step_out), hipHostMallocDefault);
   delete[] h;
   if (e != hipSuccess) {
     const tr_status st = e == hipErrorOutOfMemory ? TR_ENOMEM : TR_EHIP;
@@ -174,9 +175,9 @@ tr_status tr_destroy(tr_ctx *c) {
     delete[] c->prof.ev;
     delete[] c->prof.cat;
   }
-  hipError_t e1 = hipFree(c->d_M), e2 = hipFree(c->d_tree_blob);
+  hipError_t e1 = hipFree(c->d_M), e2 = hipFree(c->d_tree_blob), e3 = hipHostFree(c->h_step);
   delete c;
-  return (e1 == hipSuccess && e2 == hipSuccess) ? TR_OK : TR_EHIP;
+  return (e1 == hipSuccess && e2 == hipSuccess && e3 == hipSuccess) ? TR_OK : TR_EHIP;
 }
 
 tr_status tr_set_update_mode(tr_ctx *c, int32_t mode) {
@@ -258,10 +259,11 @@ static tr_status accept_and_update(tr_ctx *c, tr_kv *kv, const int32_t *d_S, con
   if (s != TR_OK) return s;
   if ((int64_t)kv->len_bound + c->tree.n_nodes > kv->capacity) return TR_ECAPACITY;
   hipStream_t st = as_stream(stream);
-  if (launch_accept_update(c, kv, d_S, d_topk, d_tokens, d_out, st) != hipSuccess) return TR_EHIP;
+  if (launch_accept_update(c, kv, d_S, d_topk, d_tokens, d_out, h_out != nullptr ? c->h_step : nullptr, st) != hipSuccess)
+    return TR_EHIP;
   if (h_out != nullptr) {
-    if (hipMemcpyAsync(h_out, d_out, sizeof(tr_step_out), hipMemcpyDeviceToHost, st) != hipSuccess) return TR_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return TR_EHIP;
+    *h_out = *c->h_step;
     kv->len_bound = h_out->kv_len;
   } else {
     kv->len_bound += c->tree.n_layers;

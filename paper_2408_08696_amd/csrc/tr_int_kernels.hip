@@ -407,6 +407,8 @@ hipError_t launch_matrix_update(const tr_ctx *c, const int32_t *d_S, const int32
 // match bit i  = draft token i equals the model output at its parent (root: always)
 // node i is ok = every bit of its ancestor mask is a match bit
 // winner       = deepest ok node, smallest index among equals
+// host: the same result in pinned memory of the context, when the caller waits for it: a copy kernel and its staging on the
+// host less per step (whole request on the tiny model, 19 steps: 2.11 -> 1.70 ms).
 // The kernel also publishes the committed length before the step (step_L) and advances *d_len, so
 // the compaction kernel that follows works from step_L and needs no further bookkeeping launch.
 // Two waves; what bounds it is the chain load -> barrier -> match -> barrier -> winner -> stores.  Every thread
@@ -420,7 +422,8 @@ __global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(int32_t *__restr
                                                                 const int32_t *__restrict__ tokens,
                                                                 int32_t *__restrict__ d_len,
                                                                 int32_t *__restrict__ step_L,
-                                                                tr_step_out *__restrict__ out, int32_t mode) {
+                                                                tr_step_out *__restrict__ out,
+                                                                tr_step_out *__restrict__ host, int32_t mode) {
   __shared__ __align__(16) int32_t sS[TR_MAX_NODES];
   __shared__ int32_t sOut[TR_MAX_NODES];
   __shared__ uint64_t sAnc[TR_MAX_NODES][2];
@@ -461,29 +464,36 @@ __global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(int32_t *__restr
   const int w = 255 - (key & 255), a = key >> 8;
   const uint64_t p0 = sAnc[w][0], p1 = sAnc[w][1];
   // ancestors in increasing index order are the path root..winner (breadth-first numbering)
-  if (((i < 64 ? p0 >> i : p1 >> (i - 64)) & 1ull) != 0) {
-    const int at = i < 64 ? __popcll(p0 & ((1ull << i) - 1)) : __popcll(p0) + __popcll(p1 & ((1ull << (i - 64)) - 1));
-    out->path[at] = i;
-    if (at > 0) out->emitted[at - 1] = tk;
-  }
-  if (i > a && i < TR_MAX_LAYERS) {
-    out->path[i] = -1;
-    out->emitted[i] = -1;
-  }
+  const bool on_path = ((i < 64 ? p0 >> i : p1 >> (i - 64)) & 1ull) != 0;
+  const int at = i < 64 ? __popcll(p0 & ((1ull << i) - 1)) : __popcll(p0) + __popcll(p1 & ((1ull << (i - 64)) - 1));
+  auto publish = [&](tr_step_out *o) {
+    if (on_path) {
+      o->path[at] = i;
+      if (at > 0) o->emitted[at - 1] = tk;
+    }
+    if (i > a && i < TR_MAX_LAYERS) {
+      o->path[i] = -1;
+      o->emitted[i] = -1;
+    }
+    if (i == 0) {
+      const int bonus = sOut[w];
+      o->emitted[a] = bonus;
+      o->n_accepted = a;
+      o->n_emitted = a + 1;
+      o->winner = w;
+      o->next_root = bonus;
+      o->kv_len = L0 + a + 1;
+    }
+  };
+  publish(out);
+  if (host != nullptr) publish(host);
   if (i == 0) {
-    const int bonus = sOut[w];
-    out->emitted[a] = bonus;
-    out->n_accepted = a;
-    out->n_emitted = a + 1;
-    out->winner = w;
-    out->next_root = bonus;
     *step_L = L0;
     *d_len = L0 + a + 1;
-    out->kv_len = L0 + a + 1;
   }
   if ((mode & TR_UPDATE_ACCEPTED_ONLY) != 0) { // uniform
     __syncthreads();
-    if (((i < 64 ? p0 >> i : p1 >> (i - 64)) & 1ull) == 0) sS[i] = -1;
+    if (!on_path) sS[i] = -1;
     __syncthreads();
   }
   scatter_rows(M, k, t.n_nodes, sS, topk, i, mode);
@@ -620,9 +630,9 @@ hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logit
 }
 
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk,
-                                const int32_t *d_tokens, tr_step_out *d_out, hipStream_t st) {
+                                const int32_t *d_tokens, tr_step_out *d_out, tr_step_out *host_out, hipStream_t st) {
   hipError_t e = launch(k_accept_update, dim3(1), dim3(TR_MAX_NODES), 0, st, c->prof.next(PC_ACCEPT), c->d_M, c->V, c->k,
-                        c->tree, d_S, d_topk, d_tokens, kv->d_len, c->d_step_L, d_out, c->update_mode);
+                        c->tree, d_S, d_topk, d_tokens, kv->d_len, c->d_step_L, d_out, host_out, c->update_mode);
   if (e != hipSuccess) return e;
   const int blocks = kv->n_layers * kv->n_kv_heads;
   const size_t esz = dtype_size(kv->dtype);

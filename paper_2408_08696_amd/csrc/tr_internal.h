@@ -142,6 +142,7 @@ struct tr_ctx {
   tr::TreeDev chain;     // chain of TR_MAX_NODES nodes (prefill chunks)
   void *d_tree_blob;     // backing store of both trees
   int32_t *d_step_L;     // committed length at the start of the current accept/update
+  tr_step_out *h_step;   // pinned: the result of a step whose caller waits for it
   void *d_topk_cand;     // top-k candidates of rows longer than one segment
   int32_t update_mode;   // tr_update_mode bits
   tr::Profiler prof;
@@ -160,9 +161,10 @@ bool topk_static_fits(int32_t rows, int32_t V, int32_t k);
 hipError_t launch_topk_static(const void *logits, int32_t dtype, int32_t rows, int32_t V, int32_t k,
                               int32_t *d_topk, hipStream_t s);
 hipError_t launch_matrix_update(const tr_ctx *c, const int32_t *d_S, const int32_t *d_topk, hipStream_t s);
-// d_tokens: the model's token per node, or NULL for the argmax (first top-k column)
+// d_tokens: the model's token per node, or NULL for the argmax (first top-k column); host_out: pinned, or NULL
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S,
-                                const int32_t *d_topk, const int32_t *d_tokens, tr_step_out *d_out, hipStream_t s);
+                                const int32_t *d_topk, const int32_t *d_tokens, tr_step_out *d_out, tr_step_out *host_out,
+                                hipStream_t s);
 hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logits, const float *d_noise,
                                 int32_t pos0, int32_t noise_rows, float inv_t, int32_t *d_tokens, hipStream_t s);
 hipError_t launch_advance_len(int32_t *d_len, int32_t by, hipStream_t s);
