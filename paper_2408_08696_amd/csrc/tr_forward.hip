@@ -274,13 +274,14 @@ static_assert(NORM_CHUNK == 128 * 8, "one block iteration covers 128 threads x 8
 constexpr int NORM_MAX_PARTS = 4;
 static_assert(NORM_MAX_PARTS >= GEMM_MAX_SPLITS && NORM_MAX_PARTS >= WIDE_MAX_SPLITS, "all partial sums are read at once");
 
-__device__ inline void norm_operand(const float (&v)[8], bool live, const bf16_t *__restrict__ g, int row, int j, int32_t d,
+// Both are one memory round trip long and nothing else counts: every load, the gain's too, is issued before the first
+// use, and the stores come after the last wait (a wait for a load also waits for the stores before it).
+__device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 &gv, int row, int j, int32_t d,
                                     int32_t row_tiles, bf16_t *__restrict__ xg_frag, float *__restrict__ ssq_at, bool row_on) {
   __shared__ float red[2];
   float ss = 0.f;
   uint4 pk = uint4{0u, 0u, 0u, 0u};
   if (live) {
-    const uint4 gv = *reinterpret_cast<const uint4 *>(g + j);
     const uint32_t gw[4] = {gv.x, gv.y, gv.z, gv.w};
     uint32_t o[4];
 #pragma unroll
@@ -298,37 +299,52 @@ __device__ inline void norm_operand(const float (&v)[8], bool live, const bf16_t
   if (threadIdx.x == 0 && row_on) *ssq_at = red[0] + red[1];
 }
 
+template <int PARTS>
 __global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const float *__restrict__ part,
-                                                  int32_t n_part, size_t part_stride, const bf16_t *__restrict__ g,
-                                                  int32_t n, int32_t d, int32_t row_tiles,
-                                                  bf16_t *__restrict__ xg_frag, float *__restrict__ ssq,
-                                                  int32_t n_chunks) {
+                                                  size_t part_stride, const bf16_t *__restrict__ g, int32_t n, int32_t d,
+                                                  int32_t row_tiles, bf16_t *__restrict__ xg_frag,
+                                                  float *__restrict__ ssq, int32_t n_chunks) {
   const int row = blockIdx.x, chunk = blockIdx.y;
   const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
   const bool live = row < n && j < d;
   float v[8];
+  uint4 gv;
   if (live) {
     float *xr = x + (size_t)row * d + j;
     const float *pr = part + (size_t)row * d + j;
     float4 a = *reinterpret_cast<const float4 *>(xr), b = *reinterpret_cast<const float4 *>(xr + 4);
-    float4 pa[NORM_MAX_PARTS], pb[NORM_MAX_PARTS];
+    gv = *reinterpret_cast<const uint4 *>(g + j);
+    float4 pa[PARTS], pb[PARTS];
 #pragma unroll
-    for (int s = 0; s < NORM_MAX_PARTS; ++s)
-      if (s < n_part) {
-        pa[s] = *reinterpret_cast<const float4 *>(pr + (size_t)s * part_stride);
-        pb[s] = *reinterpret_cast<const float4 *>(pr + (size_t)s * part_stride + 4);
-      }
+    for (int s = 0; s < PARTS; ++s) {
+      pa[s] = *reinterpret_cast<const float4 *>(pr + (size_t)s * part_stride);
+      pb[s] = *reinterpret_cast<const float4 *>(pr + (size_t)s * part_stride + 4);
+    }
+    __builtin_amdgcn_sched_barrier(0); // all of them on their way before the first sum
 #pragma unroll
-    for (int s = 0; s < NORM_MAX_PARTS; ++s)
-      if (s < n_part) {
-        a.x += pa[s].x; a.y += pa[s].y; a.z += pa[s].z; a.w += pa[s].w;
-        b.x += pb[s].x; b.y += pb[s].y; b.z += pb[s].z; b.w += pb[s].w;
-      }
+    for (int s = 0; s < PARTS; ++s) {
+      a.x += pa[s].x; a.y += pa[s].y; a.z += pa[s].z; a.w += pa[s].w;
+      b.x += pb[s].x; b.y += pb[s].y; b.z += pb[s].z; b.w += pb[s].w;
+    }
     *reinterpret_cast<float4 *>(xr) = a;
     *reinterpret_cast<float4 *>(xr + 4) = b;
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
   }
-  norm_operand(v, live, g, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
+  norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
+}
+
+// n_part 1 .. NORM_MAX_PARTS partial sums
+static hipError_t launch_add_frag(int n_part, int chunks, float *x, const float *part, size_t part_stride, const bf16_t *g,
+                                  int32_t n, int32_t d, int32_t row_tiles, bf16_t *xg_frag, float *ssq, KernelTimer tm,
+                                  hipStream_t st) {
+  const dim3 grid(row_tiles * 16, chunks), block(128);
+  switch (n_part) {
+  case 1: return launch(k_add_frag<1>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
+  case 2: return launch(k_add_frag<2>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
+  case 3: return launch(k_add_frag<3>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
+  case 4: return launch(k_add_frag<4>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
+  }
+  return hipErrorInvalidValue;
 }
 
 __global__ __launch_bounds__(128) void k_embed_frag(const bf16_t *__restrict__ E, int32_t V, const int32_t *__restrict__ tok,
@@ -345,18 +361,21 @@ __global__ __launch_bounds__(128) void k_embed_frag(const bf16_t *__restrict__ E
   const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
   const bool live = row < n && j < d;
   float v[8];
+  uint4 gv;
   if (live) {
+    gv = *reinterpret_cast<const uint4 *>(g + j);
     int t = tok[row];
     t = t < 0 ? 0 : (t >= V ? V - 1 : t);
     bf16_t e[8];
     __builtin_memcpy(e, E + (size_t)t * d + j, 16);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = bf16_to_f32(e[i]);
     float *xr = x + (size_t)row * d + j;
     *reinterpret_cast<float4 *>(xr) = float4{v[0], v[1], v[2], v[3]};
     *reinterpret_cast<float4 *>(xr + 4) = float4{v[4], v[5], v[6], v[7]};
   }
-  norm_operand(v, live, g, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
+  norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
 }
 
 // row-major bf16 [n, K] -> fragment order (standalone linear op only)
@@ -409,8 +428,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
                 xn, ssq, nch));
   int pending = 0; // partial sums waiting in ypart
   auto add_norm = [&](const void *gain) {
-    return launch(k_add_frag, dim3(NT * 16, nch), dim3(128), 0, st, prof_next(prof, PC_NORM), x, ypart, pending, ystride,
-                  (const T *)gain, n, d, NT, xn, ssq, nch);
+    return launch_add_frag(pending, nch, x, ypart, ystride, (const T *)gain, n, d, NT, xn, ssq, prof_next(prof, PC_NORM), st);
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
@@ -505,8 +523,7 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
                 xn, ssq, nch));
   int pending = 0;
   auto add_norm = [&](const void *gain) {
-    return launch(k_add_frag, dim3(RT * 16, nch), dim3(128), 0, st, no_timer, x, ypart, pending, ystride,
-                  (const T *)gain, n, d, RT, xn, ssq, nch);
+    return launch_add_frag(pending, nch, x, ypart, ystride, (const T *)gain, n, d, RT, xn, ssq, no_timer, st);
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];

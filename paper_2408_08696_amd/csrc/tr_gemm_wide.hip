@@ -338,7 +338,7 @@ struct WideShape {
   int rb, nw;
   double step_us;
 };
-static constexpr WideShape WIDE_SHAPES[5] = {{8, 8, 0.31}, {8, 12, 0.42}, {16, 8, 0.45}, {16, 12, 0.585}, {16, 16, 0.70}};
+static constexpr WideShape WIDE_SHAPES[5] = {{8, 8, 0.27}, {8, 12, 0.42}, {16, 8, 0.45}, {16, 12, 0.585}, {16, 16, 0.70}};
 
 // Chooses the workgroup shape and the K-splits, fills the tile assignment and launches.  g.n is the total row count
 // (<= WIDE_MAX_ROWS); a_frag / h_frag use ceil(n / 16) row tiles; the RMS scale takes at most 8 partial sums per
@@ -357,7 +357,7 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles
   auto groups_of = [&](int nw) { return (total + nw / unit - 1) / (nw / unit); };
   // Cost in us: rounds of 256 workgroups, each its k-steps plus 8 for ramp and epilogue, plus what a partial sum costs
-  // to write (3.5 TB/s) and to read back (5 TB/s).
+  // to write (4.6 TB/s) and to read back in the residual kernel (2.9 TB/s).
   const int KT = g.K / 32;
   int shape = 0, best_splits = 1;
   double best = 1e30;
@@ -368,7 +368,7 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
       if (sp > 1 && (per_k < 16 || (sp - 1) * per_k >= KT)) continue; // no empty share, none that is all ramp
       const int rounds = (groups_of(WIDE_SHAPES[v].nw) * row_blocks * sp + 255) / 256;
       double cost = rounds * (per_k * WIDE_SHAPES[v].step_us + 8.0);
-      if (sp > 1) cost += sp * (64.0 * g.n * total) * (1 / 3.5e6 + 1 / 5e6);
+      if (sp > 1) cost += sp * (64.0 * g.n * total) * (1 / 4.6e6 + 1 / 2.9e6);
       if (cost < best) {
         best = cost;
         shape = v;
