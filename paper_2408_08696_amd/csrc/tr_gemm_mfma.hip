@@ -34,6 +34,7 @@ namespace tr {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int GEMM_WAVES = 8;
@@ -95,13 +96,30 @@ constexpr size_t gemm_tail_red_bytes(int p, int nt, int mode, int gw, bool scale
   return (size_t)units0 * (mode == GEMM_SWIGLU ? 2 : 1) * gw * 1024;
 }
 
+// keeps a uniform kernel argument in scalar registers across the main loop; left alone the compiler reads it again behind
+// the reduction, a scalar memory round trip in the tail
+template <typename T>
+__device__ inline T hold(T v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+template <typename T>
+__device__ inline T *hold(T *p) {
+  auto g = (__attribute__((address_space(1))) T *)p;
+  asm volatile("" : "+s"(g));
+  return (T *)g;
+}
+
 template <int NT, int NW, int MODE, int GW, bool SCALED>
 __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
+  // GEMM_ROPE is GEMM_STORE with the fused Q/K/V epilogue: its rotary factors and the committed length are loaded behind
+  // the first weight tiles, so that the tail has no load left (it took three dependent round trips there)
   // SWIGLU: NW = 2P; weight tiles 0..P-1 come from the gate matrix, P..2P-1 from the up matrix
   constexpr int P = MODE == GEMM_SWIGLU ? NW / 2 : NW; // distinct out-tiles per workgroup
   constexpr int PF = gemm_pf(NW, NT, GW);
   extern __shared__ float red[];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // in a scalar register: the k-loop's branches are uniform
   const int KT = g.K / 32;
 
   // out-tiles owned by this workgroup: the T tiles are dealt to the G workgroups in contiguous ranges of
@@ -127,6 +145,10 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
 
   // this workgroup's K-range and this wave's k-tiles in it: kt = kt0 + wave + 8*i
   const int split = blockIdx.y;
+  const int n_rows = hold(g.n);
+  float *const y = MODE == GEMM_STORE ? hold(g.y + (size_t)split * g.split_stride) : nullptr;
+  const int ldy = MODE == GEMM_STORE ? hold(g.ldy) : 0;
+  bf16_t *const h_frag = MODE == GEMM_SWIGLU ? hold(g.h_frag) : nullptr;
   const int per = (KT + g.splits - 1) / g.splits;
   const int kt0 = split * per;
   const int kt1 = kt0 + per < KT ? kt0 + per : KT;
@@ -159,17 +181,63 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) aq[stage][t] = abase[(kt * NT + t) * 64];
   };
+  constexpr int TPU = MODE == GEMM_SWIGLU ? 2 : 1;
+  constexpr int U = P * NT;
+  constexpr int UPW = (U + GW - 1) / GW;
+  const int r = lane & 15, gq = lane >> 4;
+  GemmRope rp{};
+  int L = 0;
+  f32x2 rope_c[MODE == GEMM_ROPE ? UPW : 1], rope_s[MODE == GEMM_ROPE ? UPW : 1];
+  if (MODE == GEMM_ROPE) {
+    rp.q = hold(g.rope.q); rp.k_layer = hold(g.rope.k_layer); rp.v_layer = hold(g.rope.v_layer);
+    rp.H = hold(g.rope.H); rp.Hkv = hold(g.rope.Hkv); rp.hd = hold(g.rope.hd); rp.cap = hold(g.rope.cap);
+    rp.tiled = hold(g.rope.tiled);
+    L = *g.rope.d_len;
 #pragma unroll
-  for (int j = 0; j < PF; ++j)
-    if (j < nsteps) issue(j, j);
-  for (int base = 0; base < nsteps; base += PF) {
+    for (int i = 0; i < UPW; ++i) {
+      const int id = wave * UPW + i, u = id / NT, row = 16 * (id - u * NT) + r;
+      const int o = (tile0 + u) * 16 + 4 * gq, head = o / rp.hd, dd = o - head * rp.hd;
+      const bool on = id < U && u < n_valid && row < n_rows && head < rp.H + rp.Hkv;
+      const float *cs = g.rope.rope + (on ? (size_t)row * rp.hd + (dd >> 1) : 0);
+      rope_c[i] = *reinterpret_cast<const f32x2 *>(cs);
+      rope_s[i] = *reinterpret_cast<const f32x2 *>(cs + rp.hd / 2);
+    }
+  }
+
+  auto multiply = [&](int j) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int u = 0; u < NW; ++u) acc[u][t] = mfma16(wq[j][u], aq[j][t], acc[u][t]);
+  };
+  // The steady part has no condition in it, so that the compiler's wait for a stage leaves the younger ones under way;
+  // with a test per step it waits for every load once in PF steps (80 rows: 7B gate/up 36.6 -> 36.3 us, Q/K/V with the
+  // loads out of its tail 26.3 -> 25.9, o and down 34.2 -> 33.7).  One row tile keeps the tests: 70B gate/up takes 173 us
+  // without them against 155.
+  int base = 0;
+  if (NT > 1 && nsteps >= 2 * PF) {
+#pragma unroll
+    for (int j = 0; j < PF; ++j) issue(j, j);
+    do {
+#pragma unroll
+      for (int j = 0; j < PF; ++j) {
+        multiply(j);
+        __builtin_amdgcn_sched_barrier(0); // keep this order: the scheduler would gather the loads behind several stages
+        issue(j, base + j + PF);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      base += PF;
+    } while (base + 2 * PF <= nsteps);
+  } else {
+#pragma unroll
+    for (int j = 0; j < PF; ++j)
+      if (j < nsteps) issue(j, j);
+  }
+  for (; base < nsteps; base += PF) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
       if (base + j < nsteps) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int u = 0; u < NW; ++u) acc[u][t] = mfma16(wq[j][u], aq[j][t], acc[u][t]);
+        multiply(j);
         if (base + j + PF < nsteps) issue(j, base + j + PF);
       }
     }
@@ -181,9 +249,6 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   // GW partials in wave order (a fixed order: results are run-to-run identical).  When the GW partials of
   // all tiles fit LDS this is one pass; otherwise two, the first for the units of waves 0 .. GW/2-1.
   // Every wave then scales, activates and stores its own few tiles, instead of one wave storing them all.
-  constexpr int TPU = MODE == GEMM_SWIGLU ? 2 : 1;
-  constexpr int U = P * NT;
-  constexpr int UPW = (U + GW - 1) / GW;
   constexpr int OWN0 = gemm_tail_one_pass(P, NT, MODE, GW, SCALED) ? GW : GW / 2; // waves 0 .. OWN0-1 own pass 0
   float4 *red4 = reinterpret_cast<float4 *>(red); // [unit slot * TPU + k][GW][64]
   float *sc_lds = red + gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) / sizeof(float); // [NT * 16], SCALED only
@@ -235,7 +300,6 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     if (pass == 0 && OWN0 * UPW < U) __syncthreads(); // pass 1 reuses the buffer
   }
 
-  const int r = lane & 15, gq = lane >> 4;
 #pragma unroll
   for (int i = 0; i < UPW; ++i) {
     const int id = wave * UPW + i;
@@ -245,22 +309,19 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     const int row = 16 * t + r;
     const float sc_row = SCALED ? sc_lds[row] : 1.0f;
     const int o = (tile0 + u) * 16 + 4 * gq;
-    if (MODE == GEMM_STORE) {
-      if (row >= g.n) continue;
+    if (MODE != GEMM_SWIGLU) {
+      if (row >= n_rows) continue;
       const f32x4 v = f32x4{fin[i][0][0] * sc_row, fin[i][0][1] * sc_row, fin[i][0][2] * sc_row, fin[i][0][3] * sc_row};
-      if (g.rope.q == nullptr) {
-        float *yb = g.y + (size_t)split * g.split_stride + (size_t)row * g.ldy;
-        *reinterpret_cast<float4 *>(yb + o) = float4{v[0], v[1], v[2], v[3]};
+      if (MODE == GEMM_STORE) {
+        *reinterpret_cast<float4 *>(y + (size_t)row * ldy + o) = float4{v[0], v[1], v[2], v[3]};
       } else {
         // fused Q/K/V epilogue: features o .. o+3 of the concatenated [q | k | v] outputs, in the
         // interleaved order of the packed wq / wk rows: (o, o+1) and (o+2, o+3) are rotation pairs
-        const GemmRope &rp = g.rope;
         const int hd = rp.hd, head = o / hd, dd = o - head * hd;
-        const int pos = *rp.d_len + row;
+        const int pos = L + row;
         float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
         if (head < rp.H + rp.Hkv) {
-          const float *cs = rp.rope + (size_t)row * hd + (dd >> 1);
-          const float c0 = cs[0], c1 = cs[1], s0 = cs[hd / 2], s1 = cs[hd / 2 + 1];
+          const float c0 = rope_c[i][0], c1 = rope_c[i][1], s0 = rope_s[i][0], s1 = rope_s[i][1];
           a0 = v[0] * c0 - v[1] * s0; b0 = v[1] * c0 + v[0] * s0;
           a1 = v[2] * c1 - v[3] * s1; b1 = v[3] * c1 + v[2] * s1;
         }
@@ -285,7 +346,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     } else {
       // h[row, o .. o+3] = bf16(silu(gate) * up), written in fragment order over (k = o, NT row tiles);
       // rows past n are written as zeros so the consumer's operand tiles are fully defined
-      const bool live = row < g.n;
+      const bool live = row < n_rows;
       const f32x4 gt = f32x4{fin[i][0][0] * sc_row, fin[i][0][1] * sc_row, fin[i][0][2] * sc_row, fin[i][0][3] * sc_row};
       const f32x4 up = f32x4{fin[i][TPU - 1][0] * sc_row, fin[i][TPU - 1][1] * sc_row, fin[i][TPU - 1][2] * sc_row, fin[i][TPU - 1][3] * sc_row};
       ushort4 hv;
@@ -294,7 +355,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
       hv.z = live ? f32_to_bf16(gt[2] / (1.0f + __expf(-gt[2])) * up[2]) : (bf16_t)0;
       hv.w = live ? f32_to_bf16(gt[3] / (1.0f + __expf(-gt[3])) * up[3]) : (bf16_t)0;
       const size_t slot = ((size_t)(o >> 5) * NT + t) * 64 + r + 16 * ((o & 31) >> 3);
-      store_stream(g.h_frag + slot * 8 + (o & 7), hv);
+      store_stream(h_frag + slot * 8 + (o & 7), hv);
     }
   }
 }
@@ -375,6 +436,10 @@ static hipError_t launch_ks(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
 // the whole of LDS can hold partial tiles
 template <int NT, int P, int MODE, int GW = GEMM_WAVES>
 static hipError_t launch_k(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
+  if (MODE == GEMM_STORE && g.rope.q != nullptr) { // the fused Q/K/V projection: complete sums of a normalised input
+    if (g.row_ssq == nullptr || g.splits != 1) return hipErrorInvalidValue;
+    return launch_ks<NT, P, GEMM_ROPE, GW, true>(g, st, tm);
+  }
   if (g.row_ssq != nullptr) return launch_ks<NT, P, MODE, GW, true>(g, st, tm);
   return launch_ks<NT, P, MODE, GW, false>(g, st, tm);
 }

@@ -4,7 +4,7 @@
 
 namespace tr {
 
-enum GemmMode { GEMM_STORE = 0, GEMM_SWIGLU = 2 };
+enum GemmMode { GEMM_STORE = 0, GEMM_ROPE = 1 /* GEMM_STORE with GemmRope, picked by the launch */, GEMM_SWIGLU = 2 };
 
 // Streaming store for activations that the next kernel reads once: written through as issued, so the
 // kernel does not end with dirty L2 lines to write back before its successor may start (the consumers
