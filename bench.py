@@ -229,7 +229,7 @@ def main():
             torch.cuda.synchronize()
             dtp = (time.perf_counter() - t0) / a.steps
             rows.append({"prompt_tokens": pl - 1, "ms": dtp * 1e3, "tokens_per_s": (pl - 1) / dtp,
-                         "weight_reads": -(-(pl - 1) // 512)})
+                         "weight_reads": -(-(pl - 1) // 2048)})
             say(rows[-1])
         print(json.dumps({"metric": "prompt ingestion time", "unit": "ms", "n_gpus": 1, "steps": a.steps,
                           "dtype": "bf16", "data": "synthetic",
