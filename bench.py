@@ -357,7 +357,7 @@ def main():
                    "n_layers": sh.n_layers, "d_model": sh.d_model, "vocab": sh.vocab},
         "tokens_per_s": steps_s * mat, "mat": mat,
         "prefill": {"prompt_tokens": len(prompt) - 1, "ms": prefill_s * 1e3,
-                    "tokens_per_s": (len(prompt) - 1) / prefill_s, "how": "passes of up to 512 rows: wide projection kernel, attention per block of 128 rows"},
+                    "tokens_per_s": (len(prompt) - 1) / prefill_s, "how": "passes of up to 2048 rows: wide projection kernel, one attention launch per layer"},
         "step_roofline": step_roofline, "roofline": roofline,
         "breakdown_ms_per_step": breakdown,
     }
