@@ -312,7 +312,10 @@ tr_status tr_prefill(tr_ctx *ctx, const tr_model *model, tr_kv *kv, const int32_
  * Single operations of the step, exposed for kernel-level parity tests and microbenchmarks.
  *
  * tr_op_topk: argtopk of each of n_rows rows of d_logits ([device], dtype f32 or bf16,
- *   [n_rows, V] with V the context's vocabulary) into d_topk [device] int32 [n_rows, k].
+ *   [n_rows, V] with V the context's vocabulary) into d_topk [device] int32 [n_rows, k].  Every place is
+ *   written whatever the row holds.  NaN: for k <= 8 and 8 <= V <= 131072 it ranks before +inf, or behind
+ *   -inf if its sign bit is set; otherwise it is never chosen, and places that nothing is left for hold
+ *   0x7FFFFFFF.
  * tr_op_matrix_update: the M scatter of tr_accept_and_update alone, all N nodes, last wins.
  * tr_op_tree_attention: the attention of one layer.  d_q [device] [N, n_heads, head_dim]
  *   (already rotated), cache layer `layer` of kv holding L committed positions plus the N tree

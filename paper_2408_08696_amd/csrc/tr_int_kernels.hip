@@ -102,8 +102,11 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk(const T *__restrict__ log
 // to LDS as 64-bit keys whose unsigned order is the total order of k_topk (the float mapped to an order-preserving
 // unsigned, with -0 folded onto +0, in the high word; the complemented index in the low word; key 0 is "nothing"), and
 // each finds its place by counting the keys above it.  Per element that is one load, one maximum and no 64-bit
-// arithmetic.  Rows whose ties put more than TOPK_LIST elements at or above the threshold are selected by k exact
-// passes over the registers instead.  A row of several segments leaves k keys per segment to k_topk_merge.
+// arithmetic.  Segments whose ties put more than TOPK_LIST elements at or above the threshold are selected by k exact
+// passes over the registers instead, and so are segments with a NaN in them, which no threshold can be trusted with.  A
+// row of several segments leaves k keys per segment to k_topk_merge.
+// Every place of every row is written.  nan_ranks: a NaN takes the place of its bits (before +inf, or behind -inf with the
+// sign bit set); else it is no candidate, as in k_topk, and a place nothing is left for holds TOPK_NONE.
 // What bounds it: latency (launch, one load round trip, three barriers).  80 rows of 32000 bf16 logits took 12.4 + 5.8 us
 // as "every wave selects its own k best by k rounds of 64-bit maxima, a second kernel merges 32 waves per row" (the
 // rounds are ~900 clocks of vector ALU each).
@@ -114,13 +117,19 @@ constexpr int TOPK_SEG = TOPK_SEL_THREADS * TOPK_EPT;
 constexpr int TOPK_LIST = 1024;                          // candidates kept in LDS
 constexpr int TOPK_MAX_SEGS = 64;
 constexpr int TOPK_ROW_SLOTS = TOPK_MAX_SEGS * TOPK_WAVES; // scratch keys per row
+constexpr int32_t TOPK_NONE = 0x7FFFFFFF;                // id of a place without a candidate
+constexpr int TOPK_NAN_K = 8;                            // NaN ranks for k up to this on rows of TOPK_NAN_K ..
+constexpr int TOPK_STATIC_MAX_V = 131072;                // .. TOPK_STATIC_MAX_V elements (what tr.h states)
 
 __device__ inline uint64_t topk_key(float v, int32_t idx) {
   uint32_t u = __float_as_uint(v + 0.0f); // -0 + 0 = +0
   u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
   return ((uint64_t)u << 32) | (uint32_t)~idx;
 }
-// Wave-wide maximum on the vector ALU alone: four data-parallel-primitive exchanges (lane ^ 1, lane ^ 2,
+__device__ inline int32_t topk_id(uint64_t key) { return key == 0 ? TOPK_NONE : (int32_t)~(uint32_t)key; }
+// NaN if either is (one instruction: v_maximum3_f32)
+__device__ inline float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+// Wave-wide maximum (NaN if any lane's value is) on the vector ALU alone: four data-parallel-primitive exchanges (lane ^ 1, lane ^ 2,
 // mirror inside 8 lanes, mirror inside the row of 16) leave every lane with its row's maximum, and the
 // four row maxima are read out as scalars.  All 64 lanes must be active.
 template <int CTRL>
@@ -128,19 +137,20 @@ __device__ inline float dpp_f32(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
 __device__ inline float wave_max_f32(float x) {
-  x = fmaxf(x, dpp_f32<0xB1>(x));  // quad_perm [1,0,3,2]
-  x = fmaxf(x, dpp_f32<0x4E>(x));  // quad_perm [2,3,0,1]
-  x = fmaxf(x, dpp_f32<0x141>(x)); // row_half_mirror
-  x = fmaxf(x, dpp_f32<0x140>(x)); // row_mirror
+  x = max_or_nan(x, dpp_f32<0xB1>(x));  // quad_perm [1,0,3,2]
+  x = max_or_nan(x, dpp_f32<0x4E>(x));  // quad_perm [2,3,0,1]
+  x = max_or_nan(x, dpp_f32<0x141>(x)); // row_half_mirror
+  x = max_or_nan(x, dpp_f32<0x140>(x)); // row_mirror
   auto lane = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
-  return fmaxf(fmaxf(lane(0), lane(16)), fmaxf(lane(32), lane(48)));
+  return max_or_nan(max_or_nan(lane(0), lane(16)), max_or_nan(lane(32), lane(48)));
 }
 
 // VEC: 16-byte loads (base and row pitch 16-byte aligned, at least one full vector per thread of the workgroup, so
 // that every wave has elements); otherwise one element per load.
 template <typename T, bool VEC>
 __global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__restrict__ logits, int32_t V, int32_t k,
-                                                                  int32_t seg_len, int32_t *__restrict__ out,
+                                                                  int32_t seg_len, int32_t nan_ranks,
+                                                                  int32_t *__restrict__ out,
                                                                   uint64_t *__restrict__ cand) {
   constexpr int E = VEC ? 16 / (int)sizeof(T) : 1; // elements per load
   __shared__ float wmax[TOPK_WAVES];
@@ -173,14 +183,16 @@ __global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__res
   if (tid == 0) count = 0;
   float m = v[0];
 #pragma unroll
-  for (int i = 1; i < TOPK_EPT; ++i) m = fmaxf(m, v[i]);
+  for (int i = 1; i < TOPK_EPT; ++i) m = max_or_nan(m, v[i]);
   const float wm = wave_max_f32(m);
   if (lane == 0) wmax[wave] = wm;
   __syncthreads();
   // threshold: the wave maximum of rank k - 1 (waves without elements count as -inf, which admits every element)
   float thr;
+  bool exact; // uniform over the workgroup
   {
     const float mine = wmax[lane & (TOPK_WAVES - 1)];
+    exact = __any(mine != mine);
     int rank = 0;
 #pragma unroll
     for (int j = 0; j < TOPK_WAVES; ++j) {
@@ -188,9 +200,9 @@ __global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__res
       rank += (o > mine || (o == mine && j < (lane & (TOPK_WAVES - 1)))) ? 1 : 0;
     }
     const uint64_t at = __ballot(rank == k - 1);
-    thr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_ctzll(at)));
+    thr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), at != 0 ? __builtin_ctzll(at) : 0));
   }
-  if (m >= thr) {
+  if (m >= thr && !exact) {
 #pragma unroll
     for (int i = 0; i < TOPK_EPT; ++i) {
       const int j = index_of(i);
@@ -204,10 +216,10 @@ __global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__res
   const int n = count;
   auto emit = [&](int rank, uint64_t key) {
     if (cand != nullptr) cand[((size_t)row * gridDim.x + seg) * k + rank] = key;
-    else out[(size_t)row * k + rank] = (int32_t)~(uint32_t)key;
+    else out[(size_t)row * k + rank] = topk_id(key);
   };
   if (cand != nullptr && tid >= cnt && tid < k) emit(tid, 0); // a last segment shorter than k
-  if (n <= TOPK_LIST) {
+  if (!exact && n <= TOPK_LIST) {
     if (tid < n) {
       const uint64_t key = list[tid];
       int rank = 0;
@@ -217,13 +229,13 @@ __global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__res
     }
     return;
   }
-  uint64_t prev = ~0ull; // n is uniform over the workgroup
+  uint64_t prev = ~0ull; // n is uniform over the workgroup too
   for (int p = 0; p < k; ++p) {
     uint64_t best = 0;
 #pragma unroll
     for (int i = 0; i < TOPK_EPT; ++i) {
       const int j = index_of(i);
-      const uint64_t key = j < cnt ? topk_key(v[i], lo + j) : 0;
+      const uint64_t key = j < cnt && (nan_ranks != 0 || v[i] == v[i]) ? topk_key(v[i], lo + j) : 0;
       if (key < prev && key > best) best = key;
     }
     for (int off = 32; off > 0; off >>= 1) {
@@ -240,7 +252,8 @@ __global__ __launch_bounds__(TOPK_SEL_THREADS) void k_topk_select(const T *__res
   }
 }
 
-// one workgroup per row: the k best of n_cand keys by counting the keys above each
+// one workgroup per row: the k best of n_cand keys by counting the keys above each (keys that are nothing: behind all
+// others, in their own order)
 __global__ __launch_bounds__(256) void k_topk_merge(const uint64_t *__restrict__ cand, int32_t n_cand, int32_t k,
                                                     int32_t *__restrict__ out) {
   __shared__ uint64_t list[TOPK_ROW_SLOTS];
@@ -249,11 +262,12 @@ __global__ __launch_bounds__(256) void k_topk_merge(const uint64_t *__restrict__
   __syncthreads();
   for (int c = threadIdx.x; c < n_cand; c += 256) {
     const uint64_t key = list[c];
-    if (key == 0) continue;
     int rank = 0;
 #pragma unroll 8
     for (int j = 0; j < n_cand; ++j) rank += list[j] > key ? 1 : 0;
-    if (rank < k) out[(size_t)row * k + rank] = (int32_t)~(uint32_t)key;
+    if (key == 0)
+      for (int j = 0; j < c; ++j) rank += list[j] == 0 ? 1 : 0;
+    if (rank < k) out[(size_t)row * k + rank] = topk_id(key);
   }
 }
 
@@ -262,12 +276,13 @@ static hipError_t topk_select(const T *logits, int32_t rows, int32_t V, int32_t 
                               uint64_t *cand, KernelTimer tm, hipStream_t st) {
   constexpr int E = 16 / (int)sizeof(T);
   const int seg_len = segs == 1 ? V : ((V + segs - 1) / segs + 7) / 8 * 8; // <= TOPK_SEG, which is a multiple of 8
+  const int nan_ranks = k <= TOPK_NAN_K && V >= TOPK_NAN_K && V <= TOPK_STATIC_MAX_V;
   // vectors only where each thread gets one: on shorter rows they would leave waves empty and with them no threshold
   if (V % E == 0 && (uintptr_t)logits % 16 == 0 && seg_len >= TOPK_SEL_THREADS * E)
-    return launch(k_topk_select<T, true>, dim3(segs, rows), dim3(TOPK_SEL_THREADS), 0, st, tm, logits, V, k, seg_len, out,
-                  cand);
-  return launch(k_topk_select<T, false>, dim3(segs, rows), dim3(TOPK_SEL_THREADS), 0, st, tm, logits, V, k, seg_len, out,
-                cand);
+    return launch(k_topk_select<T, true>, dim3(segs, rows), dim3(TOPK_SEL_THREADS), 0, st, tm, logits, V, k, seg_len,
+                  nan_ranks, out, cand);
+  return launch(k_topk_select<T, false>, dim3(segs, rows), dim3(TOPK_SEL_THREADS), 0, st, tm, logits, V, k, seg_len,
+                nan_ranks, out, cand);
 }
 
 hipError_t launch_topk(const void *logits, int32_t dtype, int32_t rows, int32_t V, int32_t k, int32_t *d_topk,
@@ -310,7 +325,6 @@ size_t topk_scratch_bytes() { return (size_t)TR_MAX_NODES * TOPK_ROW_SLOTS * siz
 // asked once per device with that device current.
 // ---------------------------------------------------------------------------------------------
 constexpr size_t TOPK_STATIC_BYTES = (size_t)TR_MAX_NODES * TOPK_ROW_SLOTS * sizeof(uint64_t); // 1 MiB
-constexpr int TOPK_STATIC_MAX_V = 131072;
 static __device__ __align__(256) unsigned char scratch[TOPK_STATIC_BYTES];
 
 constexpr int MAX_DEVICES = 64;

@@ -136,6 +136,50 @@ def test_topk_segment_edges(dtype, V, k):
     ctx.close()
 
 
+def _topk_with_nan(x, k):
+    """What rows with NaN give.  k <= 8 and 8 <= V <= 131072: a NaN ranks by its bits, before +inf or behind -inf; else NaN
+    is never chosen and places without a candidate hold 0x7FFFFFFF."""
+    V = len(x)
+    if k <= 8 and 8 <= V <= 131072:
+        u = (x + np.float32(0.0)).view(np.uint32)
+        u = np.where(u >> 31, ~u, u | np.uint32(0x80000000))
+        return np.lexsort((np.arange(V), -u.astype(np.int64)))[:k].tolist()
+    ids = np.flatnonzero(~np.isnan(x))
+    order = ids[np.lexsort((ids, -x[ids]))][:k].tolist()
+    return order + [0x7FFFFFFF] * (k - len(order))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V,k", [(7, 7), (8, 8), (449, 8), (2000, 8), (2000, 12), (32768, 8), (32768, 16), (70000, 8), (98312, 16),
+                                 (131073, 8), (20003, 17)])
+def test_topk_rows_with_nan(dtype, V, k):
+    """Every place of every row is written, whatever the NaNs: rows of nothing else, with fewer numbers than k, with NaN
+    in all waves of a segment, in one segment of several, of both signs, beside infinities, and a row without any."""
+    require_gpu()
+    say("topk NaN", dtype, V, k)
+    x = synth.normal_tensor((8, V), 3.0, seed=V + k, dtype=dtype)
+    nan = float("nan")
+    x[0, :] = nan
+    x[1, :] = nan
+    x[1, V // 2], x[1, V - 1] = 1.0, -2.0
+    x[2, ::5] = nan
+    x[3, V // 3] = nan
+    x[4, :V // 3] = nan                       # a whole segment of the long rows
+    x[5, 1::3] = torch.tensor(nan, dtype=dtype).neg()
+    x[5, 0], x[5, 2] = float("inf"), -float("inf")
+    x[6, V - 1] = nan
+    x[6, :2] = -float("inf")
+    ctx = _ctx(synth.single(), V, k)
+    d_topk = torch.full((8, k), -7, dtype=torch.int32, device="cuda")
+    ctx.op_topk(torch.zeros(8, V, dtype=dtype, device="cuda"), d_topk)  # scratch of another call
+    d_topk.fill_(-7)
+    ctx.op_topk(x.cuda(), d_topk)
+    got = d_topk.cpu().numpy()
+    for r in range(8):
+        assert got[r].tolist() == _topk_with_nan(x[r].float().numpy(), k), (V, k, r)
+    ctx.close()
+
+
 @pytest.mark.parametrize("name", ["tree80", "wide128", "tree15"])
 def test_matrix_update_last_wins(name):
     require_gpu()
