@@ -156,13 +156,15 @@ __global__ __launch_bounds__(256) void k_attn_generic(const T *__restrict__ q, c
       const int cnt = total - base < 256 ? total - base : 256;
       int e = grp * span;
       const int e1 = e + span < cnt ? e + span : cnt;
-      for (; e + 4 <= e1; e += 4) { // weights of keys nobody sees are exact zeros and the cache holds finite values
+      // a key without weight adds nothing, whatever its value: another branch of the tree may hold no finite one
+      auto seen = [](float pe, T v) { return pe != 0.f ? to_f32<T>(v) : 0.f; };
+      for (; e + 4 <= e1; e += 4) {
         T vv[4];
         __builtin_memcpy(vv, vr + e, 4 * sizeof(T));
         const float4 pe = *reinterpret_cast<const float4 *>(sp + e);
-        acc += pe.x * to_f32<T>(vv[0]) + pe.y * to_f32<T>(vv[1]) + pe.z * to_f32<T>(vv[2]) + pe.w * to_f32<T>(vv[3]);
+        acc += pe.x * seen(pe.x, vv[0]) + pe.y * seen(pe.y, vv[1]) + pe.z * seen(pe.z, vv[2]) + pe.w * seen(pe.w, vv[3]);
       }
-      for (; e < e1; ++e) acc += sp[e] * to_f32<T>(vr[e]);
+      for (; e < e1; ++e) acc += sp[e] * seen(sp[e], vr[e]);
     }
     __syncthreads();
   }

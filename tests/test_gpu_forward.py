@@ -370,6 +370,43 @@ def test_tree_attention_matches_per_path_attention(tmpl_name, H, Hkv, L, tiled):
     say("worst relative error", worst)
 
 
+@pytest.mark.parametrize("dtype,hd", [("f32", 64), ("bf16", 128), ("f32", 30)])
+def test_generic_attention_ignores_what_a_node_does_not_see(dtype, hd):
+    """Shape-generic attention: a tree node whose value vector is not finite reaches its descendants and itself, and
+    leaves every other row what it is with a finite one."""
+    require_gpu()
+    say("generic attention, non-finite sibling", dtype, hd)
+    t = synth.tree15()
+    tree = O.make_tree(t.parent, t.rank, K)
+    n, H, Hkv, L = t.n_nodes, 4, 2, 260
+    sh = synth.ModelShape("att", 1, H * hd, H, Hkv, hd, 64, 64, dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q = synth.normal_tensor((n, H, hd), 1.0, seed=1, dtype=dt).cuda()
+    kp = synth.normal_tensor((1, Hkv, L + n + 5, hd), 1.0, seed=2, dtype=dt)
+    vp = synth.normal_tensor((1, Hkv, L + n + 5, hd), 1.0, seed=3, dtype=dt)
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    outs = []
+    bad = {2: float("nan"), 5: float("inf")}
+    for values in ({}, bad):
+        kv = tr.KVDesc(sh, capacity=L + n + 5, tiled=False)
+        kv.reset(L)
+        pad = kv.capacity - kp.shape[2]
+        k, v = (torch.nn.functional.pad(a, (0, 0, 0, pad)) for a in (kp, vp))
+        for node, x in values.items():
+            v[0, :, L + node, :] = x
+        kv_fill(kv, k.cuda(), v.cuda())
+        out = torch.zeros(n, H, hd, dtype=dt, device="cuda")
+        ws = torch.empty(16 * 128 * H * (2 + hd) * 4 + 4096, dtype=torch.uint8, device="cuda")
+        ctx.op_tree_attention(kv, 0, H, q, out, ws)
+        outs.append(out.cpu())
+    for i in range(n):
+        if set(tree.paths[i]) & set(bad):
+            assert not outs[1][i].isfinite().any(), i
+        else:
+            assert torch.equal(outs[0][i], outs[1][i]), i
+    ctx.close()
+
+
 @pytest.mark.parametrize("tmpl_name,H,Hkv,L", [("single", 16, 2, 0), ("single", 16, 2, 40), ("single", 64, 8, 800), ("prefix3", 64, 8, 3001),
                                                ("prefix20", 8, 8, 900), ("prefix32", 4, 4, 1201),               # one tile of 32 rows
                                                ("prefix8", 64, 8, 1500), ("prefix40", 2, 2, 7190),              # two
