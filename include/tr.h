@@ -269,7 +269,8 @@ tr_status tr_accept_and_update(tr_ctx *ctx, tr_kv *kv, const int32_t *d_S, const
  *
  *   tr_op_sample: d_tokens[i] = argmax_j ( d_logits[i][j] * inv_temperature
  *                                          + d_noise[(L + depth(i)) - noise_pos0][j] ),
- *     ties to the smallest j, for the N nodes of the context's tree; the multiply and the add are
+ *     ties to the smallest j, a NaN never chosen (a row of nothing else gives token 0), for the N nodes
+ *     of the context's tree; the multiply and the add are
  *     two separately rounded float32 operations.  d_logits [device] float32 [N, V] as written by
  *     tr_verify_forward; d_noise [device] float32 [noise_rows, V], row r holding the noise of
  *     sequence position noise_pos0 + r (standard Gumbel values give a draw from softmax(logits/T);

@@ -572,7 +572,8 @@ __global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__rest
 // are kept separate (no fused multiply-add): they decide an integer, and whoever repeats them rounds
 // the same way.  One workgroup of 16 waves per node; a thread has U vectors of both rows in flight, which is what
 // counts (every node's compute unit pulls two rows of V floats): 128 nodes x 32000 took 39 us with 4 waves and one
-// element of each row in flight, 9.3 now.  VEC: 16-byte loads (V a multiple of 4, both bases aligned).
+// element of each row in flight, 9.3 now.  VEC: 16-byte loads (V a multiple of 4, both bases aligned).  A NaN is never
+// drawn (it is no candidate, so it cannot stand in a thread's or a wave's place either); a row of nothing else gives 0.
 // ---------------------------------------------------------------------------------------------
 constexpr int SAMPLE_THREADS = 1024;
 template <bool VEC>
@@ -607,7 +608,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *_
       for (int e = 0; e < E; ++e) {
         const int j = j0 + u * SAMPLE_THREADS * E + e;
         const float y = __fadd_rn(__fmul_rn(a[u][e], inv_t), b[u][e]);
-        if (j < V && (y > best || bj == 0x7fffffff)) { // j grows, so on equal values the earlier index stays
+        if (j < V && (y > best || (bj == 0x7fffffff && y == y))) { // j grows, so on equal values the earlier index stays
           best = y;
           bj = j;
         }
@@ -631,7 +632,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *_
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < SAMPLE_THREADS / 64; ++w) merge(sv[w], si[w]);
-    tokens[i] = bj;
+    tokens[i] = bj != 0x7fffffff ? bj : 0;
   }
 }
 

@@ -380,3 +380,29 @@ def test_sample_tokens_edges(V):
     depth = O.make_tree(t.parent, t.rank, 8).depth
     assert tokens.cpu().tolist() == O.sample_tokens(logits.numpy(), [int(d) for d in depth], 2.0, noise.numpy()).tolist()
     ctx.close()
+
+
+@pytest.mark.parametrize("V", [1003, 16384])
+def test_sample_tokens_skips_nan(V):
+    """A NaN is never drawn and hides no other token, wherever it lies (first element of a thread, of a wave); a row of
+    nothing else gives token 0."""
+    require_gpu()
+    say("sample NaN", V)
+    t = synth.chain(5)
+    ctx = tr.Context(V, 8, t.parent, t.rank, t.n_layers)
+    kv = tr.KVDesc(synth.ModelShape("s", 1, 128, 1, 1, 128, 128, V, "bf16"), 160)
+    kv.reset(3)
+    logits = synth.normal_tensor((t.n_nodes, V), 3.0, seed=V, dtype=torch.float32)
+    nan = float("nan")
+    logits[0, 0] = nan
+    logits[1, ::256] = nan                     # first element of every wave
+    logits[1, 258] = logits[1][~logits[1].isnan()].max() + 1
+    logits[2, ::2] = nan
+    logits[3, :] = nan
+    logits[4, :1000] = nan
+    noise = torch.zeros(t.n_layers, V)
+    tokens = torch.full((t.n_nodes,), -7, dtype=torch.int32, device="cuda")
+    ctx.op_sample(kv, logits.cuda(), noise.cuda(), 2.0, tokens, noise_pos0=3)
+    want = [0 if r.isnan().all() else int(torch.where(r.isnan(), -float("inf"), r).argmax()) for r in logits]
+    assert tokens.cpu().tolist() == want
+    ctx.close()
