@@ -180,7 +180,7 @@ __global__ __launch_bounds__(RW * KS * 64) void k_attn_rows(const bf16_t *__rest
       den += ml.y * w;
       v += xa[(k * RW * 32 + r) * 32 + (c ^ (r & 31))] * w;
     }
-    v *= den > 0.f ? 1.0f / den : 0.f;
+    v *= nsplit == 1 || den > 0.f ? 1.0f / den : 0.f; // a share may have seen no key of the row, the whole sequence not
     const int nd = r / G, hh = hk * G + (r - nd * G);
     if (nsplit == 1) {
       const ushort4 o = ushort4{f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};

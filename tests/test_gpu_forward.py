@@ -418,6 +418,39 @@ def test_few_rows_attention(tmpl_name, H, Hkv, L):
     test_tree_attention_matches_per_path_attention(tmpl_name, H, Hkv, L, True)
 
 
+@pytest.mark.parametrize("tmpl_name,H,Hkv,L", [("single", 16, 2, 40), ("prefix3", 64, 8, 150), ("prefix3", 64, 8, 3001)])
+def test_few_rows_attention_without_a_finite_score(tmpl_name, H, Hkv, L):
+    """A row whose query is not a number, or whose scores are all -inf, has no softmax: its result is NaN with one key
+    share and with several, and the other rows are what they are without it."""
+    require_gpu()
+    say("few rows, no finite score", tmpl_name, H, Hkv, L)
+    t = synth.prefix_template(int(tmpl_name[6:])) if tmpl_name.startswith("prefix") else synth.TEMPLATES[tmpl_name]()
+    n = t.n_nodes
+    kv = tr.KVDesc(synth.ModelShape("att", 1, H * 128, H, Hkv, 128, 64, 64, "bf16"), capacity=L + n)
+    kv.reset(L)
+    kp = synth.normal_tensor((1, Hkv, kv.capacity, 128), 1.0, seed=2, dtype=torch.bfloat16)
+    vp = synth.normal_tensor((1, Hkv, kv.capacity, 128), 1.0, seed=3, dtype=torch.bfloat16)
+    kp[0, 0, :L + n, 5] = -float("inf")        # K/V head 0: -inf wherever the query's feature 5 is positive
+    kv_fill(kv, kp.cuda(), vp.cuda())
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    ws = torch.empty(16 * 128 * H * 130 * 4 + 4096, dtype=torch.uint8, device="cuda")
+    q = synth.normal_tensor((n, H, 128), 1.0, seed=1, dtype=torch.bfloat16)
+    q[:, :, 5] = 1.0
+    outs = []
+    for bad in (False, True):
+        if bad:
+            q[n - 1, H - 1, 17] = float("nan")
+        out = torch.zeros(n, H, 128, dtype=torch.bfloat16, device="cuda")
+        ctx.op_tree_attention(kv, 0, H, q.cuda(), out, ws)
+        outs.append(out.cpu())
+    G = H // Hkv
+    assert outs[0][:, :G].isnan().all() and outs[0][:, G:].isfinite().all()
+    assert outs[1][n - 1, H - 1].isnan().all()
+    outs[1][n - 1, H - 1] = outs[0][n - 1, H - 1]
+    assert torch.equal(outs[0][:, G:], outs[1][:, G:])
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,K_,O_,splits", [(80, 4096, 4096, 2), (80, 11008, 4096, 2), (81, 4096, 1024, 4),
                                             (1, 4096, 512, 1), (128, 512, 2048, 1), (16, 256, 64, 1),
                                             (80, 1024, 32000, 1), (80, 4096, 12288, 1), (37, 96, 32, 3),
