@@ -217,9 +217,9 @@ tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_
  * n_kv_heads K/V heads, n_nodes tree nodes and a host bound len_bound on committed length + tree nodes
  * (diagnostic; touches no GPU): plan[0] = query heads one workgroup serves (heads sharing a K/V head
  * share its staged tiles), plan[1] = key-axis splits, or 0 for the one-launch form short sequences take (one
- * workgroup per query head and tile of 16 nodes, its waves splitting the keys, no merge pass).  Few nodes on long
- * sequences take a form of their own (all heads of a group in one workgroup) that is not described here: plan is
- * then what they would get otherwise.  plan is [host], 2 values.  TR_EINVAL for null
+ * workgroup per query head and tile of 16 nodes, its waves splitting the keys, no merge pass), or -s for the form
+ * that few nodes take on other lengths (all heads of a group are rows of one operand, s key shares, no merge
+ * pass if s = 1).  plan is [host], 2 values.  TR_EINVAL for null
  * plan, n_kv_heads < 1, n_heads not a positive multiple of n_kv_heads, n_nodes outside 1..TR_MAX_NODES
  * or len_bound < 1.
  */

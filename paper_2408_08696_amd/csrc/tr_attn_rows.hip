@@ -227,7 +227,7 @@ bool attn_rows_better(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
 }
 
 // Key shares: one, without a merge launch (4.8 us), up to six steps; else all compute units, at least a step each.
-static int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
+int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
   const int steps = ((len_bound + 31) / 32 + key_groups(n * (H / Hkv)) - 1) / key_groups(n * (H / Hkv));
   if (steps <= 6) return 1;
   int s = 256 / Hkv;

@@ -148,6 +148,7 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
 // The same for few rows per K/V head (tr_attn_rows.hip; n * H / Hkv <= 128), and whether it is the faster form;
 // launch_attn_mfma goes there by itself.  launch_attn_merge: part_rows rows per (split, head) in the partial buffers.
 bool attn_rows_better(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound);
+int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound); // its key shares (1: no merge launch)
 hipError_t launch_attn_rows(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
                             int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
                             float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st);

@@ -250,7 +250,8 @@ def plan_projection(n_rows: int, in_f: int, out_f: int, fused_pair: bool = False
 
 
 def plan_attention(n_heads: int, n_kv_heads: int, n_nodes: int, len_bound: int):
-    """(query heads per workgroup, key-axis splits) of one tree-attention launch."""
+    """(query heads per workgroup, key-axis splits; 0: one-launch form, -s: few-rows form in s shares) of one
+    tree-attention launch."""
     plan = (C.c_int32 * 2)()
     _check(lib().tr_plan_attention(n_heads, n_kv_heads, n_nodes, len_bound, plan), "tr_plan_attention")
     return tuple(plan)

@@ -146,6 +146,10 @@ def test_attention_plan(lib):
             prev = 1
             for L in (1, 31, 32, 33, 64, 100, 600, 2048, 8192, 65536):
                 hpw, ns = tr.plan_attention(H, Hkv, n, L)
+                if ns < 0:                                            # few-rows form: the whole group in a workgroup
+                    assert hpw == H // Hkv and n * hpw <= 128 and (hpw > 2 or L > 832)
+                    assert -ns <= 32 and -ns <= -(-L // 32) and (ns == -1 or -ns * Hkv <= 256)
+                    continue
                 if ns == 0:                                           # one-launch form: short sequences only
                     assert hpw == 1 and L <= 832 and H // Hkv <= 2 and prev <= 1
                     continue
@@ -162,6 +166,9 @@ def test_attention_plan(lib):
     assert tr.plan_attention(64, 8, 80, 600)[1] >= 1                      # eight query heads per K/V head: split form
     assert tr.plan_attention(40, 40, 80, 2128) == (1, 6)
     assert tr.plan_attention(64, 8, 80, 4176)[0] == 2
+    assert tr.plan_attention(64, 8, 15, 16015) == (8, -32)                # all eight heads of a group, 32 key shares
+    assert tr.plan_attention(32, 32, 1, 2049) == (1, -8)
+    assert tr.plan_attention(16, 2, 1, 100) == (8, -1)                    # one share: no merge pass
 
 
 def test_static_topk_validates_before_touching_the_gpu(lib):
