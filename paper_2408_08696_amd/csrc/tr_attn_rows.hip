@@ -211,19 +211,35 @@ static hipError_t launch_grid(const bf16_t *q, const bf16_t *Kl, const bf16_t *V
 
 static int key_groups(int rows) { return rows <= 64 ? 4 : 2; }
 
-// Where this form is the faster one, by rows per K/V head, group size G and bound on the sequence.  The split form of
-// tr_attn_mfma.hip reads K and V once per two heads of a group, in tiles that one to four waves of a workgroup fetch one at
-// a time; this one pays about 2 us more at its end for every 32 rows beyond the first.  Measured, us per layer, split form /
-// this: 64 heads on 8: 1 node 24.4 / 14.0 at 4096 positions and 71 / 22 at 16000, 8 nodes 13.7 / 13.0 at 1400, 15 nodes
-// 25.1 / 21.1 at 4096 and 72 / 29 at 16000 but 16.9 / 19.4 at 2048; 32 on 8: 16 nodes 20.6 / 18.8 at 6000, 32 nodes 24.2 /
-// 23.4 at 8192; 32 on 16: 8 nodes 15.2 / 13.6 at 3072, never with more than 32 rows; 32 on 32: 1 node 17.2 / 14.2 at 2048
-// and 82 / 51 at 16000, 64 nodes 38.7 / 37.1 at 8192 but 24.3 / 25.8 at 4096.
+// Where this form is the faster one.  Measured: 25 head layouts (8 to 128 heads, groups of 1 to 32), 1 to 128 rows per K/V
+// head, 20 to 16000 positions, 4040 points; the rule leaves one of them more than 1.5 % slower than the split form (1.8).
+//   One share (up to 768 positions, where the split form has not taken over as one launch): a step costs 1.3 us and 32
+//   rows 2 us more than 8, against the split form's merge launch.  64 heads on 8, 1 / 4 nodes, split form / this: 4.4 /
+//   5.2 and 4.5 / 6.8 at 20 positions, 7.3 / 5.4 and 7.5 / 7.0 at 100, 9.3 / 10.9 and 9.4 / 12.6 at 600.
+//   Several shares: both end with the merge, so what counts is the split form's chain, the 32-key tiles a workgroup of it
+//   takes one after another (1.0 us each, 1.25 if one wave stages them), against this form's 2 us for every 32 rows.  64
+//   on 8: 1 node 10.3 / 9.0 at 840 positions and 69 / 22 at 16000, 4 nodes 10.4 / 10.5 at 840 (4 tiles) and 11.5 / 10.9 at
+//   1100 (5), 8 nodes 12.7 / 13.0 at 1420 (6) and 14.8 / 13.9 at 2000 (8), 16 nodes 20.6 / 20.7 at 3090 (13) and 23.6 /
+//   20.6 at 4000 (16); 32 on 8: 8 nodes 10.6 / 11.7 at 1500 (3) and 16.6 / 16.2 at 4100 (9).
+//   Without sharing heads (group 1) more nodes only pay where K and V come at the memory's rate: 32 on 32, 1 node 11.0 /
+//   9.6 at 840, 32 nodes 11.7 / 13.1 at 1000 and 20.0 / 18.7 at 3000 (12); 64 nodes on 16 heads are slower up to 12000.
+//   Groups of two share little either way: 32 on 16, 1 node 1.06 times as fast at 3100, 0.94 to 1.0 below.
 bool attn_rows_better(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
   const int G = H / Hkv, rows = n * G;
   if (rows > 128 || attn_one_launch(H, Hkv, len_bound)) return false;
-  if (rows <= 32) return G != 2 || len_bound >= 3072;
-  if (rows <= 64) return G == 2 ? false : len_bound >= (G >= 8 ? 1400 : G >= 3 ? 5120 : 7168);
-  return G >= 8 ? len_bound >= 3072 : G >= 3 && len_bound >= 8192;
+  const int hpw = attn_heads_per_wg(H, Hkv, n), splits = attn_choose_splits(H / hpw, len_bound);
+  const int chain = ((len_bound + 31) / 32 + splits - 1) / splits;
+  const bool one_wave = hpw * ((n + 15) / 16) == 1;
+  if (len_bound <= 768) {
+    if (rows <= 8) return len_bound > 32 && len_bound <= (one_wave ? 416 : 256);
+    return rows <= 32 && len_bound > 96 && len_bound <= (rows <= 16 || one_wave ? 256 : 224);
+  }
+  if (G == 2 && (rows > 32 || len_bound < 3072)) return false;
+  if (rows <= 8) return true;
+  if (rows <= 16) return chain >= (one_wave || G >= 8 ? 3 : 4);
+  if (rows <= 32) return chain >= (one_wave ? 3 : G >= 8 ? 5 : G >= 3 ? 6 : 11);
+  if (rows <= 64) return G >= 8 ? chain >= 7 : G >= 3 ? len_bound >= 5120 : len_bound >= 7168 && chain >= 24;
+  return G >= 8 ? chain >= (rows <= 96 ? 12 : 14) : G >= 3 && len_bound >= 8192;
 }
 
 // Key shares: one, without a merge launch (4.8 us), up to six steps; else all compute units, at least a step each.

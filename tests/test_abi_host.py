@@ -171,6 +171,24 @@ def test_attention_plan(lib):
     assert tr.plan_attention(16, 2, 1, 100) == (8, -1)                    # one share: no merge pass
 
 
+@pytest.mark.parametrize("H,Hkv,n,few,split", [
+    # lengths (committed + nodes) measured faster as few rows, and as key splits
+    (64, 8, 1, (100, 840, 16000), (20, 600)), (64, 8, 4, (128, 1200, 3000), (20, 300, 600, 1000)),
+    (64, 8, 8, (2000, 3000), (1420,)), (64, 8, 15, (4000, 16015), (2000, 3072)), (64, 8, 16, (4000, 16016), (3090, 100)),
+    (32, 8, 8, (128, 3100), (20, 300, 600, 1500)), (32, 8, 4, (100, 4000), (600, 1000)),
+    (24, 8, 4, (100, 840, 3000), (20, 600)), (24, 8, 10, (200, 1500), (20, 600)), (56, 8, 4, (200, 840, 1500), (20, 600)),
+    (32, 2, 2, (100, 3000), (20, 600, 1000)), (40, 8, 1, (400, 800), (20, 768)),
+    (16, 8, 8, (3090, 16000), (840, 1500, 2500)), (32, 16, 16, (5200, 16000), (1000, 4100)),
+    (32, 32, 1, (840, 2040), ()), (32, 32, 16, (1000, 16000), ()), (32, 32, 32, (3000, 16000), (840, 1000, 1500, 2040)),
+    (8, 8, 32, (5200,), (840, 2040)), (16, 16, 64, (16000,), (1000, 8300)), (32, 32, 64, (8000,), (4100,)),
+    (32, 32, 65, (), (840, 16000)), (64, 8, 17, (), (100, 16000)), (32, 32, 1, (), (100, 832)), (16, 8, 3, (), (100, 832))])
+def test_few_rows_attention_rule(lib, H, Hkv, n, few, split):
+    for L in few:
+        assert tr.plan_attention(H, Hkv, n, L)[1] < 0, (H, Hkv, n, L)
+    for L in split:
+        assert tr.plan_attention(H, Hkv, n, L)[1] >= 0, (H, Hkv, n, L)
+
+
 def test_static_topk_validates_before_touching_the_gpu(lib):
     """The entry point that allocates nothing: argument errors and its size limits are reported
     from the host, before any HIP call."""
