@@ -309,7 +309,7 @@ tr_status tr_prefill(tr_ctx *c, const tr_model *m, tr_kv *kv, const int32_t *d_t
   if ((int64_t)kv->len_bound + n_tokens > kv->capacity) return TR_ECAPACITY;
   if (ws_bytes < plan_workspace(*m).total) return TR_ECAPACITY;
   hipStream_t st = as_stream(stream);
-  const int most = prefill_rows(*m, *kv, ws_bytes);
+  const int most = prefill_rows(*m, *kv, ws, ws_bytes);
   int rows = most;
   if (most > NP && n_tokens > most) { // passes of about the same size: a short last one would stream all weights for a few rows
     const int passes = (n_tokens + most - 1) / most;

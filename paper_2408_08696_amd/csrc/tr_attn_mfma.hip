@@ -500,7 +500,7 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
                             int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
                             float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st) {
   if (Hkv < 1 || H % Hkv != 0) return hipErrorInvalidValue;
-  if (attn_rows_better(H, Hkv, n, len_bound))
+  if (attn_rows_better(H, Hkv, n, len_bound) && starts_on_16(Kl) && starts_on_16(Vl))
     return launch_attn_rows(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, part_ml, part_acc, out, out_row_tiles, prof, st);
   const KernelTimer tm = prof_next(prof, PC_ATTN);
   if (attn_one_launch(H, Hkv, len_bound)) {

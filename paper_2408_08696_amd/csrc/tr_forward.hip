@@ -572,20 +572,27 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
   return hipSuccess;
 }
 
-static bool wide_supported(const tr_model &m, const tr_kv &kv) {
-  return packed_supported(m) && kv.layout == TR_KV_TILED && kv.dtype == TR_BF16 && m.head_dim == 128 &&
-         m.d_model >= 64 && m.d_ffn >= 64;
+static bool wide_supported(const tr_model &m, const tr_kv &kv, const void *ws) {
+  if (!packed_supported(m) || kv.layout != TR_KV_TILED || kv.dtype != TR_BF16 || m.head_dim != 128 || m.d_model < 64 ||
+      m.d_ffn < 64)
+    return false;
+  bool on = starts_on_16(ws) && starts_on_16(kv.k) && starts_on_16(kv.v); // what its kernels load straight into LDS
+  for (int l = 0; l < m.n_layers; ++l) {
+    const tr_layer &w = m.layers[l];
+    for (const void *p : {w.wq, w.wk, w.wv, w.wo, w.w_gate, w.w_up, w.w_down}) on = on && starts_on_16(p);
+  }
+  return on;
 }
 
-int32_t prefill_rows(const tr_model &m, const tr_kv &kv, size_t ws_bytes) {
-  if (!wide_supported(m, kv)) return NP;
+int32_t prefill_rows(const tr_model &m, const tr_kv &kv, const void *ws, size_t ws_bytes) {
+  if (!wide_supported(m, kv, ws)) return NP;
   return ws_bytes >= plan_workspace(m, NPW_MOST).total ? NPW_MOST : NPW;
 }
 
 hipError_t run_prefill_pass(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n, int32_t most,
                             const int32_t *d_tokens, void *ws, hipStream_t st) {
-  if (n > NP && wide_supported(m, kv) && n <= most) return forward_wide(m, kv, n, most, d_tokens, (unsigned char *)ws, st);
-  if (n > NP) return hipErrorInvalidValue;
+  if (n > most) return hipErrorInvalidValue;
+  if (n > NP) return forward_wide(m, kv, n, most, d_tokens, (unsigned char *)ws, st);
   return run_forward(m, kv, chain, n, d_tokens, nullptr, ws, nullptr, st);
 }
 
@@ -619,6 +626,12 @@ size_t linear_workspace_bytes(int32_t n, int32_t in_f, int32_t out_f, int32_t sp
 hipError_t run_linear(const void *x, const void *w, int32_t dtype, int32_t layout, int32_t n, int32_t in_f,
                       int32_t out_f, int32_t splits, float *y, void *ws, hipStream_t st) {
   if (layout == TR_PACKED) {
+    if (n > NP && !(starts_on_16(w) && starts_on_16(ws))) { // the decode kernel, NP rows at a time
+      for (int lo = 0; lo < n; lo += NP)
+        TR_TRY(run_linear((const bf16_t *)x + (size_t)lo * in_f, w, dtype, layout, n - lo < NP ? n - lo : NP, in_f, out_f, splits,
+                          y + (size_t)lo * out_f, ws, st));
+      return hipSuccess;
+    }
     const int NT = (n + 15) / 16;
     bf16_t *frag = (bf16_t *)ws;
     float *part = (float *)((unsigned char *)ws + align256((size_t)NT * 16 * in_f * 2));

@@ -174,10 +174,10 @@ hipError_t launch_stream(const void *src, void *dst, size_t bytes, hipStream_t s
 // Runs rows `tokens` through the model.  `write_logits` may be NULL (no LM head).
 hipError_t run_forward(const tr_model &m, const tr_kv &kv, const TreeDev &tree, int32_t n,
                        const int32_t *d_tokens, float *write_logits, void *ws, Profiler *prof, hipStream_t s);
-// Prompt ingestion: rows one pass may take for this model, cache and workspace size (NPW_MOST or NPW on the packed path
-// with a tiled cache, else NP), and the pass itself: n <= `most` consecutive prompt tokens, causal, keys / values appended
-// at the committed length (which the caller advances afterwards), no logits.
-int32_t prefill_rows(const tr_model &m, const tr_kv &kv, size_t ws_bytes);
+// Prompt ingestion: rows one pass may take for this model, cache and workspace (NPW_MOST or NPW on the packed path with a
+// tiled cache and all blocks on 16 bytes, else NP), and the pass itself: n <= `most`, which prefill_rows gave, consecutive
+// prompt tokens, causal, keys / values appended at the committed length (which the caller advances afterwards), no logits.
+int32_t prefill_rows(const tr_model &m, const tr_kv &kv, const void *ws, size_t ws_bytes);
 hipError_t run_prefill_pass(const tr_model &m, const tr_kv &kv, const TreeDev &chain, int32_t n, int32_t most,
                             const int32_t *d_tokens, void *ws, hipStream_t s);
 hipError_t run_tree_attention(const tr_kv &kv, int32_t layer, int32_t H, const TreeDev &tree,

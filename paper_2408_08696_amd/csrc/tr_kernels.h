@@ -30,6 +30,8 @@ __device__ inline void tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gba
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(gbase)
                : "memory"); // nothing the compiler emits here uses m0
 }
+// What these loads read has to start on 16 bytes; callers take a kernel with plain loads for blocks that do not.
+inline bool starts_on_16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 // Waits until at most `left` of this wave's tile loads are still under way and all its LDS reads have returned.
 template <int left>
 __device__ inline void wait_tiles() {

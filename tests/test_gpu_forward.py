@@ -505,6 +505,82 @@ def test_wide_projection_edges(n, K_, O_, splits):
     ctx.close()
 
 
+def _off_16(x):
+    """The same values in memory that starts 8 bytes behind a multiple of 16."""
+    buf = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)
+    y = buf[4:4 + x.numel()].view(x.shape).copy_(x)
+    assert y.data_ptr() % 16 == 8
+    return y
+
+
+@pytest.mark.parametrize("what", ["weights", "cache", "workspace"])
+def test_prefill_from_blocks_off_16_bytes(what):
+    """Prompt ingestion with weights, a cache or a workspace that does not start on 16 bytes (a caller's own arena): the
+    kernels that load straight into LDS are not for them; the cache comes out as from aligned ones."""
+    require_gpu()
+    say("prefill off 16 bytes", what)
+    sh = synth.SHAPES["tiny_gqa_bf16"]
+    w = to_gpu(synth.make_weights(sh, seed=6))
+    prompt = synth.zipf_prompt(sh.vocab, 301, seed=6).tolist()
+    caches = []
+    for off in (False, True):
+        eng = tr.Engine(sh, w, synth.tree15(), k=K, capacity=352)
+        if off and what == "workspace":
+            eng.ws = torch.cat([eng.ws, eng.ws[:16]])[8:]
+            assert eng.ws.data_ptr() % 16 == 8
+        elif off and what == "cache":
+            eng.kv.k, eng.kv.v = _off_16(eng.kv.k), _off_16(eng.kv.v)
+            eng.kv.c.k, eng.kv.c.v = eng.kv.k.data_ptr(), eng.kv.v.data_ptr()
+        elif off:
+            keep = [_off_16(lw["w_gate"]) for lw in eng.model.weights["layers"]]
+            for l, x in enumerate(keep):
+                eng.model._layers[l].w_gate = x.data_ptr()
+        eng.prefill(prompt)
+        torch.cuda.synchronize()
+        assert int(eng.kv.d_len.item()) == 300
+        caches.append([x[:, :, :300].float() for x in kv_plain_views(eng.kv)])
+    for a, b in zip(*caches):
+        # per row; two bf16 forwards with their sums in another order
+        err = (a - b).abs().amax(dim=(1, 3)) / a.abs().amax(dim=(1, 3))
+        assert float(err.max()) < 2e-2
+
+
+def test_attention_and_linear_from_blocks_off_16_bytes():
+    require_gpu()
+    say("attention and linear off 16 bytes")
+    sh = synth.ModelShape("att", 1, 64 * 128, 64, 8, 128, 64, 64, "bf16")
+    t = synth.prefix_template(3)
+    q = synth.normal_tensor((3, 64, 128), 1.0, seed=1, dtype=torch.bfloat16).cuda()
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    ws = torch.empty(16 * 128 * 64 * 130 * 4 + 4096, dtype=torch.uint8, device="cuda")
+    kv = tr.KVDesc(sh, capacity=1504)
+    kv.reset(1500)
+    kv.k.copy_(synth.normal_tensor(tuple(kv.k.shape), 1.0, seed=2, dtype=torch.bfloat16))
+    kv.v.copy_(synth.normal_tensor(tuple(kv.v.shape), 1.0, seed=3, dtype=torch.bfloat16))
+    assert tr.plan_attention(64, 8, 3, 1503)[1] < 0
+    outs = []
+    for off in (False, True):
+        if off:
+            kv.k, kv.v = _off_16(kv.k), _off_16(kv.v)
+            kv.c.k, kv.c.v = kv.k.data_ptr(), kv.v.data_ptr()
+        out = torch.zeros(3, 64, 128, dtype=torch.bfloat16, device="cuda")
+        ctx.op_tree_attention(kv, 0, 64, q, out, ws)
+        outs.append(out.float())
+    assert float((outs[0] - outs[1]).abs().max()) < 2e-2 * float(outs[0].abs().max())
+    n, K_, O_ = 300, 736, 2080
+    x = synth.normal_tensor((n, K_), 1.0, seed=8, dtype=torch.bfloat16).cuda()
+    w = synth.uniform_tensor((O_, K_), float(np.sqrt(3.0 / K_)), seed=9, tensor_id=1, dtype=torch.bfloat16).cuda()
+    ref = x.double() @ w.double().T
+    wp = tr.pack_weight(w)
+    ws = torch.empty((n + 15) // 16 * 16 * K_ * 2 + 512 + 2 * n * O_ * 4 + 528, dtype=torch.uint8, device="cuda")
+    for splits in (1, 2):
+        for a, b in ((_off_16(wp), ws), (wp, ws[8:])):
+            y = torch.full((n, O_), float("nan"), device="cuda")
+            ctx.op_linear(x, a, y, b, packed=True, splits=splits)
+            assert float((y.double() - ref).abs().max()) < 2e-5 * np.sqrt(K_)
+    ctx.close()
+
+
 def test_linear_row_limits():
     """Packed weights take up to TR_PREFILL_ROWS rows (the prompt-ingestion kernel above TR_MAX_NODES), row-major
     ones TR_MAX_NODES; one more is TR_EINVAL, on the host, before any launch."""
