@@ -420,9 +420,9 @@ tr_status tr_profile_enable(tr_ctx *c, int32_t enable) {
 
 tr_status tr_profile_read(tr_ctx *c, tr_profile_entry *h, int32_t max_entries, int32_t *n_entries) {
   static const char *const names[PC_COUNT] = {"build_tree", "embed_rope_table", "residual_norm", "qkv_proj",
-                                              "rope_kv_write", "tree_attention", "attention_merge", "o_proj",
-                                              "gate_up_swiglu", "down_proj", "lm_head", "topk", "topk_merge",
-                                              "accept_update", "compact_kv", "sample_tokens"};
+                                              "tree_attention", "attention_merge", "o_proj", "gate_up_swiglu",
+                                              "down_proj", "lm_head", "topk", "topk_merge", "accept_update",
+                                              "compact_kv", "sample_tokens"};
   if (c == nullptr || h == nullptr || n_entries == nullptr || max_entries < 0) return TR_EINVAL;
   Profiler &p = c->prof;
   if (hipDeviceSynchronize() != hipSuccess) return TR_EHIP;

@@ -1,4 +1,4 @@
-// Tree attention for few query rows per K/V head (up to 128 pairs of node and query head): every K/V byte is read once.
+// Tree attention for few query rows per K/V head (up to 64 nodes and 128 pairs of node and query head): every K/V byte is read once.
 //
 // The queries that share a K/V head are the rows of one operand, row = node * group + head of the group, so that a group's
 // heads share each K/V tile in a workgroup's LDS instead of re-reading it from L2 one workgroup after another.  A workgroup
@@ -23,6 +23,8 @@ __device__ inline f32x16 mfma32r(const u32x4 &a, const u32x4 &b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+constexpr int ROWS_NODES = NP / 2; // most nodes: half as many as the partial buffers are made for, in twice the shares
+
 constexpr size_t rows_lds_bytes(int rw, int ks, int d) { // the rings; at the end the accumulators and (maximum, sum)
   const size_t ring = (size_t)ks * d * 16384, meet = (size_t)ks * rw * 32 * (512 + 8);
   return ring > meet ? ring : meet;
@@ -34,8 +36,7 @@ __global__ __launch_bounds__(RW * KS * 64) void k_attn_rows(const bf16_t *__rest
                                                             int32_t cap, int32_t n, const uint64_t *__restrict__ anc,
                                                             const int32_t *__restrict__ d_len, int32_t nsplit,
                                                             float *__restrict__ part_ml, float *__restrict__ part_acc,
-                                                            int32_t part_rows, bf16_t *__restrict__ out,
-                                                            int32_t out_row_tiles) {
+                                                            bf16_t *__restrict__ out, int32_t out_row_tiles) {
   constexpr int LOADS = (16 + RW - 1) / RW; // tile loads of a wave per step
   extern __shared__ u32x4 lds[];            // [KS][D][K 8 tiles | V 8 tiles][64]
   const int tid = threadIdx.x, lane = tid & 63;
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(RW * KS * 64) void k_attn_rows(const bf16_t *__rest
       const size_t idx = out_row_tiles > 0 ? act_frag_index(nd, hh * 128 + 4 * c, out_row_tiles) : ((size_t)nd * H + hh) * 128 + 4 * c;
       store_stream(out + idx, o);
     } else {
-      const size_t prow = ((size_t)split * H + hh) * part_rows + nd;
+      const size_t prow = ((size_t)split * H + hh) * ROWS_NODES + nd;
       if (c == 0) *reinterpret_cast<float2 *>(part_ml + prow * 2) = float2{top, den};
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = fminf(fmaxf(v[e], -65504.0f), 65504.0f); // saturate, as in k_attn_mfma
@@ -199,14 +200,13 @@ __global__ __launch_bounds__(RW * KS * 64) void k_attn_rows(const bf16_t *__rest
 template <int RW, int KS, int D>
 static hipError_t launch_grid(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
                               int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t nsplit, float *part_ml,
-                              float *part_acc, int32_t part_rows, bf16_t *out, int32_t out_row_tiles, hipStream_t st,
-                              KernelTimer tm) {
+                              float *part_acc, bf16_t *out, int32_t out_row_tiles, hipStream_t st, KernelTimer tm) {
   constexpr int smem = (int)rows_lds_bytes(RW, KS, D);
   static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_rows<RW, KS, D>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
   if (!once) return hipErrorInvalidValue;
   return launch(k_attn_rows<RW, KS, D>, dim3(Hkv, nsplit), dim3(RW * KS * 64), smem, st, tm, q, Kl, Vl, H, Hkv, cap, n, anc,
-                d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles);
+                d_len, nsplit, part_ml, part_acc, out, out_row_tiles);
 }
 
 static int key_groups(int rows) { return rows <= 64 ? 4 : 2; }
@@ -226,7 +226,7 @@ static int key_groups(int rows) { return rows <= 64 ? 4 : 2; }
 //   Groups of two share little either way: 32 on 16, 1 node 1.06 times as fast at 3100, 0.94 to 1.0 below.
 bool attn_rows_better(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
   const int G = H / Hkv, rows = n * G;
-  if (rows > 128 || attn_one_launch(H, Hkv, len_bound)) return false;
+  if (n > ROWS_NODES || rows > 128 || attn_one_launch(H, Hkv, len_bound)) return false;
   const int hpw = attn_heads_per_wg(H, Hkv, n), splits = attn_choose_splits(H / hpw, len_bound);
   const int chain = ((len_bound + 31) / 32 + splits - 1) / splits;
   const bool one_wave = hpw * ((n + 15) / 16) == 1;
@@ -247,8 +247,7 @@ int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
   const int steps = ((len_bound + 31) / 32 + key_groups(n * (H / Hkv)) - 1) / key_groups(n * (H / Hkv));
   if (steps <= 6) return 1;
   int s = 256 / Hkv;
-  const int most = n <= 64 ? 2 * ATTN_MAX_SPLITS : ATTN_MAX_SPLITS; // what the partial buffers hold
-  if (s > most) s = most;
+  if (s > 2 * ATTN_MAX_SPLITS) s = 2 * ATTN_MAX_SPLITS; // what the partial buffers hold with ROWS_NODES nodes each
   if (s > steps) s = steps;
   return s < 1 ? 1 : s;
 }
@@ -256,20 +255,20 @@ int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound) {
 hipError_t launch_attn_rows(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
                             int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
                             float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st) {
-  if (Hkv < 1 || H % Hkv != 0 || n < 1 || n * (H / Hkv) > 128) return hipErrorInvalidValue;
-  const int rows = n * (H / Hkv), nsplit = attn_rows_splits(H, Hkv, n, len_bound), part_rows = n <= 64 ? 64 : NP;
+  if (Hkv < 1 || H % Hkv != 0 || n < 1 || n > ROWS_NODES || n * (H / Hkv) > 128) return hipErrorInvalidValue;
+  const int rows = n * (H / Hkv), nsplit = attn_rows_splits(H, Hkv, n, len_bound);
   const KernelTimer tm = prof_next(prof, PC_ATTN);
   hipError_t e;
   if (rows <= 32)
-    e = launch_grid<1, 4, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+    e = launch_grid<1, 4, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, st, tm);
   else if (rows <= 64)
-    e = launch_grid<2, 4, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+    e = launch_grid<2, 4, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, st, tm);
   else if (rows <= 96)
-    e = launch_grid<3, 2, 4>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+    e = launch_grid<3, 2, 4>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, st, tm);
   else
-    e = launch_grid<4, 2, 4>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, part_rows, out, out_row_tiles, st, tm);
+    e = launch_grid<4, 2, 4>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, st, tm);
   if (e != hipSuccess || nsplit == 1) return e;
-  return launch_attn_merge(part_ml, part_acc, part_rows, H, n, nsplit, out, out_row_tiles, prof_next(prof, PC_ATTN_MERGE), st);
+  return launch_attn_merge(part_ml, part_acc, ROWS_NODES, H, n, nsplit, out, out_row_tiles, prof_next(prof, PC_ATTN_MERGE), st);
 }
 
 } // namespace tr

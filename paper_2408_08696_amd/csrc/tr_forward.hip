@@ -23,10 +23,11 @@ Workspace plan_workspace(const tr_model &m, int rows) {
   const size_t esz = dtype_size(m.dtype);
   const size_t hq = (size_t)m.n_heads * m.head_dim;
   const size_t R = generic ? NP : rows; // rows of the activation buffers
+  const size_t packed = generic ? 0 : 1; // what only the packed path uses
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
   w.x = take(R * m.d_model * 4);
-  w.xn = take(R * m.d_model * esz);
+  w.xn = take(packed * R * m.d_model * esz);
   w.q = take(R * hq * esz);
   w.attn = take(R * hq * esz);
   w.h = take(R * m.d_ffn * esz);
@@ -34,9 +35,9 @@ Workspace plan_workspace(const tr_model &m, int rows) {
   w.logits = take((size_t)NP * m.vocab * 4);
   w.part_ml = take((size_t)ATTN_MAX_SPLITS * NP * m.n_heads * 2 * 4);
   w.part_acc = take((size_t)ATTN_MAX_SPLITS * NP * m.n_heads * m.head_dim * 4);
-  w.ypart = take((generic ? (size_t)GEMM_MAX_SPLITS * NP : (size_t)WIDE_PART_ROWS) * m.d_model * 4);
-  static_assert(WIDE_PART_ROWS >= GEMM_MAX_SPLITS * NP && WIDE_PART_ROWS >= NPW_MOST, "ypart serves both paths");
-  w.ssq = take(R * ((m.d_model + 1023) / 1024) * 4);
+  w.ypart = take(packed * WIDE_PART_ROWS * m.d_model * 4);
+  static_assert(WIDE_PART_ROWS >= GEMM_MAX_SPLITS * NP && WIDE_PART_ROWS >= NPW_MOST, "ypart serves steps and passes");
+  w.ssq = take(packed * R * ((m.d_model + 1023) / 1024) * 4);
   w.total = off;
   return w;
 }

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
             *reinterpret_cast<float4 *>(g.y + (size_t)split * g.split_stride + (size_t)row * g.ldy + o) =
                 float4{v[0], v[1], v[2], v[3]};
           } else {
-            // fused Q/K/V epilogue, as in the decode kernel: (o, o+1) and (o+2, o+3) are rotation pairs
+            // fused Q/K/V epilogue, as in the decode kernel, into a tiled cache: (o, o+1) and (o+2, o+3) are rotation pairs
             const GemmRope &rp = g.rope;
             const int hd = rp.hd, head = o / hd, dd = o - head * hd;
             const int pos = *rp.d_len + row;
@@ -281,18 +281,12 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
             if (head < rp.H + rp.Hkv) {
               bf16_t *dst;
               if (head < rp.H) dst = rp.q + ((size_t)row * rp.H + head) * hd + dd;
-              else if (rp.tiled) dst = rp.k_layer + (size_t)(head - rp.H) * rp.cap * hd + kv_k_index(pos, dd);
-              else dst = rp.k_layer + ((size_t)(head - rp.H) * rp.cap + pos) * hd + dd;
+              else dst = rp.k_layer + (size_t)(head - rp.H) * rp.cap * hd + kv_k_index(pos, dd);
               *reinterpret_cast<ushort4 *>(dst) = ushort4{e0, e1, e2, e3};
             } else {
               bf16_t *dst = rp.v_layer + (size_t)(head - rp.H - rp.Hkv) * hd * rp.cap;
-              if (rp.tiled) {
-                dst[kv_v_index(pos, dd)] = e0; dst[kv_v_index(pos, dd + 1)] = e1;
-                dst[kv_v_index(pos, dd + 2)] = e2; dst[kv_v_index(pos, dd + 3)] = e3;
-              } else {
-                dst[(size_t)dd * rp.cap + pos] = e0; dst[(size_t)(dd + 1) * rp.cap + pos] = e1;
-                dst[(size_t)(dd + 2) * rp.cap + pos] = e2; dst[(size_t)(dd + 3) * rp.cap + pos] = e3;
-              }
+              dst[kv_v_index(pos, dd)] = e0; dst[kv_v_index(pos, dd + 1)] = e1;
+              dst[kv_v_index(pos, dd + 2)] = e2; dst[kv_v_index(pos, dd + 3)] = e3;
             }
           }
         } else {
@@ -352,6 +346,7 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
   if (g.mode == GEMM_SWIGLU && g.row_ssq == nullptr) return hipErrorInvalidValue;
+  if (g.rope.q != nullptr && !g.rope.tiled) return hipErrorInvalidValue;
   const bool may_split = g.mode == GEMM_STORE && g.rope.q == nullptr && g.row_ssq == nullptr && max_splits > 1;
   const int row_tiles = (g.n + 15) / 16;
   const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles

@@ -67,7 +67,8 @@ struct TreeDev {
 // the packed path serves, the activation buffers (x, xn, q, attn, h, rope, ssq) hold the `rows` of one prompt-ingestion
 // pass and ypart WIDE_PART_ROWS.  NPW rows are what every workspace must have; tr_workspace_bytes asks for NPW_MOST,
 // enough for whole rounds of the projections' largest workgroup shape at every width (4095 tokens of 8 70B-wide layers:
-// 50.7 ms in passes of 512 rows, 40.8 in passes of 2048 with their attention in one launch), and a pass takes as many rows as its workspace was sized for.
+// 50.7 ms in passes of 512 rows, 40.8 in passes of 2048 with their attention in one launch), and a pass takes as many rows
+// as its workspace was sized for.
 struct Workspace {
   size_t x;        // float  [NP, d]            residual stream
   size_t xn;       // T      [NP, d]            normalised activations (packed path)
@@ -78,8 +79,8 @@ struct Workspace {
   size_t logits;   // float  [NP, V]            used when the caller passes no logits buffer
   size_t part_ml;  // float  [SPLITS, NP, H, 2] attention split partials: running max, sum
   size_t part_acc; // float  [SPLITS, NP, H, hd]
-  size_t ypart;    // float  [GEMM_MAX_SPLITS, NP, d] K-split partial sums of o_proj / down_proj
-  size_t ssq;      // float  [NP, ceil(d/1024)] per-row partial sums of squares of the residual stream
+  size_t ypart;    // float  [GEMM_MAX_SPLITS, NP, d] K-split partial sums of o_proj / down_proj (packed path)
+  size_t ssq;      // float  [NP, ceil(d/1024)] per-row partial sums of squares of the residual stream (packed path)
   size_t total;
 };
 constexpr int NP = TR_MAX_NODES;
@@ -97,7 +98,7 @@ Workspace plan_workspace(const tr_model &m, int rows = NPW);
 // two is the kernel's own duration, without the launch latency an event pair recorded around a launch
 // would include.
 // ---------------------------------------------------------------------------------------------
-enum ProfCat { PC_BUILD = 0, PC_EMBED, PC_NORM, PC_QKV, PC_ROPE, PC_ATTN, PC_ATTN_MERGE, PC_OPROJ, PC_GATEUP, PC_DOWN,
+enum ProfCat { PC_BUILD = 0, PC_EMBED, PC_NORM, PC_QKV, PC_ATTN, PC_ATTN_MERGE, PC_OPROJ, PC_GATEUP, PC_DOWN,
                PC_LMHEAD, PC_TOPK, PC_TOPK_MERGE, PC_ACCEPT, PC_COMPACT, PC_SAMPLE, PC_COUNT };
 struct KernelTimer {
   hipEvent_t start = nullptr, stop = nullptr; // both null: launch untimed

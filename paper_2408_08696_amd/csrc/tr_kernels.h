@@ -147,7 +147,7 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
                             int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, float *part_ml,
                             float *part_acc, bf16_t *out, int32_t out_row_tiles, Profiler *prof, hipStream_t st);
 
-// The same for few rows per K/V head (tr_attn_rows.hip; n * H / Hkv <= 128), and whether it is the faster form;
+// The same for few rows per K/V head (tr_attn_rows.hip; n <= 64, n * H / Hkv <= 128), and whether it is the faster form;
 // launch_attn_mfma goes there by itself.  launch_attn_merge: part_rows rows per (split, head) in the partial buffers.
 bool attn_rows_better(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound);
 int attn_rows_splits(int32_t H, int32_t Hkv, int32_t n, int32_t len_bound); // its key shares (1: no merge launch)
