@@ -188,42 +188,90 @@ def test_prefill_crosses_chunk_boundaries():
         assert np.abs(vg[l] - kv.v[l][:299]).max() < 1e-4
 
 
-@pytest.mark.parametrize("shape_name,plen", [("tiny_bf16", 100), ("tiny_bf16", 150), ("tiny_gqa_bf16", 150),
-                                             ("tiny_bf16", 513), ("tiny_gqa_bf16", 600), ("tiny_bf16", 700),
-                                             ("zoo_heads32", 300), ("tiny_gqa_bf16", 1100), ("tiny_bf16", 2049)])
-def test_packed_prefill_cache_matches_oracle(shape_name, plen):
-    """Packed bf16 models rotate and store queries, keys and values in the epilogue of the fused Q/K/V
-    projection; the committed cache must hold the oracle's keys (read back through the interleaved feature
-    order of such models) and values, to bf16 accuracy.  With a tiled cache, prompts beyond 128 tokens go
-    through the wide projection kernel in passes of up to 512 rows with attention per block of 128: the
-    lengths cover one decode-path pass (99 rows), a ragged second block (149), exactly one full pass (512), a
-    full pass plus a decode-path remainder (599 = 512 + 87), plus a ragged wide pass (699 = 512 + 187), a
-    single-layer model (only the Q/K/V projection runs), two full passes (1099 = 512 + 512 + 75) and four (2048)."""
-    require_gpu()
-    say("packed prefill cache", shape_name, plen)
-    sh = synth.SHAPES[shape_name]
-    w = synth.make_weights(sh, seed=2)
-    wn = synth.weights_to_numpy(w)
-    prompt = synth.zipf_prompt(sh.vocab, plen, seed=2).tolist()
-    eng = tr.Engine(sh, to_gpu(w), synth.tree15(), k=K, capacity=plen + 106)
-    assert eng.model.packed and eng.kv.tiled
-    eng.prefill(prompt)
-    torch.cuda.synchronize()
-    n = plen - 1
-    assert int(eng.kv.d_len.item()) == n and eng.kv.c.len_bound == n
-    cfg = oracle_cfg(sh)
-    kv = O.KVCache(cfg, plen + 106)
-    O.prefill(cfg, wn, kv, prompt[:-1])
+HEADS32 = synth.ModelShape("heads32", 2, 256, 32, 32, 128, 672, 2048, "bf16")
+HEADS64_8 = synth.ModelShape("heads64_8", 2, 256, 64, 8, 128, 672, 2048, "bf16")
+
+
+def _shape(name):
+    return {"heads32": HEADS32, "heads64_8": HEADS64_8}.get(name) or synth.SHAPES[name]
+
+
+def _smallest_workspace(eng):
+    """Cuts the engine's workspace to what passes of 512 rows need."""
+    sh = eng.shape  # bytes per row of the activation buffers: x, xn, q, attn, h, rope, ssq
+    per_row = sh.d_model * 6 + sh.n_heads * sh.head_dim * 4 + sh.d_ffn * 2 + sh.head_dim * 4 + (sh.d_model + 1023) // 1024 * 4
+    eng.ws = eng.ws[:eng.ws.numel() - 1536 * per_row]
+
+
+def _cache_against_oracle(eng, kv, n):
     kp, vp = kv_plain_views(eng.kv, k_interleaved=True)
     kg = kp[:, :, :n, :].permute(0, 2, 1, 3).float().cpu().numpy()
     vg = vp[:, :, :n, :].permute(0, 2, 1, 3).float().cpu().numpy()
-    for l in range(sh.n_layers):
+    for l in range(eng.shape.n_layers):
         # per row, so that a wrong row in one block cannot hide behind the largest entry of the whole cache
         dk = np.abs(kg[l] - kv.k[l][:n]).max(axis=(1, 2)) / np.abs(kv.k[l][:n]).max(axis=(1, 2))
         dv = np.abs(vg[l] - kv.v[l][:n]).max(axis=(1, 2)) / np.abs(kv.v[l][:n]).max(axis=(1, 2))
         say("layer", l, "relative K error", dk.max(), "at row", int(dk.argmax()), "V error", dv.max(), "at row",
             int(dv.argmax()))
         assert dk.max() < 2e-2 and dv.max() < 2e-2
+
+
+@pytest.mark.parametrize("shape_name,plen,small", [("tiny_bf16", 100, False), ("tiny_bf16", 150, False),
+                                                   ("tiny_gqa_bf16", 150, False), ("tiny_bf16", 513, False),
+                                                   ("tiny_gqa_bf16", 600, False), ("tiny_bf16", 700, False),
+                                                   ("zoo_heads32", 300, False), ("tiny_gqa_bf16", 1100, False),
+                                                   ("tiny_bf16", 2049, False),
+                                                   # several passes
+                                                   ("tiny_gqa_bf16", 2101, False), ("tiny_gqa_bf16", 600, True),
+                                                   ("tiny_bf16", 1100, True), ("tiny_bf16", 514, True)])
+def test_packed_prefill_cache_matches_oracle(shape_name, plen, small):
+    """Packed bf16 models rotate and store queries, keys and values in the epilogue of the fused Q/K/V
+    projection; the committed cache must hold the oracle's keys (read back through the interleaved feature
+    order of such models) and values, to bf16 accuracy.  With a tiled cache, prompts beyond 128 tokens go
+    through the ingestion kernels in passes of up to 2048 rows, or 512 with the smallest workspace (`small`): the
+    lengths cover one decode-path pass (99 rows), a ragged second row block (149), whole row blocks (512, 2048), ragged
+    ones (599, 699, 1099), a single-layer model (only the Q/K/V projection runs), two wide passes (2100 = 1280 + 820),
+    wide passes with a short one behind them that the decode kernels take (599 = 512 + 87, 513 = 512 + 1) and three
+    (1099 = 512 + 512 + 75)."""
+    require_gpu()
+    say("packed prefill cache", shape_name, plen, small)
+    sh = _shape(shape_name)
+    w = synth.make_weights(sh, seed=2)
+    wn = synth.weights_to_numpy(w)
+    prompt = synth.zipf_prompt(sh.vocab, plen, seed=2).tolist()
+    eng = tr.Engine(sh, to_gpu(w), synth.tree15(), k=K, capacity=plen + 106)
+    assert eng.model.packed and eng.kv.tiled
+    if small:
+        _smallest_workspace(eng)
+    eng.prefill(prompt)
+    torch.cuda.synchronize()
+    n = plen - 1
+    assert int(eng.kv.d_len.item()) == n and eng.kv.c.len_bound == n
+    kv = O.KVCache(oracle_cfg(sh), plen + 106)
+    O.prefill(oracle_cfg(sh), wn, kv, prompt[:-1])
+    _cache_against_oracle(eng, kv, n)
+
+
+@pytest.mark.parametrize("shape_name,lens", [("heads64_8", (131, 530)), ("heads32", (129, 1160))])
+def test_ingestion_attention_forms_match_oracle(shape_name, lens):
+    """The ingestion attention where a launch has more than one workgroup per compute unit (64 heads x 5 row blocks, 32 x
+    10), two heads of a group in a workgroup or one head alone, behind an odd committed length: the second layer's keys
+    and values carry its result, per row."""
+    require_gpu()
+    say("ingestion attention", shape_name, lens)
+    sh = _shape(shape_name)
+    w = synth.make_weights(sh, seed=7)
+    wn = synth.weights_to_numpy(w)
+    n = sum(lens)
+    prompt = synth.zipf_prompt(sh.vocab, n + 1, seed=7).tolist()
+    eng = tr.Engine(sh, to_gpu(w), synth.tree15(), k=K, capacity=n + 40)
+    eng.prefill(prompt[:lens[0] + 1])
+    eng.prefill(prompt[lens[0]:], keep_cache=True)
+    torch.cuda.synchronize()
+    assert int(eng.kv.d_len.item()) == n
+    kv = O.KVCache(oracle_cfg(sh), n + 40, np.float32)
+    O.prefill(oracle_cfg(sh), wn, kv, prompt[:n], np.float32)
+    _cache_against_oracle(eng, kv, n)
 
 
 @pytest.mark.parametrize("shape_name,lens", [("tiny_bf16", (2400,)), ("tiny_gqa_bf16", (2400,)), ("tiny_gqa_bf16", (131, 1000, 300)),
@@ -234,32 +282,36 @@ def test_prefill_same_cache_with_the_smallest_workspace(shape_name, lens):
     group, one head) differ, the sums only in their order.  Runs of several calls start at odd committed lengths."""
     require_gpu()
     say("prefill workspace", shape_name, lens)
-    sh = {"heads32": synth.ModelShape("heads32", 2, 256, 32, 32, 128, 672, 2048, "bf16"),
-          "heads64_8": synth.ModelShape("heads64_8", 2, 256, 64, 8, 128, 672, 2048, "bf16")}.get(shape_name) or synth.SHAPES[shape_name]
+    sh = _shape(shape_name)
     w = to_gpu(synth.make_weights(sh, seed=6))
     prompt = synth.zipf_prompt(sh.vocab, sum(lens) + 1, seed=6).tolist()
     caches = []
     for small in (False, True):
         eng = tr.Engine(sh, w, synth.tree15(), k=K, capacity=sum(lens) + 40)
-        if small:  # bytes per row of the activation buffers: x, xn, q, attn, h, rope, ssq
-            hq = sh.n_heads * sh.head_dim
-            per_row = sh.d_model * 6 + hq * 4 + sh.d_ffn * 2 + sh.head_dim * 4 + (sh.d_model + 1023) // 1024 * 4
-            eng.ws = eng.ws[:eng.ws.numel() - 1536 * per_row]
+        if small:
+            _smallest_workspace(eng)
         lo = 0
         for i, n in enumerate(lens):
             eng.prefill(prompt[lo:lo + n + 1], keep_cache=i > 0)
             lo += n
         assert int(eng.kv.d_len.item()) == lo
-        caches.append((eng.kv.k.clone(), eng.kv.v.clone()))
+        caches.append((eng.kv.k.clone(), eng.kv.v.clone(), *kv_plain_views(eng.kv)))
         if small:
             eng.ws = eng.ws[:-1]
             with pytest.raises(tr.TRError) as e:
                 eng.prefill(prompt[:140])
             assert e.value.status == tr.TR_ECAPACITY
-    for a, b in zip(*caches):
+    for i, (a, b) in enumerate(zip(*caches)):
         a, b = a.float(), b.float()
-        # a bf16 value that sums of another order round the other way is 2^-8 off; two layers carry a few of them on
-        assert float((a - b).norm() / a.norm()) < 4e-3 and float((a - b).abs().max()) < 6e-2 * float(a.abs().max())
+        if i < 2:
+            # a bf16 value that sums of another order round the other way is 2^-8 off; two layers carry a few of them on
+            assert float((a - b).norm() / a.norm()) < 4e-3 and float((a - b).abs().max()) < 6e-2 * float(a.abs().max())
+        else:
+            # a row on its own: each of the five bf16 roundings on the way may fall the other way, 5 x 2^-8 (measured 8e-3)
+            a, b = a[:, :, :sum(lens)], b[:, :, :sum(lens)]
+            err = (a - b).abs().amax(dim=(1, 3)) / a.abs().amax(dim=(1, 3))
+            say("largest difference of a row", float(err.max()))
+            assert float(err.max()) < 2e-2
 
 
 def test_packed_prefill_appends_after_a_committed_prefix():
@@ -281,14 +333,7 @@ def test_packed_prefill_appends_after_a_committed_prefix():
     cfg = oracle_cfg(sh)
     kv = O.KVCache(cfg, 720)
     O.prefill(cfg, wn, kv, prompt[:n])
-    kp, vp = kv_plain_views(eng.kv, k_interleaved=True)
-    kg = kp[:, :, :n, :].permute(0, 2, 1, 3).float().cpu().numpy()
-    vg = vp[:, :, :n, :].permute(0, 2, 1, 3).float().cpu().numpy()
-    for l in range(sh.n_layers):
-        dk = np.abs(kg[l] - kv.k[l][:n]).max(axis=(1, 2)) / np.abs(kv.k[l][:n]).max(axis=(1, 2))
-        dv = np.abs(vg[l] - kv.v[l][:n]).max(axis=(1, 2)) / np.abs(kv.v[l][:n]).max(axis=(1, 2))
-        say("layer", l, "relative K error", dk.max(), "V error", dv.max())
-        assert dk.max() < 2e-2 and dv.max() < 2e-2
+    _cache_against_oracle(eng, kv, n)
 
 
 def test_pack_weight_rope_interleaves_rows():
@@ -411,10 +456,22 @@ def test_generic_attention_ignores_what_a_node_does_not_see(dtype, hd):
                                                ("prefix20", 8, 8, 900), ("prefix32", 4, 4, 1201),               # one tile of 32 rows
                                                ("prefix8", 64, 8, 1500), ("prefix40", 2, 2, 7190),              # two
                                                ("prefix12", 64, 8, 3100), ("prefix24", 16, 4, 8200),            # three
-                                               ("tree15", 64, 8, 3333), ("prefix16", 8, 1, 5001)])              # four
+                                               ("tree15", 64, 8, 3333), ("prefix16", 8, 1, 5001),               # four
+                                               # what the rule gives the form: 32, 64, 96 and 128 rows, one share and several,
+                                               # groups of one, two and such that rows do not fall on their bounds by shifts
+                                               ("single", 16, 2, 32), ("prefix10", 12, 4, 97), ("prefix3", 14, 2, 219),
+                                               ("prefix32", 8, 8, 5170), ("prefix16", 16, 8, 5190), ("prefix10", 12, 4, 1500),
+                                               ("prefix4", 14, 2, 1100), ("prefix5", 56, 8, 5120), ("prefix21", 6, 2, 5100),
+                                               ("prefix13", 28, 4, 8180), ("prefix18", 28, 4, 8193), ("prefix42", 24, 8, 8200),
+                                               ("prefix8", 64, 8, 2000), ("prefix16", 64, 8, 4001)])
 def test_few_rows_attention(tmpl_name, H, Hkv, L):
     """The form for few (node, head) rows per K/V head, every row-tile count of it: sequences shorter than its first step,
-    one key share and many, last tiles partly tree, partly past the end."""
+    one key share and many, last tiles partly tree, partly past the end.  Sizes around its use that the rule leaves to the
+    other forms stay in the list; those it takes are asserted."""
+    n = (synth.prefix_template(int(tmpl_name[6:])) if tmpl_name.startswith("prefix") else synth.TEMPLATES[tmpl_name]()).n_nodes
+    left = {("single", 16, 2, 0), ("prefix20", 8, 8, 900), ("prefix32", 4, 4, 1201), ("prefix8", 64, 8, 1500),
+            ("prefix40", 2, 2, 7190), ("prefix16", 8, 1, 5001)}
+    assert (tr.plan_attention(H, Hkv, n, L + n)[1] < 0) == ((tmpl_name, H, Hkv, L) not in left)
     test_tree_attention_matches_per_path_attention(tmpl_name, H, Hkv, L, True)
 
 
@@ -461,11 +518,10 @@ def test_few_rows_attention_without_a_finite_score(tmpl_name, H, Hkv, L):
 def test_linear_bf16_packed_matches_oracle_matmul(n, K_, O_, splits):
     """The projection kernel alone (packed weights, MFMA) against a float64 matrix product of the
     same bf16 values; also checks the repack kernel, since a misplaced element would show here.
-    Row counts above 128 reach the prompt-ingestion kernel, whose launcher picks the workgroup shape (12 out-tiles
-    x 2 row tiles per wave, 6 x 4 with one workgroup over all rows, or 6 x 2) and the K-splits from a cost model:
-    the cases cover one and two row blocks, ragged out-tile groups (2080 features), an odd number of k-steps
-    (736), the 6 x 4 shape (18432 features), and K-split shares that are rounded to whole stages and leave a
-    shorter last share (11008, 2240 in-features)."""
+    Row counts above 128 reach the prompt-ingestion kernel, whose launcher picks the workgroup shape (8 or 16 row
+    tiles x 8, 12 or 16 out-tiles) and the K-splits from a cost model: the cases cover one and several row blocks,
+    ragged out-tile groups (2080 features), an odd number of k-steps (736) and K-split shares that leave a shorter
+    last share (2240 in-features); test_wide_projection_edges has every shape."""
     require_gpu()
     say("linear packed", n, K_, O_, splits)
     x = synth.normal_tensor((n, K_), 1.0, seed=n + K_, dtype=torch.bfloat16)

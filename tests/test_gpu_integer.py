@@ -289,6 +289,25 @@ def test_accept_update_compact_matches_oracle(name, kvmode):
         assert len(depths) >= min(3, tree.n_layers)
 
 
+@pytest.mark.parametrize("hd,dtype", [(256, "f32"), (256, "bf16"), (254, "f32")])
+def test_accept_compacts_the_widest_heads(hd, dtype):
+    """Compaction stages 32 rows of keys and values of a head: 64 KiB of LDS at the largest head dimension in float32."""
+    require_gpu()
+    t = synth.tree15()
+    tree = O.make_tree(t.parent, t.rank, K)
+    S = np.arange(t.n_nodes) + 1
+    topk = np.full((t.n_nodes, K), 63)
+    node = t.n_nodes - 1
+    for i in range(1, len(tree.paths[node])):
+        topk[tree.paths[node][i - 1], 0] = S[tree.paths[node][i]]
+    say("accept, head dim", hd, dtype)
+    h, _, kc, vc, ctx = _run_accept(t, S, topk, hd=hd, dtype=dtype)
+    assert list(h.path[:h.n_emitted]) == list(tree.paths[node]) and h.n_accepted == len(tree.paths[node]) - 1
+    for i, p in enumerate(tree.paths[node]):
+        assert (kc[:, :, 10 + i, :] == 100.0 + p).all() and (vc[:, :, 10 + i, :] == -(100.0 + p)).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("mode", [tr.TR_UPDATE_FIRST, tr.TR_UPDATE_ACCEPTED_ONLY,
                                   tr.TR_UPDATE_FIRST | tr.TR_UPDATE_ACCEPTED_ONLY])
 def test_update_variants_match_oracle(mode):
