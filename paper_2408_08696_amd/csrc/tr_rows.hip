@@ -216,7 +216,11 @@ static hipError_t launch_rows_rt(const RowsArgs &p, hipStream_t st, KernelTimer 
   const int NT = (p.n + 15) / 16;
   const int tiles = EPI == ROWS_SWIGLU ? (p.O + 7) / 8 : (p.O + 15) / 16;
   if (NT == 1) return launch(k_rows<T, 1, NORM, EPI>, dim3(tiles, 1), dim3(ROWS_WAVES * 64), 0, st, tm, p);
-  if (NT == 2) return launch(k_rows<T, 2, NORM, EPI>, dim3(tiles, 1), dim3(ROWS_WAVES * 64), 0, st, tm, p);
+  // Four row tiles read a weight half as often as two, but a wave's loads and products per k-step are twice as many, and
+  // that chain is the launch's time while every workgroup has a compute unit to itself.  float32, 64 rows, us with four /
+  // two tiles: 512 -> 512 9.5 / 6.3, 1027 -> 512 13.3 / 9.3, 2048 -> 512 23.0 / 15.4 (a wave per output: 8.5, 12.4, 19.5).
+  if (tiles * ((NT + 1) / 2) <= 256)
+    return launch(k_rows<T, 2, NORM, EPI>, dim3(tiles, (NT + 1) / 2), dim3(ROWS_WAVES * 64), 0, st, tm, p);
   return launch(k_rows<T, 4, NORM, EPI>, dim3(tiles, (NT + 3) / 4), dim3(ROWS_WAVES * 64), 0, st, tm, p);
 }
 

@@ -712,7 +712,9 @@ def test_pack_rejects_bad_sizes():
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n,K,O", [(1, 1, 1), (15, 128, 1024), (16, 344, 17), (17, 385, 33), (33, 31, 16), (64, 500, 20),
-                                   (65, 1027, 15), (128, 192, 130)])
+                                   (65, 1027, 15), (128, 192, 130),
+                                   # two row tiles a workgroup up to 256 workgroups, four beyond
+                                   (48, 96, 2048), (64, 64, 2049), (113, 40, 1024), (128, 33, 1040)])
 def test_row_major_linear_edges(dtype, n, K, O):
     """Row-major projections around the kernel's units (16 outputs, 1 / 2 / 4 row tiles per workgroup, k-steps of 64
     bytes dealt to four waves, 16-byte chunks that end inside or straddle a row's end, rows that start off 16 bytes)."""
