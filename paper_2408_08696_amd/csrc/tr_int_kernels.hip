@@ -570,22 +570,21 @@ __global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__rest
 //   argmax_j ( logits[i][j] * inv_t + noise[L + depth(i) - pos0][j] ),   ties to the smallest j,
 // i.e. a draw from softmax(logits / T) when the noise is standard Gumbel.  The two float32 operations
 // are kept separate (no fused multiply-add): they decide an integer, and whoever repeats them rounds
-// the same way.  One workgroup of 16 waves per node; a thread has U vectors of both rows in flight, which is what
+// the same way.  One workgroup of 16 waves per node (4 for short rows); a thread has U vectors of both rows in flight, which is what
 // counts (every node's compute unit pulls two rows of V floats): 128 nodes x 32000 took 39 us with 4 waves and one
 // element of each row in flight, 9.3 now.  VEC: 16-byte loads (V a multiple of 4, both bases aligned).  A NaN is never
 // drawn (it is no candidate, so it cannot stand in a thread's or a wave's place either); a row of nothing else gives 0.
 // ---------------------------------------------------------------------------------------------
-constexpr int SAMPLE_THREADS = 1024;
-template <bool VEC>
-__global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *__restrict__ logits,
+template <bool VEC, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_sample_tokens(const float *__restrict__ logits,
                                                                   const float *__restrict__ noise, int32_t V, int32_t pos0,
                                                                   int32_t noise_rows, float inv_t,
                                                                   const int32_t *__restrict__ depth,
                                                                   const int32_t *__restrict__ d_len,
                                                                   int32_t *__restrict__ tokens) {
   constexpr int E = VEC ? 4 : 1, U = 4;
-  __shared__ float sv[SAMPLE_THREADS / 64];
-  __shared__ int32_t si[SAMPLE_THREADS / 64];
+  __shared__ float sv[THREADS / 64];
+  __shared__ int32_t si[THREADS / 64];
   const int i = blockIdx.x;
   int row = *d_len + depth[i] - pos0;
   row = row < 0 ? 0 : (row >= noise_rows ? noise_rows - 1 : row); // the host checked the range; never read outside
@@ -593,11 +592,11 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *_
   const float *nz = noise + (size_t)row * V;
   float best = -__builtin_huge_valf();
   int bj = 0x7fffffff;
-  for (int j0 = threadIdx.x * E; j0 < V; j0 += SAMPLE_THREADS * E * U) {
+  for (int j0 = threadIdx.x * E; j0 < V; j0 += THREADS * E * U) {
     float a[U][E], b[U][E];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = j0 + u * SAMPLE_THREADS * E;
+      const int j = j0 + u * THREADS * E;
       const int jc = j < V ? j : j0; // past the end: an element seen before, skipped below
       __builtin_memcpy(a[u], lg + jc, sizeof(a[u]));
       __builtin_memcpy(b[u], nz + jc, sizeof(b[u]));
@@ -606,7 +605,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *_
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const int j = j0 + u * SAMPLE_THREADS * E + e;
+        const int j = j0 + u * THREADS * E + e;
         const float y = __fadd_rn(__fmul_rn(a[u][e], inv_t), b[u][e]);
         if (j < V && (y > best || (bj == 0x7fffffff && y == y))) { // j grows, so on equal values the earlier index stays
           best = y;
@@ -631,7 +630,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *_
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < SAMPLE_THREADS / 64; ++w) merge(sv[w], si[w]);
+    for (int w = 1; w < THREADS / 64; ++w) merge(sv[w], si[w]);
     tokens[i] = bj != 0x7fffffff ? bj : 0;
   }
 }
@@ -639,9 +638,13 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_tokens(const float *_
 hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logits, const float *d_noise,
                                 int32_t pos0, int32_t noise_rows, float inv_t, int32_t *d_tokens, hipStream_t st) {
   const bool vec = c->V % 4 == 0 && (uintptr_t)d_logits % 16 == 0 && (uintptr_t)d_noise % 16 == 0;
-  return launch(vec ? k_sample_tokens<true> : k_sample_tokens<false>, dim3(c->tree.n_nodes), dim3(SAMPLE_THREADS), 0, st,
-                c->prof.next(PC_SAMPLE), d_logits, d_noise, c->V, pos0, noise_rows, inv_t, c->tree.depth, kv->d_len,
-                d_tokens);
+  // short rows: four waves have all of it under way at once, and fewer meet at the end (80 nodes x 1000: 3.7 us against 4.2
+  // with 16 waves, x 4096 4.15 / 5.8; the kernel before, four waves with an element each: 3.9 and 5.6)
+  const bool few = c->V <= 4096;
+  auto kernel = few ? (vec ? k_sample_tokens<true, 256> : k_sample_tokens<false, 256>)
+                    : (vec ? k_sample_tokens<true, 1024> : k_sample_tokens<false, 1024>);
+  return launch(kernel, dim3(c->tree.n_nodes), dim3(few ? 256 : 1024), 0, st, c->prof.next(PC_SAMPLE), d_logits, d_noise,
+                c->V, pos0, noise_rows, inv_t, c->tree.depth, kv->d_len, d_tokens);
 }
 
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk,

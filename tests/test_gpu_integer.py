@@ -378,9 +378,9 @@ def test_sample_tokens_match_oracle(V, L):
         ctx.op_sample(kv, logits.cuda(), noise.cuda(), 0.0, tokens)
 
 
-@pytest.mark.parametrize("V", [8, 1023, 4097, 16384, 16388, 20003])
+@pytest.mark.parametrize("V", [8, 1023, 1024, 4095, 4096, 4097, 4100, 16384, 16388, 20003])
 def test_sample_tokens_edges(V):
-    """Draws at vocabularies around the kernel's pass (1024 threads, 4 loads of 1 or 4 elements each), with equal
+    """Draws at vocabularies around the kernel's pass (256 or 1024 threads, 4 loads of 1 or 4 elements each), with equal
     values in different threads and at the row's ends."""
     require_gpu()
     say("sample edges", V)
