@@ -180,6 +180,22 @@ def test_topk_rows_with_nan(dtype, V, k):
     ctx.close()
 
 
+@pytest.mark.parametrize("rows,V,k", [(256, 300, 9), (257, 300, 9), (257, 288, 9), (300, 577, 9), (300, 512, 16), (300, 700, 16)])
+def test_topk_many_short_rows(rows, V, k):
+    """Rows of fewer waves than k, on both sides of the bounds between the list and k passes."""
+    require_gpu()
+    say("topk short rows", rows, V, k)
+    x = synth.normal_tensor((rows, V), 3.0, seed=V, dtype=torch.bfloat16)
+    x[5, :] = 1.0
+    ctx = _ctx(synth.single(), V, k)
+    d_topk = torch.full((rows, k), -1, dtype=torch.int32, device="cuda")
+    ctx.op_topk(x.cuda(), d_topk)
+    got = d_topk.cpu().numpy()
+    for r in range(rows):
+        assert got[r].tolist() == O.topk_ids(x[r].float().numpy(), k).tolist(), (V, r)
+    ctx.close()
+
+
 @pytest.mark.parametrize("name", ["tree80", "wide128", "tree15"])
 def test_matrix_update_last_wins(name):
     require_gpu()
