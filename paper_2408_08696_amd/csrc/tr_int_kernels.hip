@@ -385,6 +385,10 @@ __device__ inline void scatter_rows(int32_t *__restrict__ M, int32_t k, int n_no
   if (i >= n_nodes) return;
   const int tok = sTok[i];
   if (tok < 0) return;
+  if (n_nodes == 1) { // a step of one token: nothing to compare (fetching the code that does: 3.1 us against 2.5)
+    for (int c = 0; c < k; ++c) M[(size_t)tok * k + c] = topk[(size_t)i * k + c];
+    return;
+  }
   int32_t row[8];
   if (k == 8) __builtin_memcpy(row, topk + (size_t)i * 8, 32); // on its way while the occurrences are compared
   int lo = TR_MAX_NODES, hi = -1; // first and last occurrence

@@ -196,7 +196,7 @@ def test_topk_many_short_rows(rows, V, k):
     ctx.close()
 
 
-@pytest.mark.parametrize("name", ["tree80", "wide128", "tree15"])
+@pytest.mark.parametrize("name", ["tree80", "wide128", "tree15", "single"])
 def test_matrix_update_last_wins(name):
     require_gpu()
     t = synth.TEMPLATES[name]()
