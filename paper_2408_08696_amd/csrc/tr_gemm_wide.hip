@@ -358,11 +358,15 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   double best = 1e30;
   for (int v = 0; v < 5; ++v) {
     const int row_blocks = (row_tiles + WIDE_SHAPES[v].rb - 1) / WIDE_SHAPES[v].rb;
+    // A single row block with fewer tiles than the shape has loads a neighbour in their place, which costs next to nothing:
+    // 161 rows, 8192 -> 8192, 8 x 8 tiles in two shares 60.8 us, 16 x 8 in four 49.8; 145 rows, 13824 -> 5120, 65.5 / 59.6.
+    const int row_here = row_tiles < WIDE_SHAPES[v].rb ? row_tiles : WIDE_SHAPES[v].rb;
+    const double step_us = WIDE_SHAPES[v].step_us * (row_here + WIDE_SHAPES[v].nw) / (WIDE_SHAPES[v].rb + WIDE_SHAPES[v].nw);
     for (int sp = 1; sp <= (may_split ? max_splits : 1); ++sp) {
       const int per_k = (KT + sp - 1) / sp;
       if (sp > 1 && (per_k < 16 || (sp - 1) * per_k >= KT)) continue; // no empty share, none that is all ramp
       const int rounds = (groups_of(WIDE_SHAPES[v].nw) * row_blocks * sp + 255) / 256;
-      double cost = rounds * (per_k * WIDE_SHAPES[v].step_us + 8.0);
+      double cost = rounds * (per_k * step_us + 8.0);
       if (sp > 1) cost += sp * (64.0 * g.n * total) * (1 / 4.6e6 + 1 / 2.9e6);
       if (cost < best) {
         best = cost;

@@ -539,9 +539,10 @@ def test_linear_bf16_packed_matches_oracle_matmul(n, K_, O_, splits):
 
 @pytest.mark.parametrize("n,K_,O_,splits", [# workgroups of 8 x 8 tiles: fewer k-steps than ring slots, an odd number
                                             (129, 64, 64, 1), (135, 96, 256, 1), (200, 160, 64, 1), (257, 1120, 8224, 2),
-                                            (512, 4096, 4096, 4),                 # 8 x 8, split over k
-                                            (511, 4096, 12288, 1), (129, 1056, 24576, 1),  # 8 x 12
-                                            (500, 96, 12320, 1), (511, 4096, 4640, 3),  # 16 x 8
+                                            (512, 4096, 4096, 4), (511, 4096, 4640, 3),  # 8 x 8, split over k and not
+                                            (511, 4096, 12288, 1), (250, 1056, 24576, 1),  # 8 x 12
+                                            (500, 96, 12320, 1),                  # 16 x 8; one ragged row block, split
+                                            (129, 1056, 24576, 1), (145, 3072, 6144, 4),
                                             (505, 1056, 16416, 1), (385, 96, 20512, 1),                        # 16 x 12
                                             (505, 736, 28704, 1), (400, 224, 32000, 1), (512, 64, 28704, 1)])  # 16 x 16
 def test_wide_projection_edges(n, K_, O_, splits):
