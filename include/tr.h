@@ -299,10 +299,11 @@ tr_status tr_accept_and_update_sampled(tr_ctx *ctx, tr_kv *kv, const int32_t *d_
  * *kv->d_len and kv->len_bound by n_tokens.  No logits, no matrix update (the paper updates M only
  * from decoding steps, Section 3.3).  Packed bf16 models with a tiled cache take up to 2048 tokens
  * per pass (with a workspace smaller than tr_workspace_bytes asks for, up to 512; several passes
- * get about equal shares), with projection and attention kernels of their own; the last layer
- * stops after its K/V are cached.  All other models, and passes of at most TR_MAX_NODES tokens, go
- * through the decode-step kernels TR_MAX_NODES tokens at a time.  Same arithmetic per token either
- * way.  Errors: TR_EINVAL (NULL, n_tokens < 0, model / cache
+ * get equal shares rounded up to 256 tokens, the last what is left), with projection and attention
+ * kernels of their own; the last layer stops after its K/V are cached.  All other models, calls whose
+ * workspace, cache or packed matrices do not start on 16 bytes, and passes of at most TR_MAX_NODES
+ * tokens go through the decode-step kernels TR_MAX_NODES tokens at a time.  Same arithmetic per token
+ * either way.  Errors: TR_EINVAL (NULL, n_tokens < 0, model / cache
  * mismatch), TR_ECAPACITY (kv->len_bound + n_tokens beyond the capacity, workspace too small even for that
  * size), TR_EHIP.  n_tokens == 0 is a no-op.
  */

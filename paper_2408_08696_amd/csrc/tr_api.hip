@@ -311,9 +311,11 @@ tr_status tr_prefill(tr_ctx *c, const tr_model *m, tr_kv *kv, const int32_t *d_t
   hipStream_t st = as_stream(stream);
   const int most = prefill_rows(*m, *kv, ws, ws_bytes);
   int rows = most;
-  if (most > NP && n_tokens > most) { // passes of about the same size: a short last one would stream all weights for a few rows
+  // Several passes share the tokens in whole row blocks of the projection kernel (256 rows): the last takes what is left,
+  // which may be little (2048 x 7 + 1 tokens with the full workspace, 513 with passes of 512).
+  if (most > NP && n_tokens > most) {
     const int passes = (n_tokens + most - 1) / most;
-    rows = ((n_tokens + passes - 1) / passes + 255) / 256 * 256; // whole row blocks of the projection kernel
+    rows = ((n_tokens + passes - 1) / passes + 255) / 256 * 256;
   }
   for (int lo = 0; lo < n_tokens; lo += rows) {
     const int n = n_tokens - lo < rows ? n_tokens - lo : rows;

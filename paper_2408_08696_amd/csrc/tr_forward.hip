@@ -1,13 +1,14 @@
 // Verification forward: one pass of a Llama-style decoder over the N tree nodes (Section 2.2).
-// This file holds the orchestration and the shape-generic kernels (any head_dim, f32 or bf16
-// storage, plain ALU arithmetic).  The bf16 hot shapes are routed to the MFMA kernels in
-// tr_gemm_mfma.hip / tr_attn_mfma.hip.
+// This file holds the orchestration, the embedding and residual / norm kernels and the shape-generic
+// attention (any head_dim, f32 or bf16 storage, plain ALU arithmetic).  Models in the packed layout go
+// through the projections in tr_gemm_mfma.hip / tr_gemm_wide.hip, all others through tr_rows.hip; a tiled
+// cache through the attention in tr_attn_*.hip.
 //
-// Arithmetic contract of the bf16 path (both generic and MFMA kernels): the residual stream, the
+// Arithmetic contract of the bf16 path (both generic and packed): the residual stream, the
 // softmax statistics, all accumulators and the logits are float32; operands of every contraction
 // (normalised activations, rotated Q/K, V, attention output, SwiGLU output) are rounded to bf16.
-// In the packed path the RMS scale is applied after the contraction (it is a per-row scalar), i.e.
-// the rounded operand is x * gain instead of x * gain * scale.
+// The RMS scale is applied after the contraction (it is a per-row scalar), i.e. the rounded operand
+// is x * gain instead of x * gain * scale, in float32 models too.
 #include "tr_internal.h"
 #include "tr_kernels.h"
 

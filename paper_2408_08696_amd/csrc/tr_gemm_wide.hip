@@ -19,7 +19,8 @@
 // that unit's time.  Measured without effect: weight tiles at other strides or in another k order per workgroup, wave
 // priorities; slower: touching lines ahead of the loads to bring them into L2 (the touches go through the same path).
 // 512 rows, us per launch, this kernel / one that took weights through registers and activations straight to the
-// operands (8 x 1 wave grid): 7B gate/up 83 / 94, o + down 80 / 103, 70B gate/up 391 / 489, o + down 276 / 360.
+// operands (8 x 1 wave grid): 7B gate/up 79 / 94, Q/K/V 60 / 61, o + down 80 / 103, 70B gate/up 392 / 489, o + down 276 /
+// 360, Q/K/V 108 / 97.
 //
 // Same packed weight layout, fragment-ordered activations and epilogues (plain store, RoPE + cache append,
 // SwiGLU) as the decode kernel.

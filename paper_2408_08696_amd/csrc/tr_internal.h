@@ -11,7 +11,7 @@
 namespace tr {
 
 // ---------------------------------------------------------------------------------------------
-// bf16 storage helpers (round-to-nearest-even; NaN inputs are not supported anywhere on the path)
+// bf16 storage helpers (round-to-nearest-even; the quiet NaN that arithmetic makes stays one, other payloads may not)
 // ---------------------------------------------------------------------------------------------
 typedef uint16_t bf16_t;
 

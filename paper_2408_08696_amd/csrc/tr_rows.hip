@@ -6,8 +6,8 @@
 // A workgroup of four waves owns one tile of 16 outputs and RT tiles of 16 rows; the waves take interleaved k-steps of
 // 64 bytes of each row (the 16x16 matrix-core product of the element type: 4 x v_mfma_f32_16x16x4_f32 or one
 // v_mfma_f32_16x16x32_bf16, A = weights, B = activations, lane l supplying 16 bytes of row l % 16 at k-offset
-// 16 (l / 16) bytes of both) and load all they can before the first product, so that up to K = 24 k-steps a launch is
-// one round trip.  The four partial sums meet in LDS.  Lane l then holds outputs 4 (l / 16) .. + 3 of row l % 16.
+// 16 (l / 16) bytes of both) and load all they can before the first product, so that a launch is one round trip up to 24
+// k-steps with one row tile, 16 with two and 12 with four.  The four partial sums meet in LDS.  Lane l then holds outputs 4 (l / 16) .. + 3 of row l % 16.
 //   prologue  RMSNorm: the operand is T(x * gain), the row's scale 1 / sqrt(mean(x^2) + eps) is collected from the same
 //             loads and applied to the sums (it is a scalar per row).
 //   epilogues store, residual add into x, SwiGLU, and RoPE with the query / cache writes.  For the last two the tile's

@@ -201,7 +201,7 @@ def test_static_topk_validates_before_touching_the_gpu(lib):
     assert f(p, tr.TR_F32, -1, 64, 8, p, None) == tr.TR_EINVAL
     assert f(p, tr.TR_F32, 4, 0, 8, p, None) == tr.TR_EINVAL
     assert f(p, tr.TR_F32, 4, 4, 8, p, None) == tr.TR_EINVAL                      # k > V
-    assert f(p, tr.TR_F32, 4, 64, 9, p, None) == tr.TR_ECAPACITY                  # k beyond the two-stage kernels
+    assert f(p, tr.TR_F32, 4, 64, 9, p, None) == tr.TR_ECAPACITY                  # more candidates than it takes
     assert f(p, tr.TR_F32, tr.TR_MAX_NODES + 1, 64, 8, p, None) == tr.TR_ECAPACITY
     assert f(p, tr.TR_F32, 4, 131073, 8, p, None) == tr.TR_ECAPACITY              # beyond the static scratch
     assert f(p, tr.TR_F32, 4, 7, 7, p, None) == tr.TR_ECAPACITY                   # V below the kernels' minimum

@@ -92,8 +92,8 @@ def test_topk_other_k():
 
 @pytest.mark.parametrize("V", [8, 9, 1023, 1025, 2049, 131072, 131073, 152064])
 def test_topk_vocabulary_edges(V):
-    """Vocabularies around the kernel's units: below and above one wave's 1024 elements, the largest row
-    the two-stage path takes (128 waves) and the first sizes beyond it (one-kernel path); ties included."""
+    """Vocabularies from the smallest to the largest of one and of several segments, around 1024 elements (one a
+    thread) and around the largest row that tr_op_topk_static takes (131072); ties included."""
     require_gpu()
     rows = 5
     say("topk edges", V)
