@@ -8,6 +8,11 @@
 // v_mfma_f32_16x16x32_bf16, A = weights, B = activations, lane l supplying 16 bytes of row l % 16 at k-offset
 // 16 (l / 16) bytes of both) and load all they can before the first product, so that a launch is one round trip up to 24
 // k-steps with one row tile, 16 with two and 12 with four.  The four partial sums meet in LDS.  Lane l then holds outputs 4 (l / 16) .. + 3 of row l % 16.
+// A k-step is summed on its own (float32: its four products in a tree) and added to one of as many running sums as a wave
+// loads k-steps ahead, so that no result is the end of a long chain: relative error against float64 at K = 512 / 4096 in
+// float32 8.4e-8 / 1.03e-7, with one running sum per wave 2.1e-7 / 5.8e-7 and a wave per output 8.6e-8 / 1.6e-7; the tiny
+// model's logits 1.8e-7, 2.5e-7 and 2.1e-7.  It costs up to a third where the products are the time (64 rows, 4096 -> 4096
+// 44 -> 61 us; a wave per output 159) and nothing on the tiny model.
 //   prologue  RMSNorm: the operand is T(x * gain), the row's scale 1 / sqrt(mean(x^2) + eps) is collected from the same
 //             loads and applied to the sums (it is a scalar per row).
 //   epilogues store, residual add into x, SwiGLU, and RoPE with the query / cache writes.  For the last two the tile's
@@ -43,14 +48,17 @@ __device__ inline u32x4 load_chunk(const T *row, int k, int K) {
   return v;
 }
 
-__device__ inline f32x4 product(float, const u32x4 &w, const u32x4 &a, f32x4 c) {
+// the sum of one k-step, on its own
+__device__ inline f32x4 product(float, const u32x4 &w, const u32x4 &a) {
+  f32x4 c[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[e]), __uint_as_float(a[e]), c, 0, 0, 0);
-  return c;
+    c[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[e]), __uint_as_float(a[e]), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+  return (c[0] + c[1]) + (c[2] + c[3]);
 }
-__device__ inline f32x4 product(bf16_t, const u32x4 &w, const u32x4 &a, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+__device__ inline f32x4 product(bf16_t, const u32x4 &w, const u32x4 &a) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a),
+                                                 f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 }
 
 // T(x * gain) of E elements from k on, and the sum of their squares
@@ -59,12 +67,13 @@ __device__ inline u32x4 normed_chunk(const float *x, const T *gain, int k, int K
   constexpr int E = 16 / (int)sizeof(T);
   const u32x4 gv = load_chunk<T>(gain, k, K);
   T out[E];
+  float sq[E];
   if constexpr (sizeof(T) == 4) {
     const u32x4 xv = load_chunk<float>(x, k, K);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float v = __uint_as_float(xv[e]);
-      ss += v * v;
+      sq[e] = v * v;
       out[e] = v * __uint_as_float(gv[e]);
     }
   } else {
@@ -75,11 +84,16 @@ __device__ inline u32x4 normed_chunk(const float *x, const T *gain, int k, int K
       for (int e = 0; e < 4; ++e) {
         const float v = __uint_as_float(xv[e]);
         const uint32_t gw = gv[(4 * h + e) >> 1];
-        ss += v * v;
+        sq[4 * h + e] = v * v;
         out[4 * h + e] = f32_to_bf16(v * bf16_to_f32((bf16_t)(e & 1 ? gw >> 16 : gw & 0xFFFFu)));
       }
     }
   }
+#pragma unroll
+  for (int s = E / 2; s > 0; s /= 2)
+#pragma unroll
+    for (int e = 0; e < s; ++e) sq[e] += sq[e + s];
+  ss += sq[0];
   u32x4 r;
   __builtin_memcpy(&r, out, 16);
   return r;
@@ -119,11 +133,12 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(RowsArgs p) {
     const int row = row0 + 16 * t + r;
     arow[t] = (size_t)(row < p.n ? row : p.n - 1) * p.K;
   }
-  f32x4 acc[RT];
+  f32x4 acc[PF][RT];
   float ss[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < PF; ++s) acc[s][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     ss[t] = 0.f;
   }
   for (int k0 = wave * KSTEP; k0 < p.K; k0 += ROWS_WAVES * PF * KSTEP) {
@@ -141,11 +156,15 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(RowsArgs p) {
 #pragma unroll
     for (int j = 0; j < PF; ++j)
 #pragma unroll
-      for (int t = 0; t < RT; ++t) acc[t] = product(T{}, wq[j], aq[j][t], acc[t]);
+      for (int t = 0; t < RT; ++t) acc[j][t] += product(T{}, wq[j], aq[j][t]);
   }
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
-    part[wave][t][lane] = acc[t];
+#pragma unroll
+    for (int s = 1; s < PF; s *= 2) // pairs, then pairs of those
+#pragma unroll
+      for (int i = 0; i + s < PF; i += 2 * s) acc[i][t] += acc[i + s][t];
+    part[wave][t][lane] = acc[0][t];
     if (NORM) {
       float s = ss[t];
       s += __shfl_xor(s, 16);
@@ -215,11 +234,11 @@ template <typename T, bool NORM, int EPI>
 static hipError_t launch_rows_rt(const RowsArgs &p, hipStream_t st, KernelTimer tm) {
   const int NT = (p.n + 15) / 16;
   const int tiles = EPI == ROWS_SWIGLU ? (p.O + 7) / 8 : (p.O + 15) / 16;
-  if (NT == 1) return launch(k_rows<T, 1, NORM, EPI>, dim3(tiles, 1), dim3(ROWS_WAVES * 64), 0, st, tm, p);
-  // Four row tiles read a weight half as often as two, but a wave's loads and products per k-step are twice as many, and
-  // that chain is the launch's time while every workgroup has a compute unit to itself.  float32, 64 rows, us with four /
-  // two tiles: 512 -> 512 9.5 / 6.3, 1027 -> 512 13.3 / 9.3, 2048 -> 512 23.0 / 15.4 (a wave per output: 8.5, 12.4, 19.5).
-  if (tiles * ((NT + 1) / 2) <= 256)
+  // More row tiles a workgroup read a weight less often, but a wave's loads and products per k-step are as many more, and that
+  // chain is the launch's time while every workgroup has a compute unit to itself: the fewest that still do so.  float32, 64
+  // rows, us with four tiles / one: 512 -> 512 9.5 / 6.5, 2048 -> 512 22.9 / 14.3 (a wave per output: 8.5 and 19.4).
+  if (NT == 1 || tiles * NT <= 256) return launch(k_rows<T, 1, NORM, EPI>, dim3(tiles, NT), dim3(ROWS_WAVES * 64), 0, st, tm, p);
+  if (NT == 2 || tiles * ((NT + 1) / 2) <= 256)
     return launch(k_rows<T, 2, NORM, EPI>, dim3(tiles, (NT + 1) / 2), dim3(ROWS_WAVES * 64), 0, st, tm, p);
   return launch(k_rows<T, 4, NORM, EPI>, dim3(tiles, (NT + 3) / 4), dim3(ROWS_WAVES * 64), 0, st, tm, p);
 }

@@ -714,8 +714,8 @@ def test_pack_rejects_bad_sizes():
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n,K,O", [(1, 1, 1), (15, 128, 1024), (16, 344, 17), (17, 385, 33), (33, 31, 16), (64, 500, 20),
                                    (65, 1027, 15), (128, 192, 130),
-                                   # two row tiles a workgroup up to 256 workgroups, four beyond
-                                   (48, 96, 2048), (64, 64, 2049), (113, 40, 1024), (128, 33, 1040)])
+                                   # one, two and four row tiles a workgroup, on both sides of 256 workgroups
+                                   (64, 64, 1024), (65, 40, 1024), (48, 96, 2048), (64, 64, 2049), (113, 40, 1024), (128, 33, 1040)])
 def test_row_major_linear_edges(dtype, n, K, O):
     """Row-major projections around the kernel's units (16 outputs, 1 / 2 / 4 row tiles per workgroup, k-steps of 64
     bytes dealt to four waves, 16-byte chunks that end inside or straddle a row's end, rows that start off 16 bytes)."""
@@ -730,4 +730,25 @@ def test_row_major_linear_edges(dtype, n, K, O):
     # products are exact in float32 for bf16 and rounded once for float32; K - 1 sums, each off by half an ulp
     bound = (K + 1) * 2.0 ** -24 * (x.double().abs() @ w.double().abs().t())
     assert bool(((y.cpu().double() - want).abs() <= bound).all())
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,K,O", [(1, 128, 384), (15, 344, 128), (80, 512, 512), (80, 1024, 512), (64, 4096, 512), (128, 4096, 2048),
+                                   (33, 2048, 2048), (16, 11008, 512)])
+def test_row_major_linear_accumulates_in_short_chains(dtype, n, K, O):
+    """Row-major projections against float64, all errors together: no more than 64 running sums of K / 64 products each and
+    a tree over them leave, whose roundings of half an ulp add up as a random walk (one running sum per wave leaves up to
+    three times as much)."""
+    require_gpu()
+    say("row-major linear, precision", dtype, n, K, O)
+    x = synth.normal_tensor((n, K), 1.0, seed=K, dtype=dtype).cuda()
+    w = synth.normal_tensor((O, K), 1.0, seed=O + 1, dtype=dtype).cuda()
+    ctx = tr.Context(64, 8, [-1], [-1], 1)
+    y = torch.zeros(n, O, device="cuda")
+    ctx.op_linear(x, w, y)
+    want = x.double() @ w.double().t()
+    err = float((y.double() - want).norm() / want.norm())
+    say("relative error", err)
+    assert err < 2.0 ** -24 * (1.3 + np.sqrt(K) / 32)
     ctx.close()
