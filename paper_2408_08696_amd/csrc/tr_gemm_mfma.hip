@@ -85,7 +85,8 @@ hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t
 // LDS the tail needs: the GW partials of the tiles of one reduce-scatter pass, plus the per-row scales when
 // the epilogue applies an RMS scale.  One pass if all tiles fit the 160 KB of a CU, else two (the first
 // covers the units of waves 0 .. GW/2-1).
-constexpr size_t gemm_scale_lds_bytes(int nt, bool scaled) { return scaled ? (size_t)nt * 16 * sizeof(float) : 0; }
+constexpr int MOST_SSQ = 8; // partial sums of squares of a row
+constexpr size_t gemm_scale_lds_bytes(int nt, bool scaled) { return scaled ? (size_t)nt * 16 * (1 + MOST_SSQ) * sizeof(float) : 0; }
 constexpr bool gemm_tail_one_pass(int p, int nt, int mode, int gw, bool scaled) {
   return (size_t)p * nt * (mode == GEMM_SWIGLU ? 2 : 1) * gw * 1024 + gemm_scale_lds_bytes(nt, scaled) <= 160 * 1024;
 }
@@ -126,20 +127,29 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   // T/G tiles, the first T%G of them one longer (the host picks G >= T/P, so no range exceeds P).  Tiles
   // are numbered across the concatenated segments (weight matrices) and each looks up its own segment,
   // so a workgroup may straddle two matrices.
+  // All arguments are needed at once and come in one batch of scalar loads.  A loop over the matrices per tile, the scale's
+  // loads and the rotary factors in front of the first weight tile took 0.9 to 1.9 us to get there, this takes 0.3 to 0.5:
+  // step of the 7B shape with 1 / 80 / 128 nodes 2868 / 3772 / 4835 -> 2820 / 3745 / 4722 us.
   const int bx = blockIdx.x;
   const int tile0 = bx * g.part_q + (bx < g.part_rem ? bx : g.part_rem);
   const int n_valid = g.part_q + (bx < g.part_rem ? 1 : 0);
-  const u32x4 *wbase[NW];
+  typedef __attribute__((address_space(1))) const u32x4 *global_tiles; // said outright: the masks below hide it
+  global_tiles wbase[NW];
+  const bf16_t *w0 = g.seg[0].w, *w1 = MODE == GEMM_SWIGLU ? g.w2 : g.seg[1].w, *w2 = g.seg[2].w;
+  const int end0 = g.end0, end1 = g.end1;
 #pragma unroll
   for (int u = 0; u < P; ++u) {
-    int t = tile0 + (u < n_valid ? u : 0); // unused slots re-read the first tile (a cache hit), never stored
-    int sidx = 0;
-    while (sidx + 1 < g.n_seg && t >= g.seg[sidx].out_tiles) {
-      t -= g.seg[sidx].out_tiles;
-      ++sidx;
+    const int t = tile0 + (u < n_valid ? u : 0); // unused slots re-read the first tile (a cache hit), never stored
+    const bf16_t *w = w0;
+    int at = t;
+    if (MODE == GEMM_ROPE) { // bit masks, no branch or loop over the matrices: their loads came one after another
+      const int64_t in1 = -(int64_t)(t >= end0 && t < end1), in2 = -(int64_t)(t >= end1);
+      const uint64_t b0 = (uint64_t)w0, b1 = (uint64_t)w1, b2 = (uint64_t)w2;
+      w = reinterpret_cast<const bf16_t *>(b0 ^ ((b0 ^ b1) & in1) ^ ((b0 ^ b2) & in2));
+      at = t - (end0 & (int)in1) - (end1 & (int)in2);
     }
-    wbase[u] = reinterpret_cast<const u32x4 *>(g.seg[sidx].w) + (size_t)t * KT * 64 + lane;
-    if (MODE == GEMM_SWIGLU) wbase[P + u] = reinterpret_cast<const u32x4 *>(g.w2) + (size_t)t * KT * 64 + lane;
+    wbase[u] = (global_tiles)reinterpret_cast<const u32x4 *>(w) + (size_t)at * KT * 64 + lane;
+    if (MODE == GEMM_SWIGLU) wbase[P + u] = (global_tiles)reinterpret_cast<const u32x4 *>(w1) + (size_t)at * KT * 64 + lane;
   }
   const u32x4 *abase = reinterpret_cast<const u32x4 *>(g.a_frag) + lane;
 
@@ -149,9 +159,8 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   float *const y = MODE == GEMM_STORE ? hold(g.y + (size_t)split * g.split_stride) : nullptr;
   const int ldy = MODE == GEMM_STORE ? hold(g.ldy) : 0;
   bf16_t *const h_frag = MODE == GEMM_SWIGLU ? hold(g.h_frag) : nullptr;
-  const int per = (KT + g.splits - 1) / g.splits;
-  const int kt0 = split * per;
-  const int kt1 = kt0 + per < KT ? kt0 + per : KT;
+  const int kt0 = split * g.split_kt;
+  const int kt1 = kt0 + g.split_kt < KT ? kt0 + g.split_kt : KT;
   const int first = kt0 + wave;
   const int nsteps = first < kt1 ? (kt1 - first + GW - 1) / GW : 0;
 
@@ -160,18 +169,6 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   for (int u = 0; u < NW; ++u)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // per-row RMS scale for the epilogue (SCALED kernels, wave 0 only).  Lane group g fetches chunks g and g+4
-  // of its row's sums of squares now, with no dependent arithmetic, so the loads retire under the main
-  // loop; the tail adds the groups with two shuffles (n_ssq <= 8) and hands the scales out through LDS.
-  float row_ss[NT][2];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int row = 16 * t + (lane & 15), c0 = lane >> 4;
-    const bool on = SCALED && wave == 0 && row < g.n;
-    row_ss[t][0] = on && c0 < g.n_ssq ? g.row_ssq[(size_t)row * g.n_ssq + c0] : 0.f;
-    row_ss[t][1] = on && c0 + 4 < g.n_ssq ? g.row_ssq[(size_t)row * g.n_ssq + c0 + 4] : 0.f;
-  }
 
   u32x4 wq[PF][NW], aq[PF][NT];
   auto issue = [&](int stage, int step) {
@@ -185,24 +182,41 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   constexpr int U = P * NT;
   constexpr int UPW = (U + GW - 1) / GW;
   const int r = lane & 15, gq = lane >> 4;
+  // What only the epilogue needs is asked for behind the first weight tiles.  Sums of squares go straight to LDS: wave w
+  // fetches those of row tiles w, w + GW, .. and turns them into scales itself.
+  float *const sc_lds = red + gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) / sizeof(float); // [NT * 16], SCALED only
+  float *const ssq_lds = sc_lds + NT * 16;                                                  // [NT][16 * MOST_SSQ]
   GemmRope rp{};
   int L = 0;
   f32x2 rope_c[MODE == GEMM_ROPE ? UPW : 1], rope_s[MODE == GEMM_ROPE ? UPW : 1];
-  if (MODE == GEMM_ROPE) {
-    rp.q = hold(g.rope.q); rp.k_layer = hold(g.rope.k_layer); rp.v_layer = hold(g.rope.v_layer);
-    rp.H = hold(g.rope.H); rp.Hkv = hold(g.rope.Hkv); rp.hd = hold(g.rope.hd); rp.cap = hold(g.rope.cap);
-    rp.tiled = hold(g.rope.tiled);
-    L = *g.rope.d_len;
-#pragma unroll
-    for (int i = 0; i < UPW; ++i) {
-      const int id = wave * UPW + i, u = id / NT, row = 16 * (id - u * NT) + r;
-      const int o = (tile0 + u) * 16 + 4 * gq, head = o / rp.hd, dd = o - head * rp.hd;
-      const bool on = id < U && u < n_valid && row < n_rows && head < rp.H + rp.Hkv;
-      const float *cs = g.rope.rope + (on ? (size_t)row * rp.hd + (dd >> 1) : 0);
-      rope_c[i] = *reinterpret_cast<const f32x2 *>(cs);
-      rope_s[i] = *reinterpret_cast<const f32x2 *>(cs + rp.hd / 2);
+  auto issue_epilogue = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    if (SCALED) {
+      for (int t = wave; t < NT; t += GW) {
+        const int words = (n_rows - 16 * t < 16 ? n_rows - 16 * t : 16) * g.n_ssq;
+        for (int i = 0; i < words; i += 64)
+          if (i + lane < words)
+            word_to_lds((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)(ssq_lds + t * 16 * MOST_SSQ + i),
+                        lane * 4, reinterpret_cast<uint64_t>(g.row_ssq + t * 16 * g.n_ssq + i));
+      }
     }
-  }
+    if (MODE == GEMM_ROPE) {
+      rp.q = hold(g.rope.q); rp.k_layer = hold(g.rope.k_layer); rp.v_layer = hold(g.rope.v_layer);
+      rp.H = hold(g.rope.H); rp.Hkv = hold(g.rope.Hkv); rp.hd = hold(g.rope.hd); rp.cap = hold(g.rope.cap);
+      rp.tiled = hold(g.rope.tiled);
+      L = *g.rope.d_len;
+#pragma unroll
+      for (int i = 0; i < UPW; ++i) {
+        const int id = wave * UPW + i, u = id / NT, row = 16 * (id - u * NT) + r;
+        const int o = (tile0 + u) * 16 + 4 * gq, head = o / rp.hd, dd = o - head * rp.hd;
+        const bool on = id < U && u < n_valid && row < n_rows && head < rp.H + rp.Hkv;
+        const float *cs = g.rope.rope + (on ? (size_t)row * rp.hd + (dd >> 1) : 0);
+        rope_c[i] = *reinterpret_cast<const f32x2 *>(cs);
+        rope_s[i] = *reinterpret_cast<const f32x2 *>(cs + rp.hd / 2);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
   auto multiply = [&](int j) {
 #pragma unroll
@@ -218,6 +232,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   if (NT > 1 && nsteps >= 2 * PF) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) issue(j, j);
+    issue_epilogue();
     do {
 #pragma unroll
       for (int j = 0; j < PF; ++j) {
@@ -232,6 +247,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < PF; ++j)
       if (j < nsteps) issue(j, j);
+    issue_epilogue();
   }
   for (; base < nsteps; base += PF) {
 #pragma unroll
@@ -251,11 +267,12 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   // Every wave then scales, activates and stores its own few tiles, instead of one wave storing them all.
   constexpr int OWN0 = gemm_tail_one_pass(P, NT, MODE, GW, SCALED) ? GW : GW / 2; // waves 0 .. OWN0-1 own pass 0
   float4 *red4 = reinterpret_cast<float4 *>(red); // [unit slot * TPU + k][GW][64]
-  float *sc_lds = red + gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) / sizeof(float); // [NT * 16], SCALED only
-  if (SCALED && wave == 0) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      float ss = row_ss[t][0] + row_ss[t][1];
+  if (SCALED) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int t = wave; t < NT; t += GW) {
+      const int row = lane & 15;
+      float ss = 0.f;
+      for (int c = lane >> 4; c < g.n_ssq; c += 4) ss += ssq_lds[t * 16 * MOST_SSQ + row * g.n_ssq + c];
       ss += __shfl_xor(ss, 16);
       ss += __shfl_xor(ss, 32);
       if (lane < 16) sc_lds[16 * t + lane] = 1.0f / sqrtf(ss / (float)g.norm_dim + g.eps);
@@ -437,9 +454,10 @@ static hipError_t launch_ks(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
 template <int NT, int P, int MODE, int GW = GEMM_WAVES>
 static hipError_t launch_k(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
   if (MODE == GEMM_STORE && g.rope.q != nullptr) { // the fused Q/K/V projection: complete sums of a normalised input
-    if (g.row_ssq == nullptr || g.splits != 1) return hipErrorInvalidValue;
+    if (g.row_ssq == nullptr || g.splits != 1 || g.n_seg != 3) return hipErrorInvalidValue;
     return launch_ks<NT, P, GEMM_ROPE, GW, true>(g, st, tm);
   }
+  if (g.n_seg != 1) return hipErrorInvalidValue;
   if (g.row_ssq != nullptr) return launch_ks<NT, P, MODE, GW, true>(g, st, tm);
   return launch_ks<NT, P, MODE, GW, false>(g, st, tm);
 }
@@ -489,6 +507,10 @@ hipError_t launch_gemm_mfma(const GemmArgs &args, hipStream_t st, KernelTimer tm
   GemmArgs g = args;
   g.part_q = g.total_tiles / g.groups;
   g.part_rem = g.total_tiles % g.groups;
+  g.end0 = g.seg[0].out_tiles;
+  g.end1 = g.end0 + g.seg[1].out_tiles;
+  g.split_kt = (g.K / 32 + g.splits - 1) / g.splits;
+  if (g.row_ssq != nullptr && g.n_ssq > MOST_SSQ) return hipErrorInvalidValue;
   switch ((g.n + 15) / 16) {
   case 1: return launch_nt<1>(g, st, tm);
   case 2: return launch_nt<2>(g, st, tm);

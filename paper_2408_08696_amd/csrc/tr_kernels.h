@@ -38,6 +38,11 @@ __device__ inline void wait_tiles() {
   static_assert(left >= 0 && left < 64, "six bits of vmcnt");
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(left) : "memory");
 }
+// The same for single words: lane l's four bytes at gbase + voff land at lds_off + 4 l; voff of a lane that is off is unused.
+__device__ inline void word_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_off), "v"(voff), "s"(gbase)
+               : "memory");
+}
 __device__ inline void meet_waves() { asm volatile("s_barrier" ::: "memory"); }
 
 struct GemmSeg {
@@ -83,6 +88,8 @@ struct GemmArgs {
   int32_t tiles_per_wg; // most out-tiles (SWIGLU: gate/up tile pairs) a workgroup handles per pass
   int32_t groups;       // workgroups per K-split; each owns a contiguous ~total_tiles/groups out-tiles
   int32_t part_q, part_rem; // total_tiles / groups and total_tiles % groups (filled by launch_gemm_mfma)
+  int32_t end0, end1;       // first out-tiles of the second and third matrix (filled by launch_gemm_mfma)
+  int32_t split_kt;         // k-tiles of a K-split (filled by launch_gemm_mfma)
   GemmRope rope;            // Q/K/V epilogue (see above), off when rope.q == nullptr
 };
 
