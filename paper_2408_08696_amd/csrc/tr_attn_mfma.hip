@@ -22,6 +22,8 @@
 // With more than one split, split s owns tiles s, s + nsplit, ...; each writes (max, sum, normalised O in
 // half precision) per node and k_attn_merge combines them in split order.  K/V are read with streaming
 // loads: they are used once per call and would otherwise push the activations out of L2.
+#include <type_traits>
+
 #include "tr_kernels.h"
 
 namespace tr {
@@ -39,6 +41,60 @@ __device__ inline f32x4 mfma16a(const u32x4 &a, const u32x4 &b, f32x4 c) {
 
 constexpr int ATT_TILE_BYTES = 16384; // 32 keys: K 8 KiB + V 8 KiB
 constexpr float NEG_BIG = -1e30f;
+
+// End of a wave of the split forms, (head, tile of 16 nodes) over one key share: the result itself if there is only one share.
+// `lds` has 4 KiB per wave for it once every wave is done with the K/V tiles.
+__device__ inline void finish_share(const f32x4 (&acc)[8], float m, float lsum, void *lds_all, int wave, int lane, int wt, int h,
+                                    int split, int nsplit, int32_t H, int32_t n, float *__restrict__ part_ml,
+                                    float *__restrict__ part_acc, bf16_t *__restrict__ out, int32_t out_row_tiles) {
+  const int r = lane & 15, g = lane >> 4, node = wt * 16 + r;
+  if (nsplit == 1) {
+    if (node >= n) return;
+    const float inv = 1.0f / lsum;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      const int d = 16 * dt + 4 * g;
+      ushort4 o;
+      o.x = f32_to_bf16(acc[dt][0] * inv); o.y = f32_to_bf16(acc[dt][1] * inv);
+      o.z = f32_to_bf16(acc[dt][2] * inv); o.w = f32_to_bf16(acc[dt][3] * inv);
+      const size_t idx = out_row_tiles > 0 ? act_frag_index(node, h * 128 + d, out_row_tiles)
+                                           : ((size_t)node * H + h) * 128 + d;
+      store_stream(out + idx, o);
+    }
+    return;
+  }
+  // a split's partial result is its own normalised output (a convex combination of V rows, so it fits
+  // half precision with 2^-11 relative error, below the bf16 rounding of the merged output) plus (m, l).
+  // The wave's 16 x 128 block is turned through LDS so that a node's 256 bytes leave as whole lines.
+  const size_t prow = ((size_t)split * H + h) * NP + wt * 16;
+  if (g == 0 && node < n) {
+    part_ml[(prow + r) * 2] = m;
+    part_ml[(prow + r) * 2 + 1] = lsum;
+  }
+  const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+  __syncthreads(); // every wave is done with the last K/V tile
+  // row r keeps its 16-byte chunk c at slot c ^ r, so the 16 rows of one store hit distinct banks
+  char *blk = reinterpret_cast<char *>(lds_all) + wave * 4096;
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+    // clamped to the half-precision range: a value-cache entry beyond +-65504 saturates instead of
+    // turning into an infinity that the merge would spread over the row
+    f32x4 o = acc[dt] * inv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], -65504.0f), 65504.0f);
+    *reinterpret_cast<f16x4 *>(blk + r * 256 + (((2 * dt + (g >> 1)) ^ r) << 4) + 8 * (g & 1)) =
+        __builtin_convertvector(o, f16x4);
+  }
+  // the wave reads back only what it wrote itself; its LDS operations complete in order
+  asm volatile("" ::: "memory");
+  u32x4 *pa = reinterpret_cast<u32x4 *>(part_acc);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = i * 64 + lane, rr = c >> 4, cc = c & 15;
+    const u32x4 v = *reinterpret_cast<const u32x4 *>(blk + rr * 256 + ((cc ^ rr) << 4));
+    if (wt * 16 + rr < n) pa[(prow + rr) * 16 + cc] = v; // plain store: the merge pass finds these in L2
+  }
+}
 
 template <int NT, int HPW>
 __global__ __launch_bounds__(NT * HPW * 64) void k_attn_mfma(const bf16_t *__restrict__ q, const bf16_t *__restrict__ Kl,
@@ -195,54 +251,205 @@ __global__ __launch_bounds__(NT * HPW * 64) void k_attn_mfma(const bf16_t *__res
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) acc[dt] = mfma16a(vt[dt * 64 + lane], pf, acc[dt]);
   }
-  const float lsum = accl[0];
+  finish_share(acc, m, accl[0], lds_all, wave, lane, wt, h, split, nsplit, H, n, part_ml, part_acc, out, out_row_tiles);
+}
 
-  if (nsplit == 1) {
-    if (node >= n) return;
-    const float inv = 1.0f / lsum;
+// ---------------------------------------------------------------------------------------------
+// The split form for longer shares.  Same mapping, shares and arithmetic per score as k_attn_mfma, but tiles go memory -> LDS by
+// direct loads, 64 keys (32 KiB) a step in a ring of two, the first of them asked for before the committed length is known;
+// the waves meet and the running maximum moves once per 64 keys, and the operands of a contraction are read from LDS together.
+// Queries and ancestor masks come the same way, in front of the tiles, through what is the second step's place: a plain load
+// behind them would wait for every tile.
+// What bounds it: the stream of K and V at 5.8 TB/s (32 heads, 80 nodes, 16000 positions); below about 2000 positions launch,
+// a trip to memory (1.8 us), 1.2 us per 64 keys, 1 us of write-back and the merge launch.  us per layer with the merge,
+// k_attn_mfma / this, 80 nodes: 32 heads on 32 14.3 / 14.2 at 1024 positions, 16.0 / 14.9 at 1700, 24.7 / 22.2 at 4096,
+// 63.9 / 56.5 at 16000; 40 on 40 19.4 / 17.8 at 2048; 64 on 8 18.2 / 18.7 at 1024, 30.0 / 29.7 at 4096, 36.0 / 33.6 at 6000.
+// A ring of four steps, all asked for at once, takes 1.2 us more: the burst holds up its own first tiles.
+// ---------------------------------------------------------------------------------------------
+constexpr int RING_STEPS = 2;
+constexpr int RING_STEP_BYTES = 2 * ATT_TILE_BYTES; // 64 keys
+constexpr int RING_WAVE_BYTES = 5 * 1024;           // a wave's queries (16 x 128) and ancestor masks at the start
+constexpr int ring_lds_bytes(int waves) {
+  const int steps = RING_STEPS * RING_STEP_BYTES, start = (RING_STEPS - 1) * RING_STEP_BYTES + waves * RING_WAVE_BYTES;
+  return steps > start ? steps : start;
+}
+
+template <int NT, int HPW>
+__global__ __launch_bounds__(NT * HPW * 64) void k_attn_ring(const bf16_t *__restrict__ q, const bf16_t *__restrict__ Kl,
+                                                            const bf16_t *__restrict__ Vl, int32_t H, int32_t Hkv,
+                                                            int32_t cap, int32_t n, const uint64_t *__restrict__ anc,
+                                                            const int32_t *__restrict__ d_len, int32_t bound_tiles,
+                                                            int32_t nsplit, float *__restrict__ part_ml,
+                                                            float *__restrict__ part_acc, bf16_t *__restrict__ out,
+                                                            int32_t out_row_tiles) {
+  constexpr int W = NT * HPW, D = RING_STEPS;
+  constexpr int B = 32 / W, REM = 32 % W; // tile loads (1 KiB) of a wave per step; the first REM waves take one more
+  extern __shared__ u32x4 ring[];         // [D][tile 0: K 8 | V 8, tile 1: K 8 | V 8][64]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int wt = wave % NT;
+  const int hk = blockIdx.x, split = blockIdx.z;
+  const int h = hk * (H / Hkv) + blockIdx.y * HPW + wave / NT;
+  const int node = wt * 16 + r, node_c = node < n ? node : n - 1;
+  const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)ring;
+
+  // queries and masks: Q^T operand of lane (node r, group g) is Q[node][32 c + 8 g .. + 7] for d-step c
+  constexpr int OWN = (D - 1) * RING_STEP_BYTES;
+  {
+    const uint32_t own = ring0 + OWN + wave * RING_WAVE_BYTES;
+    const uint32_t qoff = ((uint32_t)(node_c * H + h) * 128 + 8 * g) * 2;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-      const int d = 16 * dt + 4 * g;
-      ushort4 o;
-      o.x = f32_to_bf16(acc[dt][0] * inv); o.y = f32_to_bf16(acc[dt][1] * inv);
-      o.z = f32_to_bf16(acc[dt][2] * inv); o.w = f32_to_bf16(acc[dt][3] * inv);
-      const size_t idx = out_row_tiles > 0 ? act_frag_index(node, h * 128 + d, out_row_tiles)
-                                           : ((size_t)node * H + h) * 128 + d;
-      store_stream(out + idx, o);
+    for (int c = 0; c < 4; ++c) tile_to_lds(own + c * 1024, qoff + c * 64, reinterpret_cast<uint64_t>(q));
+    tile_to_lds(own + 4096, node_c * 16, reinterpret_cast<uint64_t>(anc));
+  }
+  const uint64_t kbase = reinterpret_cast<uint64_t>(Kl + (size_t)hk * cap * 128);
+  const uint64_t vbase = reinterpret_cast<uint64_t>(Vl + (size_t)hk * cap * 128);
+  const uint32_t voff = lane * 16;
+  // step s of this share: tiles split + 2 s nsplit and nsplit further; a tile past `last` loads `last` again
+  auto load_step = [&](int s, int last) {
+    const uint32_t at = ring0 + (s % D) * RING_STEP_BYTES;
+    const int t0 = split + 2 * s * nsplit, t1 = t0 + nsplit;
+    const int c0 = t0 < last ? t0 : last, c1 = t1 < last ? t1 : last;
+#pragma unroll 8 // one wave alone has 32: their addresses at once would spill
+    for (int i = 0; i < B + (REM > 0 ? 1 : 0); ++i) {
+      const int j = wave + W * i;
+      if (i < B || wave < REM)
+        tile_to_lds(at + j * 1024, voff, ((j & 8) ? vbase : kbase) + ((uint64_t)(j < 16 ? c0 : c1) * 8 + (j & 7)) * 1024);
     }
-    return;
-  }
-  // a split's partial result is its own normalised output (a convex combination of V rows, so it fits
-  // half precision with 2^-11 relative error, below the bf16 rounding of the merged output) plus (m, l).
-  // The wave's 16 x 128 block is turned through LDS so that a node's 256 bytes leave as whole lines.
-  const size_t prow = ((size_t)split * H + h) * NP + wt * 16;
-  if (g == 0 && node < n) {
-    part_ml[(prow + r) * 2] = m;
-    part_ml[(prow + r) * 2 + 1] = lsum;
-  }
-  const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
-  __syncthreads(); // every wave is done with the last K/V tile
-  // row r keeps its 16-byte chunk c at slot c ^ r, so the 16 rows of one store hit distinct banks
-  char *blk = reinterpret_cast<char *>(lds_all) + wave * 4096;
+  };
+  // at most `steps` (0 or 1) steps of this wave's loads still under way
+  auto wait_steps = [&](int steps) {
+    static_assert(D == 2, "one step ahead");
+    if (steps <= 0) wait_tiles<0>();
+    else if (REM > 0 && wave < REM) wait_tiles<B + 1>();
+    else wait_tiles<B>();
+  };
+  auto steps_of = [&](int tiles) { return tiles > split ? (tiles - split + 2 * nsplit - 1) / (2 * nsplit) : 0; };
+
+  // the host's bound of the sequence says what to ask for before the length is known
+  const int cap_tiles = cap >> 5;
+  const int early = bound_tiles < cap_tiles ? bound_tiles : cap_tiles;
+  int issued = steps_of(early);
+  issued = issued < D - 1 ? issued : D - 1;
+  for (int s = 0; s < issued; ++s) load_step(s, early - 1);
+  const int L = *d_len;
+
+  wait_steps(issued); // the queries and masks are this wave's own
+  u32x4 qf[4];
+  uint64_t a0, a1;
+  {
+    const u32x4 *own = ring + (OWN + wave * RING_WAVE_BYTES) / 16;
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) {
-    // clamped to the half-precision range: a value-cache entry beyond +-65504 saturates instead of
-    // turning into an infinity that the merge would spread over the row
-    f32x4 o = acc[dt] * inv;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = fminf(fmaxf(o[e], -65504.0f), 65504.0f);
-    *reinterpret_cast<f16x4 *>(blk + r * 256 + (((2 * dt + (g >> 1)) ^ r) << 4) + 8 * (g & 1)) =
-        __builtin_convertvector(o, f16x4);
+    for (int c = 0; c < 4; ++c) qf[c] = own[c * 64 + lane];
+    const u32x4 am = own[256 + lane];
+    a0 = (uint64_t)am[0] | ((uint64_t)am[1] << 32);
+    a1 = (uint64_t)am[2] | ((uint64_t)am[3] << 32);
   }
-  // the wave reads back only what it wrote itself; its LDS operations complete in order
-  asm volatile("" ::: "memory");
-  u32x4 *pa = reinterpret_cast<u32x4 *>(part_acc);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = i * 64 + lane, rr = c >> 4, cc = c & 15;
-    const u32x4 v = *reinterpret_cast<const u32x4 *>(blk + rr * 256 + ((cc ^ rr) << 4));
-    if (wt * 16 + rr < n) pa[(prow + rr) * 16 + cc] = v; // plain store: the merge pass finds these in L2
+  const int total = L + n, n_tiles = (total + 31) >> 5;
+  const int steps = steps_of(n_tiles);
+  if (n_tiles > early) { // a sequence beyond the bound: what was clamped to it is asked for again
+    wait_tiles<0>();
+    issued = 0;
   }
+
+  f32x4 acc[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 accl = f32x4{0.f, 0.f, 0.f, 0.f}; // row sums of the rounded probabilities, as in k_attn_mfma
+  const u32x4 ones = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+  float m = NEG_BIG;
+  const float sc = 0.08838834764831845f * 1.4426950408889634f; // 1/sqrt(128) * log2(e)
+
+  auto multiply = [&](auto tiles_c, const u32x4 *kv, int t0) {
+    constexpr int TILES = decltype(tiles_c)::value;
+    // all of a contraction's LDS reads first: left alone, the compiler puts each in front of its product and waits for it
+    u32x4 op[TILES][8];
+#pragma unroll
+    for (int k = 0; k < TILES; ++k)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) op[k][c] = kv[k * 1024 + c * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sv[2 * TILES];
+#pragma unroll
+    for (int i = 0; i < 2 * TILES; ++i) sv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < 2 * TILES; ++i) sv[i] = mfma16a(op[i >> 1][(i & 1) * 4 + c], qf[c], sv[i]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < TILES; ++k)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) op[k][c] = kv[k * 1024 + (8 + c) * 64 + lane]; // the values, behind the softmax
+    __builtin_amdgcn_sched_barrier(0);
+    if ((t0 + (TILES - 1) * nsplit) * 32 + 32 > L) { // uniform: some keys are tree nodes, or past the last
+#pragma unroll
+      for (int i = 0; i < 2 * TILES; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = (t0 + (i >> 1) * nsplit) * 32 + (i & 1) * 16 + 4 * g + e - L;
+          const int bit = (int)((j < 64 ? a0 : a1) >> (j & 63)) & 1; // no branch: 32 of them would cost more than the tile
+          sv[i][e] = ((int)(j < 0) | ((int)(j < n) & bit)) != 0 ? sv[i][e] : -INFINITY;
+        }
+    }
+    float mx = sv[0][0];
+#pragma unroll
+    for (int i = 0; i < 2 * TILES; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sv[i][e]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx * sc);
+    if (__any(m_new > m)) {
+      const float corr = __builtin_amdgcn_exp2f(m - m_new);
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) {
+        acc[dt][0] *= corr; acc[dt][1] *= corr; acc[dt][2] *= corr; acc[dt][3] *= corr;
+      }
+      accl[0] *= corr; accl[1] *= corr; accl[2] *= corr; accl[3] *= corr;
+      m = m_new;
+    }
+    // m is finite, so an invisible key's probability is exactly 0, also in a row that has seen no key yet
+#pragma unroll
+    for (int k = 0; k < TILES; ++k) {
+      u32x4 pf;
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const f32x4 &s4 = sv[2 * k + (e >> 2)];
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s4[e & 3], sc, -m));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s4[(e & 3) + 1], sc, -m));
+        pf[e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{p0, p1}, bf16x2));
+      }
+      accl = mfma16a(ones, pf, accl);
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) acc[dt] = mfma16a(op[k][dt], pf, acc[dt]);
+    }
+  };
+
+  for (int s = 0; s < steps; ++s) { // uniform over the workgroup
+    if (issued <= s) { // nothing was asked for ahead (only behind a sequence beyond the bound)
+      load_step(s, n_tiles - 1);
+      issued = s + 1;
+    }
+    wait_steps(issued - s - 1);
+    meet_waves(); // this step's tiles are there, and every wave has read the previous step's and its queries
+    while (issued < steps && issued < s + D) {
+      load_step(issued, n_tiles - 1);
+      ++issued;
+    }
+    const int t0 = split + 2 * s * nsplit;
+    const u32x4 *kv = ring + (s % D) * (RING_STEP_BYTES / 16);
+    if constexpr (W <= 8) { // the registers of three waves on a SIMD do not hold the operands of two tiles
+      if (t0 + nsplit < n_tiles) multiply(std::integral_constant<int, 2>{}, kv, t0);
+      else multiply(std::integral_constant<int, 1>{}, kv, t0);
+    } else {
+      multiply(std::integral_constant<int, 1>{}, kv, t0);
+      if (t0 + nsplit < n_tiles) multiply(std::integral_constant<int, 1>{}, kv + 1024, t0 + nsplit);
+    }
+  }
+  wait_tiles<0>(); // loads beyond a sequence shorter than the bound have landed
+  finish_share(acc, m, accl[0], ring, wave, lane, wt, h, split, nsplit, H, n, part_ml, part_acc, out, out_row_tiles);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -469,23 +676,37 @@ int attn_choose_splits(int32_t head_groups, int32_t len_bound) {
 
 template <int NT, int HPW>
 static hipError_t launch_attn_k(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
-                                int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t nsplit, float *part_ml,
-                                float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm, hipStream_t st) {
-  return launch(k_attn_mfma<NT, HPW>, dim3(Hkv, H / Hkv / HPW, nsplit), dim3(NT * HPW * 64), 0, st, tm, q, Kl, Vl, H, Hkv,
-                cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles);
+                                int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, int32_t nsplit,
+                                float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm,
+                                hipStream_t st) {
+  const dim3 grid(Hkv, H / Hkv / HPW, nsplit), block(NT * HPW * 64);
+  // 32-key tiles a workgroup takes one after another.  With fewer the two forms are within 1 %, or k_attn_mfma is ahead (128
+  // nodes, 32 heads, 777 positions, 4 tiles: 15.0 / 15.2; 80 nodes, 64 heads on 8, ten waves: 18.2 / 18.7 at 5 tiles, 22.3 / 22.6
+  // at 9, 30.0 / 29.7 at 17).
+  const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
+  if (chain >= (NT * HPW > 8 ? 12 : 5) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
+    constexpr int smem = ring_lds_bytes(NT * HPW);
+    static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_ring<NT, HPW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
+    if (!once) return hipErrorInvalidValue;
+    return launch(k_attn_ring<NT, HPW>, grid, block, smem, st, tm, q, Kl, Vl, H, Hkv, cap, n, anc, d_len,
+                  (len_bound + 31) / 32, nsplit, part_ml, part_acc, out, out_row_tiles);
+  }
+  return launch(k_attn_mfma<NT, HPW>, grid, block, 0, st, tm, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc,
+                out, out_row_tiles);
 }
 
 template <int NT>
 static hipError_t launch_attn_nt(int hpw, const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv,
-                                 int32_t cap, int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t nsplit,
-                                 float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm,
-                                 hipStream_t st) {
+                                 int32_t cap, int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound,
+                                 int32_t nsplit, float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles,
+                                 KernelTimer tm, hipStream_t st) {
   if constexpr (NT <= 6) {
     if (hpw == 2)
-      return launch_attn_k<NT, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st);
+      return launch_attn_k<NT, 2>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st);
   }
   if (hpw != 1) return hipErrorInvalidValue;
-  return launch_attn_k<NT, 1>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st);
+  return launch_attn_k<NT, 1>(q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st);
 }
 
 // The one-launch form pays when a compute unit can pull its head's whole sequence in less time than the
@@ -515,14 +736,14 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
   const int nsplit = attn_choose_splits(H / hpw, len_bound);
   hipError_t e = hipErrorInvalidValue;
   switch ((n + 15) / 16) {
-  case 1: e = launch_attn_nt<1>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 2: e = launch_attn_nt<2>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 3: e = launch_attn_nt<3>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 4: e = launch_attn_nt<4>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 5: e = launch_attn_nt<5>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 6: e = launch_attn_nt<6>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 7: e = launch_attn_nt<7>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
-  case 8: e = launch_attn_nt<8>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 1: e = launch_attn_nt<1>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 2: e = launch_attn_nt<2>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 3: e = launch_attn_nt<3>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 4: e = launch_attn_nt<4>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 5: e = launch_attn_nt<5>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 6: e = launch_attn_nt<6>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 7: e = launch_attn_nt<7>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
+  case 8: e = launch_attn_nt<8>(hpw, q, Kl, Vl, H, Hkv, cap, n, anc, d_len, len_bound, nsplit, part_ml, part_acc, out, out_row_tiles, tm, st); break;
   }
   if (e != hipSuccess || nsplit == 1) return e;
   return launch_attn_merge(part_ml, part_acc, NP, H, n, nsplit, out, out_row_tiles, prof_next(prof, PC_ATTN_MERGE), st);

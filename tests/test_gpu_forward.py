@@ -415,6 +415,47 @@ def test_tree_attention_matches_per_path_attention(tmpl_name, H, Hkv, L, tiled):
     say("worst relative error", worst)
 
 
+@pytest.mark.parametrize("tmpl_name,H,Hkv,L,slack", [
+    # shares of an even and an odd number of tiles, the last step full, of one tile, partly tree, past the end
+    ("tree80", 8, 8, 2500, 0), ("tree80", 8, 8, 2591, 0), ("tree81", 8, 8, 2592, 0), ("wide128", 8, 8, 2465, 0),
+    ("prefix33", 8, 8, 2480, 0), ("prefix49", 40, 40, 1000, 0), ("prefix17", 16, 8, 2700, 0), ("prefix96", 16, 8, 6100, 0),
+    ("tree80", 64, 8, 3100, 0), ("wide128", 64, 8, 600, 0), ("prefix16", 6, 2, 2600, 0), ("prefix65", 6, 2, 2600, 0), ("single", 256, 256, 900, 0),
+    # the host's bound of the length is an estimate: above and (a step that reads more than it promised) below the true one
+    ("tree80", 8, 8, 2500, 300), ("tree80", 8, 8, 2500, -300), ("tree80", 64, 8, 3100, 64), ("tree80", 64, 8, 3100, -64)])
+def test_tree_attention_long_shares(tmpl_name, H, Hkv, L, slack):
+    """The split form for long key shares at the edges of its steps, against softmax attention in float64.  bf16 results
+    (2^-9 relative) of half-precision partial results (2^-12) and bf16 probabilities (2^-9 each, averaged): 1e-2 of the
+    row's largest value."""
+    require_gpu()
+    say("tree attention, long shares", tmpl_name, H, Hkv, L, slack)
+    t = synth.prefix_template(int(tmpl_name[6:])) if tmpl_name.startswith("prefix") else synth.TEMPLATES[tmpl_name]()
+    tree = O.make_tree(t.parent, t.rank, K)
+    n, hd = t.n_nodes, 128
+    sh = synth.ModelShape("att", 1, H * hd, H, Hkv, hd, 64, 64, "bf16")
+    kv = tr.KVDesc(sh, capacity=L + n + 320)
+    kv.reset(L)
+    kv.c.len_bound = L + slack
+    q = synth.normal_tensor((n, H, hd), 1.0, seed=1, dtype=torch.bfloat16)
+    kp = synth.normal_tensor((1, Hkv, kv.capacity, hd), 1.0, seed=2, dtype=torch.bfloat16)
+    vp = synth.normal_tensor((1, Hkv, kv.capacity, hd), 1.0, seed=3, dtype=torch.bfloat16)
+    kv_fill(kv, kp.cuda(), vp.cuda())
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    out = torch.zeros(n, H, hd, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(16 * 128 * H * (2 + hd) * 4 + 4096, dtype=torch.uint8, device="cuda")
+    ctx.op_tree_attention(kv, 0, H, q.cuda(), out, ws)
+    seen = torch.zeros(n, L + n, dtype=torch.bool)
+    seen[:, :L] = True
+    for i in range(n):
+        seen[i, [L + j for j in tree.paths[i]]] = True
+    for h in range(0, H, max(1, H // 8)):
+        g = h // (H // Hkv)
+        s = q[:, h].double() @ kp[0, g, :L + n].double().T / hd ** 0.5
+        ref = torch.softmax(s.masked_fill(~seen, -float("inf")), -1) @ vp[0, g, :L + n].double()
+        err = (out[:, h].cpu().double() - ref).abs().amax(1) / ref.abs().amax(1)
+        assert err.max() <= 1e-2, (h, err.max())
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,hd", [("f32", 64), ("bf16", 128), ("f32", 30)])
 def test_generic_attention_ignores_what_a_node_does_not_see(dtype, hd):
     """Shape-generic attention: a tree node whose value vector is not finite reaches its descendants and itself, and
