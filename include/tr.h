@@ -202,7 +202,8 @@ tr_status tr_pack_weight_rope(const void *d_src, void *d_dst, int32_t out_f, int
 /*
  * Launch plan of one packed projection (diagnostic; touches no GPU).  For n_rows activation rows
  * (tree nodes, Section 2.2: all nodes of the draft tree go through the model in one forward) and a
- * weight of [out_f, in_f], reports what tr_verify_forward would launch: plan[0] = most 16-row weight
+ * weight of [out_f, in_f], reports what the decode projection kernel takes (tr_verify_forward sends matrices of very many
+ * rows to the prompt-ingestion kernel instead, where that is faster): plan[0] = most 16-row weight
  * tiles one workgroup owns (gate/up tile pairs when fused_pair != 0, where out_f counts one of the two
  * matrices), plan[1] = workgroups per split of the input dimension, plan[2] = splits of the input
  * dimension (1 .. max_splits; always 1 when fused_pair).  plan is [host], 3 values.

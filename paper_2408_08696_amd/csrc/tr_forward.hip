@@ -408,6 +408,19 @@ static bool packed_supported(const tr_model &m) {
          hk % 32 == 0 && m.vocab % 32 == 0;
 }
 
+// One projection of a tree step by the faster of its two kernels; fills g.splits.
+static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipStream_t st) {
+  bool on = starts_on_16(g.a_frag) && starts_on_16(g.w2); // what goes straight into LDS
+  for (int i = 0; i < g.n_seg; ++i) on = on && starts_on_16(g.seg[i].w);
+  Rows8Plan plan;
+  if (on && rows8_plan(g, max_splits, &plan)) {
+    g.splits = plan.splits;
+    return launch_gemm_rows8(g, plan, st, tm);
+  }
+  gemm_plan(g, max_splits);
+  return launch_gemm_mfma(g, st, tm);
+}
+
 static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeDev &tree, int32_t n, const int32_t *tok,
                                  float *logits_out, unsigned char *ws, Profiler *prof, hipStream_t st) {
   typedef bf16_t T;
@@ -449,8 +462,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
       // needs complete sums); wq and wk are packed with interleaved rows for that
       g.rope = GemmRope{q, (T *)kv.k + (size_t)l * lsz, (T *)kv.v + (size_t)l * lsz, rope, kv.d_len,
                         H, Hkv, hd, kv.capacity, kv.layout};
-      gemm_plan(g, 1);
-      TR_TRY(launch_gemm_mfma(g, st, prof_next(prof, PC_QKV)));
+      TR_TRY(project(g, 1, prof_next(prof, PC_QKV), st));
     }
     TR_TRY(attention_dispatch<T>(kv, l, H, tree, n, q, attn, NT, (float *)(ws + w.part_ml), (float *)(ws + w.part_acc),
                                  prof, st));
@@ -459,9 +471,8 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
       g.a_frag = attn; g.n = n; g.K = hq;
       g.seg[0] = GemmSeg{(const T *)lw.wo, d / 16};
       g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      gemm_plan(g, GEMM_MAX_SPLITS);
+      TR_TRY(project(g, GEMM_MAX_SPLITS, prof_next(prof, PC_OPROJ), st));
       pending = g.splits;
-      TR_TRY(launch_gemm_mfma(g, st, prof_next(prof, PC_OPROJ)));
     }
     TR_TRY(add_norm(lw.ffn_norm));
     {
@@ -470,17 +481,15 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
       g.seg[0] = GemmSeg{(const T *)lw.w_gate, F / 16};
       g.n_seg = 1; g.w2 = (const T *)lw.w_up; g.h_frag = hbuf; g.mode = GEMM_SWIGLU;
       g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
-      gemm_plan(g, 1);
-      TR_TRY(launch_gemm_mfma(g, st, prof_next(prof, PC_GATEUP)));
+      TR_TRY(project(g, 1, prof_next(prof, PC_GATEUP), st));
     }
     {
       GemmArgs g{};
       g.a_frag = hbuf; g.n = n; g.K = F;
       g.seg[0] = GemmSeg{(const T *)lw.w_down, d / 16};
       g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      gemm_plan(g, GEMM_MAX_SPLITS);
+      TR_TRY(project(g, GEMM_MAX_SPLITS, prof_next(prof, PC_DOWN), st));
       pending = g.splits;
-      TR_TRY(launch_gemm_mfma(g, st, prof_next(prof, PC_DOWN)));
     }
   }
   if (logits_out != nullptr) {
@@ -490,8 +499,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
     g.seg[0] = GemmSeg{(const T *)m.lm_head, m.vocab / 16};
     g.n_seg = 1; g.y = logits_out; g.ldy = m.vocab; g.split_stride = 0; g.mode = GEMM_STORE;
     g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
-    gemm_plan(g, 1);
-    TR_TRY(launch_gemm_mfma(g, st, prof_next(prof, PC_LMHEAD)));
+    TR_TRY(project(g, 1, prof_next(prof, PC_LMHEAD), st));
   }
   return hipSuccess;
 }

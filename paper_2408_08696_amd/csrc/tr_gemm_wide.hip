@@ -60,7 +60,7 @@ __device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
 
 // RP2 x NP2: pairs of row tiles x pairs of out-tiles per wave; WR x WC: the workgroup's wave grid (WR * WC = 8).
 // SwiGLU: an out-tile pair is (gate tile, up tile) of the same 16 features.
-template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D>
+template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN>
 __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32_t row_tiles) {
   constexpr int RB = 2 * RP2 * WR, NW = 2 * NP2 * WC; // row tiles and out-tiles of the workgroup
   constexpr int T = RB + NW;                          // tiles per k-step
@@ -146,6 +146,31 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[u][j][e] = 0.f;
   u32x4 wf[2][NP2][2], af[2][RP2][2]; // operands of the current and the next k-step
+  // CHAIN > 0: sums of CHAIN k-steps, added up here.  A chain over all of k loses more to rounding than the decode kernel.
+  f32x16 total[CHAIN > 0 ? NP2 : 1][CHAIN > 0 ? RP2 : 1];
+  int chained = 0;
+  if constexpr (CHAIN > 0) {
+#pragma unroll
+    for (int u = 0; u < NP2; ++u)
+#pragma unroll
+      for (int j = 0; j < RP2; ++j) total[u][j] = acc[u][j];
+  }
+  auto end_chain = [&](int steps) {
+    if constexpr (CHAIN > 0) {
+      chained += steps;
+      if (chained < CHAIN) return;
+      chained = 0;
+#pragma unroll
+      for (int u = 0; u < NP2; ++u)
+#pragma unroll
+        for (int j = 0; j < RP2; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            total[u][j][e] += acc[u][j][e];
+            acc[u][j][e] = 0.f;
+          }
+    }
+  };
 
   constexpr int READS = 2 * (NP2 + RP2), MFMAS = 2 * NP2 * RP2;
   constexpr int RPM = (READS + MFMAS - 2) / (MFMAS - 1); // operand reads behind an MFMA (1 where they fit, 2 cost 1 %)
@@ -225,10 +250,20 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   for (; s + 2 <= nk - D; s += 2) {
     k_step(set0, std::true_type{}, s);
     k_step(set1, std::true_type{}, s + 1);
+    end_chain(2);
   }
   for (; s < nk; s += 2) {
     k_step(set0, std::false_type{}, s);
     k_step(set1, std::false_type{}, s + 1);
+    end_chain(2);
+  }
+  if constexpr (CHAIN > 0) {
+#pragma unroll
+    for (int u = 0; u < NP2; ++u)
+#pragma unroll
+      for (int j = 0; j < RP2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[u][j][e] += total[u][j][e];
   }
   const int rt0 = rb * RB + wr * 2 * RP2;
   if (rt0 >= row_tiles) return;
@@ -312,19 +347,19 @@ bool gemm_wide_supported(int32_t n, int32_t K, int32_t O) {
   return n >= 1 && n <= WIDE_MAX_ROWS && K % 32 == 0 && K >= 64 && O % 32 == 0;
 }
 
-template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D>
+template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN>
 static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
   constexpr int smem = D * (2 * RP2 * WR + 2 * NP2 * WC) * 1024;
-  static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D>),
+  static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D, CHAIN>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
   if (!once) return hipErrorInvalidValue;
-  return launch(k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D>, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
+  return launch(k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D, CHAIN>, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
 }
-template <int RP2, int NP2, int WR, int WC, int D>
+template <int RP2, int NP2, int WR, int WC, int D, int CHAIN = 0>
 static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
-  if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D>(g, row_tiles, grid, st, tm);
-  if (g.row_ssq != nullptr) return launch_ks<GEMM_STORE, true, RP2, NP2, WR, WC, D>(g, row_tiles, grid, st, tm);
-  return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D>(g, row_tiles, grid, st, tm);
+  if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
+  if (g.row_ssq != nullptr) return launch_ks<GEMM_STORE, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
+  return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
 }
 
 // The workgroup shapes: row tiles x out-tiles, and the measured us of one k-step when every compute unit has a
@@ -392,6 +427,60 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   case 3: return launch_shape<2, 3, 4, 2, 5>(g, row_tiles, grid, st, tm);
   }
   return launch_shape<2, 4, 4, 2, 5>(g, row_tiles, grid, st, tm);
+}
+
+// Tree steps (n <= 128) of matrices with many out-tiles: one block of eight row tiles x 8 or 16 out-tiles per workgroup.
+// Every workgroup loads the activations of its k range, so what the compute units pull is (out-tiles + row tiles) per out-tile;
+// the decode kernel, whose waves each hold all accumulators of the workgroup, ends at 6 or 8 out-tiles (6 from 81 rows on),
+// this one shares them out over its waves.  It needs the chip full of workgroups, since each pulls no faster for being
+// alone.  us per launch, decode kernel / this, 16 / 48 / 80 / 96 / 128 rows:
+//   70B gate/up, 224 x 16 out-tiles   160 / 144   162 / 144   165 / 140   200 / 142   233 / 150
+//   70B LM head, 501 x 16             323 / 348   388 / 353   395 / 347   465 / 338   513 / 346
+//   70B down, 64 x 8 in four shares    70 /  73    75 /  72    78 /  75    93 /  80   108 /  84
+//   70B o, the same                    23 /  27    25 /  27    29 /  28    30 /  30    35 /  32
+//   13B gate/up, 216 x 8               45 /  46    53 /  48    55 /  52    68 /  54    79 /  59
+//   13B LM head, 250 x 8               49 /  53    57 /  56    59 /  57    76 /  59    88 /  64
+//   7B LM head, 250 x 8                47 /  45    49 /  50    51 /  48    63 /  49    73 /  52
+// where the chip is not filled: 7B gate/up, 172 x 8   30 / 37   31 / 36   35 / 40   39 / 43   46 / 46.
+// So: at least 200 workgroups per round of 256, and with fewer than 65 rows only shares of k that
+// are long.  Matrices with K below 4096 were not measured and stay.
+bool rows8_plan(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan) {
+  if (g.n < 1 || g.n > NP || g.K < 4096 || g.K % 32 != 0 || (g.row_ssq != nullptr && g.n_ssq > 8)) return false;
+  if (g.mode == GEMM_SWIGLU ? g.row_ssq == nullptr : g.mode != GEMM_STORE || g.rope.q != nullptr) return false;
+  int32_t total = 0;
+  for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
+  const int unit = g.mode == GEMM_SWIGLU ? 2 : 1, NT = (g.n + 15) / 16, KT = g.K / 32;
+  auto fills = [](int wgs) { return wgs >= (wgs + 255) / 256 * 200; };
+  const int g16 = (total + 16 / unit - 1) / (16 / unit), g8 = (total + 8 / unit - 1) / (8 / unit);
+  if (fills(g16) && (g16 <= 256 || NT >= 3)) {
+    *plan = Rows8Plan{16, g16, 1};
+    return true;
+  }
+  const bool may_split = g.mode == GEMM_STORE && g.row_ssq == nullptr;
+  for (int sp = may_split ? max_splits : 1; sp >= 1; --sp) {
+    const int per_k = (KT + sp - 1) / sp;
+    if (per_k < 16 || (sp - 1) * per_k >= KT || !fills(g8 * sp)) continue;
+    if (!(NT >= 5 || (NT == 3 && per_k >= 160) || (NT >= 2 && per_k >= 200))) continue;
+    *plan = Rows8Plan{8, g8, sp};
+    return true;
+  }
+  return false;
+}
+
+hipError_t launch_gemm_rows8(const GemmArgs &args, const Rows8Plan &plan, hipStream_t st, KernelTimer tm) {
+  GemmArgs g = args;
+  g.total_tiles = 0;
+  for (int i = 0; i < g.n_seg; ++i) g.total_tiles += g.seg[i].out_tiles;
+  g.tiles_per_wg = plan.out_tiles / (g.mode == GEMM_SWIGLU ? 2 : 1);
+  g.groups = plan.groups;
+  g.part_q = g.total_tiles / g.groups;
+  g.part_rem = g.total_tiles % g.groups;
+  g.splits = plan.splits;
+  const int row_tiles = (g.n + 15) / 16;
+  const unsigned grid = (unsigned)(((g.groups + 7) / 8) * 8 * g.splits);
+  // chains of 16 k-steps: a sum goes through no more additions than in the decode kernel, whose eight waves share the k range
+  if (plan.out_tiles == 8) return launch_shape<1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
+  return launch_shape<2, 2, 2, 4, 6, 16>(g, row_tiles, grid, st, tm);
 }
 
 } // namespace tr

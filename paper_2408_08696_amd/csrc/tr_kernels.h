@@ -116,6 +116,13 @@ constexpr int WIDE_MAX_SPLITS = 4;
 bool gemm_wide_supported(int32_t n, int32_t K, int32_t O);
 hipError_t launch_gemm_wide(const GemmArgs &g, int32_t max_splits, int32_t *out_splits, hipStream_t st,
                             KernelTimer tm = KernelTimer{});
+// The same kernel for a tree step's rows (n <= TR_MAX_NODES), where it is the faster one: true and the plan, else
+// launch_gemm_mfma is.  Operands have to start on 16 bytes.
+struct Rows8Plan {
+  int32_t out_tiles, groups, splits; // out-tiles per workgroup, workgroups per K-split
+};
+bool rows8_plan(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan);
+hipError_t launch_gemm_rows8(const GemmArgs &g, const Rows8Plan &plan, hipStream_t st, KernelTimer tm = KernelTimer{});
 hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t K, int32_t rope_hd, hipStream_t st);
 
 // Shape-generic projections on row-major weights with their prologue and epilogue (tr_rows.hip).

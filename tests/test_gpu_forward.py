@@ -643,6 +643,46 @@ def test_prefill_from_blocks_off_16_bytes(what):
         assert float(err.max()) < 2e-2
 
 
+@pytest.mark.parametrize("shape,nodes", [
+    # gate/up and LM head of 201 groups of 8 out-tiles (the last one partly filled): from 65 rows on
+    (synth.ModelShape("rows8_narrow", 1, 4096, 2, 1, 128, 12832, 25632, "bf16"), (64, 65, 80, 81, 97, 128)),
+    # gate/up of 201 groups of 16 at any row count, down of 51 groups of 8 in four shares of unequal length
+    (synth.ModelShape("rows8_wide", 1, 6432, 2, 1, 128, 25632, 320, "bf16"), (1, 16, 17, 33, 49, 80, 128))])
+def test_step_projections_with_many_out_tiles(shape, nodes):
+    """Steps whose large matrices go through the kernel that shares operands in LDS against the same steps with those
+    matrices off 16 bytes, where the decode kernel takes them.  With the LM head alone moved the logits are the same sums in
+    another order: each side keeps chains of at most 64 sums and a tree or a chain of at most 16 over them, each sum rounded
+    to half an ulp of at most sum |a w|; |a| is at most 6 and the RMS scale leaves it unit variance, so sum |a w| <= 3 sqrt(K)
+    here.  With gate/up and down moved too the bf16 roundings of the SwiGLU output may flip."""
+    require_gpu()
+    w = synth.make_weights(shape, seed=4, device="cuda")
+    model = tr.ModelDesc(shape, w)
+    lw = model.weights["layers"][0]
+    for n in nodes:
+        say("step projections", shape.name, n)
+        t = synth.prefix_template(n) if n > 1 else synth.single()
+        logits = []
+        for moved in ((), ("lm_head",), ("lm_head", "w_gate", "w_up", "w_down")):
+            keep = {m: _off_16(model.weights[m] if m == "lm_head" else lw[m]) for m in moved}
+            eng = tr.Engine(shape, None, t, k=K, capacity=320, model=tr.ModelDesc(shape, model.weights, pack=True, prepacked=True))
+            for m, x in keep.items():
+                setattr(eng.model.c if m == "lm_head" else eng.model._layers[0], m, x.data_ptr())
+            gen = torch.Generator("cuda").manual_seed(n)
+            eng.kv.k.normal_(generator=gen)
+            eng.kv.v.normal_(generator=gen)
+            eng.kv.reset(150)
+            eng.ctx.matrix_load(np.random.default_rng(n).integers(0, shape.vocab, (shape.vocab, K), dtype=np.int32))
+            eng.root.fill_(7)
+            eng.step()
+            torch.cuda.synchronize()
+            logits.append(eng.logits.clone())
+            del eng, keep
+        a, b, c = logits
+        assert bool(a.isfinite().all())
+        assert float((a - b).abs().max()) <= 2 * 80 * 2.0 ** -24 * 3 * shape.d_model ** 0.5
+        assert float((a - c).norm() / a.norm()) < 1e-2
+
+
 def test_attention_and_linear_from_blocks_off_16_bytes():
     require_gpu()
     say("attention and linear off 16 bytes")
