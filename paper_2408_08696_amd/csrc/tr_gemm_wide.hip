@@ -59,19 +59,22 @@ __device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
 }
 
 // RP2 x NP2: pairs of row tiles x pairs of out-tiles per wave; WR x WC: the workgroup's wave grid (WR * WC = 8).
+// KG = 2: two such groups of waves take even and odd k-tiles (both in each step of the ring, T tiles each) and the first adds the
+// other's sums at the end; WR * WC * KG = 8.
 // SwiGLU: an out-tile pair is (gate tile, up tile) of the same 16 features.
-template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN>
+template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN, int KG>
 __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32_t row_tiles) {
   constexpr int RB = 2 * RP2 * WR, NW = 2 * NP2 * WC; // row tiles and out-tiles of the workgroup
   constexpr int T = RB + NW;                          // tiles per k-step
-  constexpr int C = (T + WIDE_WAVES - 1) / WIDE_WAVES;      // tile loads of a wave per k-step
-  constexpr bool HALVES = T % WIDE_WAVES != 0;              // the last of them is half a tile
-  static_assert(T % WIDE_WAVES == 0 || T % WIDE_WAVES == WIDE_WAVES / 2, "whole and half tiles only");
-  static_assert(WR * WC == WIDE_WAVES && D * T <= 160 && D >= 3, "the ring is the compute unit's LDS at most");
-  extern __shared__ u32x4 ring[]; // [D][T][64]
+  constexpr int TS = KG * T;                          // tiles per step of the ring
+  constexpr int C = (TS + WIDE_WAVES - 1) / WIDE_WAVES;     // tile loads of a wave per step
+  constexpr bool HALVES = TS % WIDE_WAVES != 0;             // the last of them is half a tile
+  static_assert(TS % WIDE_WAVES == 0 || TS % WIDE_WAVES == WIDE_WAVES / 2, "whole and half tiles only");
+  static_assert(WR * WC * KG == WIDE_WAVES && D * TS <= 160 && D >= 3, "the ring is the compute unit's LDS at most");
+  extern __shared__ u32x4 ring[]; // [D][TS][64]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // in a scalar register: what depends on it alone is uniform
-  const int wr = wave / WC, wc = wave % WC;
+  const int kg = wave / (WR * WC), wr = wave / WC % WR, wc = wave % WC;
   const int KT = g.K / 32;
   // linear id -> (k-split, out-tile group, row block): ids that differ by 8 share an XCD, so the row blocks of
   // a group are 8 apart; groups are numbered (id % 8) + 8 * (id / (8 * row_blocks))
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   if (bx >= g.groups) return; // uniform over the workgroup (group count not a multiple of 8)
   const int per_k = (KT + g.splits - 1) / g.splits;
   const int k0 = split * per_k, k1 = k0 + per_k < KT ? k0 + per_k : KT;
-  const int nk = k1 - k0; // >= 1: the launch leaves no split empty
+  const int nk = (k1 - k0) / KG; // >= 1: the launch leaves no split empty; KG = 2: an even number of k-tiles
   const int tile0 = bx * g.part_q + (bx < g.part_rem ? bx : g.part_rem);
   const int n_valid = g.part_q + (bx < g.part_rem ? 1 : 0);
 
@@ -92,15 +95,17 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   // to wait for).  Row tiles past the last and unused out-tile slots load a neighbour again; nothing of theirs is stored.
   uint64_t src[C];
   uint32_t dst[C], step[C];
+  bool of_rows[C];
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const bool half = HALVES && i == C - 1;
-    const int j = WIDE_WAVES * i + (half ? wave >> 1 : wave);
+    const int slot = WIDE_WAVES * i + (half ? wave >> 1 : wave), k = KG > 1 ? slot / T : 0, j = slot - k * T;
+    of_rows[i] = j < RB;
     if (j < RB) {
       int rt = rb * RB + j;
       rt = rt < row_tiles ? rt : row_tiles - 1;
-      src[i] = reinterpret_cast<uint64_t>(g.a_frag) + ((uint64_t)k0 * row_tiles + rt) * 1024;
-      step[i] = (uint32_t)row_tiles * 1024;
+      src[i] = reinterpret_cast<uint64_t>(g.a_frag) + ((uint64_t)(k0 + k) * row_tiles + rt) * 1024;
+      step[i] = (uint32_t)row_tiles * KG * 1024;
     } else {
       const int u = j - RB;
       const int uu = MODE == GEMM_SWIGLU ? u >> 1 : u;
@@ -111,10 +116,10 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
         ++sidx;
       }
       const bf16_t *mat = (MODE == GEMM_SWIGLU && (u & 1)) ? g.w2 : g.seg[sidx].w;
-      src[i] = reinterpret_cast<uint64_t>(mat) + ((uint64_t)t * KT + k0) * 1024;
-      step[i] = 1024;
+      src[i] = reinterpret_cast<uint64_t>(mat) + ((uint64_t)t * KT + k0 + k) * 1024;
+      step[i] = KG * 1024;
     }
-    dst[i] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)ring + j * 1024;
+    dst[i] = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)ring + slot * 1024;
     if (half) {
       src[i] += (wave & 1) * 512;
       dst[i] += (wave & 1) * 512;
@@ -123,7 +128,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   const uint32_t voff = lane * 16;
   auto load = [&](int i, uint32_t slot_off) { // the i-th load of the next k-step, into the ring slot at this offset
     if (HALVES && i == C - 1) half_tile_to_lds(dst[i] + slot_off, voff, src[i]);
-    else if (i * WIDE_WAVES < RB) tile_to_lds(dst[i] + slot_off, voff, src[i]);
+    else if (KG > 1 ? of_rows[i] : i * WIDE_WAVES < RB) tile_to_lds(dst[i] + slot_off, voff, src[i]);
     else w_tile_to_lds(dst[i] + slot_off, voff, src[i]);
     src[i] += step[i];
   };
@@ -135,8 +140,8 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   // elements 4q .. 4q + 3, features 8 q + 4 (l / 32) .. + 3 of the 32 the out-tile pair spans.
   const int half_sel = (lane >> 4) & 1, hb = lane >> 5;
   const int frag = half_sel * 64 + (lane & 15) + 16 * hb; // in 16-byte units; + 32 for the second k-half
-  const char *abase = reinterpret_cast<const char *>(ring + wr * (2 * RP2) * 64 + frag);
-  const char *wbase = reinterpret_cast<const char *>(ring + (RB + wc * (2 * NP2)) * 64 + frag);
+  const char *abase = reinterpret_cast<const char *>(ring + (kg * T + wr * (2 * RP2)) * 64 + frag);
+  const char *wbase = reinterpret_cast<const char *>(ring + (kg * T + RB + wc * (2 * NP2)) * 64 + frag);
 
   f32x16 acc[NP2][RP2];
 #pragma unroll
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   // One k-step s in ring slot `slot` (a byte offset): its operands (set SET) were read during s - 1; the tiles of s + 1
   // must have landed for every wave, and its own slot, which every wave has read, takes k-step s + D.  Of the
   // min(s + D, nk) k-steps requested so far, those past s + 1 may stay under way.  STEADY: s + D < nk.
-  constexpr uint32_t SLOT = T * 1024;
+  constexpr uint32_t SLOT = TS * 1024;
   uint32_t slot = 0;
   auto k_step = [&](auto set_c, auto steady_c, int s) {
     constexpr int SET = decltype(set_c)::value;
@@ -264,6 +269,27 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
       for (int j = 0; j < RP2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[u][j][e] += total[u][j][e];
+  }
+  if constexpr (KG > 1) {
+    static_assert(KG == 2 && WR * WC * NP2 * RP2 * 4 <= D * TS, "the second group's sums fit the ring");
+    f32x4 *xa = reinterpret_cast<f32x4 *>(ring) + (size_t)(wave % (WR * WC)) * (NP2 * RP2 * 4 * 64) + lane;
+    wait_tiles<0>();
+    __syncthreads(); // everyone has read the last k-step
+    if (kg == 1) {
+#pragma unroll
+      for (int i = 0; i < NP2 * RP2 * 4; ++i) {
+        const f32x16 &a = acc[i / (4 * RP2)][i / 4 % RP2];
+        xa[i * 64] = f32x4{a[4 * (i & 3)], a[4 * (i & 3) + 1], a[4 * (i & 3) + 2], a[4 * (i & 3) + 3]};
+      }
+    }
+    __syncthreads();
+    if (kg == 1) return;
+#pragma unroll
+    for (int i = 0; i < NP2 * RP2 * 4; ++i) {
+      const f32x4 o = xa[i * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i / (4 * RP2)][i / 4 % RP2][4 * (i & 3) + e] += o[e];
+    }
   }
   const int rt0 = rb * RB + wr * 2 * RP2;
   if (rt0 >= row_tiles) return;
@@ -347,13 +373,14 @@ bool gemm_wide_supported(int32_t n, int32_t K, int32_t O) {
   return n >= 1 && n <= WIDE_MAX_ROWS && K % 32 == 0 && K >= 64 && O % 32 == 0;
 }
 
-template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN>
+template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN, int KG = 1>
 static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
-  constexpr int smem = D * (2 * RP2 * WR + 2 * NP2 * WC) * 1024;
-  static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D, CHAIN>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
+  constexpr auto kernel = &k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D, CHAIN, KG>;
+  constexpr int smem = D * KG * (2 * RP2 * WR + 2 * NP2 * WC) * 1024;
+  static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         smem) == hipSuccess;
   if (!once) return hipErrorInvalidValue;
-  return launch(k_gemm_wide<MODE, SCALED, RP2, NP2, WR, WC, D, CHAIN>, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
+  return launch(kernel, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
 }
 template <int RP2, int NP2, int WR, int WC, int D, int CHAIN = 0>
 static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
@@ -441,9 +468,11 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
 //   13B gate/up, 216 x 8               45 /  46    53 /  48    55 /  52    68 /  54    79 /  59
 //   13B LM head, 250 x 8               49 /  53    57 /  56    59 /  57    76 /  59    88 /  64
 //   7B LM head, 250 x 8                47 /  45    49 /  50    51 /  48    63 /  49    73 /  52
-// where the chip is not filled: 7B gate/up, 172 x 8   30 / 37   31 / 36   35 / 40   39 / 43   46 / 46.
-// So: at least 200 workgroups per round of 256, and with fewer than 65 rows only shares of k that
-// are long.  Matrices with K below 4096 were not measured and stay.
+// where the chip is not filled: 7B gate/up, 172 x 8   30 / 37   31 / 36   35 / 40   39 / 43   46 / 46; it takes 230 x 6 with two
+// groups of waves on even and odd k-tiles (a wave's 2 x 2 tiles of 8 x 6 leave four waves idle): 81, 97, 112, 128 rows
+// 41.2 / 40.2, 44.0 / 41.5, 44.5 / 42.1, 47.9 / 44.0.
+// So: at least 200 workgroups per round of 256, and with fewer than 65 rows only shares of k that are long.  Matrices with
+// K below 4096 were not measured and stay.
 bool rows8_plan(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan) {
   if (g.n < 1 || g.n > NP || g.K < 4096 || g.K % 32 != 0 || (g.row_ssq != nullptr && g.n_ssq > 8)) return false;
   if (g.mode == GEMM_SWIGLU ? g.row_ssq == nullptr : g.mode != GEMM_STORE || g.rope.q != nullptr) return false;
@@ -464,6 +493,11 @@ bool rows8_plan(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan) {
     *plan = Rows8Plan{8, g8, sp};
     return true;
   }
+  const int g6 = (total + 2) / 3;
+  if (g.mode == GEMM_SWIGLU && NT >= 6 && KT % 2 == 0 && fills(g6)) {
+    *plan = Rows8Plan{6, g6, 1};
+    return true;
+  }
   return false;
 }
 
@@ -479,6 +513,7 @@ hipError_t launch_gemm_rows8(const GemmArgs &args, const Rows8Plan &plan, hipStr
   const int row_tiles = (g.n + 15) / 16;
   const unsigned grid = (unsigned)(((g.groups + 7) / 8) * 8 * g.splits);
   // chains of 16 k-steps: a sum goes through no more additions than in the decode kernel, whose eight waves share the k range
+  if (plan.out_tiles == 6) return launch_ks<GEMM_SWIGLU, true, 1, 3, 4, 1, 5, 16, 2>(g, row_tiles, grid, st, tm);
   if (plan.out_tiles == 8) return launch_shape<1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
   return launch_shape<2, 2, 2, 4, 6, 16>(g, row_tiles, grid, st, tm);
 }

@@ -647,7 +647,10 @@ def test_prefill_from_blocks_off_16_bytes(what):
     # gate/up and LM head of 201 groups of 8 out-tiles (the last one partly filled): from 65 rows on
     (synth.ModelShape("rows8_narrow", 1, 4096, 2, 1, 128, 12832, 25632, "bf16"), (64, 65, 80, 81, 97, 128)),
     # gate/up of 201 groups of 16 at any row count, down of 51 groups of 8 in four shares of unequal length
-    (synth.ModelShape("rows8_wide", 1, 6432, 2, 1, 128, 25632, 320, "bf16"), (1, 16, 17, 33, 49, 80, 128))])
+    (synth.ModelShape("rows8_wide", 1, 6432, 2, 1, 128, 25632, 320, "bf16"), (1, 16, 17, 33, 49, 80, 128)),
+    # gate/up of 201 groups of 6 from 81 rows on, an odd and an even number of k-tiles for each of the two wave groups
+    (synth.ModelShape("rows8_pairs_odd", 1, 4160, 2, 1, 128, 9632, 320, "bf16"), (80, 81, 96, 97, 113, 128)),
+    (synth.ModelShape("rows8_pairs_even", 1, 4224, 2, 1, 128, 9664, 320, "bf16"), (81, 112, 128))])
 def test_step_projections_with_many_out_tiles(shape, nodes):
     """Steps whose large matrices go through the kernel that shares operands in LDS against the same steps with those
     matrices off 16 bytes, where the decode kernel takes them.  With the LM head alone moved the logits are the same sums in
