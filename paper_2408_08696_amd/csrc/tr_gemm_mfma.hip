@@ -366,13 +366,10 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
       const bool live = row < n_rows;
       const f32x4 gt = f32x4{fin[i][0][0] * sc_row, fin[i][0][1] * sc_row, fin[i][0][2] * sc_row, fin[i][0][3] * sc_row};
       const f32x4 up = f32x4{fin[i][TPU - 1][0] * sc_row, fin[i][TPU - 1][1] * sc_row, fin[i][TPU - 1][2] * sc_row, fin[i][TPU - 1][3] * sc_row};
-      ushort4 hv;
-      hv.x = live ? f32_to_bf16(gt[0] / (1.0f + __expf(-gt[0])) * up[0]) : (bf16_t)0;
-      hv.y = live ? f32_to_bf16(gt[1] / (1.0f + __expf(-gt[1])) * up[1]) : (bf16_t)0;
-      hv.z = live ? f32_to_bf16(gt[2] / (1.0f + __expf(-gt[2])) * up[2]) : (bf16_t)0;
-      hv.w = live ? f32_to_bf16(gt[3] / (1.0f + __expf(-gt[3])) * up[3]) : (bf16_t)0;
+      const u32x2s hv = u32x2s{live ? bf16_pair(silu(gt[0]) * up[0], silu(gt[1]) * up[1]) : 0u,
+                               live ? bf16_pair(silu(gt[2]) * up[2], silu(gt[3]) * up[3]) : 0u};
       const size_t slot = ((size_t)(o >> 5) * NT + t) * 64 + r + 16 * ((o & 31) >> 3);
-      store_stream(h_frag + slot * 8 + (o & 7), hv);
+      __builtin_nontemporal_store(hv, reinterpret_cast<u32x2s *>(h_frag + slot * 8 + (o & 7)));
     }
   }
 }

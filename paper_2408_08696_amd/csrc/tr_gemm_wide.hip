@@ -33,6 +33,7 @@ namespace tr {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
@@ -53,6 +54,13 @@ __device__ inline void half_tile_to_lds(uint32_t lds_off, uint32_t voff, uint64_
   asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, 0xffffffff\n\tglobal_load_lds_dwordx4 %1, %2 nt\n\ts_mov_b64 exec, -1"
                ::"s"(lds_off), "v"(voff), "s"(gbase) : "memory");
 }
+// Words (a0, a1) hold features 4 hb .. + 3 and (b0, b1) 8 + 4 hb .. + 3 of a row's sixteen in lane 32 hb + row; the result holds
+// features 8 hb .. + 7.
+__device__ inline uint4 eight_features(uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1) {
+  const auto s0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false); // lanes 32 .. 63 of the first with 0 .. 31 of the second
+  const auto s1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+  return uint4{s0[0], s1[0], s0[1], s1[1]};
+}
 template <typename F, int... J>
 __device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
   (f(std::integral_constant<int, J>{}), ...);
@@ -64,6 +72,7 @@ __device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
 // SwiGLU: an out-tile pair is (gate tile, up tile) of the same 16 features.
 template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN, int KG>
 __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32_t row_tiles) {
+  constexpr bool ROPE = MODE == GEMM_ROPE; // GEMM_STORE with the fused Q/K/V epilogue
   constexpr int RB = 2 * RP2 * WR, NW = 2 * NP2 * WC; // row tiles and out-tiles of the workgroup
   constexpr int T = RB + NW;                          // tiles per k-step
   constexpr int TS = KG * T;                          // tiles per step of the ring
@@ -95,7 +104,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   // to wait for).  Row tiles past the last and unused out-tile slots load a neighbour again; nothing of theirs is stored.
   uint64_t src[C];
   uint32_t dst[C], step[C];
-  bool of_rows[C];
+  bool of_rows[C]; // KG = 2 mixes both kinds in a load (all without the streaming hint: 7B gate/up of 128 rows 44 -> 47 us)
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const bool half = HALVES && i == C - 1;
@@ -257,6 +266,21 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
     k_step(set1, std::true_type{}, s + 1);
     end_chain(2);
   }
+  // The last tiles are under way: what the epilogue needs of its rows comes behind them.
+  const int pos0 = ROPE ? *g.rope.d_len : 0;
+  float ssq[SCALED ? RP2 : 1][4];
+  if (SCALED) {
+#pragma unroll
+    for (int j = 0; j < RP2; ++j) {
+      const int row = 16 * (rb * RB + wr * 2 * RP2 + 2 * j) + (lane & 31);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int at = hb + 2 * c;
+        ssq[j][c] = g.row_ssq[(size_t)(row < g.n ? row : g.n - 1) * g.n_ssq + (at < g.n_ssq ? at : 0)];
+      }
+    }
+    asm volatile("" ::: "memory"); // here and not where they are used
+  }
   for (; s < nk; s += 2) {
     k_step(set0, std::false_type{}, s);
     k_step(set1, std::false_type{}, s + 1);
@@ -294,75 +318,100 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   const int rt0 = rb * RB + wr * 2 * RP2;
   if (rt0 >= row_tiles) return;
 
-  // epilogue from registers
+  // Epilogue from registers, bound by its vector instructions and stores.  us of a workgroup's time, with the RMS partial sums, the
+  // rotary factors and the committed length asked for one after another where they were used, an integer division per four
+  // features, float division, rounding to bf16 by integer arithmetic and 8-byte stores / now: 7B, 511 rows: gate/up 4.8 / 2.2 of
+  // 77, Q/K/V 7.7 / 4.9 of 57; 70B, 2048 rows, a round: gate/up 7.2 / 2.9 of 190, Q/K/V 20.7 / 11.5 of 165.
 #pragma unroll
   for (int j = 0; j < RP2; ++j) {
     const int row = 16 * (rt0 + 2 * j) + (lane & 31);
     const int rt = row >> 4, r = row & 15;
+    f32x2 rope_c[ROPE ? NP2 * 4 : 1], rope_s[ROPE ? NP2 * 4 : 1];
+    if constexpr (ROPE) { // head_dim is 128 (tiled cache): eight out-tiles a head
+      const float *cs = g.rope.rope + (size_t)(row < g.n ? row : g.n - 1) * 128;
+#pragma unroll
+      for (int i = 0; i < NP2 * 4; ++i) {
+        const int t = tile0 + 2 * (wc * NP2 + (i >> 2)) + ((i & 3) >> 1);
+        const float *at = cs + (t & 7) * 8 + 4 * (i & 1) + 2 * hb;
+        rope_c[i] = *reinterpret_cast<const f32x2 *>(at);
+        rope_s[i] = *reinterpret_cast<const f32x2 *>(at + 64);
+      }
+      __builtin_amdgcn_sched_barrier(0); // all of them on their way before the first store
+    }
     if (rt >= row_tiles) continue;
     float sc_row = 1.0f;
-    if (SCALED) { // per-row RMS scale from n_ssq (<= 8) partial sums of squares; the row's two lanes fetch alternate chunks
+    if (SCALED) { // per-row RMS scale; the row's two lanes hold alternate partial sums
       float ss = 0.f;
-      if (row < g.n) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (hb + 2 * c < g.n_ssq) ss += g.row_ssq[(size_t)row * g.n_ssq + hb + 2 * c];
-      }
+      for (int c = 0; c < 4; ++c)
+        if (hb + 2 * c < g.n_ssq) ss += ssq[j][c];
       ss += __shfl_xor(ss, 32);
       sc_row = 1.0f / sqrtf(ss / (float)g.norm_dim + g.eps);
     }
+    // A lane's accumulator elements are features 8 q + 4 hb .. + 3 of an out-tile for q = 0, 1.  In 16 bits the two lanes of a row
+    // exchange halves, so that each has eight neighbouring features and stores them at once.
 #pragma unroll
     for (int p2 = 0; p2 < NP2; ++p2) {
+      const f32x16 &a = acc[p2][j];
 #pragma unroll
-      for (int q = 0; q < (MODE == GEMM_SWIGLU ? 2 : 4); ++q) {
-        // STORE: elements 4q .. 4q+3 are features 8 (q & 1) + 4 hb .. + 3 of out-tile 2 p2 + q / 2
-        // SWIGLU: elements 4q .. (gate) and 8 + 4q .. (up) are features 8 q + 4 hb .. + 3 of tile p2
-        const int u = MODE == GEMM_SWIGLU ? wc * NP2 + p2 : 2 * (wc * NP2 + p2) + (q >> 1);
+      for (int half = 0; half < (MODE == GEMM_SWIGLU ? 1 : 2); ++half) { // out-tile u; SWIGLU: gate elements 0 .. 7, up 8 .. 15
+        const int u = MODE == GEMM_SWIGLU ? wc * NP2 + p2 : 2 * (wc * NP2 + p2) + half;
         if (u >= n_valid) continue;
-        const int o = (tile0 + u) * 16 + 8 * (MODE == GEMM_SWIGLU ? q : (q & 1)) + 4 * hb;
-        const f32x16 &a = acc[p2][j];
-        if (MODE == GEMM_STORE) {
+        const int t = tile0 + u;
+        if constexpr (MODE == GEMM_STORE) {
           if (row >= g.n) continue;
-          const f32x4 v = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]} * sc_row;
-          if (g.rope.q == nullptr) {
-            *reinterpret_cast<float4 *>(g.y + (size_t)split * g.split_stride + (size_t)row * g.ldy + o) =
+#pragma unroll
+          for (int q = 2 * half; q < 2 * half + 2; ++q) {
+            const f32x4 v = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]} * sc_row;
+            *reinterpret_cast<float4 *>(g.y + (size_t)split * g.split_stride + (size_t)row * g.ldy + t * 16 + 8 * (q & 1) + 4 * hb) =
                 float4{v[0], v[1], v[2], v[3]};
-          } else {
-            // fused Q/K/V epilogue, as in the decode kernel, into a tiled cache: (o, o+1) and (o+2, o+3) are rotation pairs
-            const GemmRope &rp = g.rope;
-            const int hd = rp.hd, head = o / hd, dd = o - head * hd;
-            const int pos = *rp.d_len + row;
-            float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
+          }
+        } else if constexpr (ROPE) {
+          // fused Q/K/V epilogue, as in the decode kernel, into a tiled cache: neighbouring features are rotation pairs
+          const GemmRope &rp = g.rope;
+          const int head = t >> 3, pos = pos0 + row;
+          uint32_t w[2][2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int q = 2 * half + i;
+            const f32x4 v = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]} * sc_row;
             if (head < rp.H + rp.Hkv) {
-              const float *cs = rp.rope + (size_t)row * hd + (dd >> 1);
-              const float c0 = cs[0], c1 = cs[1], s0 = cs[hd / 2], s1 = cs[hd / 2 + 1];
-              a0 = v[0] * c0 - v[1] * s0; b0 = v[1] * c0 + v[0] * s0;
-              a1 = v[2] * c1 - v[3] * s1; b1 = v[3] * c1 + v[2] * s1;
-            }
-            const bf16_t e0 = f32_to_bf16(a0), e1 = f32_to_bf16(b0), e2 = f32_to_bf16(a1), e3 = f32_to_bf16(b1);
-            if (head < rp.H + rp.Hkv) {
-              bf16_t *dst;
-              if (head < rp.H) dst = rp.q + ((size_t)row * rp.H + head) * hd + dd;
-              else dst = rp.k_layer + (size_t)(head - rp.H) * rp.cap * hd + kv_k_index(pos, dd);
-              *reinterpret_cast<ushort4 *>(dst) = ushort4{e0, e1, e2, e3};
+              const f32x2 c = rope_c[p2 * 4 + q], sn = rope_s[p2 * 4 + q];
+              w[i][0] = bf16_pair(v[0] * c[0] - v[1] * sn[0], v[1] * c[0] + v[0] * sn[0]);
+              w[i][1] = bf16_pair(v[2] * c[1] - v[3] * sn[1], v[3] * c[1] + v[2] * sn[1]);
             } else {
-              bf16_t *dst = rp.v_layer + (size_t)(head - rp.H - rp.Hkv) * hd * rp.cap;
-              dst[kv_v_index(pos, dd)] = e0; dst[kv_v_index(pos, dd + 1)] = e1;
-              dst[kv_v_index(pos, dd + 2)] = e2; dst[kv_v_index(pos, dd + 3)] = e3;
+              w[i][0] = bf16_pair(v[0], v[1]);
+              w[i][1] = bf16_pair(v[2], v[3]);
+            }
+          }
+          const uint4 e = eight_features(w[0][0], w[0][1], w[1][0], w[1][1]);
+          const int dd = (t & 7) * 16 + 8 * hb;
+          if (row >= g.n) continue;
+          if (head < rp.H + rp.Hkv) {
+            bf16_t *dst;
+            if (head < rp.H) dst = rp.q + ((size_t)row * rp.H + head) * 128 + dd;
+            else dst = rp.k_layer + (size_t)(head - rp.H) * rp.cap * 128 + kv_k_index(pos, dd);
+            *reinterpret_cast<uint4 *>(dst) = e;
+          } else {
+            bf16_t *dst = rp.v_layer + (size_t)(head - rp.H - rp.Hkv) * 128 * rp.cap + kv_v_index(pos, dd);
+            const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { // features of an out-tile sit in neighbouring lane slots
+              dst[16 * i] = (bf16_t)ew[i];
+              dst[16 * i + 8] = (bf16_t)(ew[i] >> 16);
             }
           }
         } else {
-          // h[row, o .. o+3] = bf16(silu(gate) * up) in fragment order over all row tiles; rows past n are zeros
+          // h[row, ..] = bf16(silu(gate) * up) in fragment order over all row tiles; rows past n are zeros
+          uint32_t w[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            w[i] = bf16_pair(silu(a[2 * i] * sc_row) * (a[8 + 2 * i] * sc_row), silu(a[2 * i + 1] * sc_row) * (a[9 + 2 * i] * sc_row));
+          const uint4 e = eight_features(w[0], w[1], w[2], w[3]);
           const bool live = row < g.n;
-          const f32x4 gt = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]} * sc_row;
-          const f32x4 up = f32x4{a[8 + 4 * q], a[9 + 4 * q], a[10 + 4 * q], a[11 + 4 * q]} * sc_row;
-          ushort4 hv;
-          hv.x = live ? f32_to_bf16(gt[0] / (1.0f + __expf(-gt[0])) * up[0]) : (bf16_t)0;
-          hv.y = live ? f32_to_bf16(gt[1] / (1.0f + __expf(-gt[1])) * up[1]) : (bf16_t)0;
-          hv.z = live ? f32_to_bf16(gt[2] / (1.0f + __expf(-gt[2])) * up[2]) : (bf16_t)0;
-          hv.w = live ? f32_to_bf16(gt[3] / (1.0f + __expf(-gt[3])) * up[3]) : (bf16_t)0;
-          const size_t fslot = ((size_t)(o >> 5) * row_tiles + rt) * 64 + r + 16 * ((o & 31) >> 3);
-          store_stream(g.h_frag + fslot * 8 + (o & 7), hv);
+          const u32x4 hv = live ? u32x4{e.x, e.y, e.z, e.w} : u32x4{0u, 0u, 0u, 0u};
+          const size_t fslot = ((size_t)(t >> 1) * row_tiles + rt) * 64 + r + 16 * (2 * (t & 1) + hb);
+          __builtin_nontemporal_store(hv, reinterpret_cast<u32x4 *>(g.h_frag) + fslot);
         }
       }
     }
@@ -385,6 +434,9 @@ static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hip
 template <int RP2, int NP2, int WR, int WC, int D, int CHAIN = 0>
 static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
   if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
+  if constexpr (CHAIN == 0) { // a step's Q/K/V projection is the decode kernel's
+    if (g.rope.q != nullptr) return launch_ks<GEMM_ROPE, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
+  }
   if (g.row_ssq != nullptr) return launch_ks<GEMM_STORE, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
   return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
 }
@@ -409,7 +461,7 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
   if (g.mode == GEMM_SWIGLU && g.row_ssq == nullptr) return hipErrorInvalidValue;
-  if (g.rope.q != nullptr && !g.rope.tiled) return hipErrorInvalidValue;
+  if (g.rope.q != nullptr && (!g.rope.tiled || g.rope.hd != 128 || g.row_ssq == nullptr || g.mode != GEMM_STORE)) return hipErrorInvalidValue;
   const bool may_split = g.mode == GEMM_STORE && g.rope.q == nullptr && g.row_ssq == nullptr && max_splits > 1;
   const int row_tiles = (g.n + 15) / 16;
   const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles
