@@ -680,11 +680,11 @@ static hipError_t launch_attn_k(const bf16_t *q, const bf16_t *Kl, const bf16_t 
                                 float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm,
                                 hipStream_t st) {
   const dim3 grid(Hkv, H / Hkv / HPW, nsplit), block(NT * HPW * 64);
-  // 32-key tiles a workgroup takes one after another.  With fewer the two forms are within 1 %, or k_attn_mfma is ahead (128
-  // nodes, 32 heads, 777 positions, 4 tiles: 15.0 / 15.2; 80 nodes, 64 heads on 8, ten waves: 18.2 / 18.7 at 5 tiles, 22.3 / 22.6
-  // at 9, 30.0 / 29.7 at 17).
+  // 32-key tiles a workgroup takes one after another.  With fewer the two forms are within 1 %, or k_attn_mfma is ahead: 128
+  // nodes, 32 heads, 777 positions (4 tiles) 15.0 / 15.2; 80 nodes, 32 heads, 1024 (5) 14.0 / 14.2; 80 nodes, 64 heads on 8, ten
+  // waves 18.2 / 18.7 at 5 tiles, 22.3 / 22.6 at 9, 30.0 / 29.7 at 17.
   const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
-  if (chain >= (NT * HPW > 8 ? 12 : 5) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
+  if (chain >= (NT * HPW > 8 ? 12 : 6) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
     constexpr int smem = ring_lds_bytes(NT * HPW);
     static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_ring<NT, HPW>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
