@@ -330,7 +330,7 @@ def main():
     gu_bytes = 2 * sh.d_ffn * sh.d_model * 2                       # gate + up weights, bf16, read once
     gu_avg_s = gu_ms / gu_launches * 1e-3
     achieved = gu_bytes / gu_avg_s / 1e9
-    roofline = {"kernel": "gate_up_swiglu (k_gemm_mfma, fused gate/up projection + SwiGLU)", "bound": "hbm",
+    roofline = {"kernel": "gate_up_swiglu (k_gemm_mfma, at the larger shapes k_gemm_wide; fused gate/up projection + SwiGLU)", "bound": "hbm",
                 "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS,
                 "traffic": None, "avg_launch_us": gu_avg_s * 1e6, "algorithmic_bytes_per_launch": gu_bytes,
                 "timing": "per-dispatch start/stop events (hipExtLaunchKernelGGL) over the profiled steps",
