@@ -320,8 +320,9 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
 
   // Epilogue from registers, bound by its vector instructions and stores.  us of a workgroup's time, with the RMS partial sums, the
   // rotary factors and the committed length asked for one after another where they were used, an integer division per four
-  // features, float division, rounding to bf16 by integer arithmetic and 8-byte stores / now: 7B, 511 rows: gate/up 4.8 / 2.2 of
-  // 77, Q/K/V 7.7 / 4.9 of 57; 70B, 2048 rows, a round: gate/up 7.2 / 2.9 of 190, Q/K/V 20.7 / 11.5 of 165.
+  // features, rounding to bf16 by integer arithmetic and 8-byte stores / now: 7B, 511 rows: gate/up 4.8 / 2.2 of 77, Q/K/V 7.7 / 4.9
+  // of 57; 70B, 2048 rows, a round: gate/up 7.2 / 2.9 of 190, Q/K/V 20.7 / 11.5 of 165.  (Gate/up's second figure is with a
+  // reciprocal for SwiGLU's division; the division adds 0.2 % to a prompt of 511 tokens at 7B width, 0.5 % to 4095 at 70B width.)
 #pragma unroll
   for (int j = 0; j < RP2; ++j) {
     const int row = 16 * (rt0 + 2 * j) + (lane & 31);

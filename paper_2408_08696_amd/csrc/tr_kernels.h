@@ -22,11 +22,10 @@ __device__ inline uint32_t bf16_pair(float lo, float hi) {
   typedef __attribute__((ext_vector_type(2))) __bf16 b2;
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, b2));
 }
-// x / (1 + e^-x).  The quotient by the hardware's reciprocal (1 ulp) in place of the ten instructions of an exactly rounded
-// division: like e^-x itself it is off by less than 2^-22, and the result is rounded to bf16 (4 million normal x of deviation 0.3
-// to 60 and y, silu(x) y against float64: relative error after the rounding 1.657e-3 to 1.660e-3, the same in all digits with
-// the division).  Below x = -87.3 it is -0 instead of some 1e-37.
-__device__ inline float silu(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
+// x / (1 + e^-x), the quotient correctly rounded.  The hardware's reciprocal in its place saves ten instructions, but it is
+// one more rounding in float32 and gives 0 from x = -87.3 down, where 1 / (1 + e^-x) is no normal number and the quotient, some
+// 1e-36, still is.  e^-x itself is off by up to |x| 2^-24 or so relatively (the rounding of its exponent).
+__device__ inline float silu(float x) { return x / (1.0f + __expf(-x)); }
 
 // Fragment order (see tr_gemm_mfma.hip): a tile of 16 rows x 32 k is 64 lane slots of 8 bf16;
 // element (row r, k) of an operand with T row tiles lives in tile (k/32, r/16) at lane slot

@@ -686,6 +686,75 @@ def test_step_projections_with_many_out_tiles(shape, nodes):
         assert float((a - c).norm() / a.norm()) < 1e-2
 
 
+def _ffn_step(shape, n, w_gate, w_up, w_down, offset=0.0, moved=()):
+    """One step whose logits are the residual stream behind the feed-forward block: attention adds nothing (wo = 0), only the
+    first half of the features carries the tokens (feature 0 of it is `offset` for every one if that is not 0), w_down writes
+    the second half alone, and the LM head is the identity.  Row i of the logits is the row of the stream, rounded to bf16, times
+    one RMS scale, which the first half gives back.  Returns the stream [n, d] and the tokens' embeddings, both in float64.
+    `moved` names weights that start off 16 bytes."""
+    d = shape.d_model
+    assert shape.vocab == d and shape.n_layers == 1
+    w = synth.make_weights(shape, seed=4, device="cuda")
+    w["embed"][:, d // 2:] = 0
+    if offset:
+        w["embed"][:, 0] = offset
+    w["lm_head"] = torch.eye(d, dtype=torch.bfloat16, device="cuda")
+    w["layers"][0].update(wo=torch.zeros_like(w["layers"][0]["wo"]), w_gate=w_gate, w_up=w_up, w_down=w_down)
+    eng = tr.Engine(shape, w, synth.prefix_template(n) if n > 1 else synth.single(), k=K, capacity=320)
+    keep = {m: _off_16(eng.model.weights["layers"][0][m]) for m in moved}
+    for m, x in keep.items():
+        setattr(eng.model._layers[0], m, x.data_ptr())
+    eng.kv.reset(150)
+    eng.ctx.matrix_load(np.random.default_rng(n).integers(0, shape.vocab, (shape.vocab, K), dtype=np.int32))
+    eng.root.fill_(7)
+    eng.step()
+    torch.cuda.synchronize()
+    xe = w["embed"][eng.S.long()].double()
+    first = xe[:, :d // 2]
+    scale = (eng.logits[:, :d // 2].double() * first).sum(1) / (first * first).sum(1)
+    return eng.logits.double() / scale[:, None], xe, scale
+
+
+@pytest.mark.parametrize("d,F,n", [(512, 1024, 80), (512, 1056, 5), (4096, 12832, 80), (4096, 25632, 49), (4096, 9632, 113)])
+def test_swiglu_over_the_range_of_the_gate(d, F, n):
+    """silu(gate) * up, rounded once to bf16, for gates from -110 to 100 against float64, in the decode kernel and in every form of
+    the one that shares operands in LDS.  Besides its rounding, 2^-8, a result carries what the float32 sums are off by: a chain of up to
+    64 additions, each rounded to half an ulp of up to 110 for the gate (2.5e-4 in all) and of a few units for up (1e-5).
+    Below -88.7 e^-gate is beyond float32 and the result 0."""
+    require_gpu()
+    say("swiglu over the gate's range", d, F, n)
+    shape = synth.ModelShape("gates", 1, d, 2, 1, 128, F, d, "bf16")
+    lw = synth.layer_weights(shape, 0, seed=9, device="cuda")
+    gen = torch.Generator("cuda").manual_seed(F + n)
+    rms = ((64 + (d // 2 - 1)) / d) ** 0.5
+    want = -110.0 * torch.rand(F, device="cuda", generator=gen)          # mostly negative: a few large rows do not set the scale
+    at = torch.rand(F, device="cuda", generator=gen)
+    want = torch.where(at < 0.35, -87.9 + 0.8 * (at / 0.35 - 0.5), want) # where the quotient leaves the normal numbers
+    want = torch.where(at > 0.98, 20 * torch.rand(F, device="cuda", generator=gen), want)
+    want = torch.where(at > 0.997, 100.0, want)
+    want[F - 16] = 100.0
+    w_gate = lw["w_gate"] / 8
+    w_gate[:, 0] = want * rms / 8.0
+    sel = torch.randperm(F, generator=gen, device="cuda")[:d // 2]
+    sel[:16], sel[-16:] = torch.arange(16, device="cuda"), torch.arange(F - 16, F, device="cuda")
+    w_down = torch.zeros(d, F, dtype=torch.bfloat16, device="cuda")
+    w_down[d // 2 + torch.arange(d // 2, device="cuda"), sel] = 1
+    got, xe, scale = _ffn_step(shape, n, w_gate, lw["w_up"], w_down, offset=8.0)
+    got = got[:, d // 2:]
+    sc = 1 / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
+    gate, up = (xe @ w_gate[sel].double().T) * sc, (xe @ lw["w_up"][sel].double().T) * sc
+    sig = torch.sigmoid(gate)
+    ref = gate * sig * up
+    sure = (gate > -88.6) & (ref.abs() * scale[:, None] > 2.0 ** -124)   # normal numbers all the way
+    assert int(((gate < -87.4) & sure).sum()) > 50 and float(gate.max()) > 80
+    bound = 2.0 ** -8 * ref.abs() + 2.5e-4 * (up * sig * (1 + gate * (1 - sig))).abs() + 1e-5 * (gate * sig).abs()
+    err = ((got - ref).abs() / bound)[sure]
+    say("largest error over its bound", float(err.max()))
+    assert float(err.max()) < 1.01
+    rest = ~sure
+    assert bool((got[rest].abs() <= ref[rest].abs() * 1.01 + 2.0 ** -120).all())
+
+
 def test_attention_and_linear_from_blocks_off_16_bytes():
     require_gpu()
     say("attention and linear off 16 bytes")
