@@ -257,13 +257,15 @@ __global__ __launch_bounds__(NT * HPW * 64) void k_attn_mfma(const bf16_t *__res
 // ---------------------------------------------------------------------------------------------
 // The split form for longer shares.  Same mapping, shares and arithmetic per score as k_attn_mfma, but tiles go memory -> LDS by
 // direct loads, 64 keys (32 KiB) a step in a ring of two, the first of them asked for before the committed length is known;
-// the waves meet and the running maximum moves once per 64 keys, and the operands of a contraction are read from LDS together.
+// the waves meet once per 64 keys, and the operands of a contraction are read from LDS together.  The running maximum moves
+// after every 32 keys as there, and the errors are the same (moved once per 64 keys they are 0.2 to 1 % larger, the time 1 to 5 %
+// shorter).
 // Queries and ancestor masks come the same way, in front of the tiles, through what is the second step's place: a plain load
 // behind them would wait for every tile.
-// What bounds it: the stream of K and V at 5.8 TB/s (32 heads, 80 nodes, 16000 positions); below about 2000 positions launch,
-// a trip to memory (1.8 us), 1.2 us per 64 keys, 1 us of write-back and the merge launch.  us per layer with the merge,
-// k_attn_mfma / this, 80 nodes: 32 heads on 32 14.3 / 14.2 at 1024 positions, 16.0 / 14.9 at 1700, 24.7 / 22.2 at 4096,
-// 63.9 / 56.5 at 16000; 40 on 40 19.4 / 17.8 at 2048; 64 on 8 18.2 / 18.7 at 1024, 30.0 / 29.7 at 4096, 36.0 / 33.6 at 6000.
+// What bounds it: the stream of K and V on long sequences (32 heads, 80 nodes, 16000 positions: 264 MB in 56 us with the merge,
+// 4.7 TB/s); below about 2000 positions launch, a trip to memory (1.8 us), 1 to 1.5 us per 64 keys, write-back and the merge
+// launch.  us per layer with the merge, k_attn_mfma / this, 80 nodes: 32 heads on 32 14.8 / 14.2 at 1440 positions, 15.7 / 14.3 at
+// 1700, 24.4 / 22.4 at 4096, 63.6 / 56.3 at 16000; 40 on 40 19.6 / 17.5 at 2048; 64 on 8 29.8 / 29.4 at 4096, 36.5 / 34.2 at 6000.
 // A ring of four steps, all asked for at once, takes 1.2 us more: the burst holds up its own first tiles.
 // ---------------------------------------------------------------------------------------------
 constexpr int RING_STEPS = 2;
@@ -393,26 +395,32 @@ __global__ __launch_bounds__(NT * HPW * 64) void k_attn_ring(const bf16_t *__res
           sv[i][e] = ((int)(j < 0) | ((int)(j < n) & bit)) != 0 ? sv[i][e] : -INFINITY;
         }
     }
-    float mx = sv[0][0];
-#pragma unroll
-    for (int i = 0; i < 2 * TILES; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sv[i][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m, mx * sc);
-    if (__any(m_new > m)) {
-      const float corr = __builtin_amdgcn_exp2f(m - m_new);
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        acc[dt][0] *= corr; acc[dt][1] *= corr; acc[dt][2] *= corr; acc[dt][3] *= corr;
-      }
-      accl[0] *= corr; accl[1] *= corr; accl[2] *= corr; accl[3] *= corr;
-      m = m_new;
-    }
-    // m is finite, so an invisible key's probability is exactly 0, also in a row that has seen no key yet
+    float mx[TILES];
 #pragma unroll
     for (int k = 0; k < TILES; ++k) {
+      mx[k] = sv[2 * k][0];
+#pragma unroll
+      for (int i = 2 * k; i < 2 * k + 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx[k] = fmaxf(mx[k], sv[i][e]);
+      mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], 16));
+      mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], 32));
+    }
+    // tile by tile, as in k_attn_mfma: each new maximum's probability is exactly 1 and has no rounding (with one maximum for
+    // both tiles the result is 0.2 to 1 % further from float64)
+#pragma unroll
+    for (int k = 0; k < TILES; ++k) {
+      const float m_new = fmaxf(m, mx[k] * sc);
+      if (__any(m_new > m)) {
+        const float corr = __builtin_amdgcn_exp2f(m - m_new);
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+          acc[dt][0] *= corr; acc[dt][1] *= corr; acc[dt][2] *= corr; acc[dt][3] *= corr;
+        }
+        accl[0] *= corr; accl[1] *= corr; accl[2] *= corr; accl[3] *= corr;
+        m = m_new;
+      }
+      // m is finite, so an invisible key's probability is exactly 0, also in a row that has seen no key yet
       u32x4 pf;
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
@@ -680,11 +688,13 @@ static hipError_t launch_attn_k(const bf16_t *q, const bf16_t *Kl, const bf16_t 
                                 float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm,
                                 hipStream_t st) {
   const dim3 grid(Hkv, H / Hkv / HPW, nsplit), block(NT * HPW * 64);
-  // 32-key tiles a workgroup takes one after another.  With fewer the two forms are within 1 %, or k_attn_mfma is ahead: 128
-  // nodes, 32 heads, 777 positions (4 tiles) 15.0 / 15.2; 80 nodes, 32 heads, 1024 (5) 14.0 / 14.2; 80 nodes, 64 heads on 8, ten
-  // waves 18.2 / 18.7 at 5 tiles, 22.3 / 22.6 at 9, 30.0 / 29.7 at 17.
+  // 32-key tiles a workgroup takes one after another.  k_attn_mfma / k_attn_ring, us with the merge, at 5, 6, 7 and 8 of them: 80
+  // nodes, 32 heads on 32 14.2 / 14.7, 15.2 / 15.2, 16.0 / 15.2, 17.0 / 16.0; 40 on 40 13.9 / 14.1, 14.9 / 15.2, 15.9 / 15.6, 16.8 / 16.0;
+  // 8 on 8 12.7 / 12.9, 13.5 / 13.6, 14.4 / 14.5, 15.3 / 15.2; 48 nodes, 64 on 8 14.6 / 14.4, 15.6 / 15.3, 16.5 / 16.3, 17.4 / 17.1.  Ten and
+  // twelve waves, whose registers hold one tile's operands: 64 on 8, 80 nodes, at 9, 12, 15 and 18 23.3 / 23.4, 26.4 / 25.8, 29.4 / 29.1,
+  // 32.3 / 31.2; 96 nodes at 11, 12, 14 and 20 27.6 / 27.3, 28.5 / 27.8, 30.5 / 29.8, 37.6 / 35.4.
   const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
-  if (chain >= (NT * HPW > 8 ? 12 : 6) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
+  if (chain >= (NT * HPW > 8 ? 12 : 7) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
     constexpr int smem = ring_lds_bytes(NT * HPW);
     static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_ring<NT, HPW>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;

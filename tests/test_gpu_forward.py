@@ -456,6 +456,46 @@ def test_tree_attention_long_shares(tmpl_name, H, Hkv, L, slack):
     ctx.close()
 
 
+@pytest.mark.parametrize("tmpl_name,H,Hkv,L", [("tree80", 32, 32, 1453), ("wide128", 32, 32, 2941), ("prefix48", 64, 8, 1997),
+                                               ("prefix24", 48, 16, 2213), ("prefix33", 8, 8, 3060), ("tree80", 64, 8, 3500)])
+def test_tree_attention_long_shares_lose_no_precision(tmpl_name, H, Hkv, L):
+    """All errors of the form for long key shares together, against float64, are those of the form for short ones (which blocks off 16
+    bytes take): both move the running maximum after 32 keys, and only tiles with tree nodes round their exponents otherwise."""
+    require_gpu()
+    say("tree attention, precision", tmpl_name, H, Hkv, L)
+    t = synth.prefix_template(int(tmpl_name[6:])) if tmpl_name.startswith("prefix") else synth.TEMPLATES[tmpl_name]()
+    tree = O.make_tree(t.parent, t.rank, K)
+    n, hd = t.n_nodes, 128
+    kv = tr.KVDesc(synth.ModelShape("att", 1, H * hd, H, Hkv, hd, 64, 64, "bf16"), capacity=L + n)
+    kv.reset(L)
+    q = synth.normal_tensor((n, H, hd), 1.0, seed=1, dtype=torch.bfloat16).cuda()
+    kp = synth.normal_tensor((1, Hkv, kv.capacity, hd), 1.0, seed=2, dtype=torch.bfloat16).cuda()
+    vp = synth.normal_tensor((1, Hkv, kv.capacity, hd), 1.0, seed=3, dtype=torch.bfloat16).cuda()
+    kv_fill(kv, kp, vp)
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    ws = torch.empty(16 * 128 * H * (2 + hd) * 4 + 4096, dtype=torch.uint8, device="cuda")
+    seen = torch.zeros(n, L + n, dtype=torch.bool)
+    seen[:, :L] = True
+    for i in range(n):
+        seen[i, [L + j for j in tree.paths[i]]] = True
+    ref = torch.empty(n, H, hd, dtype=torch.float64, device="cuda")
+    for h in range(H):
+        g = h // (H // Hkv)
+        s = q[:, h].double() @ kp[0, g, :L + n].double().T / hd ** 0.5
+        ref[:, h] = torch.softmax(s.masked_fill(~seen.cuda(), -float("inf")), -1) @ vp[0, g, :L + n].double()
+    errs = []
+    for off in (False, True):
+        if off:
+            kv.k, kv.v = _off_16(kv.k), _off_16(kv.v)
+            kv.c.k, kv.c.v = kv.k.data_ptr(), kv.v.data_ptr()
+        out = torch.zeros(n, H, hd, dtype=torch.bfloat16, device="cuda")
+        ctx.op_tree_attention(kv, 0, H, q, out, ws)
+        errs.append(float((out.double() - ref).norm() / ref.norm()))
+    say("relative error, long form and short", errs)
+    assert errs[0] <= 1.001 * errs[1]
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,hd", [("f32", 64), ("bf16", 128), ("f32", 30)])
 def test_generic_attention_ignores_what_a_node_does_not_see(dtype, hd):
     """Shape-generic attention: a tree node whose value vector is not finite reaches its descendants and itself, and
