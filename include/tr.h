@@ -200,10 +200,10 @@ tr_status tr_pack_weight_rope(const void *d_src, void *d_dst, int32_t out_f, int
                               int32_t head_dim, void *stream);
 
 /*
- * Launch plan of one packed projection (diagnostic; touches no GPU).  For n_rows activation rows
+ * Launch plan of one packed projection by the decode projection kernel (diagnostic; touches no GPU), which is the one
+ * tr_op_linear takes for up to TR_MAX_NODES rows; tr_plan_step_projection says what a step launches.  For n_rows activation rows
  * (tree nodes, Section 2.2: all nodes of the draft tree go through the model in one forward) and a
- * weight of [out_f, in_f], reports what the decode projection kernel takes (tr_verify_forward sends matrices of very many
- * rows to the prompt-ingestion kernel instead, where that is faster): plan[0] = most 16-row weight
+ * weight of [out_f, in_f]: plan[0] = most 16-row weight
  * tiles one workgroup owns (gate/up tile pairs when fused_pair != 0, where out_f counts one of the two
  * matrices), plan[1] = workgroups per split of the input dimension, plan[2] = splits of the input
  * dimension (1 .. max_splits; always 1 when fused_pair).  plan is [host], 3 values.
@@ -212,6 +212,17 @@ tr_status tr_pack_weight_rope(const void *d_src, void *d_dst, int32_t out_f, int
  */
 tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t fused_pair,
                              int32_t max_splits, int32_t *plan);
+
+/*
+ * What tr_verify_forward launches for one packed projection of a step (diagnostic; touches no GPU): plan[0..2] as in
+ * tr_plan_projection, plan[3] = 0 for the decode projection kernel, 1 for the kernel that shares operands in LDS, which
+ * matrices of very many rows take (with weights and workspace on 16 bytes, else the decode kernel's plan holds).  out_f is the sum
+ * over the three matrices of the Q/K/V projection, one of the two of gate/up.  plan is [host], 4 values.
+ * TR_EINVAL for null plan, an unknown projection, or a shape the packed kernels do not take.
+ */
+typedef enum { TR_PROJ_QKV = 0, TR_PROJ_O_DOWN = 1, TR_PROJ_GATE_UP = 2, TR_PROJ_LM_HEAD = 3 } tr_projection;
+tr_status tr_plan_step_projection(int32_t projection, int32_t n_rows, int32_t in_f, int32_t out_f,
+                                  int32_t *plan);
 
 /*
  * Launch plan of the tree-attention kernel (Section 2.2 "Tree Attention") for n_heads query heads over
@@ -226,6 +237,17 @@ tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_
  */
 tr_status tr_plan_attention(int32_t n_heads, int32_t n_kv_heads, int32_t n_nodes, int32_t len_bound,
                             int32_t *plan);
+
+/*
+ * Which form of the tree-attention kernel these arguments of tr_plan_attention take with a tiled cache on 16 bytes
+ * (diagnostic; touches no GPU): few rows, one launch, or key shares that a workgroup takes in 32-key tiles (short ones) or in steps
+ * of 64 keys (long ones).  form is [host].  Errors as tr_plan_attention.
+ */
+typedef enum {
+  TR_ATT_FEW_ROWS = 0, TR_ATT_ONE_LAUNCH = 1, TR_ATT_SHORT_SHARES = 2, TR_ATT_LONG_SHARES = 3
+} tr_attention_form;
+tr_status tr_plan_attention_form(int32_t n_heads, int32_t n_kv_heads, int32_t n_nodes, int32_t len_bound,
+                                 int32_t *form);
 
 /* Bytes of [device] workspace tr_verify_forward / tr_prefill need for this model (256-aligned). */
 tr_status tr_workspace_bytes(const tr_ctx *ctx, const tr_model *model, size_t *bytes);

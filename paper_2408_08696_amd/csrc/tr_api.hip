@@ -214,6 +214,24 @@ tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_
   return TR_OK;
 }
 
+tr_status tr_plan_step_projection(int32_t projection, int32_t n_rows, int32_t in_f, int32_t out_f, int32_t *plan) {
+  if (plan == nullptr || projection < TR_PROJ_QKV || projection > TR_PROJ_LM_HEAD || !gemm_mfma_supported(n_rows, in_f, out_f))
+    return TR_EINVAL;
+  const bool pair = projection == TR_PROJ_GATE_UP;
+  const int32_t max_splits = projection == TR_PROJ_O_DOWN ? GEMM_MAX_SPLITS : 1;
+  Rows8Plan p;
+  if (projection != TR_PROJ_QKV && rows8_plan(n_rows, in_f, out_f / 16, pair, max_splits, &p)) {
+    plan[0] = p.out_tiles / (pair ? 2 : 1);
+    plan[1] = p.groups;
+    plan[2] = p.splits;
+    plan[3] = 1;
+    return TR_OK;
+  }
+  gemm_choose(n_rows, in_f, out_f / 16, pair, max_splits, &plan[0], &plan[1], &plan[2]);
+  plan[3] = 0;
+  return TR_OK;
+}
+
 tr_status tr_plan_attention(int32_t n_heads, int32_t n_kv_heads, int32_t n_nodes, int32_t len_bound, int32_t *plan) {
   if (plan == nullptr || n_kv_heads < 1 || n_heads < n_kv_heads || n_heads % n_kv_heads != 0 || n_nodes < 1 ||
       n_nodes > TR_MAX_NODES || len_bound < 1)
@@ -230,6 +248,16 @@ tr_status tr_plan_attention(int32_t n_heads, int32_t n_kv_heads, int32_t n_nodes
   }
   plan[0] = attn_heads_per_wg(n_heads, n_kv_heads, n_nodes);
   plan[1] = attn_choose_splits(n_heads / plan[0], len_bound);
+  return TR_OK;
+}
+
+tr_status tr_plan_attention_form(int32_t n_heads, int32_t n_kv_heads, int32_t n_nodes, int32_t len_bound, int32_t *form) {
+  int32_t plan[2];
+  const tr_status st = form == nullptr ? TR_EINVAL : tr_plan_attention(n_heads, n_kv_heads, n_nodes, len_bound, plan);
+  if (st != TR_OK) return st;
+  if (plan[1] < 0) *form = TR_ATT_FEW_ROWS;
+  else if (plan[1] == 0) *form = TR_ATT_ONE_LAUNCH;
+  else *form = attn_long_shares((n_nodes + 15) / 16 * plan[0], len_bound, plan[1]) ? TR_ATT_LONG_SHARES : TR_ATT_SHORT_SHARES;
   return TR_OK;
 }
 

@@ -682,19 +682,23 @@ int attn_choose_splits(int32_t head_groups, int32_t len_bound) {
   return s < 1 ? 1 : s;
 }
 
+// 32-key tiles a workgroup takes one after another.  k_attn_mfma / k_attn_ring, us with the merge, at 5, 6, 7 and 8 of them: 80
+// nodes, 32 heads on 32 14.2 / 14.7, 15.2 / 15.2, 16.0 / 15.2, 17.0 / 16.0; 40 on 40 13.9 / 14.1, 14.9 / 15.2, 15.9 / 15.6, 16.8 / 16.0;
+// 8 on 8 12.7 / 12.9, 13.5 / 13.6, 14.4 / 14.5, 15.3 / 15.2; 48 nodes, 64 on 8 14.6 / 14.4, 15.6 / 15.3, 16.5 / 16.3, 17.4 / 17.1.  Ten and
+// twelve waves, whose registers hold one tile's operands: 64 on 8, 80 nodes, at 9, 12, 15 and 18 23.3 / 23.4, 26.4 / 25.8, 29.4 / 29.1,
+// 32.3 / 31.2; 96 nodes at 11, 12, 14 and 20 27.6 / 27.3, 28.5 / 27.8, 30.5 / 29.8, 37.6 / 35.4.
+bool attn_long_shares(int32_t waves, int32_t len_bound, int32_t nsplit) {
+  const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
+  return chain >= (waves > 8 ? 12 : 7);
+}
+
 template <int NT, int HPW>
 static hipError_t launch_attn_k(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,
                                 int32_t n, const uint64_t *anc, const int32_t *d_len, int32_t len_bound, int32_t nsplit,
                                 float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm,
                                 hipStream_t st) {
   const dim3 grid(Hkv, H / Hkv / HPW, nsplit), block(NT * HPW * 64);
-  // 32-key tiles a workgroup takes one after another.  k_attn_mfma / k_attn_ring, us with the merge, at 5, 6, 7 and 8 of them: 80
-  // nodes, 32 heads on 32 14.2 / 14.7, 15.2 / 15.2, 16.0 / 15.2, 17.0 / 16.0; 40 on 40 13.9 / 14.1, 14.9 / 15.2, 15.9 / 15.6, 16.8 / 16.0;
-  // 8 on 8 12.7 / 12.9, 13.5 / 13.6, 14.4 / 14.5, 15.3 / 15.2; 48 nodes, 64 on 8 14.6 / 14.4, 15.6 / 15.3, 16.5 / 16.3, 17.4 / 17.1.  Ten and
-  // twelve waves, whose registers hold one tile's operands: 64 on 8, 80 nodes, at 9, 12, 15 and 18 23.3 / 23.4, 26.4 / 25.8, 29.4 / 29.1,
-  // 32.3 / 31.2; 96 nodes at 11, 12, 14 and 20 27.6 / 27.3, 28.5 / 27.8, 30.5 / 29.8, 37.6 / 35.4.
-  const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
-  if (chain >= (NT * HPW > 8 ? 12 : 7) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
+  if (attn_long_shares(NT * HPW, len_bound, nsplit) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
     constexpr int smem = ring_lds_bytes(NT * HPW);
     static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_ring<NT, HPW>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;

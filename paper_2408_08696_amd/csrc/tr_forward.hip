@@ -408,12 +408,18 @@ static bool packed_supported(const tr_model &m) {
          hk % 32 == 0 && m.vocab % 32 == 0;
 }
 
-// One projection of a tree step by the faster of its two kernels; fills g.splits.
+// One projection of a tree step by the faster of its two kernels; fills g.splits.  (tr_plan_step_projection says which.)
 static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipStream_t st) {
+  int32_t total = 0;
   bool on = starts_on_16(g.a_frag) && starts_on_16(g.w2); // what goes straight into LDS
-  for (int i = 0; i < g.n_seg; ++i) on = on && starts_on_16(g.seg[i].w);
+  for (int i = 0; i < g.n_seg; ++i) {
+    total += g.seg[i].out_tiles;
+    on = on && starts_on_16(g.seg[i].w);
+  }
+  const bool swiglu = g.mode == GEMM_SWIGLU, scaled = g.row_ssq != nullptr;
+  on = on && g.rope.q == nullptr && (scaled ? g.n_ssq <= 8 : !swiglu);
   Rows8Plan plan;
-  if (on && rows8_plan(g, max_splits, &plan)) {
+  if (on && rows8_plan(g.n, g.K, total, swiglu, swiglu || scaled ? 1 : max_splits, &plan)) {
     g.splits = plan.splits;
     return launch_gemm_rows8(g, plan, st, tm);
   }

@@ -526,28 +526,24 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
 // 41.2 / 40.2, 44.0 / 41.5, 44.5 / 42.1, 47.9 / 44.0.
 // So: at least 200 workgroups per round of 256, and with fewer than 65 rows only shares of k that are long.  Matrices with
 // K below 4096 were not measured and stay.
-bool rows8_plan(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan) {
-  if (g.n < 1 || g.n > NP || g.K < 4096 || g.K % 32 != 0 || (g.row_ssq != nullptr && g.n_ssq > 8)) return false;
-  if (g.mode == GEMM_SWIGLU ? g.row_ssq == nullptr : g.mode != GEMM_STORE || g.rope.q != nullptr) return false;
-  int32_t total = 0;
-  for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
-  const int unit = g.mode == GEMM_SWIGLU ? 2 : 1, NT = (g.n + 15) / 16, KT = g.K / 32;
+bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, Rows8Plan *plan) {
+  if (n < 1 || n > NP || K < 4096 || K % 32 != 0) return false;
+  const int unit = swiglu ? 2 : 1, NT = (n + 15) / 16, KT = K / 32;
   auto fills = [](int wgs) { return wgs >= (wgs + 255) / 256 * 200; };
-  const int g16 = (total + 16 / unit - 1) / (16 / unit), g8 = (total + 8 / unit - 1) / (8 / unit);
+  const int g16 = (total_tiles + 16 / unit - 1) / (16 / unit), g8 = (total_tiles + 8 / unit - 1) / (8 / unit);
   if (fills(g16) && (g16 <= 256 || NT >= 3)) {
     *plan = Rows8Plan{16, g16, 1};
     return true;
   }
-  const bool may_split = g.mode == GEMM_STORE && g.row_ssq == nullptr;
-  for (int sp = may_split ? max_splits : 1; sp >= 1; --sp) {
+  for (int sp = max_splits; sp >= 1; --sp) {
     const int per_k = (KT + sp - 1) / sp;
     if (per_k < 16 || (sp - 1) * per_k >= KT || !fills(g8 * sp)) continue;
     if (!(NT >= 5 || (NT == 3 && per_k >= 160) || (NT >= 2 && per_k >= 200))) continue;
     *plan = Rows8Plan{8, g8, sp};
     return true;
   }
-  const int g6 = (total + 2) / 3;
-  if (g.mode == GEMM_SWIGLU && NT >= 6 && KT % 2 == 0 && fills(g6)) {
+  const int g6 = (total_tiles + 2) / 3;
+  if (swiglu && NT >= 6 && KT % 2 == 0 && fills(g6)) {
     *plan = Rows8Plan{6, g6, 1};
     return true;
   }

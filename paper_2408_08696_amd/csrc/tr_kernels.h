@@ -128,11 +128,11 @@ bool gemm_wide_supported(int32_t n, int32_t K, int32_t O);
 hipError_t launch_gemm_wide(const GemmArgs &g, int32_t max_splits, int32_t *out_splits, hipStream_t st,
                             KernelTimer tm = KernelTimer{});
 // The same kernel for a tree step's rows (n <= TR_MAX_NODES), where it is the faster one: true and the plan, else
-// launch_gemm_mfma is.  Operands have to start on 16 bytes.
+// launch_gemm_mfma is.  Operands have to start on 16 bytes.  max_splits > 1: a plain store without an RMS scale.
 struct Rows8Plan {
   int32_t out_tiles, groups, splits; // out-tiles per workgroup, workgroups per K-split
 };
-bool rows8_plan(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan);
+bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, Rows8Plan *plan);
 hipError_t launch_gemm_rows8(const GemmArgs &g, const Rows8Plan &plan, hipStream_t st, KernelTimer tm = KernelTimer{});
 hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t K, int32_t rope_hd, hipStream_t st);
 
@@ -166,6 +166,8 @@ hipError_t launch_rows(const RowsArgs &p, int32_t dtype, hipStream_t st, KernelT
 // uses for H / that many head groups and this bound on committed length + nodes.
 int attn_heads_per_wg(int32_t H, int32_t Hkv, int32_t n);
 int attn_choose_splits(int32_t head_groups, int32_t len_bound);
+// whether workgroups of this many waves take their key shares in 64-key steps (k_attn_ring) or tile by tile (k_attn_mfma)
+bool attn_long_shares(int32_t waves, int32_t len_bound, int32_t nsplit);
 // true: one launch without key splits or merge pass (short sequences); then the two values above do not apply
 bool attn_one_launch(int32_t H, int32_t Hkv, int32_t len_bound);
 hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,

@@ -69,7 +69,9 @@ _SIGS = {
     "tr_build_tree": [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p],
     "tr_workspace_bytes": [C.c_void_p, C.POINTER(Model), C.POINTER(C.c_size_t)],
     "tr_plan_projection": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
+    "tr_plan_step_projection": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_attention": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
+    "tr_plan_attention_form": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_verify_forward": [C.c_void_p, C.POINTER(Model), C.POINTER(KV), C.c_void_p, C.c_void_p,
                           C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p],
     "tr_accept_and_update": [C.c_void_p, C.POINTER(KV), C.c_void_p, C.c_void_p, C.c_void_p,
@@ -243,10 +245,29 @@ class Context:
 
 
 def plan_projection(n_rows: int, in_f: int, out_f: int, fused_pair: bool = False, max_splits: int = 4):
-    """(weight tiles per workgroup, workgroups per split, splits) of one packed projection launch."""
+    """(weight tiles per workgroup, workgroups per split, splits) of one packed projection by the decode kernel."""
     plan = (C.c_int32 * 3)()
     _check(lib().tr_plan_projection(n_rows, in_f, out_f, int(fused_pair), max_splits, plan), "tr_plan_projection")
     return tuple(plan)
+
+
+PROJECTIONS = ("qkv", "o_down", "gate_up", "lm_head")
+ATTENTION_FORMS = ("few_rows", "one_launch", "short_shares", "long_shares")
+
+
+def plan_step_projection(projection: str, n_rows: int, in_f: int, out_f: int):
+    """(weight tiles per workgroup, workgroups per split, splits, kernel) of what a step launches; kernel 0 is the decode
+    projection kernel, 1 the one that shares operands in LDS."""
+    plan = (C.c_int32 * 4)()
+    _check(lib().tr_plan_step_projection(PROJECTIONS.index(projection), n_rows, in_f, out_f, plan), "tr_plan_step_projection")
+    return tuple(plan)
+
+
+def plan_attention_form(n_heads: int, n_kv_heads: int, n_nodes: int, len_bound: int) -> str:
+    """Which of ATTENTION_FORMS one tree-attention launch takes."""
+    form = C.c_int32()
+    _check(lib().tr_plan_attention_form(n_heads, n_kv_heads, n_nodes, len_bound, C.byref(form)), "tr_plan_attention_form")
+    return ATTENTION_FORMS[form.value]
 
 
 def plan_attention(n_heads: int, n_kv_heads: int, n_nodes: int, len_bound: int):

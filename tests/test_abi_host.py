@@ -132,6 +132,45 @@ def test_projection_plans_of_the_7b_step_fill_the_chip(lib):
         assert groups * splits >= 230, (in_f, out_f, p, groups, splits)
 
 
+def test_step_projection_plan_rejects_bad_shapes(lib):
+    plan = (C.c_int32 * 4)()
+    f = lib.tr_plan_step_projection
+    assert f(1, 80, 4096, 4096, None) == tr.TR_EINVAL
+    assert f(-1, 80, 4096, 4096, plan) == tr.TR_EINVAL and f(4, 80, 4096, 4096, plan) == tr.TR_EINVAL
+    assert f(1, 0, 4096, 4096, plan) == tr.TR_EINVAL and f(1, 129, 4096, 4096, plan) == tr.TR_EINVAL
+    assert f(1, 80, 4100, 4096, plan) == tr.TR_EINVAL and f(1, 80, 4096, 4100, plan) == tr.TR_EINVAL
+
+
+@pytest.mark.parametrize("projection", tr.PROJECTIONS)
+def test_step_projection_plans_cover_every_tile_and_k_step_once(lib, projection):
+    for n in (1, 16, 17, 33, 49, 65, 80, 81, 97, 128):
+        for in_f in (64, 4096, 4160, 5120, 8192, 11008, 16384, 28672):
+            for out_f in (32, 4096, 6432, 8192, 9632, 11008, 12832, 25632, 28672, 32000, 51232, 64000, 80000, 128256):
+                tiles, pair = out_f // 16, projection == "gate_up"
+                p, groups, splits, kernel = tr.plan_step_projection(projection, n, in_f, out_f)
+                ms = 4 if projection == "o_down" else 1
+                assert 1 <= splits <= ms and 1 <= groups <= tiles
+                assert groups * p >= tiles and -(-tiles // groups) <= p       # one owner a tile, no share beyond the variant
+                if kernel == 0:
+                    assert (p, groups, splits) == tr.plan_projection(n, in_f, out_f, pair, ms)
+                    continue
+                assert projection != "qkv" and in_f >= 4096                   # the rest was not measured
+                assert p * (2 if pair else 1) in ((6, 8, 16) if pair else (8, 16))
+                per_k = -(-(in_f // 32) // splits)
+                assert (splits - 1) * per_k < in_f // 32 and per_k >= 16      # no share of k is empty
+                assert p * 2 != 6 or not pair or (in_f // 32) % 2 == 0        # its two groups of waves take the same k-steps
+                wgs = groups * splits
+                assert wgs >= -(-wgs // 256) * 200
+
+
+def test_step_projections_of_the_7b_step_fill_the_chip(lib):
+    # what an 80-node step of the 7B shape launches: the LM head shares operands in LDS
+    for projection, in_f, out_f, kernel in (("qkv", 4096, 12288, 0), ("o_down", 4096, 4096, 0), ("gate_up", 4096, 11008, 0),
+                                            ("o_down", 11008, 4096, 0), ("lm_head", 4096, 32000, 1)):
+        p, groups, splits, k = tr.plan_step_projection(projection, 80, in_f, out_f)
+        assert groups * splits >= 230 and k == kernel, (projection, p, groups, splits, k)
+
+
 def test_attention_plan(lib):
     plan = (C.c_int32 * 2)()
     assert lib.tr_plan_attention(32, 32, 80, 600, None) == tr.TR_EINVAL
@@ -169,6 +208,27 @@ def test_attention_plan(lib):
     assert tr.plan_attention(64, 8, 15, 16015) == (8, -32)                # all eight heads of a group, 32 key shares
     assert tr.plan_attention(32, 32, 1, 2049) == (1, -8)
     assert tr.plan_attention(16, 2, 1, 100) == (8, -1)                    # one share: no merge pass
+
+
+@pytest.mark.parametrize("H,Hkv,n,short,long_", [
+    # lengths (committed + nodes) whose shares are 32-key tiles one after another, and steps of 64 keys: seven tiles a share, ...
+    (32, 32, 80, (840, 1104, 1536), (1537, 16080)), (32, 32, 128, (905, 1536), (1537, 2048)), (8, 8, 80, (3072,), (3073,)),
+    (40, 40, 80, (1152,), (1153, 2128)), (64, 8, 48, (1536,), (1537, 4096)), (256, 256, 66, (), (840, 1500)),
+    # ... twelve for ten and twelve waves
+    (64, 8, 80, (2816,), (2817, 4176)), (64, 8, 96, (2816,), (2817,)), (32, 8, 80, (5632,), (5633,))])
+def test_long_share_attention_rule(lib, H, Hkv, n, short, long_):
+    for L in short:
+        assert tr.plan_attention_form(H, Hkv, n, L) == "short_shares", L
+    for L in long_:
+        assert tr.plan_attention_form(H, Hkv, n, L) == "long_shares", L
+
+
+def test_attention_forms(lib):
+    form = C.c_int32()
+    assert lib.tr_plan_attention_form(32, 32, 80, 600, None) == tr.TR_EINVAL
+    assert lib.tr_plan_attention_form(32, 5, 80, 600, C.byref(form)) == tr.TR_EINVAL
+    assert tr.plan_attention_form(32, 32, 80, 600) == "one_launch"
+    assert tr.plan_attention_form(64, 8, 15, 16015) == "few_rows" and tr.plan_attention_form(256, 256, 1, 900) == "few_rows"
 
 
 @pytest.mark.parametrize("H,Hkv,n,few,split", [
