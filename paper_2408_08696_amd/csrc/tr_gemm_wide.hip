@@ -517,13 +517,18 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
 //   70B gate/up, 224 x 16 out-tiles   160 / 144   162 / 144   165 / 140   200 / 142   233 / 150
 //   70B LM head, 501 x 16             323 / 348   388 / 353   395 / 347   465 / 338   513 / 346
 //   70B down, 64 x 8 in four shares    70 /  73    75 /  72    78 /  75    93 /  80   108 /  84
-//   70B o, the same                    23 /  27    25 /  27    29 /  28    30 /  30    35 /  32
 //   13B gate/up, 216 x 8               45 /  46    53 /  48    55 /  52    68 /  54    79 /  59
 //   13B LM head, 250 x 8               49 /  53    57 /  56    59 /  57    76 /  59    88 /  64
 //   7B LM head, 250 x 8                47 /  45    49 /  50    51 /  48    63 /  49    73 /  52
 // where the chip is not filled: 7B gate/up, 172 x 8   30 / 37   31 / 36   35 / 40   39 / 43   46 / 46; it takes 230 x 6 with two
 // groups of waves on even and odd k-tiles (a wave's 2 x 2 tiles of 8 x 6 leave four waves idle): 81, 97, 112, 128 rows
 // 41.2 / 40.2, 44.0 / 41.5, 44.5 / 42.1, 47.9 / 44.0.
+// Shares of k (o and down, in four) from 128 k-steps on.  A wave of the decode kernel has an eighth of a share in one chain, so with
+// shorter ones its sums were the better (relative error against float64, decode kernel / this, 80 rows: 4096 -> 6656 0.99e-7 / 1.28e-7,
+// 6656 -> 6656 1.20e-7 / 1.30e-7, 16384 -> 6656 1.85e-7 / 1.37e-7), and with 64 groups this kernel is slower there: 6656 -> 8192, 80 /
+// 96 / 128 rows 23.6 / 27.6, 25.7 / 28.5, 29.7 / 30.8 us, 10240 -> 8192 33.6 / 35.6, 36.7 / 38.0, 42.2 / 41.1.  From 65 rows on, 50 to 64
+// groups, the time is 0.94 to 0.98 of the decode kernel's at 80 rows, 0.82 to 0.93 at 96, 0.75 to 0.88 beyond; from 170 k-steps on it is
+// 0.84 to 1.00 at 17 to 64 rows too (22016 -> 8192, 16 / 32 / 48 / 64 rows 0.96, 0.84, 0.95, 0.95; 128 k-steps 1.07, 0.99, 1.01, 1.03).
 // So: at least 200 workgroups per round of 256, and with fewer than 65 rows only shares of k that are long.  Matrices with
 // K below 4096 were not measured and stay.
 bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, Rows8Plan *plan) {
@@ -537,8 +542,12 @@ bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t 
   }
   for (int sp = max_splits; sp >= 1; --sp) {
     const int per_k = (KT + sp - 1) / sp;
-    if (per_k < 16 || (sp - 1) * per_k >= KT || !fills(g8 * sp)) continue;
-    if (!(NT >= 5 || (NT == 3 && per_k >= 160) || (NT >= 2 && per_k >= 200))) continue;
+    if ((sp - 1) * per_k >= KT || !fills(g8 * sp)) continue;
+    if (sp > 1) {
+      if (per_k < 128 || !(NT >= 5 || (NT >= 2 && per_k >= 170))) continue;
+    } else if (!(NT >= 5 || (NT == 3 && per_k >= 160) || (NT >= 2 && per_k >= 200))) {
+      continue;
+    }
     *plan = Rows8Plan{8, g8, sp};
     return true;
   }

@@ -157,10 +157,24 @@ def test_step_projection_plans_cover_every_tile_and_k_step_once(lib, projection)
                 assert projection != "qkv" and in_f >= 4096                   # the rest was not measured
                 assert p * (2 if pair else 1) in ((6, 8, 16) if pair else (8, 16))
                 per_k = -(-(in_f // 32) // splits)
-                assert (splits - 1) * per_k < in_f // 32 and per_k >= 16      # no share of k is empty
+                assert (splits - 1) * per_k < in_f // 32                      # no share of k is empty
+                assert splits == 1 or per_k >= 128                            # shorter chains in the decode kernel, see below
                 assert p * 2 != 6 or not pair or (in_f // 32) % 2 == 0        # its two groups of waves take the same k-steps
                 wgs = groups * splits
                 assert wgs >= -(-wgs // 256) * 200
+
+
+@pytest.mark.parametrize("in_f,out_f,shared,decode", [
+    # rows for which o and down share operands in LDS, in four shares of k, and for which they do not: never where a wave of the decode
+    # kernel has shorter chains of sums (an eighth of a share, against 16 k-steps), nor where it is the faster one
+    (4096, 6656, (), (1, 16, 80, 128)), (6656, 6656, (), (80, 96, 128)), (8192, 8192, (), (1, 48, 80, 128)),
+    (11008, 8192, (), (80, 128)), (16256, 8192, (), (80, 128)), (16384, 8192, (65, 80, 128), (1, 16, 17, 48, 64)),
+    (22016, 8192, (17, 48, 64, 65, 128), (1, 16)), (28672, 8192, (17, 48, 80, 128), (1, 16)), (28672, 6208, (), (80, 128))])
+def test_projections_in_shares_of_k(lib, in_f, out_f, shared, decode):
+    for n in shared:
+        assert tr.plan_step_projection("o_down", n, in_f, out_f)[2:] == (4, 1), n
+    for n in decode:
+        assert tr.plan_step_projection("o_down", n, in_f, out_f)[3] == 0, n
 
 
 def test_step_projections_of_the_7b_step_fill_the_chip(lib):
