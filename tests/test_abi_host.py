@@ -164,6 +164,30 @@ def test_step_projection_plans_cover_every_tile_and_k_step_once(lib, projection)
                 assert wgs >= -(-wgs // 256) * 200
 
 
+@pytest.mark.parametrize("projection,in_f,out_f,out_tiles,shared,decode", [
+    # rows for which a matrix shares operands in LDS, 16, 8 or 6 out-tiles a workgroup, and for which the decode kernel is as fast or
+    # faster: one round of 16 out-tiles, few groups of them and many, ...
+    ("gate_up", 8192, 28672, 16, (17, 32, 33, 64, 128), (1, 15, 16)), ("gate_up", 8192, 32768, 16, (33, 48, 80, 128), (1, 16, 17, 32)),
+    ("gate_up", 4096, 28672, 16, (33, 49, 65, 128), (1, 16, 32)), ("lm_head", 4096, 64000, 16, (33, 64, 128), (1, 16, 17, 32)),
+    ("lm_head", 5120, 51200, 16, (17, 32, 48, 128), (1, 16)), ("lm_head", 8192, 64000, 16, (33, 128), (1, 16, 32)),
+    # ... several rounds, ...
+    ("lm_head", 8192, 128256, 16, (33, 49, 80, 128), (1, 16, 32)), ("lm_head", 4096, 128256, 16, (49, 64, 80, 128), (1, 16, 32, 48)),
+    # ... 8 out-tiles, ...
+    ("lm_head", 4096, 32000, 8, (65, 80, 128), (1, 16, 33, 48, 49, 64)), ("lm_head", 5120, 32000, 8, (33, 48, 65, 128), (1, 16, 32, 49, 64)),
+    ("gate_up", 5120, 13824, 8, (33, 48, 65, 80, 128), (1, 16, 17, 32, 49, 64)), ("gate_up", 8192, 16384, 8, (48, 80, 128), (1, 32, 64)),
+    ("gate_up", 4096, 16384, 8, (65, 128), (1, 48, 64)), ("lm_head", 8192, 80000, 8, (48, 65, 128), (1, 16, 32, 64)),
+    # ... 6, and matrices that do not fill the chip, or of short rows
+    ("gate_up", 4096, 11008, 6, (97, 112, 128), (1, 80, 81, 96)), ("gate_up", 8192, 22016, 6, (97, 128), (64, 80, 96)),
+    ("gate_up", 4128, 11008, 6, (), (97, 128)), ("lm_head", 4096, 25440, 8, (), (80, 128)), ("lm_head", 4064, 32000, 8, (), (80, 128)),
+    ("qkv", 8192, 51200, 16, (), (1, 80, 128))])
+def test_projections_that_share_operands(lib, projection, in_f, out_f, out_tiles, shared, decode):
+    for n in shared:
+        p, _, splits, kernel = tr.plan_step_projection(projection, n, in_f, out_f)
+        assert (p * (2 if projection == "gate_up" else 1), splits, kernel) == (out_tiles, 1, 1), n
+    for n in decode:
+        assert tr.plan_step_projection(projection, n, in_f, out_f)[3] == 0, n
+
+
 @pytest.mark.parametrize("in_f,out_f,shared,decode", [
     # rows for which o and down share operands in LDS, in four shares of k, and for which they do not: never where a wave of the decode
     # kernel has shorter chains of sums (an eighth of a share, against 16 k-steps), nor where it is the faster one
