@@ -432,14 +432,11 @@ static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hip
   if (!once) return hipErrorInvalidValue;
   return launch(kernel, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
 }
-template <int RP2, int NP2, int WR, int WC, int D, int CHAIN = 0>
+template <int RP2, int NP2, int WR, int WC, int D>
 static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
-  if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
-  if constexpr (CHAIN == 0) { // a step's Q/K/V projection is the decode kernel's
-    if (g.rope.q != nullptr) return launch_ks<GEMM_ROPE, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
-  }
-  if (g.row_ssq != nullptr) return launch_ks<GEMM_STORE, true, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
-  return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D, CHAIN>(g, row_tiles, grid, st, tm);
+  if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
+  if (g.rope.q != nullptr) return launch_ks<GEMM_ROPE, true, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
+  return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
 }
 
 // The workgroup shapes: row tiles x out-tiles, and the measured us of one k-step when every compute unit has a
@@ -451,8 +448,8 @@ struct WideShape {
 static constexpr WideShape WIDE_SHAPES[5] = {{8, 8, 0.27}, {8, 12, 0.42}, {16, 8, 0.45}, {16, 12, 0.585}, {16, 16, 0.70}};
 
 // Chooses the workgroup shape and the K-splits, fills the tile assignment and launches.  g.n is the total row count
-// (<= WIDE_MAX_ROWS); a_frag / h_frag use ceil(n / 16) row tiles; the RMS scale takes at most 8 partial sums per
-// row and SwiGLU needs it.  max_splits > 1 (plain store without scale only): y[s] = y + s * split_stride receives the
+// (<= WIDE_MAX_ROWS); a_frag / h_frag use ceil(n / 16) row tiles; SwiGLU and Q/K/V come with the RMS scale of at most 8 partial
+// sums per row, a plain store without.  max_splits > 1 (plain store only): y[s] = y + s * split_stride receives the
 // partial sum of k-range s, and *out_splits how many the launch used.
 hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *out_splits, hipStream_t st, KernelTimer tm) {
   GemmArgs g = args;
@@ -461,9 +458,9 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
   int32_t total = 0;
   for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
-  if (g.mode == GEMM_SWIGLU && g.row_ssq == nullptr) return hipErrorInvalidValue;
-  if (g.rope.q != nullptr && (!g.rope.tiled || g.rope.hd != 128 || g.row_ssq == nullptr || g.mode != GEMM_STORE)) return hipErrorInvalidValue;
-  const bool may_split = g.mode == GEMM_STORE && g.rope.q == nullptr && g.row_ssq == nullptr && max_splits > 1;
+  if ((g.mode == GEMM_SWIGLU || g.rope.q != nullptr) != (g.row_ssq != nullptr)) return hipErrorInvalidValue;
+  if (g.rope.q != nullptr && (!g.rope.tiled || g.rope.hd != 128 || g.mode != GEMM_STORE)) return hipErrorInvalidValue;
+  const bool may_split = g.row_ssq == nullptr && max_splits > 1;
   const int row_tiles = (g.n + 15) / 16;
   const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles
   auto groups_of = [&](int nw) { return (total + nw / unit - 1) / (nw / unit); };
@@ -542,7 +539,7 @@ bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t 
   const int unit = swiglu ? 2 : 1, NT = (n + 15) / 16, KT = K / 32;
   auto fills = [](int wgs) { return wgs >= (wgs + 255) / 256 * 200; };
   const int g16 = (total_tiles + 16 / unit - 1) / (16 / unit), g8 = (total_tiles + 8 / unit - 1) / (8 / unit);
-  if (fills(g16) && (NT >= 4 || (NT == 3 && (g16 <= 256 || K >= 5120)) || (NT == 2 && g16 <= 230 && K >= 5120))) {
+  if (max_splits == 1 && fills(g16) && (NT >= 4 || (NT == 3 && (g16 <= 256 || K >= 5120)) || (NT == 2 && g16 <= 230 && K >= 5120))) {
     *plan = Rows8Plan{16, g16, 1};
     return true;
   }
@@ -576,10 +573,18 @@ hipError_t launch_gemm_rows8(const GemmArgs &args, const Rows8Plan &plan, hipStr
   g.splits = plan.splits;
   const int row_tiles = (g.n + 15) / 16;
   const unsigned grid = (unsigned)(((g.groups + 7) / 8) * 8 * g.splits);
-  // chains of 16 k-steps: a sum goes through no more additions than in the decode kernel, whose eight waves share the k range
-  if (plan.out_tiles == 6) return launch_ks<GEMM_SWIGLU, true, 1, 3, 4, 1, 5, 16, 2>(g, row_tiles, grid, st, tm);
-  if (plan.out_tiles == 8) return launch_shape<1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
-  return launch_shape<2, 2, 2, 4, 6, 16>(g, row_tiles, grid, st, tm);
+  const bool swiglu = g.mode == GEMM_SWIGLU, scaled = g.row_ssq != nullptr;
+  if (g.n < 1 || g.n > NP || (scaled ? g.n_ssq > 8 || g.splits != 1 : swiglu)) return hipErrorInvalidValue;
+  // Chains of 16 k-steps: as long as a wave's in the decode kernel at K = 4096 in eight waves, or in shares of 128, and shorter than
+  // all others there.  Its MFMA adds 32 products, these 16 twice, and the errors are the same: relative to float64 1.31e-7 with both for
+  // 4096 -> 32064, 96 and 128 rows; where the decode kernel has four waves (80 rows) 1.81e-7 / 1.32e-7.
+  if (plan.out_tiles == 6 && swiglu) return launch_ks<GEMM_SWIGLU, true, 1, 3, 4, 1, 5, 16, 2>(g, row_tiles, grid, st, tm);
+  if (plan.out_tiles == 8 && swiglu) return launch_ks<GEMM_SWIGLU, true, 1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
+  if (plan.out_tiles == 8 && scaled) return launch_ks<GEMM_STORE, true, 1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
+  if (plan.out_tiles == 8) return launch_ks<GEMM_STORE, false, 1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
+  if (plan.out_tiles == 16 && swiglu) return launch_ks<GEMM_SWIGLU, true, 2, 2, 2, 4, 6, 16>(g, row_tiles, grid, st, tm);
+  if (plan.out_tiles == 16 && scaled) return launch_ks<GEMM_STORE, true, 2, 2, 2, 4, 6, 16>(g, row_tiles, grid, st, tm);
+  return hipErrorInvalidValue;
 }
 
 } // namespace tr
