@@ -113,7 +113,7 @@ __device__ inline T *hold(T *p) {
 
 template <int NT, int NW, int MODE, int GW, bool SCALED>
 __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
-  // GEMM_ROPE is GEMM_STORE with the fused Q/K/V epilogue: its rotary factors and the committed length are loaded ahead of
+  // GEMM_ROPE is GEMM_STORE with the fused Q/K/V epilogue: its rotary factors and the committed length are asked for behind
   // the first weight tiles, so that the tail has no load left (it took three dependent round trips there)
   // SWIGLU: NW = 2P; weight tiles 0..P-1 come from the gate matrix, P..2P-1 from the up matrix
   constexpr int P = MODE == GEMM_SWIGLU ? NW / 2 : NW; // distinct out-tiles per workgroup

@@ -1,4 +1,5 @@
-// Projection GEMM for prompt ingestion: y[n, O] = a[n, K] * w[O, K]^T with n up to WIDE_MAX_ROWS rows at once.
+// Projection GEMM whose waves share both operands in LDS: y[n, O] = a[n, K] * w[O, K]^T with n up to WIDE_MAX_ROWS rows at
+// once.  All projections of prompt ingestion above TR_MAX_NODES rows, and a tree step's matrices of many out-tiles (rows8_plan).
 //
 // A workgroup of eight waves owns NW consecutive out-tiles and RB row tiles (16 x 16 tiles = 256 x 256 outputs in the
 // largest shape); its waves form a WR x WC grid over that block, so that a tile loaded once serves WC or WR of them.
@@ -6,7 +7,8 @@
 // tile is one contiguous KiB on both sides) into a ring of D k-steps, D - 1 of them under way while one is multiplied.
 // A wave reads the operands of k-step s + 1 between the MFMAs of k-step s and meets the others once per k-step; the
 // MFMAs that follow the barrier have their operands in registers already.  A wave ends with the sums over its k range
-// for its outputs: no cross-wave reduction, the epilogue runs from registers.  Projections with few out-tiles (o and
+// for its outputs, and the epilogue runs from registers: no cross-wave reduction, but for the form of two groups of waves
+// (KG = 2), whose sums meet in LDS once.  Projections with few out-tiles (o and
 // down) are split over k so that the launch still fills the chip; the residual kernel adds the partial sums.  Row
 // blocks of one out-tile group have linear ids congruent modulo 8, land on one XCD and share its weights in that L2.
 //
