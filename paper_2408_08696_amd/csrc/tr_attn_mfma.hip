@@ -21,7 +21,8 @@
 // p - L of the node's ancestor mask is set.  Invisible keys get probability exactly 0.
 // With more than one split, split s owns tiles s, s + nsplit, ...; each writes (max, sum, normalised O in
 // half precision) per node and k_attn_merge combines them in split order.  K/V are read with streaming
-// loads: they are used once per call and would otherwise push the activations out of L2.
+// loads: they are used once per call and would otherwise push the activations out of L2 (the direct loads of
+// k_attn_ring do without: steps of the 13B and 70B shapes were the same with the hint, within 1 % of noise).
 #include <type_traits>
 
 #include "tr_kernels.h"
@@ -261,10 +262,10 @@ __global__ __launch_bounds__(NT * HPW * 64) void k_attn_mfma(const bf16_t *__res
 // shorter).
 // Queries and ancestor masks come the same way, in front of the tiles, through what is the second step's place: a plain load
 // behind them would wait for every tile.
-// What bounds it: the stream of K and V on long sequences (32 heads, 80 nodes, 16000 positions: 264 MB in 56 us with the merge,
-// 4.7 TB/s); below about 2000 positions launch, a trip to memory (1.8 us), 1 to 1.5 us per 64 keys, write-back and the merge
-// launch.  us per layer with the merge, k_attn_mfma / this, 80 nodes: 32 heads on 32 14.8 / 14.2 at 1440 positions, 15.7 / 14.3 at
-// 1700, 24.4 / 22.4 at 4096, 63.6 / 56.3 at 16000; 40 on 40 19.6 / 17.5 at 2048; 64 on 8 29.8 / 29.4 at 4096, 36.5 / 34.2 at 6000.
+// What bounds it: the stream of K and V on long sequences (32 heads, 80 nodes, 16000 positions: 264 MB in 58 us, 4.5 TB/s); below
+// about 2000 positions launch, a trip to memory (1.8 us), 1 to 1.5 us per 64 keys and write-back.  us without the merge, k_attn_mfma /
+// this, 80 nodes: 32 heads on 32 19.8 / 18.9 at 4013 positions, 34.2 / 31.8 at 8192, 60.8 / 58.0 at 16000; 40 on 40 16.6 / 16.2 at 2221,
+// 25.1 / 24.0 at 4096; 64 on 8 25.3 / 24.3 at 4096, 73.2 / 67.6 at 16000; 48 nodes, 32 on 32 21.1 / 18.4 at 4045.
 // A ring of four steps, all asked for at once, takes 1.2 us more: the burst holds up its own first tiles.
 // ---------------------------------------------------------------------------------------------
 constexpr int RING_STEPS = 2;
@@ -681,14 +682,15 @@ int attn_choose_splits(int32_t head_groups, int32_t len_bound) {
   return s < 1 ? 1 : s;
 }
 
-// 32-key tiles a workgroup takes one after another.  k_attn_mfma / k_attn_ring, us with the merge, at 5, 6, 7 and 8 of them: 80
-// nodes, 32 heads on 32 14.2 / 14.7, 15.2 / 15.2, 16.0 / 15.2, 17.0 / 16.0; 40 on 40 13.9 / 14.1, 14.9 / 15.2, 15.9 / 15.6, 16.8 / 16.0;
-// 8 on 8 12.7 / 12.9, 13.5 / 13.6, 14.4 / 14.5, 15.3 / 15.2; 48 nodes, 64 on 8 14.6 / 14.4, 15.6 / 15.3, 16.5 / 16.3, 17.4 / 17.1.  Ten and
-// twelve waves, whose registers hold one tile's operands: 64 on 8, 80 nodes, at 9, 12, 15 and 18 23.3 / 23.4, 26.4 / 25.8, 29.4 / 29.1,
-// 32.3 / 31.2; 96 nodes at 11, 12, 14 and 20 27.6 / 27.3, 28.5 / 27.8, 30.5 / 29.8, 37.6 / 35.4.
+// 32-key tiles a workgroup takes one after another.  Time of k_attn_ring over that of k_attn_mfma, one launch behind 128 MiB of other
+// traffic and a new query block, as in a step, at 8, 10, 12, 14 and 16 tiles: 80 nodes, 32 heads on 32 1.00, 1.00, 0.96, 0.97, 0.95; 40 on 40
+// 1.03, 1.00, 0.98, 0.97, 0.96; 8 on 8 0.99, 0.98, 0.97, 0.97, 0.95; 40 on 8 0.96, 0.95, 0.95, 0.95, 0.94; 48 nodes, 32 on 32 0.96, 0.92, 0.90, 0.89,
+// 0.87; 64 nodes, 64 on 8 1.00, 0.99, 0.99, 0.99, 0.99; ten waves (80 nodes, 64 on 8) 0.98, 0.98, 0.97, 0.97, 0.98; eight waves (128 nodes) 32 on
+// 32 1.02, 1.00, 1.01, 0.99, 0.99; 40 on 40 1.02, 1.03, 1.01, 1.01, 1.00; 64 on 8 0.98, 0.96, 0.97, 0.97, 0.97.  At five and six it is up to 1.15
+// (launched back to back, with the queries in L2 already, it gains from seven on).
 bool attn_long_shares(int32_t waves, int32_t len_bound, int32_t nsplit) {
   const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
-  return chain >= (waves > 8 ? 12 : 7);
+  return chain >= (waves == 8 ? 16 : 12);
 }
 
 template <int NT, int HPW>

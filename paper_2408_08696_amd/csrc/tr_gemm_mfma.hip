@@ -129,7 +129,8 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   // so a workgroup may straddle two matrices.
   // All arguments are needed at once and come in one batch of scalar loads.  A loop over the matrices per tile, the scale's
   // loads and the rotary factors in front of the first weight tile took 0.9 to 1.9 us to get there, this takes 0.3 to 0.5:
-  // step of the 7B shape with 1 / 80 / 128 nodes 2868 / 3772 / 4835 -> 2820 / 3745 / 4722 us.
+  // step of the 7B shape with 1 / 128 nodes 3003 / 4949 -> 2955 / 4849 us (runs of one side differ by 0.8 / 0.4 %); with 80 nodes
+  // and the step of the 13B shape the difference is within that of the runs.
   const int bx = blockIdx.x;
   const int tile0 = bx * g.part_q + (bx < g.part_rem ? bx : g.part_rem);
   const int n_valid = g.part_q + (bx < g.part_rem ? 1 : 0);
