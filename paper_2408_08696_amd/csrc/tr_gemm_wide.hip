@@ -512,29 +512,30 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
 // Every workgroup loads the activations of its k range, so what the compute units pull is (out-tiles + row tiles) per out-tile;
 // the decode kernel, whose waves each hold all accumulators of the workgroup, ends at 6 or 8 out-tiles (6 from 81 rows on),
 // this one shares them out over its waves.  It needs the chip full of workgroups, since each pulls no faster for being
-// alone: 200 workgroups per round of 256 at least.  us per launch, decode kernel / this, 48 / 80 / 96 / 128 rows:
-//   70B gate/up, 224 x 16 out-tiles   162 / 144   165 / 140   200 / 142   233 / 150
-//   70B LM head, 501 x 16             388 / 353   395 / 347   465 / 338   513 / 346
-//   70B down, 64 x 8 in four shares    75 /  72    78 /  75    93 /  80   108 /  84
-//   13B gate/up, 216 x 8               53 /  48    55 /  52    68 /  54    79 /  59
-//   13B LM head, 250 x 8               57 /  56    59 /  57    76 /  59    88 /  64
-//   7B LM head, 250 x 8                49 /  50    51 /  48    63 /  49    73 /  52
-// Which rows, from this kernel's time over the decode kernel's at K = 4096, 5120, 6656 and 8192, plain and gate/up, one launch alone:
-//   16 out-tiles, one round   1-16 rows 0.83-1.17; 17-32 rows: 200 to 230 groups, K >= 5120 0.83-0.98, the others 0.70-1.06;
-//                             33-48 0.71-1.01; 49-64 0.76-1.02; 80 0.72-0.98; 96 and more 0.57-0.85
-//     two rounds and more     17-32 0.93-1.12; 33-48: K >= 5120 0.85-1.02, K = 4096 0.94-1.07; 49-64 0.85-1.02; 80 0.81-0.97;
-//                             96 and more 0.69-0.87
-//   8 out-tiles, whole k      1-32 0.83-1.21; 33-48: K >= 5120 0.83-1.01, K = 4096 0.81-1.11; 49-64 0.93-1.09 (the decode kernel's own
-//                             form of eight out-tiles is for four and five row tiles); 80 0.89-1.00; 96 and more 0.67-0.93
-//   6, gate/up alone          80 1.01-1.06; 96 0.99-1.04; 112 0.93-0.98; 128 0.92-0.99
+// alone: 200 workgroups per round of 256 at least.  All figures are of one launch behind 128 MiB of other traffic, new activations and
+// weights that no cache holds, as in a step (launched back to back this kernel looks 3 to 8 % better: the 7B LM head, 80 rows, is
+// 49.7 / 47.2 so, 49.5 / 51.8 here and 50.0 / 52.0 in a step).  us, decode kernel / this, 48 / 80 / 96 / 128 rows:
+//   70B gate/up, 224 x 16 out-tiles   159 / 148   161 / 143   198 / 148   227 / 151
+//   70B LM head, 501 x 16             384 / 346   390 / 340   462 / 333   506 / 342
+//   70B down, 64 x 8 in four shares    77 /  79    82 /  84    99 /  86   118 /  95
+//   13B gate/up, 216 x 8               52 /  48    54 /  51    68 /  55    78 /  58
+//   13B LM head, 250 x 8               58 /  54    58 /  57    76 /  60    89 /  64
+//   7B LM head, 250 x 8                49 /  53    50 /  52    63 /  50    73 /  53
+// Which rows, from this kernel's time over the decode kernel's at K = 4096, 5120, 6656 and 8192, plain and gate/up:
+//   16 out-tiles, one round   1-16 rows 0.83-1.18; 17-32 rows: 200 to 230 groups, K >= 5120 0.82-0.95, the others 0.69-1.07;
+//                             33-48 0.70-1.00; 49-64 0.76-1.01; 80 0.73-0.98; 96 and more 0.57-0.84
+//     two rounds and more     17-32 0.93-1.10; 33-48: K >= 5120 0.86-1.00, K = 4096 0.93-1.04; 49-64 0.87-1.02; 80 0.83-0.97;
+//                             96 and more 0.68-0.87
+//   8 out-tiles, whole k      1-32 0.87-1.22; 33-48: K >= 5120 0.84-0.98, K = 4096 0.84-1.14; 49-64 0.95-1.11 (the decode kernel's own
+//                             form of eight out-tiles is for four and five row tiles); 80: 200 to 230 groups 0.92-0.99, more
+//                             0.93-1.05; 96 and more 0.70-0.94
+//   6, gate/up alone          80 1.02-1.08; 96 1.00-1.03; 112 0.93-0.99; 128 0.94-0.99
 // 6 out-tiles are for the matrices that have no 200 workgroups of 8 (7B gate/up, 172), by two groups of waves on even and odd k-tiles (a
-// wave's 2 x 2 tiles of 8 x 6 leave four waves idle): 97, 112, 128 rows 44.0 / 41.5, 44.5 / 42.1, 47.9 / 44.0 us.
-// Shares of k (o and down, in four) from 128 k-steps on.  A wave of the decode kernel has an eighth of a share in one chain, so with
-// shorter ones its sums were the better (relative error against float64, decode kernel / this, 80 rows: 4096 -> 6656 0.99e-7 / 1.28e-7,
-// 6656 -> 6656 1.20e-7 / 1.30e-7, 16384 -> 6656 1.85e-7 / 1.37e-7), and with 64 groups this kernel is slower there: 6656 -> 8192, 80 /
-// 96 / 128 rows 23.6 / 27.6, 25.7 / 28.5, 29.7 / 30.8 us, 10240 -> 8192 33.6 / 35.6, 36.7 / 38.0, 42.2 / 41.1.  From 65 rows on, 50 to 64
-// groups, the time is 0.94 to 0.98 of the decode kernel's at 80 rows, 0.82 to 0.93 at 96, 0.75 to 0.88 beyond; from 170 k-steps on it is
-// 0.84 to 1.00 at 17 to 64 rows too (22016 -> 8192, 16 / 32 / 48 / 64 rows 0.96, 0.84, 0.95, 0.95; 128 k-steps 1.07, 0.99, 1.01, 1.03).
+// wave's 2 x 2 tiles of 8 x 6 leave four waves idle): 112, 128 rows 42.6 / 40.6, 44.6 / 42.7 us.
+// Shares of k (o and down, in four, 50 to 64 groups) from 128 k-steps on: 17-48 rows 0.92-1.11, 49-64 0.96-1.10, 80 0.98-1.02; 96 0.86-0.91;
+// 112 and more 0.79-0.87.  A wave of the decode kernel has an eighth of a share in one chain, so with shorter ones its sums are the better
+// (relative error against float64, decode kernel / this, 80 rows: 4096 -> 6656 0.99e-7 / 1.28e-7, 6656 -> 6656 1.20e-7 / 1.30e-7, 16384 -> 6656
+// 1.85e-7 / 1.37e-7), and with 64 groups this kernel is slower there (6656 -> 8192 at 96 rows 25.7 / 28.5 us).
 // Matrices with K below 4096 were not measured and stay.
 bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, Rows8Plan *plan) {
   if (n < 1 || n > NP || K < 4096 || K % 32 != 0) return false;
@@ -548,11 +549,9 @@ bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t 
   for (int sp = max_splits; sp >= 1; --sp) {
     const int per_k = (KT + sp - 1) / sp;
     if ((sp - 1) * per_k >= KT || !fills(g8 * sp)) continue;
-    if (sp > 1) {
-      if (per_k < 128 || !(NT >= 5 || (NT >= 2 && per_k >= 170))) continue;
-    } else if (!(NT >= 5 || (NT == 3 && K >= 5120))) {
-      continue;
-    }
+    const bool faster = sp > 1 ? per_k >= 128 && NT >= 6
+                               : NT >= 6 || (NT == 5 && g8 <= 230) || (NT == 3 && g8 <= 256 && K >= 5120);
+    if (!faster) continue;
     *plan = Rows8Plan{8, g8, sp};
     return true;
   }

@@ -173,9 +173,10 @@ def test_step_projection_plans_cover_every_tile_and_k_step_once(lib, projection)
     # ... several rounds, ...
     ("lm_head", 8192, 128256, 16, (33, 49, 80, 128), (1, 16, 32)), ("lm_head", 4096, 128256, 16, (49, 64, 80, 128), (1, 16, 32, 48)),
     # ... 8 out-tiles, ...
-    ("lm_head", 4096, 32000, 8, (65, 80, 128), (1, 16, 33, 48, 49, 64)), ("lm_head", 5120, 32000, 8, (33, 48, 65, 128), (1, 16, 32, 49, 64)),
-    ("gate_up", 5120, 13824, 8, (33, 48, 65, 80, 128), (1, 16, 17, 32, 49, 64)), ("gate_up", 8192, 16384, 8, (48, 80, 128), (1, 32, 64)),
-    ("gate_up", 4096, 16384, 8, (65, 128), (1, 48, 64)), ("lm_head", 8192, 80000, 8, (48, 65, 128), (1, 16, 32, 64)),
+    ("lm_head", 4096, 32000, 8, (81, 96, 128), (1, 16, 33, 48, 49, 64, 80)), ("lm_head", 5120, 32000, 8, (33, 48, 81, 128), (1, 16, 32, 49, 64, 80)),
+    ("gate_up", 5120, 13824, 8, (33, 48, 65, 80, 128), (1, 16, 17, 32, 49, 64)), ("gate_up", 8192, 16384, 8, (48, 81, 128), (1, 32, 64, 80)),
+    ("gate_up", 4096, 14720, 8, (65, 80, 128), (1, 48, 64)), ("gate_up", 4096, 14784, 8, (81, 128), (48, 80)),
+    ("lm_head", 8192, 80000, 8, (81, 128), (1, 16, 32, 48, 64, 80)),
     # ... 6, and matrices that do not fill the chip, or of short rows
     ("gate_up", 4096, 11008, 6, (97, 112, 128), (1, 80, 81, 96)), ("gate_up", 8192, 22016, 6, (97, 128), (64, 80, 96)),
     ("gate_up", 4128, 11008, 6, (), (97, 128)), ("lm_head", 4096, 25440, 8, (), (80, 128)), ("lm_head", 4064, 32000, 8, (), (80, 128)),
@@ -192,8 +193,8 @@ def test_projections_that_share_operands(lib, projection, in_f, out_f, out_tiles
     # rows for which o and down share operands in LDS, in four shares of k, and for which they do not: never where a wave of the decode
     # kernel has shorter chains of sums (an eighth of a share, against 16 k-steps), nor where it is the faster one
     (4096, 6656, (), (1, 16, 80, 128)), (6656, 6656, (), (80, 96, 128)), (8192, 8192, (), (1, 48, 80, 128)),
-    (11008, 8192, (), (80, 128)), (16256, 8192, (), (80, 128)), (16384, 8192, (65, 80, 128), (1, 16, 17, 48, 64)),
-    (22016, 8192, (17, 48, 64, 65, 128), (1, 16)), (28672, 8192, (17, 48, 80, 128), (1, 16)), (28672, 6208, (), (80, 128))])
+    (11008, 8192, (), (80, 128)), (16256, 8192, (), (80, 128)), (16384, 8192, (81, 96, 128), (1, 16, 48, 64, 80)),
+    (28672, 8192, (81, 128), (1, 16, 17, 48, 80)), (28672, 6208, (), (80, 128))])
 def test_projections_in_shares_of_k(lib, in_f, out_f, shared, decode):
     for n in shared:
         assert tr.plan_step_projection("o_down", n, in_f, out_f)[2:] == (4, 1), n
@@ -202,11 +203,12 @@ def test_projections_in_shares_of_k(lib, in_f, out_f, shared, decode):
 
 
 def test_step_projections_of_the_7b_step_fill_the_chip(lib):
-    # what an 80-node step of the 7B shape launches: the LM head shares operands in LDS
-    for projection, in_f, out_f, kernel in (("qkv", 4096, 12288, 0), ("o_down", 4096, 4096, 0), ("gate_up", 4096, 11008, 0),
+    # what 80- and 128-node steps of the 7B shape launch: with 128 nodes gate/up and the LM head share operands in LDS
+    for projection, in_f, out_f, kernel in (("qkv", 4096, 12288, 0), ("o_down", 4096, 4096, 0), ("gate_up", 4096, 11008, 1),
                                             ("o_down", 11008, 4096, 0), ("lm_head", 4096, 32000, 1)):
-        p, groups, splits, k = tr.plan_step_projection(projection, 80, in_f, out_f)
-        assert groups * splits >= 230 and k == kernel, (projection, p, groups, splits, k)
+        for n, want in ((80, 0), (128, kernel)):
+            p, groups, splits, k = tr.plan_step_projection(projection, n, in_f, out_f)
+            assert groups * splits >= 230 and k == want, (projection, n, p, groups, splits, k)
 
 
 def test_attention_plan(lib):
