@@ -257,7 +257,7 @@ tr_status tr_plan_attention_form(int32_t n_heads, int32_t n_kv_heads, int32_t n_
   if (st != TR_OK) return st;
   if (plan[1] < 0) *form = TR_ATT_FEW_ROWS;
   else if (plan[1] == 0) *form = TR_ATT_ONE_LAUNCH;
-  else *form = attn_long_shares((n_nodes + 15) / 16 * plan[0], len_bound, plan[1]) ? TR_ATT_LONG_SHARES : TR_ATT_SHORT_SHARES;
+  else *form = attn_long_shares((n_nodes + 15) / 16, plan[0], len_bound, plan[1]) ? TR_ATT_LONG_SHARES : TR_ATT_SHORT_SHARES;
   return TR_OK;
 }
 

@@ -682,15 +682,15 @@ int attn_choose_splits(int32_t head_groups, int32_t len_bound) {
   return s < 1 ? 1 : s;
 }
 
-// 32-key tiles a workgroup takes one after another.  Time of k_attn_ring over that of k_attn_mfma, one launch behind 128 MiB of other
-// traffic and a new query block, as in a step, at 8, 10, 12, 14 and 16 tiles: 80 nodes, 32 heads on 32 1.00, 1.00, 0.96, 0.97, 0.95; 40 on 40
-// 1.03, 1.00, 0.98, 0.97, 0.96; 8 on 8 0.99, 0.98, 0.97, 0.97, 0.95; 40 on 8 0.96, 0.95, 0.95, 0.95, 0.94; 48 nodes, 32 on 32 0.96, 0.92, 0.90, 0.89,
-// 0.87; 64 nodes, 64 on 8 1.00, 0.99, 0.99, 0.99, 0.99; ten waves (80 nodes, 64 on 8) 0.98, 0.98, 0.97, 0.97, 0.98; eight waves (128 nodes) 32 on
-// 32 1.02, 1.00, 1.01, 0.99, 0.99; 40 on 40 1.02, 1.03, 1.01, 1.01, 1.00; 64 on 8 0.98, 0.96, 0.97, 0.97, 0.97.  At five and six it is up to 1.15
-// (launched back to back, with the queries in L2 already, it gains from seven on).
-bool attn_long_shares(int32_t waves, int32_t len_bound, int32_t nsplit) {
+// 32-key tiles a workgroup takes one after another.  us a layer that whole steps are longer with k_attn_ring than with k_attn_mfma (runs of
+// a side within 0.7 us): 80 nodes, 32 heads on 32 +0.4 at 12 tiles, 0.0 at 13, -0.6 at 16, -2.1 at 20, -3.1 at 32, -7.2 at 63; 40 on 40 +1.4
+// at 12, -1.2 at 17, -2.2 at 21, -7.6 at 43, -17 at 84; 64 on 8 -0.9 at 17, -1.6 at 24, -3.7 at 63; 48 nodes, 32 on 32 -1.8 at 16, -2.9 at 20, 64
+// on 8 -3.3 at 17; 96 nodes, 32 on 32 +0.8 at 16, -0.5 at 20, -1.4 at 32, 40 on 40 -1.3 at 21, 64 on 8 -1.5 at 16; 112 nodes, 32 on 32 +1.8 at 16,
+// +0.1 at 20, -0.5 at 32, 40 on 40 -0.7 at 22; 128 nodes, 32 on 32 +1.2 at 16, +1.0 at 21, +0.5 at 32, -1.3 at 63, 40 on 40 -0.2 at 17, -2.9 at 27,
+// -4.2 at 43.  (Kernel times alone put the lines at 12 and 14; launched back to back, with the queries in L2, it gains from 7 on.)
+bool attn_long_shares(int32_t node_tiles, int32_t hpw, int32_t len_bound, int32_t nsplit) {
   const int chain = ((len_bound + 31) / 32 + nsplit - 1) / nsplit;
-  return chain >= (waves == 8 ? 16 : 12);
+  return chain >= (hpw > 1 || node_tiles <= 5 ? 16 : node_tiles <= 7 ? 24 : 40);
 }
 
 template <int NT, int HPW>
@@ -699,7 +699,7 @@ static hipError_t launch_attn_k(const bf16_t *q, const bf16_t *Kl, const bf16_t 
                                 float *part_ml, float *part_acc, bf16_t *out, int32_t out_row_tiles, KernelTimer tm,
                                 hipStream_t st) {
   const dim3 grid(Hkv, H / Hkv / HPW, nsplit), block(NT * HPW * 64);
-  if (attn_long_shares(NT * HPW, len_bound, nsplit) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
+  if (attn_long_shares(NT, HPW, len_bound, nsplit) && starts_on_16(q) && starts_on_16(Kl) && starts_on_16(Vl) && starts_on_16(anc)) {
     constexpr int smem = ring_lds_bytes(NT * HPW);
     static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_ring<NT, HPW>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;

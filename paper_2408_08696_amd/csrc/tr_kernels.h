@@ -166,8 +166,8 @@ hipError_t launch_rows(const RowsArgs &p, int32_t dtype, hipStream_t st, KernelT
 // uses for H / that many head groups and this bound on committed length + nodes.
 int attn_heads_per_wg(int32_t H, int32_t Hkv, int32_t n);
 int attn_choose_splits(int32_t head_groups, int32_t len_bound);
-// whether workgroups of this many waves take their key shares in 64-key steps (k_attn_ring) or tile by tile (k_attn_mfma)
-bool attn_long_shares(int32_t waves, int32_t len_bound, int32_t nsplit);
+// whether workgroups of this many node tiles and heads take their key shares in 64-key steps (k_attn_ring) or tile by tile
+bool attn_long_shares(int32_t node_tiles, int32_t hpw, int32_t len_bound, int32_t nsplit);
 // true: one launch without key splits or merge pass (short sequences); then the two values above do not apply
 bool attn_one_launch(int32_t H, int32_t Hkv, int32_t len_bound);
 hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl, int32_t H, int32_t Hkv, int32_t cap,

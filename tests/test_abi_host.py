@@ -251,12 +251,14 @@ def test_attention_plan(lib):
 
 
 @pytest.mark.parametrize("H,Hkv,n,short,long_", [
-    # lengths (committed + nodes) whose shares are 32-key tiles one after another, and steps of 64 keys: twelve tiles a share, ...
-    (32, 32, 80, (840, 1104, 1536, 2816), (2817, 16080)), (8, 8, 80, (3072, 5632), (5633,)), (32, 32, 112, (2816,), (2817,)),
-    (40, 40, 80, (1152, 2112), (2113, 2128)), (64, 8, 48, (1536, 2816), (2817, 4096)), (256, 256, 66, (), (840, 1500)),
-    (64, 8, 80, (2816,), (2817, 4176)), (64, 8, 96, (2816,), (2817,)), (32, 8, 80, (5632,), (5633,)),
-    # ... sixteen for eight waves
-    (32, 32, 128, (905, 1536, 3840), (3841, 16128)), (64, 8, 128, (1920,), (1921,)), (64, 8, 64, (3840,), (3841,))])
+    # lengths (committed + nodes) whose shares are 32-key tiles one after another, and steps of 64 keys: sixteen tiles a share with
+    # two heads a workgroup and up to 80 nodes, ...
+    (32, 32, 80, (840, 1104, 3840), (3841, 16080)), (8, 8, 80, (3072, 7680), (7681,)), (40, 40, 80, (1152, 2128, 2880), (2881, 4176)),
+    (256, 256, 66, (), (840, 1500)), (64, 8, 48, (1536, 3840), (3841, 4096)), (64, 8, 80, (3840,), (3841, 4176)),
+    (64, 8, 96, (3840,), (3841,)), (32, 8, 80, (7680,), (7681,)), (64, 8, 64, (3840,), (3841,)),
+    # ... 24 up to 112 nodes, 40 beyond
+    (32, 32, 81, (5888,), (5889,)), (32, 32, 112, (5888,), (5889,)), (64, 8, 112, (2944,), (2945,)),
+    (32, 32, 128, (905, 1536, 9984), (9985, 16128)), (64, 8, 113, (4992,), (4993,))])
 def test_long_share_attention_rule(lib, H, Hkv, n, short, long_):
     for L in short:
         assert tr.plan_attention_form(H, Hkv, n, L) == "short_shares", L
