@@ -244,6 +244,7 @@ static hipError_t forward_generic(const tr_model &m, const tr_kv &kv, const Tree
     p.q = q; p.k_layer = (T *)kv.k + (size_t)l * lsz; p.v_layer = (T *)kv.v + (size_t)l * lsz;
     p.rope = rope; p.d_len = kv.d_len; p.H = H; p.Hkv = Hkv; p.hd = hd; p.cap = kv.capacity; p.tiled = kv.layout;
     TR_TRY(launch_rows(p, m.dtype, st, prof_next(prof, PC_QKV)));
+    if (l == m.n_layers - 1 && logits_out == nullptr) break; // ingestion only needs the cache: nothing reads the last layer's output
     TR_TRY(attention_dispatch<T>(kv, l, H, tree, n, q, attn, 0, (float *)(ws + w.part_ml), (float *)(ws + w.part_acc),
                                  prof, st));
     TR_TRY(launch_rows(residual(attn, hq, lw.wo), m.dtype, st, prof_next(prof, PC_OPROJ)));
@@ -470,6 +471,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
                         H, Hkv, hd, kv.capacity, kv.layout};
       TR_TRY(project(g, 1, prof_next(prof, PC_QKV), st));
     }
+    if (l == m.n_layers - 1 && logits_out == nullptr) break; // as in forward_wide
     TR_TRY(attention_dispatch<T>(kv, l, H, tree, n, q, attn, NT, (float *)(ws + w.part_ml), (float *)(ws + w.part_acc),
                                  prof, st));
     {
