@@ -264,7 +264,7 @@ static hipError_t forward_generic(const tr_model &m, const tr_kv &kv, const Tree
 // ---------------------------------------------------------------------------------------------
 // packed bf16 forward: MFMA GEMMs on packed weights, activations handed from kernel to kernel in
 // fragment order, projection outputs that feed the residual stream kept as per-split partial sums
-// which the next normalisation kernel folds into x in a fixed order.
+// which the next normalisation kernel folds into x in a fixed order, or added to it by the projection itself.
 // ---------------------------------------------------------------------------------------------
 // Residual update and normalisation input, block (row, chunk of 1024 columns), 128 threads x 8 columns:
 //   x[row, c] += sum_s part[s][row, c]        (in split order)
@@ -281,8 +281,8 @@ static_assert(NORM_MAX_PARTS >= GEMM_MAX_SPLITS && NORM_MAX_PARTS >= WIDE_MAX_SP
 
 // Both are one memory round trip long and nothing else counts: every load, the gain's too, is issued before the first
 // use, and the stores come after the last wait (a wait for a load also waits for the stores before it).
-__device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 &gv, int row, int j, int32_t d,
-                                    int32_t row_tiles, bf16_t *__restrict__ xg_frag, float *__restrict__ ssq_at, bool row_on) {
+__device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 &gv, int row, int j, int32_t d, int32_t row_tiles,
+                                    bf16_t *__restrict__ xg_frag, float *__restrict__ ssq, int32_t ld_ssq, int chunk, bool row_on) {
   __shared__ float red[2];
   float ss = 0.f;
   uint4 pk = uint4{0u, 0u, 0u, 0u};
@@ -301,14 +301,19 @@ __device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
-  if (threadIdx.x == 0 && row_on) *ssq_at = red[0] + red[1];
+  if (threadIdx.x == 0 && row_on) {
+    float *at = ssq + (size_t)row * ld_ssq;
+    at[chunk] = red[0] + red[1];
+    if (chunk == (d - 1) / NORM_CHUNK)
+      for (int c = chunk + 1; c < ld_ssq; ++c) at[c] = 0.f; // sums of no chunk
+  }
 }
 
 template <int PARTS>
 __global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const float *__restrict__ part,
                                                   size_t part_stride, const bf16_t *__restrict__ g, int32_t n, int32_t d,
                                                   int32_t row_tiles, bf16_t *__restrict__ xg_frag,
-                                                  float *__restrict__ ssq, int32_t n_chunks) {
+                                                  float *__restrict__ ssq, int32_t ld_ssq) {
   const int row = blockIdx.x, chunk = blockIdx.y;
   const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
   const bool live = row < n && j < d;
@@ -335,19 +340,19 @@ __global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const f
     *reinterpret_cast<float4 *>(xr + 4) = b;
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
   }
-  norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
+  norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq, ld_ssq, chunk, row < n);
 }
 
 // n_part 1 .. NORM_MAX_PARTS partial sums
 static hipError_t launch_add_frag(int n_part, int chunks, float *x, const float *part, size_t part_stride, const bf16_t *g,
-                                  int32_t n, int32_t d, int32_t row_tiles, bf16_t *xg_frag, float *ssq, KernelTimer tm,
-                                  hipStream_t st) {
+                                  int32_t n, int32_t d, int32_t row_tiles, bf16_t *xg_frag, float *ssq, int32_t ld_ssq,
+                                  KernelTimer tm, hipStream_t st) {
   const dim3 grid(row_tiles * 16, chunks), block(128);
   switch (n_part) {
-  case 1: return launch(k_add_frag<1>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
-  case 2: return launch(k_add_frag<2>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
-  case 3: return launch(k_add_frag<3>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
-  case 4: return launch(k_add_frag<4>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, chunks);
+  case 1: return launch(k_add_frag<1>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, ld_ssq);
+  case 2: return launch(k_add_frag<2>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, ld_ssq);
+  case 3: return launch(k_add_frag<3>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, ld_ssq);
+  case 4: return launch(k_add_frag<4>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, ld_ssq);
   }
   return hipErrorInvalidValue;
 }
@@ -357,8 +362,8 @@ __global__ __launch_bounds__(128) void k_embed_frag(const bf16_t *__restrict__ E
                                                     int32_t hd, float theta, float *__restrict__ x,
                                                     float *__restrict__ rope, const bf16_t *__restrict__ g, int32_t n,
                                                     int32_t d, int32_t row_tiles, bf16_t *__restrict__ xg_frag,
-                                                    float *__restrict__ ssq, int32_t n_chunks) {
-  const int row = blockIdx.x, chunk = blockIdx.y;
+                                                    float *__restrict__ ssq, int32_t ld_ssq) {
+  const int row = blockIdx.x, chunk = blockIdx.y, n_chunks = (d + NORM_CHUNK - 1) / NORM_CHUNK;
   if (chunk == n_chunks) {
     if (row < n) rope_row(*d_len + (depth != nullptr ? depth[row] : row), hd, theta, rope + (size_t)row * hd);
     return;
@@ -380,7 +385,7 @@ __global__ __launch_bounds__(128) void k_embed_frag(const bf16_t *__restrict__ E
     *reinterpret_cast<float4 *>(xr) = float4{v[0], v[1], v[2], v[3]};
     *reinterpret_cast<float4 *>(xr + 4) = float4{v[4], v[5], v[6], v[7]};
   }
-  norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq + (size_t)row * n_chunks + chunk, row < n);
+  norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq, ld_ssq, chunk, row < n);
 }
 
 // row-major bf16 [n, K] -> fragment order (standalone linear op only)
@@ -410,7 +415,7 @@ static bool packed_supported(const tr_model &m) {
 }
 
 // One projection of a tree step by the faster of its two kernels; fills g.splits.  (tr_plan_step_projection says which.)
-static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipStream_t st) {
+static bool project_rows8(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan) {
   int32_t total = 0;
   bool on = starts_on_16(g.a_frag) && starts_on_16(g.w2); // what goes straight into LDS
   for (int i = 0; i < g.n_seg; ++i) {
@@ -418,9 +423,11 @@ static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipSt
     on = on && starts_on_16(g.seg[i].w);
   }
   const bool swiglu = g.mode == GEMM_SWIGLU, scaled = g.row_ssq != nullptr;
-  on = on && g.rope.q == nullptr && (scaled ? g.n_ssq <= 8 : !swiglu);
+  return on && g.rope.q == nullptr && (scaled ? g.n_ssq <= 8 : !swiglu) && rows8_plan(g.n, g.K, total, swiglu, swiglu || scaled ? 1 : max_splits, plan);
+}
+static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipStream_t st) {
   Rows8Plan plan;
-  if (on && rows8_plan(g.n, g.K, total, swiglu, swiglu || scaled ? 1 : max_splits, &plan)) {
+  if (project_rows8(g, max_splits, &plan)) {
     g.splits = plan.splits;
     return launch_gemm_rows8(g, plan, st, tm);
   }
@@ -444,19 +451,39 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
   float *ypart = (float *)(ws + w.ypart);
   const size_t ystride = (size_t)NP * d;
   const size_t lsz = (size_t)Hkv * kv.capacity * hd;
-  float *ssq = (float *)(ws + w.ssq);
   const int nch = (d + NORM_CHUNK - 1) / NORM_CHUNK;
+  // The sums of squares sit behind a step's partial sums, where ypart has room for many times as much, on 16 bytes whatever the
+  // workspace starts on.
+  float *ssq = (float *)(((uintptr_t)(ypart + GEMM_MAX_SPLITS * ystride) + 15) & ~(uintptr_t)15);
+  static_assert((size_t)(WIDE_PART_ROWS - GEMM_MAX_SPLITS * NP) * 32 >= (size_t)NP * 64 + 4, "d >= 32 columns hold 32 rows of 256 sums");
 
-  TR_TRY(launch(k_embed_frag, dim3(NT * 16, nch + 1), dim3(128), 0, st, prof_next(prof, PC_EMBED), (const T *)m.embed,
-                m.vocab, tok, tree.depth, kv.d_len, hd, m.rope_theta, x, rope, (const T *)m.layers[0].attn_norm, n, d, NT,
-                xn, ssq, nch));
-  int pending = 0; // partial sums waiting in ypart
-  auto add_norm = [&](const void *gain) {
-    return launch_add_frag(pending, nch, x, ypart, ystride, (const T *)gain, n, d, NT, xn, ssq, prof_next(prof, PC_NORM), st);
+  int n_ssq = (nch + 3) & ~3; // sums of squares a row has at the moment
+  TR_TRY(launch(k_embed_frag, dim3(NT * 16, nch + 1), dim3(128), 0, st,
+                prof_next(prof, PC_EMBED), (const T *)m.embed, m.vocab, tok, tree.depth, kv.d_len, hd, m.rope_theta, x, rope,
+                (const T *)m.layers[0].attn_norm, n, d, NT, xn, ssq, n_ssq));
+  // x += a * wt^T and the operand of the projection behind it: in one launch where that is faster (gemm_updates_residual) and `next`,
+  // whose sums of squares these become, is the decode kernel's
+  auto residual = [&](const T *a, int K, const void *wt, const void *gain, GemmArgs &next, ProfCat cat) {
+    GemmArgs g{};
+    g.a_frag = a; g.n = n; g.K = K;
+    g.seg[0] = GemmSeg{(const T *)wt, d / 16};
+    g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
+    n_ssq = (nch + 3) & ~3;
+    next.row_ssq = ssq; next.n_ssq = n_ssq; next.norm_dim = d; next.eps = m.rms_eps;
+    Rows8Plan r8;
+    if (!project_rows8(g, GEMM_MAX_SPLITS, &r8) && !project_rows8(next, 1, &r8)) {
+      gemm_plan(g, GEMM_MAX_SPLITS);
+      if (gemm_updates_residual(n, g.groups, g.splits)) {
+        next.n_ssq = n_ssq = (g.groups + 3) & ~3;
+        g.resid = GemmResid{x, (const T *)gain, xn, ssq, n_ssq};
+        return launch_gemm_mfma(g, st, prof_next(prof, cat));
+      }
+    }
+    TR_TRY(project(g, GEMM_MAX_SPLITS, prof_next(prof, cat), st));
+    return launch_add_frag(g.splits, nch, x, ypart, ystride, (const T *)gain, n, d, NT, xn, ssq, n_ssq, prof_next(prof, PC_NORM), st);
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
-    if (l > 0) TR_TRY(add_norm(lw.attn_norm));
     {
       GemmArgs g{};
       g.a_frag = xn; g.n = n; g.K = d;
@@ -464,7 +491,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
       g.seg[1] = GemmSeg{(const T *)lw.wk, hk / 16};
       g.seg[2] = GemmSeg{(const T *)lw.wv, hk / 16};
       g.n_seg = 3; g.mode = GEMM_STORE;
-      g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
+      g.row_ssq = ssq; g.n_ssq = n_ssq; g.norm_dim = d; g.eps = m.rms_eps;
       // RoPE and the query / cache writes happen in the projection's epilogue (one K-split: the epilogue
       // needs complete sums); wq and wk are packed with interleaved rows for that
       g.rope = GemmRope{q, (T *)kv.k + (size_t)l * lsz, (T *)kv.v + (size_t)l * lsz, rope, kv.d_len,
@@ -474,40 +501,20 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
     if (l == m.n_layers - 1 && logits_out == nullptr) break; // as in forward_wide
     TR_TRY(attention_dispatch<T>(kv, l, H, tree, n, q, attn, NT, (float *)(ws + w.part_ml), (float *)(ws + w.part_acc),
                                  prof, st));
-    {
-      GemmArgs g{};
-      g.a_frag = attn; g.n = n; g.K = hq;
-      g.seg[0] = GemmSeg{(const T *)lw.wo, d / 16};
-      g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      TR_TRY(project(g, GEMM_MAX_SPLITS, prof_next(prof, PC_OPROJ), st));
-      pending = g.splits;
+    GemmArgs up{};
+    up.a_frag = xn; up.n = n; up.K = d;
+    up.seg[0] = GemmSeg{(const T *)lw.w_gate, F / 16};
+    up.n_seg = 1; up.w2 = (const T *)lw.w_up; up.h_frag = hbuf; up.mode = GEMM_SWIGLU;
+    TR_TRY(residual(attn, hq, lw.wo, lw.ffn_norm, up, PC_OPROJ));
+    TR_TRY(project(up, 1, prof_next(prof, PC_GATEUP), st));
+    GemmArgs next{}; // the LM head, or a Q/K/V projection, which the decode kernel takes always
+    if (l == m.n_layers - 1) {
+      next.a_frag = xn; next.n = n; next.K = d;
+      next.seg[0] = GemmSeg{(const T *)m.lm_head, m.vocab / 16};
+      next.n_seg = 1; next.y = logits_out; next.ldy = m.vocab; next.mode = GEMM_STORE;
     }
-    TR_TRY(add_norm(lw.ffn_norm));
-    {
-      GemmArgs g{};
-      g.a_frag = xn; g.n = n; g.K = d;
-      g.seg[0] = GemmSeg{(const T *)lw.w_gate, F / 16};
-      g.n_seg = 1; g.w2 = (const T *)lw.w_up; g.h_frag = hbuf; g.mode = GEMM_SWIGLU;
-      g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
-      TR_TRY(project(g, 1, prof_next(prof, PC_GATEUP), st));
-    }
-    {
-      GemmArgs g{};
-      g.a_frag = hbuf; g.n = n; g.K = F;
-      g.seg[0] = GemmSeg{(const T *)lw.w_down, d / 16};
-      g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      TR_TRY(project(g, GEMM_MAX_SPLITS, prof_next(prof, PC_DOWN), st));
-      pending = g.splits;
-    }
-  }
-  if (logits_out != nullptr) {
-    TR_TRY(add_norm(m.final_norm));
-    GemmArgs g{};
-    g.a_frag = xn; g.n = n; g.K = d;
-    g.seg[0] = GemmSeg{(const T *)m.lm_head, m.vocab / 16};
-    g.n_seg = 1; g.y = logits_out; g.ldy = m.vocab; g.split_stride = 0; g.mode = GEMM_STORE;
-    g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
-    TR_TRY(project(g, 1, prof_next(prof, PC_LMHEAD), st));
+    TR_TRY(residual(hbuf, F, lw.w_down, l + 1 < m.n_layers ? m.layers[l + 1].attn_norm : m.final_norm, next, PC_DOWN));
+    if (l == m.n_layers - 1) TR_TRY(project(next, 1, prof_next(prof, PC_LMHEAD), st));
   }
   return hipSuccess;
 }
@@ -543,7 +550,7 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
                 xn, ssq, nch));
   int pending = 0;
   auto add_norm = [&](const void *gain) {
-    return launch_add_frag(pending, nch, x, ypart, ystride, (const T *)gain, n, d, RT, xn, ssq, no_timer, st);
+    return launch_add_frag(pending, nch, x, ypart, ystride, (const T *)gain, n, d, RT, xn, ssq, nch, no_timer, st);
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];

@@ -27,7 +27,8 @@
 // unit with NW as large as the register file allows.
 //
 // Epilogues: plain float32 store (per K-split), gate/up pairs through SwiGLU into the next GEMM's operand
-// order, or for the fused Q/K/V projection RoPE plus the query and KV-cache writes (GemmRope).
+// order, for the fused Q/K/V projection RoPE plus the query and KV-cache writes (GemmRope), or for o and down of few rows the update of
+// the residual stream (GemmResid).
 #include "tr_kernels.h"
 
 namespace tr {
@@ -85,13 +86,15 @@ hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t
 // LDS the tail needs: the GW partials of the tiles of one reduce-scatter pass, plus the per-row scales when
 // the epilogue applies an RMS scale.  One pass if all tiles fit the 160 KB of a CU, else two (the first
 // covers the units of waves 0 .. GW/2-1).
-constexpr int MOST_SSQ = 8; // partial sums of squares of a row
-constexpr size_t gemm_scale_lds_bytes(int nt, bool scaled) { return scaled ? (size_t)nt * 16 * (1 + MOST_SSQ) * sizeof(float) : 0; }
+// The sums of squares a row comes with lie in the place of its scale.
+constexpr size_t gemm_scale_lds_bytes(int nt, bool scaled) { return scaled ? (size_t)nt * 16 * gemm_most_ssq(nt) * sizeof(float) : 0; }
+// Tail units a wave owns: an even share, or with GEMM_RESID a row tile's.
+constexpr int gemm_units_per_wave(int p, int nt, int mode, int gw) { return mode == GEMM_RESID ? p : (p * nt + gw - 1) / gw; }
 constexpr bool gemm_tail_one_pass(int p, int nt, int mode, int gw, bool scaled) {
   return (size_t)p * nt * (mode == GEMM_SWIGLU ? 2 : 1) * gw * 1024 + gemm_scale_lds_bytes(nt, scaled) <= 160 * 1024;
 }
 constexpr size_t gemm_tail_red_bytes(int p, int nt, int mode, int gw, bool scaled) {
-  const int u = p * nt, upw = (u + gw - 1) / gw;
+  const int u = p * nt, upw = gemm_units_per_wave(p, nt, mode, gw);
   const int own0 = gemm_tail_one_pass(p, nt, mode, gw, scaled) ? gw : gw / 2;
   const int units0 = own0 * upw < u ? own0 * upw : u;
   return (size_t)units0 * (mode == GEMM_SWIGLU ? 2 : 1) * gw * 1024;
@@ -181,12 +184,12 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   };
   constexpr int TPU = MODE == GEMM_SWIGLU ? 2 : 1;
   constexpr int U = P * NT;
-  constexpr int UPW = (U + GW - 1) / GW;
+  constexpr int UPW = gemm_units_per_wave(P, NT, MODE, GW);
   const int r = lane & 15, gq = lane >> 4;
   // What only the epilogue needs is asked for behind the first weight tiles.  Sums of squares go straight to LDS: wave w
   // fetches those of row tiles w, w + GW, .. and turns them into scales itself.
-  float *const sc_lds = red + gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) / sizeof(float); // [NT * 16], SCALED only
-  float *const ssq_lds = sc_lds + NT * 16;                                                  // [NT][16 * MOST_SSQ]
+  float *const ssq_lds = red + gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) / sizeof(float); // [NT][16][n_ssq], SCALED only
+  GemmResid rs{};
   GemmRope rp{};
   int L = 0;
   f32x2 rope_c[MODE == GEMM_ROPE ? UPW : 1], rope_s[MODE == GEMM_ROPE ? UPW : 1];
@@ -195,11 +198,15 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     if (SCALED) {
       for (int t = wave; t < NT; t += GW) {
         const int words = (n_rows - 16 * t < 16 ? n_rows - 16 * t : 16) * g.n_ssq;
-        for (int i = 0; i < words; i += 64)
-          if (i + lane < words)
-            word_to_lds((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)(ssq_lds + t * 16 * MOST_SSQ + i),
-                        lane * 4, reinterpret_cast<uint64_t>(g.row_ssq + t * 16 * g.n_ssq + i));
+        for (int i = 0; i < words; i += 256)
+          if (i + lane * 4 < words)
+            tile_to_lds((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)(ssq_lds + t * 16 * g.n_ssq + i),
+                        lane * 16, reinterpret_cast<uint64_t>(g.row_ssq + t * 16 * g.n_ssq + i));
       }
+    }
+    if (MODE == GEMM_RESID) {
+      rs.x = hold(g.resid.x); rs.gain = hold(g.resid.gain); rs.xg_frag = hold(g.resid.xg_frag); rs.ssq = hold(g.resid.ssq);
+      rs.ld_ssq = hold(g.resid.ld_ssq);
     }
     if (MODE == GEMM_ROPE) {
       rp.q = hold(g.rope.q); rp.k_layer = hold(g.rope.k_layer); rp.v_layer = hold(g.rope.v_layer);
@@ -267,16 +274,38 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   // all tiles fit LDS this is one pass; otherwise two, the first for the units of waves 0 .. GW/2-1.
   // Every wave then scales, activates and stores its own few tiles, instead of one wave storing them all.
   constexpr int OWN0 = gemm_tail_one_pass(P, NT, MODE, GW, SCALED) ? GW : GW / 2; // waves 0 .. OWN0-1 own pass 0
+  static_assert(MODE != GEMM_RESID || (OWN0 == GW && NT <= GW), "a wave has whole row tiles of one pass");
   float4 *red4 = reinterpret_cast<float4 *>(red); // [unit slot * TPU + k][GW][64]
   if (SCALED) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     for (int t = wave; t < NT; t += GW) {
-      const int row = lane & 15;
+      float *const at = ssq_lds + t * 16 * g.n_ssq;
       float ss = 0.f;
-      for (int c = lane >> 4; c < g.n_ssq; c += 4) ss += ssq_lds[t * 16 * MOST_SSQ + row * g.n_ssq + c];
+      const int n4 = g.n_ssq / 4, turn = n4 >= 16 ? r : 0; // rows start apart: theirs are a multiple of all banks apart
+#pragma unroll 8
+      for (int i = gq; i < n4; i += 4) {
+        const int c = i + turn < n4 ? i + turn : i + turn - n4;
+        const float4 q = *reinterpret_cast<const float4 *>(at + r * g.n_ssq + 4 * c);
+        ss += (q.x + q.y) + (q.z + q.w);
+      }
       ss += __shfl_xor(ss, 16);
       ss += __shfl_xor(ss, 32);
-      if (lane < 16) sc_lds[16 * t + lane] = 1.0f / sqrtf(ss / (float)g.norm_dim + g.eps);
+      if (lane < 16) at[lane] = 1.0f / sqrtf(ss / (float)g.norm_dim + g.eps); // in the place of its row tile's sums
+    }
+  }
+  f32x4 x_old[MODE == GEMM_RESID ? UPW : 1];
+  uint2 gains[MODE == GEMM_RESID ? UPW : 1];
+  if (MODE == GEMM_RESID) { // on their way while the waves' sums meet
+#pragma unroll
+    for (int i = 0; i < UPW; ++i) {
+      const int row = 16 * wave + r, o = (tile0 + i) * 16 + 4 * gq;
+      x_old[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      gains[i] = uint2{0u, 0u};
+      if (wave < NT && i < n_valid && row < n_rows) {
+        const float4 xv = *reinterpret_cast<const float4 *>(rs.x + (size_t)row * g.ldy + o);
+        x_old[i] = f32x4{xv.x, xv.y, xv.z, xv.w};
+        gains[i] = *reinterpret_cast<const uint2 *>(rs.gain + o);
+      }
     }
   }
   f32x4 fin[UPW][TPU];
@@ -287,7 +316,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     for (int u = 0; u < P; ++u)
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const int id = u * NT + t;
+        const int id = MODE == GEMM_RESID ? t * P + u : u * NT + t;
         if ((id / UPW >= OWN0) != (pass == 1)) continue;
         const int slot = (id - pass * OWN0 * UPW) * TPU;
         red4[((size_t)slot * GW + wave) * 64 + lane] = float4{acc[u][t][0], acc[u][t][1], acc[u][t][2], acc[u][t][3]};
@@ -318,6 +347,33 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     if (pass == 0 && OWN0 * UPW < U) __syncthreads(); // pass 1 reuses the buffer
   }
 
+  if constexpr (MODE == GEMM_RESID) { // this wave's row tile and all out-tiles of the workgroup
+    const int row = 16 * wave + r;
+    float ss = 0.f;
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      if (wave >= NT || u >= n_valid) continue;
+      const int o = (tile0 + u) * 16 + 4 * gq;
+      const f32x4 v = x_old[u] + fin[u][0];
+      u32x2s xg = u32x2s{0u, 0u};
+      if (row < n_rows) {
+        *reinterpret_cast<float4 *>(rs.x + (size_t)row * g.ldy + o) = float4{v[0], v[1], v[2], v[3]};
+        xg = u32x2s{bf16_pair(v[0] * __uint_as_float(gains[u].x << 16), v[1] * __uint_as_float(gains[u].x & 0xFFFF0000u)),
+                    bf16_pair(v[2] * __uint_as_float(gains[u].y << 16), v[3] * __uint_as_float(gains[u].y & 0xFFFF0000u))};
+        ss += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+      }
+      const size_t slot = ((size_t)(o >> 5) * NT + wave) * 64 + r + 16 * ((o & 31) >> 3);
+      *reinterpret_cast<u32x2s *>(rs.xg_frag + slot * 8 + (o & 7)) = xg;
+    }
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    if (wave < NT && row < n_rows) {
+      if (gq == 0) rs.ssq[(size_t)row * rs.ld_ssq + bx] = ss;
+      if (bx == 0 && gq < rs.ld_ssq - g.groups) rs.ssq[(size_t)row * rs.ld_ssq + g.groups + gq] = 0.f; // sums of no group
+    }
+    return;
+  }
+
 #pragma unroll
   for (int i = 0; i < UPW; ++i) {
     const int id = wave * UPW + i;
@@ -325,7 +381,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     const int u = id / NT, t = id - u * NT;
     if (u >= n_valid) continue;
     const int row = 16 * t + r;
-    const float sc_row = SCALED ? sc_lds[row] : 1.0f;
+    const float sc_row = SCALED ? ssq_lds[t * 16 * g.n_ssq + r] : 1.0f;
     const int o = (tile0 + u) * 16 + 4 * gq;
     if (MODE != GEMM_SWIGLU) {
       if (row >= n_rows) continue;
@@ -421,6 +477,7 @@ void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t
       if (hbm_kib / 6000.0 > t) t = hbm_kib / 6000.0;
       t = rounds * (t + 3.0) + 3.0;
       if (s > 1) t += 2.0 * (s - 1) * NT * total_tiles / 8000.0 + 0.5; // extra KiB of partials written and re-read
+      if (max_splits > 1 && !gemm_updates_residual(n, groups, s)) t += 2.5; // the residual kernel's launch
       if (t < best) {
         best = t;
         bp = p;
@@ -437,7 +494,7 @@ void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t
 template <int NT, int P, int MODE, int GW, bool SCALED>
 static hipError_t launch_ks(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
   constexpr int NW = MODE == GEMM_SWIGLU ? 2 * P : P;
-  const size_t smem = gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) + gemm_scale_lds_bytes(NT, SCALED);
+  const size_t smem = gemm_tail_red_bytes(P, NT, MODE, GW, SCALED) + (SCALED ? (size_t)NT * 16 * g.n_ssq * sizeof(float) : 0);
   if (smem > 65536) {
     static bool once = [] {
       return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_mfma<NT, NW, MODE, GW, SCALED>),
@@ -456,6 +513,12 @@ static hipError_t launch_k(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
     return launch_ks<NT, P, GEMM_ROPE, GW, true>(g, st, tm);
   }
   if (g.n_seg != 1) return hipErrorInvalidValue;
+  if (g.resid.x != nullptr) {
+    if constexpr (MODE == GEMM_STORE && NT <= GEMM_RESID_ROW_TILES) {
+      if (g.row_ssq == nullptr && g.splits == 1) return launch_ks<NT, P, GEMM_RESID, GW, false>(g, st, tm);
+    }
+    return hipErrorInvalidValue;
+  }
   if (g.row_ssq != nullptr) return launch_ks<NT, P, MODE, GW, true>(g, st, tm);
   return launch_ks<NT, P, MODE, GW, false>(g, st, tm);
 }
@@ -508,7 +571,8 @@ hipError_t launch_gemm_mfma(const GemmArgs &args, hipStream_t st, KernelTimer tm
   g.end0 = g.seg[0].out_tiles;
   g.end1 = g.end0 + g.seg[1].out_tiles;
   g.split_kt = (g.K / 32 + g.splits - 1) / g.splits;
-  if (g.row_ssq != nullptr && g.n_ssq > MOST_SSQ) return hipErrorInvalidValue;
+  if (g.row_ssq != nullptr && (g.n_ssq > gemm_most_ssq((g.n + 15) / 16) || g.n_ssq % 4 != 0 || !starts_on_16(g.row_ssq)))
+    return hipErrorInvalidValue;
   switch ((g.n + 15) / 16) {
   case 1: return launch_nt<1>(g, st, tm);
   case 2: return launch_nt<2>(g, st, tm);

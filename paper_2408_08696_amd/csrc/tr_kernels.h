@@ -4,7 +4,8 @@
 
 namespace tr {
 
-enum GemmMode { GEMM_STORE = 0, GEMM_ROPE = 1 /* GEMM_STORE with GemmRope, picked by the launch */, GEMM_SWIGLU = 2 };
+enum GemmMode { GEMM_STORE = 0, GEMM_ROPE = 1 /* GEMM_STORE with GemmRope, picked by the launch */, GEMM_SWIGLU = 2,
+                GEMM_RESID = 3 /* GEMM_STORE with GemmResid, likewise */ };
 
 // Streaming store for activations that the next kernel reads once: written through as issued, so the
 // kernel does not end with dirty L2 lines to write back before its successor may start (the consumers
@@ -49,11 +50,6 @@ __device__ inline void wait_tiles() {
   static_assert(left >= 0 && left < 64, "six bits of vmcnt");
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(left) : "memory");
 }
-// The same for single words: lane l's four bytes at gbase + voff land at lds_off + 4 l; voff of a lane that is off is unused.
-__device__ inline void word_to_lds(uint32_t lds_off, uint32_t voff, uint64_t gbase) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_off), "v"(voff), "s"(gbase)
-               : "memory");
-}
 __device__ inline void meet_waves() { asm volatile("s_barrier" ::: "memory"); }
 
 struct GemmSeg {
@@ -75,6 +71,16 @@ struct GemmRope {
   int32_t H, Hkv, hd, cap, tiled;
 };
 
+// Optional epilogue of the projections that feed the residual stream (GEMM_STORE, splits == 1, x != nullptr): instead of storing y
+// for k_add_frag, add it to x and write the next projection's operand and sums of squares.
+struct GemmResid {
+  float *x;             // [n, ldy] residual stream, read and written
+  const bf16_t *gain;   // [ldy] of the normalisation that follows
+  bf16_t *xg_frag;      // bf16(x * gain), fragment order over ceil(n / 16) row tiles; rows past n zero
+  float *ssq;           // [n, ld_ssq] sums of x^2 over each workgroup's out-tiles, zeros behind the last
+  int32_t ld_ssq;       // groups rounded up to a multiple of 4
+};
+
 // y[n, O] = a[n, K] * W^T over the concatenation of up to three weight matrices (out-feature axis).
 //   GEMM_STORE : y[split][row * ldy + o] = partial sum of that K-split (float32, row-major)
 //   GEMM_SWIGLU: h_frag = bf16(silu(a W_gate^T) * (a W_up^T)) in fragment order over (k = o);
@@ -91,7 +97,8 @@ struct GemmArgs {
   size_t split_stride; // floats between consecutive partial results
   bf16_t *h_frag;
   int32_t mode;
-  // optional RMS scale applied to output row r: 1/sqrt(sum_c row_ssq[r*n_ssq + c] / norm_dim + eps)
+  // optional RMS scale applied to output row r: 1/sqrt(sum_c row_ssq[r*n_ssq + c] / norm_dim + eps); in a step n_ssq is a multiple
+  // of 4 and row_ssq starts on 16 bytes (sums that a row does not have are zeros)
   const float *row_ssq;
   int32_t n_ssq, norm_dim;
   float eps;
@@ -102,6 +109,7 @@ struct GemmArgs {
   int32_t end0, end1;       // first out-tiles of the second and third matrix (filled by launch_gemm_mfma)
   int32_t split_kt;         // k-tiles of a K-split (filled by launch_gemm_mfma)
   GemmRope rope;            // Q/K/V epilogue (see above), off when rope.q == nullptr
+  GemmResid resid;          // residual epilogue (see above), off when resid.x == nullptr
 };
 
 // Fills g.total_tiles, g.tiles_per_wg, g.groups and g.splits (<= max_splits; 1 for GEMM_SWIGLU).
@@ -115,6 +123,19 @@ inline void gemm_plan(GemmArgs &g, int32_t max_splits) {
               &g.groups, &g.splits);
 }
 
+// Whether a step's o and down update the residual stream in their own epilogue (GemmResid) instead of leaving partial sums to
+// k_add_frag: from whole sums of up to two row tiles, with a workgroup for most compute units.  One kernel then costs 0.4 us more,
+// as does the one behind it for its 256 sums of squares per row instead of 4, and the launch of 4.6 to 5 us is gone.  us per layer,
+// both o and down, k_add_frag / this: 7B width, 1 row 34.4 / 25.6; 15 rows 34.4 / 25.9.
+// More rows are split over k, and the sums of the shares are no cheaper to bring together inside the launch: 80 rows, 7B o and down 17.0 and
+// 26.4 us with k_add_frag, 16.6 and 25.8 with sums that the waves of a group send each other, and 2.6 more in the kernels behind.
+constexpr int GEMM_RESID_ROW_TILES = 2;
+// partial sums of squares per row that a step's projections take at nt row tiles
+constexpr int gemm_most_ssq(int nt) { return nt <= GEMM_RESID_ROW_TILES ? 256 : 8; }
+inline bool gemm_updates_residual(int32_t n, int32_t groups, int32_t splits) {
+  const int nt = (n + 15) / 16;
+  return splits == 1 && nt <= GEMM_RESID_ROW_TILES && groups >= 200 && groups <= gemm_most_ssq(nt);
+}
 bool gemm_mfma_supported(int32_t n, int32_t K, int32_t O);
 hipError_t launch_gemm_mfma(const GemmArgs &g, hipStream_t st, KernelTimer tm = KernelTimer{});
 // rope_hd > 0: packed row h*rope_hd + 2j + b takes source row h*rope_hd + j + b*rope_hd/2 (query / key

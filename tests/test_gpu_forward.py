@@ -789,6 +789,35 @@ def test_step_projections_in_shares_of_k(d, F, shared, nodes):
         assert float(over.max()) < 1.01, (n, float(over.max()))
 
 
+@pytest.mark.parametrize("d,F,groups", [(3232, 256, 202), (4064, 512, 254), (4096, 256, 256), (6400, 512, 200), (8192, 256, 256)])
+def test_projections_that_update_the_residual_stream(d, F, groups):
+    """o and down of one and two row tiles, which add to the residual stream in their own epilogue: the stream behind them output by
+    output as in test_step_projections_in_shares_of_k, and the RMS scale that the sums of squares of all workgroups give (the rounding of
+    d independent outputs leaves 2^-9 / sqrt(d) of it).  Gains are powers of two, so that they round nothing."""
+    require_gpu()
+    shape = synth.ModelShape("resid", 1, d, 2, 1, 128, F, d, "bf16")
+    eye = torch.eye(d, dtype=torch.bfloat16, device="cuda")
+    gen = torch.Generator("cuda").manual_seed(d)
+    gains = [(2.0 ** torch.randint(-1, 2, (d,), device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(2)]
+    taken = 0
+    for n in (1, 2, 15, 16, 17, 31, 32, 33):
+        say("residual epilogue", d, F, n)
+        _, g, splits, kernel = tr.plan_step_projection("o_down", n, F, d)
+        taken += (g, splits, kernel) == (groups, 1, 0) and n <= 32
+        eng, w, xe = _feed_forward_step(shape, n, 6, lm_head=eye, ffn_norm=gains[0], final_norm=gains[1])
+        a = xe * gains[0].double() / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
+        lw = w["layers"][0]
+        gate, up = a @ lw["w_gate"].double().T, a @ lw["w_up"].double().T
+        add = (gate * torch.sigmoid(gate) * up).to(torch.bfloat16).double() @ lw["w_down"].double().T
+        ref = xe + add
+        got = eng.logits.double() / gains[1].double()
+        scale = (got * ref).sum(1) / (ref * ref).sum(1)
+        over = (got / scale[:, None] - ref).abs() / (2.0 ** -8 * ref.abs() + 0.02 * add.std())
+        assert float(over.max()) < 1.01, (n, float(over.max()))
+        assert float((scale * (ref.square().mean(1) + shape.rms_eps).sqrt() - 1).abs().max()) < 1e-3, n
+    assert taken >= 4
+
+
 @pytest.mark.parametrize("d,vocab,out_tiles,nodes", [
     # 201 workgroups of 8 and of 16 out-tiles, the last one partly filled, and several rounds of both
     (4096, 25632, 8, (65, 80, 97, 128)), (5152, 25632, 8, (33, 48)), (4096, 76832, 8, (81, 128)), (4096, 51232, 16, (33, 49, 128)),
