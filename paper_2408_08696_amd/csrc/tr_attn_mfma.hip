@@ -475,8 +475,7 @@ constexpr size_t ATT1_LDS_BYTES = (size_t)ATT1_WAVES * 8 * 64 * 16 + (size_t)ATT
 template <int DUMMY>
 __global__ __launch_bounds__(ATT1_WAVES * 64) void k_attn_tile(const bf16_t *__restrict__ q, const bf16_t *__restrict__ Kl,
                                                              const bf16_t *__restrict__ Vl, int32_t H, int32_t Hkv,
-                                                             int32_t cap, int32_t n, int32_t NT,
-                                                             const uint64_t *__restrict__ anc,
+                                                             int32_t cap, int32_t n, const uint64_t *__restrict__ anc,
                                                              const int32_t *__restrict__ d_len, bf16_t *__restrict__ out,
                                                              int32_t out_row_tiles) {
   extern __shared__ f32x4 att1_lds[]; // ATT1_LDS_BYTES
@@ -487,7 +486,7 @@ __global__ __launch_bounds__(ATT1_WAVES * 64) void k_attn_tile(const bf16_t *__r
   // linear id -> (head, node tile): ids that differ by 8 share a head's XCD; x = id % 8 picks the head inside
   // a block of 8 heads, y = id / 8 runs over (node tile, head block)
   const int id = blockIdx.x, x8 = id & 7, y = id >> 3;
-  const int wt = y % NT, h = (y / NT) * 8 + x8;
+  const int NT = (n + 15) / 16, wt = y % NT, h = (y / NT) * 8 + x8;
   if (h >= H) return; // uniform over the workgroup (H not a multiple of 8)
   const int hk = h / (H / Hkv);
 
@@ -745,7 +744,7 @@ hipError_t launch_attn_mfma(const bf16_t *q, const bf16_t *Kl, const bf16_t *Vl,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATT1_LDS_BYTES) == hipSuccess;
     if (!once) return hipErrorInvalidValue;
     return launch(k_attn_tile<0>, dim3(((H + 7) / 8) * 8 * NT), dim3(ATT1_WAVES * 64), ATT1_LDS_BYTES, st, tm, q, Kl, Vl,
-                  H, Hkv, cap, n, NT, anc, d_len, out, out_row_tiles);
+                  H, Hkv, cap, n, anc, d_len, out, out_row_tiles);
   }
   const int hpw = attn_heads_per_wg(H, Hkv, n);
   const int nsplit = attn_choose_splits(H / hpw, len_bound);

@@ -114,8 +114,12 @@ __device__ inline T *hold(T *p) {
   return (T *)g;
 }
 
+// What the first weight tiles need leads the arguments: 14 words, which come in scalar registers with the wave.  w1: the second
+// matrix of Q/K/V or gate/up, w2: the third of Q/K/V.
 template <int NT, int NW, int MODE, int GW, bool SCALED>
-__global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
+__global__ __launch_bounds__(GW * 64) void k_gemm_mfma(const bf16_t *w0, const bf16_t *w1, const bf16_t *a_frag, const bf16_t *w2,
+                                                       int32_t KT, int32_t part_q, int32_t part_rem, int32_t split_kt, int32_t end0,
+                                                       int32_t end1, GemmArgs g) {
   // GEMM_ROPE is GEMM_STORE with the fused Q/K/V epilogue: its rotary factors and the committed length are asked for behind
   // the first weight tiles, so that the tail has no load left (it took three dependent round trips there)
   // SWIGLU: NW = 2P; weight tiles 0..P-1 come from the gate matrix, P..2P-1 from the up matrix
@@ -124,7 +128,6 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   extern __shared__ float red[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // in a scalar register: the k-loop's branches are uniform
-  const int KT = g.K / 32;
 
   // out-tiles owned by this workgroup: the T tiles are dealt to the G workgroups in contiguous ranges of
   // T/G tiles, the first T%G of them one longer (the host picks G >= T/P, so no range exceeds P).  Tiles
@@ -135,12 +138,10 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   // step of the 7B shape with 1 / 128 nodes 3003 / 4949 -> 2955 / 4849 us (runs of one side differ by 0.8 / 0.4 %); with 80 nodes
   // and the step of the 13B shape the difference is within that of the runs.
   const int bx = blockIdx.x;
-  const int tile0 = bx * g.part_q + (bx < g.part_rem ? bx : g.part_rem);
-  const int n_valid = g.part_q + (bx < g.part_rem ? 1 : 0);
+  const int tile0 = bx * part_q + (bx < part_rem ? bx : part_rem);
+  const int n_valid = part_q + (bx < part_rem ? 1 : 0);
   typedef __attribute__((address_space(1))) const u32x4 *global_tiles; // said outright: the masks below hide it
   global_tiles wbase[NW];
-  const bf16_t *w0 = g.seg[0].w, *w1 = MODE == GEMM_SWIGLU ? g.w2 : g.seg[1].w, *w2 = g.seg[2].w;
-  const int end0 = g.end0, end1 = g.end1;
 #pragma unroll
   for (int u = 0; u < P; ++u) {
     const int t = tile0 + (u < n_valid ? u : 0); // unused slots re-read the first tile (a cache hit), never stored
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
     wbase[u] = (global_tiles)reinterpret_cast<const u32x4 *>(w) + (size_t)at * KT * 64 + lane;
     if (MODE == GEMM_SWIGLU) wbase[P + u] = (global_tiles)reinterpret_cast<const u32x4 *>(w1) + (size_t)at * KT * 64 + lane;
   }
-  const u32x4 *abase = reinterpret_cast<const u32x4 *>(g.a_frag) + lane;
+  const u32x4 *abase = reinterpret_cast<const u32x4 *>(a_frag) + lane;
 
   // this workgroup's K-range and this wave's k-tiles in it: kt = kt0 + wave + 8*i
   const int split = blockIdx.y;
@@ -163,8 +164,8 @@ __global__ __launch_bounds__(GW * 64) void k_gemm_mfma(GemmArgs g) {
   float *const y = MODE == GEMM_STORE ? hold(g.y + (size_t)split * g.split_stride) : nullptr;
   const int ldy = MODE == GEMM_STORE ? hold(g.ldy) : 0;
   bf16_t *const h_frag = MODE == GEMM_SWIGLU ? hold(g.h_frag) : nullptr;
-  const int kt0 = split * g.split_kt;
-  const int kt1 = kt0 + g.split_kt < KT ? kt0 + g.split_kt : KT;
+  const int kt0 = split * split_kt;
+  const int kt1 = kt0 + split_kt < KT ? kt0 + split_kt : KT;
   const int first = kt0 + wave;
   const int nsteps = first < kt1 ? (kt1 - first + GW - 1) / GW : 0;
 
@@ -502,7 +503,10 @@ static hipError_t launch_ks(const GemmArgs &g, hipStream_t st, KernelTimer tm) {
     }();
     if (!once) return hipErrorInvalidValue;
   }
-  return launch(k_gemm_mfma<NT, NW, MODE, GW, SCALED>, dim3(g.groups, g.splits), dim3(GW * 64), smem, st, tm, g);
+  const int32_t end0 = g.seg[0].out_tiles, split_kt = (g.K / 32 + g.splits - 1) / g.splits;
+  return launch(k_gemm_mfma<NT, NW, MODE, GW, SCALED>, dim3(g.groups, g.splits), dim3(GW * 64), smem, st, tm, g.seg[0].w,
+                MODE == GEMM_SWIGLU ? g.w2 : g.seg[1].w, g.a_frag, g.seg[2].w, g.K / 32, g.part_q, g.part_rem, split_kt, end0,
+                end0 + g.seg[1].out_tiles, g);
 }
 // the epilogue's RMS scale is a compile-time property: without it the tail needs no scale hand-out and
 // the whole of LDS can hold partial tiles
@@ -568,9 +572,6 @@ hipError_t launch_gemm_mfma(const GemmArgs &args, hipStream_t st, KernelTimer tm
   GemmArgs g = args;
   g.part_q = g.total_tiles / g.groups;
   g.part_rem = g.total_tiles % g.groups;
-  g.end0 = g.seg[0].out_tiles;
-  g.end1 = g.end0 + g.seg[1].out_tiles;
-  g.split_kt = (g.K / 32 + g.splits - 1) / g.splits;
   if (g.row_ssq != nullptr && (g.n_ssq > gemm_most_ssq((g.n + 15) / 16) || g.n_ssq % 4 != 0 || !starts_on_16(g.row_ssq)))
     return hipErrorInvalidValue;
   switch ((g.n + 15) / 16) {

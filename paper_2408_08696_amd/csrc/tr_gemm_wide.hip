@@ -72,8 +72,11 @@ __device__ inline void for_each_step(F f, std::integer_sequence<int, J...>) {
 // KG = 2: two such groups of waves take even and odd k-tiles (both in each step of the ring, T tiles each) and the first adds the
 // other's sums at the end; WR * WC * KG = 8.
 // SwiGLU: an out-tile pair is (gate tile, up tile) of the same 16 features.
+// What the first tiles need leads the arguments and comes in scalar registers with the wave (w1: up, or the second of Q/K/V).
 template <int MODE, bool SCALED, int RP2, int NP2, int WR, int WC, int D, int CHAIN, int KG>
-__global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32_t row_tiles) {
+__global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(const bf16_t *a_frag, const bf16_t *w0, const bf16_t *w1,
+                                                              int32_t KT, int32_t row_tiles, int32_t groups, int32_t splits,
+                                                              int32_t part_q, int32_t part_rem, GemmArgs g) {
   constexpr bool ROPE = MODE == GEMM_ROPE; // GEMM_STORE with the fused Q/K/V epilogue
   constexpr int RB = 2 * RP2 * WR, NW = 2 * NP2 * WC; // row tiles and out-tiles of the workgroup
   constexpr int T = RB + NW;                          // tiles per k-step
@@ -86,20 +89,19 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // in a scalar register: what depends on it alone is uniform
   const int kg = wave / (WR * WC), wr = wave / WC % WR, wc = wave % WC;
-  const int KT = g.K / 32;
   // linear id -> (k-split, out-tile group, row block): ids that differ by 8 share an XCD, so the row blocks of
   // a group are 8 apart; groups are numbered (id % 8) + 8 * (id / (8 * row_blocks))
   const int row_blocks = (row_tiles + RB - 1) / RB;
-  const int per_split = ((g.groups + 7) / 8) * 8 * row_blocks;
+  const int per_split = ((groups + 7) / 8) * 8 * row_blocks;
   const int split = blockIdx.x / per_split, id = blockIdx.x - split * per_split;
   const int bx = (id & 7) + 8 * (id / (8 * row_blocks));
   const int rb = (id >> 3) % row_blocks;
-  if (bx >= g.groups) return; // uniform over the workgroup (group count not a multiple of 8)
-  const int per_k = (KT + g.splits - 1) / g.splits;
+  if (bx >= groups) return; // uniform over the workgroup (group count not a multiple of 8)
+  const int per_k = (KT + splits - 1) / splits;
   const int k0 = split * per_k, k1 = k0 + per_k < KT ? k0 + per_k : KT;
   const int nk = (k1 - k0) / KG; // >= 1: the launch leaves no split empty; KG = 2: an even number of k-tiles
-  const int tile0 = bx * g.part_q + (bx < g.part_rem ? bx : g.part_rem);
-  const int n_valid = g.part_q + (bx < g.part_rem ? 1 : 0);
+  const int tile0 = bx * part_q + (bx < part_rem ? bx : part_rem);
+  const int n_valid = part_q + (bx < part_rem ? 1 : 0);
 
   // The tiles of a k-step this wave loads: tile j = wave + 8 i, the first RB of them row tiles, then out-tiles (with
   // T = 8 c + 4 the last four are loaded by two waves each, half by half: every wave then has the same number of loads
@@ -115,18 +117,22 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(GemmArgs g, int32
     if (j < RB) {
       int rt = rb * RB + j;
       rt = rt < row_tiles ? rt : row_tiles - 1;
-      src[i] = reinterpret_cast<uint64_t>(g.a_frag) + ((uint64_t)(k0 + k) * row_tiles + rt) * 1024;
+      src[i] = reinterpret_cast<uint64_t>(a_frag) + ((uint64_t)(k0 + k) * row_tiles + rt) * 1024;
       step[i] = (uint32_t)row_tiles * KG * 1024;
     } else {
       const int u = j - RB;
       const int uu = MODE == GEMM_SWIGLU ? u >> 1 : u;
       int t = tile0 + (uu < n_valid ? uu : 0);
-      int sidx = 0;
-      while (sidx + 1 < g.n_seg && t >= g.seg[sidx].out_tiles) {
-        t -= g.seg[sidx].out_tiles;
-        ++sidx;
+      const bf16_t *mat = MODE == GEMM_SWIGLU && (u & 1) ? w1 : w0;
+      if constexpr (ROPE) {
+        if (t >= g.seg[0].out_tiles + g.seg[1].out_tiles) {
+          t -= g.seg[0].out_tiles + g.seg[1].out_tiles;
+          mat = g.seg[2].w;
+        } else if (t >= g.seg[0].out_tiles) {
+          t -= g.seg[0].out_tiles;
+          mat = w1;
+        }
       }
-      const bf16_t *mat = (MODE == GEMM_SWIGLU && (u & 1)) ? g.w2 : g.seg[sidx].w;
       src[i] = reinterpret_cast<uint64_t>(mat) + ((uint64_t)t * KT + k0 + k) * 1024;
       step[i] = KG * 1024;
     }
@@ -432,7 +438,8 @@ static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hip
   static bool once = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                          smem) == hipSuccess;
   if (!once) return hipErrorInvalidValue;
-  return launch(kernel, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g, row_tiles);
+  return launch(kernel, dim3(grid), dim3(WIDE_WAVES * 64), smem, st, tm, g.a_frag, g.seg[0].w,
+                MODE == GEMM_SWIGLU ? g.w2 : g.seg[1].w, g.K / 32, row_tiles, g.groups, g.splits, g.part_q, g.part_rem, g);
 }
 template <int RP2, int NP2, int WR, int WC, int D>
 static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {

@@ -12,20 +12,21 @@ namespace tr {
 // D-1 dependent gather rounds are separated by workgroup barriers.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(TR_MAX_NODES) void k_build_tree(const int32_t *__restrict__ M, int32_t V,
-                                                             int32_t k, TreeDev t,
-                                                             const int32_t *__restrict__ d_root,
-                                                             int32_t *__restrict__ S) {
+                                                             int32_t k, const int32_t *__restrict__ parent,
+                                                             const int32_t *__restrict__ rank,
+                                                             const int32_t *__restrict__ depth, int32_t n_nodes, int32_t n_layers,
+                                                             const int32_t *__restrict__ d_root, int32_t *__restrict__ S) {
   __shared__ int32_t s[TR_MAX_NODES];
   const int i = threadIdx.x;
-  const bool live = i < t.n_nodes;
-  const int par = live ? t.parent[i] : -1;
-  const int rk = live ? t.rank[i] : 0;
-  const int dep = live ? t.depth[i] : -1;
+  const bool live = i < n_nodes;
+  const int par = live ? parent[i] : -1;
+  const int rk = live ? rank[i] : 0;
+  const int dep = live ? depth[i] : -1;
   if (i == 0) {
     int r = *d_root;
     s[0] = r < 0 ? 0 : (r >= V ? V - 1 : r);
   }
-  for (int d = 1; d < t.n_layers; ++d) {
+  for (int d = 1; d < n_layers; ++d) {
     __syncthreads();
     if (dep == d) { // a stored candidate outside [0, V) (a caller-made top-k buffer) is clamped like the root
       const int tk = M[(size_t)s[par] * k + rk];
@@ -37,8 +38,8 @@ __global__ __launch_bounds__(TR_MAX_NODES) void k_build_tree(const int32_t *__re
 }
 
 hipError_t launch_build_tree(tr_ctx *c, const int32_t *d_root, int32_t *d_S, hipStream_t st) {
-  return launch(k_build_tree, dim3(1), dim3(TR_MAX_NODES), 0, st, c->prof.next(PC_BUILD), c->d_M, c->V, c->k, c->tree,
-                d_root, d_S);
+  return launch(k_build_tree, dim3(1), dim3(TR_MAX_NODES), 0, st, c->prof.next(PC_BUILD), c->d_M, c->V, c->k, c->tree.parent,
+                c->tree.rank, c->tree.depth, c->tree.n_nodes, c->tree.n_layers, d_root, d_S);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -438,12 +439,14 @@ hipError_t launch_matrix_update(const tr_ctx *c, const int32_t *d_S, const int32
 // tokens are compared four at a time.  With one thread walking the 80 nodes for the path and every thread walking them
 // for the repeats the launch took 15.6 us (21.9 at 128 nodes).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(int32_t *__restrict__ M, int32_t V, int32_t k,
-                                                                TreeDev t, const int32_t *__restrict__ S,
+__global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(const int32_t *__restrict__ S,
                                                                 const int32_t *__restrict__ topk,
                                                                 const int32_t *__restrict__ tokens,
-                                                                int32_t *__restrict__ d_len,
-                                                                int32_t *__restrict__ step_L,
+                                                                const uint64_t *__restrict__ anc,
+                                                                const int32_t *__restrict__ depth,
+                                                                const int32_t *__restrict__ parent, int32_t n_nodes, int32_t k,
+                                                                int32_t *__restrict__ d_len, int32_t V,
+                                                                int32_t *__restrict__ M, int32_t *__restrict__ step_L,
                                                                 tr_step_out *__restrict__ out,
                                                                 tr_step_out *__restrict__ host, int32_t mode) {
   __shared__ __align__(16) int32_t sS[TR_MAX_NODES];
@@ -452,11 +455,11 @@ __global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(int32_t *__restr
   __shared__ uint64_t mbits[2];
   __shared__ int32_t wkey[2];
   const int i = threadIdx.x;
-  const bool live = i < t.n_nodes;
+  const bool live = i < n_nodes;
   // everything that does not depend on the match is loaded up front, in one round trip
-  const uint64_t anc0 = live ? t.anc[2 * i] : 0, anc1 = live ? t.anc[2 * i + 1] : 0;
-  const int dep = live ? t.depth[i] : 0;
-  const int par = live && i > 0 ? t.parent[i] : 0;
+  const uint64_t anc0 = live ? anc[2 * i] : 0, anc1 = live ? anc[2 * i + 1] : 0;
+  const int dep = live ? depth[i] : 0;
+  const int par = live && i > 0 ? parent[i] : 0;
   const int L0 = i == 0 ? *d_len : 0;
   int tk = -1;
   if (live) {
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(int32_t *__restr
     if (!on_path) sS[i] = -1;
     __syncthreads();
   }
-  scatter_rows(M, k, t.n_nodes, sS, topk, i, mode);
+  scatter_rows(M, k, n_nodes, sS, topk, i, mode);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -657,8 +660,9 @@ hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logit
 
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk,
                                 const int32_t *d_tokens, tr_step_out *d_out, tr_step_out *host_out, hipStream_t st) {
-  hipError_t e = launch(k_accept_update, dim3(1), dim3(TR_MAX_NODES), 0, st, c->prof.next(PC_ACCEPT), c->d_M, c->V, c->k,
-                        c->tree, d_S, d_topk, d_tokens, kv->d_len, c->d_step_L, d_out, host_out, c->update_mode);
+  hipError_t e = launch(k_accept_update, dim3(1), dim3(TR_MAX_NODES), 0, st, c->prof.next(PC_ACCEPT), d_S, d_topk, d_tokens,
+                        c->tree.anc, c->tree.depth, c->tree.parent, c->tree.n_nodes, c->k, kv->d_len, c->V, c->d_M, c->d_step_L,
+                        d_out, host_out, c->update_mode);
   if (e != hipSuccess) return e;
   const int blocks = kv->n_layers * kv->n_kv_heads;
   const size_t esz = dtype_size(kv->dtype);

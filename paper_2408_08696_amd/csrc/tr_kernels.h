@@ -106,8 +106,6 @@ struct GemmArgs {
   int32_t tiles_per_wg; // most out-tiles (SWIGLU: gate/up tile pairs) a workgroup handles per pass
   int32_t groups;       // workgroups per K-split; each owns a contiguous ~total_tiles/groups out-tiles
   int32_t part_q, part_rem; // total_tiles / groups and total_tiles % groups (filled by launch_gemm_mfma)
-  int32_t end0, end1;       // first out-tiles of the second and third matrix (filled by launch_gemm_mfma)
-  int32_t split_kt;         // k-tiles of a K-split (filled by launch_gemm_mfma)
   GemmRope rope;            // Q/K/V epilogue (see above), off when rope.q == nullptr
   GemmResid resid;          // residual epilogue (see above), off when resid.x == nullptr
 };

@@ -99,8 +99,10 @@ __device__ inline u32x4 normed_chunk(const float *x, const T *gain, int k, int K
   return r;
 }
 
+// What the loads need leads the arguments: 14 words, which come in scalar registers with the wave.  n_hd: n, with ROWS_ROPE n + 2^16 hd.
 template <typename T, int RT, bool NORM, int EPI>
-__global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(RowsArgs p) {
+__global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(const void *a, const void *gain, const void *w0, const void *w1, const void *w2,
+                                                          int32_t K, int32_t O, int32_t n_hd, int32_t H, RowsArgs p) {
   constexpr int E = 16 / (int)sizeof(T), KSTEP = 4 * E;
   constexpr int PF = RT == 1 ? 6 : (RT == 2 ? 4 : 3); // k-steps a wave loads before it multiplies
   __shared__ f32x4 part[ROWS_WAVES][RT][64];
@@ -109,29 +111,31 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(RowsArgs p) {
   const int r = lane & 15, g = lane >> 4;
   const int tile = blockIdx.x, row0 = blockIdx.y * RT * 16;
 
+  const int n = EPI == ROWS_ROPE ? n_hd & 0xFFFF : n_hd;
+
   // the weight row this lane loads: output r of the tile (outputs past the end repeat the last one, never stored)
   const T *wrow;
   {
     const int pair = tile * 8 + 2 * (r >> 2) + (r & 1), second = (r >> 1) & 1;
     if (EPI == ROWS_ROPE) {
-      const int half = p.hd / 2, pc = pair < p.O / 2 ? pair : p.O / 2 - 1;
+      const int hd = n_hd >> 16, half = hd / 2, pc = pair < O / 2 ? pair : O / 2 - 1, Hkv = (O / hd - H) / 2;
       const int head = pc / half, i = pc - head * half + second * half;
-      const int seg = head < p.H ? 0 : (head < p.H + p.Hkv ? 1 : 2);
-      const int base = seg == 0 ? 0 : (seg == 1 ? p.H : p.H + p.Hkv);
-      wrow = (const T *)p.w[seg] + (size_t)((head - base) * p.hd + i) * p.K;
+      const int seg = head < H ? 0 : (head < H + Hkv ? 1 : 2);
+      const int base = seg == 0 ? 0 : (seg == 1 ? H : H + Hkv);
+      wrow = (const T *)(seg == 0 ? w0 : seg == 1 ? w1 : w2) + (size_t)((head - base) * hd + i) * K;
     } else if (EPI == ROWS_SWIGLU) {
-      const int f = pair < p.O ? pair : p.O - 1;
-      wrow = (const T *)p.w[second] + (size_t)f * p.K;
+      const int f = pair < O ? pair : O - 1;
+      wrow = (const T *)(second ? w1 : w0) + (size_t)f * K;
     } else {
-      const int o = tile * 16 + r < p.O ? tile * 16 + r : p.O - 1;
-      wrow = (const T *)p.w[0] + (size_t)o * p.K;
+      const int o = tile * 16 + r < O ? tile * 16 + r : O - 1;
+      wrow = (const T *)w0 + (size_t)o * K;
     }
   }
   size_t arow[RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t) {
     const int row = row0 + 16 * t + r;
-    arow[t] = (size_t)(row < p.n ? row : p.n - 1) * p.K;
+    arow[t] = (size_t)(row < n ? row : n - 1) * K;
   }
   f32x4 acc[PF][RT];
   float ss[RT];
@@ -141,16 +145,16 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(RowsArgs p) {
     for (int s = 0; s < PF; ++s) acc[s][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     ss[t] = 0.f;
   }
-  for (int k0 = wave * KSTEP; k0 < p.K; k0 += ROWS_WAVES * PF * KSTEP) {
+  for (int k0 = wave * KSTEP; k0 < K; k0 += ROWS_WAVES * PF * KSTEP) {
     u32x4 wq[PF], aq[PF][RT];
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
       const int k = k0 + j * ROWS_WAVES * KSTEP + g * E;
-      wq[j] = load_chunk<T>(wrow, k, p.K);
+      wq[j] = load_chunk<T>(wrow, k, K);
 #pragma unroll
       for (int t = 0; t < RT; ++t) {
-        if constexpr (NORM) aq[j][t] = normed_chunk<T>((const float *)p.a + arow[t], (const T *)p.gain, k, p.K, ss[t]);
-        else aq[j][t] = load_chunk<T>((const T *)p.a + arow[t], k, p.K);
+        if constexpr (NORM) aq[j][t] = normed_chunk<T>((const float *)a + arow[t], (const T *)gain, k, K, ss[t]);
+        else aq[j][t] = load_chunk<T>((const T *)a + arow[t], k, K);
       }
     }
 #pragma unroll
@@ -233,14 +237,19 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void k_rows(RowsArgs p) {
 template <typename T, bool NORM, int EPI>
 static hipError_t launch_rows_rt(const RowsArgs &p, hipStream_t st, KernelTimer tm) {
   const int NT = (p.n + 15) / 16;
+  if (EPI == ROWS_ROPE && (p.n > 0xFFFF || p.hd > 0x7FFF)) return hipErrorInvalidValue; // a step: at most TR_MAX_NODES rows
+  const int32_t n_hd = EPI == ROWS_ROPE ? p.n + (p.hd << 16) : p.n;
   const int tiles = EPI == ROWS_SWIGLU ? (p.O + 7) / 8 : (p.O + 15) / 16;
   // More row tiles a workgroup read a weight less often, but a wave's loads and products per k-step are as many more, and that
   // chain is the launch's time while every workgroup has a compute unit to itself: the fewest that still do so.  float32, 64
   // rows, us with four tiles / one: 512 -> 512 9.5 / 6.5, 2048 -> 512 22.9 / 14.3 (a wave per output: 8.5 and 19.4).
-  if (NT == 1 || tiles * NT <= 256) return launch(k_rows<T, 1, NORM, EPI>, dim3(tiles, NT), dim3(ROWS_WAVES * 64), 0, st, tm, p);
-  if (NT == 2 || tiles * ((NT + 1) / 2) <= 256)
-    return launch(k_rows<T, 2, NORM, EPI>, dim3(tiles, (NT + 1) / 2), dim3(ROWS_WAVES * 64), 0, st, tm, p);
-  return launch(k_rows<T, 4, NORM, EPI>, dim3(tiles, (NT + 3) / 4), dim3(ROWS_WAVES * 64), 0, st, tm, p);
+  auto go = [&](auto kernel, int row_blocks) {
+    return launch(kernel, dim3(tiles, row_blocks), dim3(ROWS_WAVES * 64), 0, st, tm, p.a, p.gain, p.w[0], p.w[1], p.w[2], p.K, p.O, n_hd,
+                  p.H, p);
+  };
+  if (NT == 1 || tiles * NT <= 256) return go(k_rows<T, 1, NORM, EPI>, NT);
+  if (NT == 2 || tiles * ((NT + 1) / 2) <= 256) return go(k_rows<T, 2, NORM, EPI>, (NT + 1) / 2);
+  return go(k_rows<T, 4, NORM, EPI>, (NT + 3) / 4);
 }
 
 template <typename T>
