@@ -297,7 +297,15 @@ __device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 
     }
     pk = uint4{o[0], o[1], o[2], o[3]};
   }
-  if (j < d) *reinterpret_cast<uint4 *>(xg_frag + act_frag_index(row, j, row_tiles)) = pk;
+  // Written through up to 1 MiB.  us a step, plain / through: 7B width, 80 nodes (640 KiB) 3713 / 3641, 13B (20 layers, 800 KiB) 3362 /
+  // 3344, 7B, 128 nodes (1 MiB) 4821 / 4805, 70B (6 layers, 80 nodes, 1.3 MiB) 2411 / 2419; prompt of 511 tokens at 7B width (16 layers)
+  // 3913 / 3986.  7B, 80 nodes, without the streaming hint 3685, with that alone 3727; with the rows of a line on one XCD 3726 plain,
+  // 3668 through.  No gain in the partial sums, x, the queries or SwiGLU's output.
+  const size_t at = act_frag_index(row, j, row_tiles);
+  if (j < d) {
+    if (row_tiles * 16 * d <= (1 << 20) / 2) store_through(xg_frag, (uint32_t)at * 2, pk);
+    else *reinterpret_cast<uint4 *>(xg_frag + at) = pk;
+  }
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();

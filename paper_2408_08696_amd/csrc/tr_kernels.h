@@ -17,6 +17,15 @@ __device__ inline void store_stream(bf16_t *p, ushort4 v) {
                               reinterpret_cast<u32x2s *>(p));
 }
 
+// Streaming and written through at once (sc1 nt), base uniform over the wave: for a step's residual kernel, in whose operand 128-byte
+// lines take 16 bytes each from eight rows and so from workgroups on eight XCDs.  Left dirty in eight L2s they are written back
+// when the kernel ends, and the projection behind it waits.
+__device__ inline void store_through(void *base, uint32_t byte, uint4 v) {
+  typedef __attribute__((ext_vector_type(4))) uint32_t u4;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFF, 0x00027000);
+  __builtin_amdgcn_raw_buffer_store_b128(u4{v.x, v.y, v.z, v.w}, rsrc, byte, 0, 18);
+}
+
 // Two floats rounded to bf16 (nearest even) in one word, by the hardware's packed conversion.
 __device__ inline uint32_t bf16_pair(float lo, float hi) {
   typedef __attribute__((ext_vector_type(2))) float f2;
