@@ -556,13 +556,26 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
   TR_TRY(launch(k_embed_frag, dim3(RT * 16, nch + 1), dim3(128), 0, st, no_timer, (const T *)m.embed, m.vocab, tok,
                 (const int32_t *)nullptr, kv.d_len, hd, m.rope_theta, x, rope, (const T *)m.layers[0].attn_norm, n, d, RT,
                 xn, ssq, nch));
-  int pending = 0;
-  auto add_norm = [&](const void *gain) {
+  // Without partial sums of either o or down, ypart holds the sums of squares they leave (a row of x is as long as its sums at least).
+  const bool fused = wide_updates_residual(n, hq, d / 16, max_splits) && wide_updates_residual(n, F, d / 16, max_splits);
+  float *const fused_ssq = (float *)(((uintptr_t)ypart + 15) & ~(uintptr_t)15);
+  int n_ssq = nch;
+  auto residual = [&](const T *a, int K, const void *wt, const void *gain) { // x += a * wt^T and the next operand
+    GemmArgs g{};
+    g.a_frag = a; g.n = n; g.K = K;
+    g.seg[0] = GemmSeg{(const T *)wt, d / 16};
+    g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
+    if (fused) {
+      ssq = fused_ssq;
+      g.resid = GemmResid{x, (const T *)gain, xn, ssq, 0};
+      return launch_gemm_wide(g, 1, &n_ssq, st);
+    }
+    int pending = 0;
+    TR_TRY(launch_gemm_wide(g, max_splits, &pending, st));
     return launch_add_frag(pending, nch, x, ypart, ystride, (const T *)gain, n, d, RT, xn, ssq, nch, no_timer, st);
   };
   for (int l = 0; l < m.n_layers; ++l) {
     const tr_layer &lw = m.layers[l];
-    if (l > 0) TR_TRY(add_norm(lw.attn_norm));
     {
       GemmArgs g{};
       g.a_frag = xn; g.n = n; g.K = d;
@@ -570,7 +583,7 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
       g.seg[1] = GemmSeg{(const T *)lw.wk, hk / 16};
       g.seg[2] = GemmSeg{(const T *)lw.wv, hk / 16};
       g.n_seg = 3; g.mode = GEMM_STORE;
-      g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
+      g.row_ssq = ssq; g.n_ssq = n_ssq; g.norm_dim = d; g.eps = m.rms_eps;
       g.rope = GemmRope{q, (T *)kv.k + (size_t)l * lsz, (T *)kv.v + (size_t)l * lsz, rope, kv.d_len,
                         H, Hkv, hd, kv.capacity, kv.layout};
       TR_TRY(launch_gemm_wide(g, 1, nullptr, st));
@@ -578,29 +591,16 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
     if (l == m.n_layers - 1) break; // ingestion only needs the cache: nothing reads the last layer's output
     TR_TRY(launch_attn_causal(q, (const T *)kv.k + (size_t)l * lsz, (const T *)kv.v + (size_t)l * lsz, H, Hkv, kv.capacity, n,
                               kv.d_len, attn, RT, st));
-    {
-      GemmArgs g{};
-      g.a_frag = attn; g.n = n; g.K = hq;
-      g.seg[0] = GemmSeg{(const T *)lw.wo, d / 16};
-      g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      TR_TRY(launch_gemm_wide(g, max_splits, &pending, st));
-    }
-    TR_TRY(add_norm(lw.ffn_norm));
+    TR_TRY(residual(attn, hq, lw.wo, lw.ffn_norm));
     {
       GemmArgs g{};
       g.a_frag = xn; g.n = n; g.K = d;
       g.seg[0] = GemmSeg{(const T *)lw.w_gate, F / 16};
       g.n_seg = 1; g.w2 = (const T *)lw.w_up; g.h_frag = hbuf; g.mode = GEMM_SWIGLU;
-      g.row_ssq = ssq; g.n_ssq = nch; g.norm_dim = d; g.eps = m.rms_eps;
+      g.row_ssq = ssq; g.n_ssq = n_ssq; g.norm_dim = d; g.eps = m.rms_eps;
       TR_TRY(launch_gemm_wide(g, 1, nullptr, st));
     }
-    {
-      GemmArgs g{};
-      g.a_frag = hbuf; g.n = n; g.K = F;
-      g.seg[0] = GemmSeg{(const T *)lw.w_down, d / 16};
-      g.n_seg = 1; g.y = ypart; g.ldy = d; g.split_stride = ystride; g.mode = GEMM_STORE;
-      TR_TRY(launch_gemm_wide(g, max_splits, &pending, st));
-    }
+    TR_TRY(residual(hbuf, F, lw.w_down, m.layers[l + 1].attn_norm));
   }
   return hipSuccess;
 }

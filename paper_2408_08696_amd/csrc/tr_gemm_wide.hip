@@ -281,10 +281,18 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(const bf16_t *a_f
 #pragma unroll
     for (int j = 0; j < RP2; ++j) {
       const int row = 16 * (rb * RB + wr * 2 * RP2 + 2 * j) + (lane & 31);
+      const float *at = g.row_ssq + (size_t)(row < g.n ? row : g.n - 1) * g.n_ssq;
+      if (CHAIN > 0 || g.n_ssq <= 8) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int at = hb + 2 * c;
-        ssq[j][c] = g.row_ssq[(size_t)(row < g.n ? row : g.n - 1) * g.n_ssq + (at < g.n_ssq ? at : 0)];
+        for (int c = 0; c < 4; ++c) ssq[j][c] = at[hb + 2 * c < g.n_ssq ? hb + 2 * c : 0];
+      } else { // a multiple of 4, of which the row's two lanes take alternate fours
+        float4 sum = float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+        for (int c = 4 * hb; c < g.n_ssq; c += 8) {
+          const float4 q = *reinterpret_cast<const float4 *>(at + c);
+          sum.x += q.x; sum.y += q.y; sum.z += q.z; sum.w += q.w;
+        }
+        ssq[j][0] = sum.x; ssq[j][1] = sum.y; ssq[j][2] = sum.z; ssq[j][3] = sum.w;
       }
     }
     asm volatile("" ::: "memory"); // here and not where they are used
@@ -348,6 +356,54 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(const bf16_t *a_f
       __builtin_amdgcn_sched_barrier(0); // all of them on their way before the first store
     }
     if (rt >= row_tiles) continue;
+    // x += the sums, the next projection's operand and this wave's sums of squares.  Bound by memory: where a launch is one round, all
+    // workgroups read and write x at once.  us at 2048 rows, plain store + residual kernel / this: 70B o 199 + 55 / 219, down 676 + 55 / 697;
+    // prompts of 1023 and 2047 tokens at 7B width (16 layers) 6706 / 6533 and 12290 / 11970, 2047 at 13B width (8) 9092 / 8925, 4095 at
+    // 70B (4) 17720 / 17580.  Streaming hints on x lose 1 to 5 %, on the operand 0.
+    if constexpr (MODE == GEMM_RESID) {
+      const bool on = row < g.n;
+      float *const xr = g.resid.x + (size_t)(on ? row : g.n - 1) * g.ldy + (tile0 + 2 * wc * NP2) * 16 + 4 * hb;
+      const bf16_t *const gr = g.resid.gain + (tile0 + 2 * wc * NP2) * 16 + 4 * hb;
+      float4 x[NP2 * 4];
+      uint2 gain[NP2 * 4];
+#pragma unroll
+      for (int i = 0; i < NP2 * 4; ++i) { // out-tiles that the workgroup does not have read its first one again
+        const int at = 2 * wc * NP2 + (i >> 1) < n_valid ? 8 * i : -(2 * wc * NP2) * 16;
+        x[i] = *reinterpret_cast<const float4 *>(xr + at);
+        gain[i] = *reinterpret_cast<const uint2 *>(gr + at);
+      }
+      __builtin_amdgcn_sched_barrier(0); // all of them on their way before the first store
+      float ss = 0.f;
+#pragma unroll
+      for (int u2 = 0; u2 < 2 * NP2; ++u2) {
+        if (2 * wc * NP2 + u2 >= n_valid) continue;
+        const int t = tile0 + 2 * wc * NP2 + u2;
+        uint32_t w[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int q = 2 * u2 + i;
+          const f32x16 &a = acc[u2 >> 1][j];
+          const int e = 4 * (q & 3);
+          const f32x4 v = f32x4{x[q].x + a[e], x[q].y + a[e + 1], x[q].z + a[e + 2], x[q].w + a[e + 3]};
+          if (on) *reinterpret_cast<float4 *>(xr + 8 * q) = float4{v[0], v[1], v[2], v[3]};
+          ss += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+          w[i][0] = bf16_pair(v[0] * __uint_as_float(gain[q].x << 16), v[1] * __uint_as_float(gain[q].x & 0xFFFF0000u));
+          w[i][1] = bf16_pair(v[2] * __uint_as_float(gain[q].y << 16), v[3] * __uint_as_float(gain[q].y & 0xFFFF0000u));
+        }
+        uint4 e = eight_features(w[0][0], w[0][1], w[1][0], w[1][1]);
+        if (!on) e = uint4{0u, 0u, 0u, 0u};
+        const size_t fslot = ((size_t)(t >> 1) * row_tiles + rt) * 64 + r + 16 * (2 * (t & 1) + hb);
+        reinterpret_cast<uint4 *>(g.resid.xg_frag)[fslot] = e;
+      }
+      ss += __shfl_xor(ss, 32);
+      if (on && hb == 0) {
+        float *const at = g.resid.ssq + (size_t)row * g.resid.ld_ssq;
+        at[bx * WC + wc] = ss;
+        if (bx == groups - 1 && wc == WC - 1)
+          for (int c = groups * WC; c < g.resid.ld_ssq; ++c) at[c] = 0.f; // sums of no wave
+      }
+      continue;
+    }
     float sc_row = 1.0f;
     if (SCALED) { // per-row RMS scale; the row's two lanes hold alternate partial sums
       float ss = 0.f;
@@ -442,8 +498,12 @@ static hipError_t launch_ks(const GemmArgs &g, int row_tiles, unsigned grid, hip
                 MODE == GEMM_SWIGLU ? g.w2 : g.seg[1].w, g.K / 32, row_tiles, g.groups, g.splits, g.part_q, g.part_rem, g);
 }
 template <int RP2, int NP2, int WR, int WC, int D>
-static hipError_t launch_shape(const GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
+static hipError_t launch_shape(GemmArgs &g, int row_tiles, unsigned grid, hipStream_t st, KernelTimer tm) {
   if (g.mode == GEMM_SWIGLU) return launch_ks<GEMM_SWIGLU, true, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
+  if (g.resid.x != nullptr) {
+    g.resid.ld_ssq = (g.groups * WC + 3) & ~3;
+    return launch_ks<GEMM_RESID, false, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
+  }
   if (g.rope.q != nullptr) return launch_ks<GEMM_ROPE, true, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
   return launch_ks<GEMM_STORE, false, RP2, NP2, WR, WC, D, 0>(g, row_tiles, grid, st, tm);
 }
@@ -456,27 +516,18 @@ struct WideShape {
 };
 static constexpr WideShape WIDE_SHAPES[5] = {{8, 8, 0.27}, {8, 12, 0.42}, {16, 8, 0.45}, {16, 12, 0.585}, {16, 16, 0.70}};
 
-// Chooses the workgroup shape and the K-splits, fills the tile assignment and launches.  g.n is the total row count
-// (<= WIDE_MAX_ROWS); a_frag / h_frag use ceil(n / 16) row tiles; SwiGLU and Q/K/V come with the RMS scale of at most 8 partial
-// sums per row, a plain store without.  max_splits > 1 (plain store only): y[s] = y + s * split_stride receives the
-// partial sum of k-range s, and *out_splits how many the launch used.
-hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *out_splits, hipStream_t st, KernelTimer tm) {
-  GemmArgs g = args;
-  if (g.n < 1 || g.n > WIDE_MAX_ROWS || g.K % 32 != 0 || g.K < 64 || (g.row_ssq != nullptr && g.n_ssq > 8))
-    return hipErrorInvalidValue;
-  int32_t total = 0;
-  for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
-  if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
-  if ((g.mode == GEMM_SWIGLU || g.rope.q != nullptr) != (g.row_ssq != nullptr)) return hipErrorInvalidValue;
-  if (g.rope.q != nullptr && (!g.rope.tiled || g.rope.hd != 128 || g.mode != GEMM_STORE)) return hipErrorInvalidValue;
-  const bool may_split = g.row_ssq == nullptr && max_splits > 1;
-  const int row_tiles = (g.n + 15) / 16;
-  const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles
-  auto groups_of = [&](int nw) { return (total + nw / unit - 1) / (nw / unit); };
+struct WidePlan {
+  int shape, splits;
+};
+static int wide_groups(int total, int nw, int unit) { return (total + nw / unit - 1) / (nw / unit); }
+
+// The workgroup shape and the K-splits of n rows; total out-tiles, of which `unit` tiles of the weights each.
+static WidePlan wide_choose(int n, int K, int total, int unit, int max_splits) {
+  const int row_tiles = (n + 15) / 16;
   // Cost in us: rounds of 256 workgroups, each its k-steps plus 8 for ramp and epilogue, plus what a partial sum costs
   // to write (4.6 TB/s) and to read back in the residual kernel (2.9 TB/s).
-  const int KT = g.K / 32;
-  int shape = 0, best_splits = 1;
+  const int KT = K / 32;
+  WidePlan plan{0, 1};
   double best = 1e30;
   for (int v = 0; v < 5; ++v) {
     const int row_blocks = (row_tiles + WIDE_SHAPES[v].rb - 1) / WIDE_SHAPES[v].rb;
@@ -484,35 +535,62 @@ hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *o
     // 161 rows, 8192 -> 8192, 8 x 8 tiles in two shares 60.8 us, 16 x 8 in four 49.8; 145 rows, 13824 -> 5120, 65.5 / 59.6.
     const int row_here = row_tiles < WIDE_SHAPES[v].rb ? row_tiles : WIDE_SHAPES[v].rb;
     const double step_us = WIDE_SHAPES[v].step_us * (row_here + WIDE_SHAPES[v].nw) / (WIDE_SHAPES[v].rb + WIDE_SHAPES[v].nw);
-    for (int sp = 1; sp <= (may_split ? max_splits : 1); ++sp) {
+    for (int sp = 1; sp <= max_splits; ++sp) {
       const int per_k = (KT + sp - 1) / sp;
       if (sp > 1 && (per_k < 16 || (sp - 1) * per_k >= KT)) continue; // no empty share, none that is all ramp
-      const int rounds = (groups_of(WIDE_SHAPES[v].nw) * row_blocks * sp + 255) / 256;
+      const int rounds = (wide_groups(total, WIDE_SHAPES[v].nw, unit) * row_blocks * sp + 255) / 256;
       double cost = rounds * (per_k * step_us + 8.0);
-      if (sp > 1) cost += sp * (64.0 * g.n * total) * (1 / 4.6e6 + 1 / 2.9e6);
+      if (sp > 1) cost += sp * (64.0 * n * total) * (1 / 4.6e6 + 1 / 2.9e6);
       if (cost < best) {
         best = cost;
-        shape = v;
-        best_splits = sp;
+        plan = WidePlan{v, sp};
       }
     }
   }
+  return plan;
+}
+bool wide_updates_residual(int32_t n, int32_t K, int32_t out_tiles, int32_t max_splits) {
+  return wide_choose(n, K, out_tiles, 1, max_splits).splits == 1;
+}
+
+// Fills the plan and the tile assignment and launches.  g.n is the total row count
+// (<= WIDE_MAX_ROWS); a_frag / h_frag use ceil(n / 16) row tiles; SwiGLU and Q/K/V come with the RMS scale of partial
+// sums per row (at most 8, or a multiple of 4 on 16 bytes), a plain store without.  max_splits > 1 (plain store only): y[s] = y + s *
+// split_stride receives the partial sum of k-range s, and *out_splits how many the launch used.  With GemmResid it is the sums of
+// squares per row that *out_splits receives.
+hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *out_splits, hipStream_t st, KernelTimer tm) {
+  GemmArgs g = args;
+  if (g.n < 1 || g.n > WIDE_MAX_ROWS || g.K % 32 != 0 || g.K < 64 || (g.row_ssq != nullptr && g.n_ssq > 8 && g.n_ssq % 4 != 0))
+    return hipErrorInvalidValue;
+  int32_t total = 0;
+  for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
+  if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
+  if ((g.mode == GEMM_SWIGLU || g.rope.q != nullptr) != (g.row_ssq != nullptr)) return hipErrorInvalidValue;
+  if (g.rope.q != nullptr && (!g.rope.tiled || g.rope.hd != 128 || g.mode != GEMM_STORE)) return hipErrorInvalidValue;
+  const bool may_split = g.row_ssq == nullptr && g.resid.x == nullptr && max_splits > 1;
+  const int row_tiles = (g.n + 15) / 16;
+  const int unit = g.mode == GEMM_SWIGLU ? 2 : 1; // a gate/up pair occupies two of the NW tiles
+  const WidePlan plan = wide_choose(g.n, g.K, total, unit, may_split ? max_splits : 1);
+  const int shape = plan.shape;
   const int nw = WIDE_SHAPES[shape].nw, row_blocks = (row_tiles + WIDE_SHAPES[shape].rb - 1) / WIDE_SHAPES[shape].rb;
   g.total_tiles = total;
   g.tiles_per_wg = nw / unit;
-  g.groups = groups_of(nw);
+  g.groups = wide_groups(total, nw, unit);
   g.part_q = total / g.groups;
   g.part_rem = total % g.groups;
-  g.splits = best_splits;
+  g.splits = plan.splits;
   if (out_splits != nullptr) *out_splits = g.splits;
   const unsigned grid = (unsigned)(((g.groups + 7) / 8) * 8 * row_blocks * g.splits);
+  hipError_t e;
   switch (shape) {
-  case 0: return launch_shape<1, 2, 4, 2, 5>(g, row_tiles, grid, st, tm);
-  case 1: return launch_shape<1, 3, 4, 2, 7>(g, row_tiles, grid, st, tm);
-  case 2: return launch_shape<2, 2, 4, 2, 6>(g, row_tiles, grid, st, tm);
-  case 3: return launch_shape<2, 3, 4, 2, 5>(g, row_tiles, grid, st, tm);
+  case 0: e = launch_shape<1, 2, 4, 2, 5>(g, row_tiles, grid, st, tm); break;
+  case 1: e = launch_shape<1, 3, 4, 2, 7>(g, row_tiles, grid, st, tm); break;
+  case 2: e = launch_shape<2, 2, 4, 2, 6>(g, row_tiles, grid, st, tm); break;
+  case 3: e = launch_shape<2, 3, 4, 2, 5>(g, row_tiles, grid, st, tm); break;
+  default: e = launch_shape<2, 4, 4, 2, 5>(g, row_tiles, grid, st, tm); break;
   }
-  return launch_shape<2, 4, 4, 2, 5>(g, row_tiles, grid, st, tm);
+  if (out_splits != nullptr && g.resid.x != nullptr) *out_splits = g.resid.ld_ssq;
+  return e;
 }
 
 // Tree steps (n <= 128) of matrices with many out-tiles: one block of eight row tiles x 8 or 16 out-tiles per workgroup.

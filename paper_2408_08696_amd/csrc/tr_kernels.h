@@ -155,6 +155,9 @@ constexpr int WIDE_MAX_SPLITS = 4;
 bool gemm_wide_supported(int32_t n, int32_t K, int32_t O);
 hipError_t launch_gemm_wide(const GemmArgs &g, int32_t max_splits, int32_t *out_splits, hipStream_t st,
                             KernelTimer tm = KernelTimer{});
+// Whether o and down of an ingestion pass are best not split over k: then they update the residual stream themselves (GemmResid; ld_ssq
+// is filled by the launch).
+bool wide_updates_residual(int32_t n, int32_t K, int32_t out_tiles, int32_t max_splits);
 // The same kernel for a tree step's rows (n <= TR_MAX_NODES), where it is the faster one: true and the plan, else
 // launch_gemm_mfma is.  Operands have to start on 16 bytes.  max_splits > 1: a plain store without an RMS scale.
 struct Rows8Plan {

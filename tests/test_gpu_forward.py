@@ -252,6 +252,28 @@ def test_packed_prefill_cache_matches_oracle(shape_name, plen, small):
     _cache_against_oracle(eng, kv, n)
 
 
+@pytest.mark.parametrize("d,F,plen", [(1056, 480, 150), (4128, 480, 300), (4096, 256, 2049), (6144, 256, 2049), (8160, 256, 2001)])
+def test_ingestion_that_updates_the_residual_stream(d, F, plen):
+    """o and down that are not split over k add to the residual stream in their own epilogue, in every workgroup shape, with out-tiles
+    missing in the last workgroup and rows in the last block; the second layer's keys and values carry what they leave, the operand and
+    the sums of squares.  Gains are powers of two, so that they round nothing."""
+    require_gpu()
+    say("ingestion with residual epilogue", d, F, plen)
+    sh = synth.ModelShape("resid", 2, d, 2, 1, 128, F, 512, "bf16")
+    w = synth.make_weights(sh, seed=8)
+    gen = torch.Generator().manual_seed(d)
+    for lw in w["layers"]:
+        for name in ("attn_norm", "ffn_norm"):
+            lw[name] = (lw[name] * 2.0 ** torch.randint(-1, 2, (d,), generator=gen)).to(torch.bfloat16)
+    prompt = synth.zipf_prompt(sh.vocab, plen, seed=8).tolist()
+    eng = tr.Engine(sh, to_gpu(w), synth.tree15(), k=K, capacity=plen + 40)
+    eng.prefill(prompt)
+    torch.cuda.synchronize()
+    kv = O.KVCache(oracle_cfg(sh), plen + 40, np.float32)
+    O.prefill(oracle_cfg(sh), synth.weights_to_numpy(w), kv, prompt[:-1], np.float32)
+    _cache_against_oracle(eng, kv, plen - 1)
+
+
 @pytest.mark.parametrize("shape_name,lens", [("heads64_8", (131, 530)), ("heads32", (129, 1160))])
 def test_ingestion_attention_forms_match_oracle(shape_name, lens):
     """The ingestion attention where a launch has more than one workgroup per compute unit (64 heads x 5 row blocks, 32 x
