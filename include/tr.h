@@ -217,7 +217,9 @@ tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_
  * What tr_verify_forward launches for one packed projection of a step (diagnostic; touches no GPU): plan[0..2] as in
  * tr_plan_projection, plan[3] = 0 for the decode projection kernel, 1 for the kernel that shares operands in LDS, which
  * matrices of very many rows take (with weights and workspace on 16 bytes, else the decode kernel's plan holds).  out_f is the sum
- * over the three matrices of the Q/K/V projection, one of the two of gate/up.  plan is [host], 4 values.
+ * over the three matrices of the Q/K/V projection, one of the two of gate/up.  plan is [host], 4 values.  Q/K/V is reported as
+ * launched with a plain cache; into a tiled one wide models (in_f from 5120 on) write it from 33 or 81 rows on by the other kernel in
+ * 2 to 4 splits of the input dimension and a launch that adds them.
  * TR_EINVAL for null plan, an unknown projection, or a shape the packed kernels do not take.
  */
 typedef enum { TR_PROJ_QKV = 0, TR_PROJ_O_DOWN = 1, TR_PROJ_GATE_UP = 2, TR_PROJ_LM_HEAD = 3 } tr_projection;

@@ -14,6 +14,8 @@
 
 namespace tr {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4q;
+
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 static bool packed_supported(const tr_model &m);
@@ -396,6 +398,60 @@ __global__ __launch_bounds__(128) void k_embed_frag(const bf16_t *__restrict__ E
   norm_operand(v, live, gv, row, j, d, row_tiles, xg_frag, ssq, ld_ssq, chunk, row < n);
 }
 
+// Q/K/V from partial sums: what the projection's own epilogue does where it is not split over k.  One memory round trip.  A block has 32
+// features and all rows, so that the cache lines of keys and values are its own; a thread four features of every 32nd row.  (64
+// features a block, half as many blocks: 7.2 us instead of 6.4 at 80 rows of 70B width.)
+template <int ROWS>
+__global__ __launch_bounds__(256) void k_qkv_finish(const float *__restrict__ part, const float *__restrict__ ssq,
+                                                    const float *__restrict__ rope, const int32_t *__restrict__ d_len,
+                                                    int32_t n, int32_t O, int32_t n_part, int32_t n_ssq, int32_t H, int32_t norm_dim,
+                                                    float eps, int32_t Hkv, int32_t cap, bf16_t *__restrict__ q,
+                                                    bf16_t *__restrict__ k_layer, bf16_t *__restrict__ v_layer) {
+  const int o = blockIdx.x * 32 + (threadIdx.x & 7) * 4, row0 = threadIdx.x >> 3;
+  const int head = o >> 7, dd = o & 127;
+  const bool rotated = head < H + Hkv;
+  f32x4q p[ROWS][GEMM_MAX_SPLITS];
+  f32x4q sq[ROWS][2];
+  float2 c[ROWS], s[ROWS];
+  const int L = *d_len;
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    const int row = row0 + 32 * i, r = row < n ? row : n - 1;
+#pragma unroll
+    for (int j = 0; j < GEMM_MAX_SPLITS; ++j)
+      p[i][j] = *reinterpret_cast<const f32x4q *>(part + ((size_t)(j < n_part ? j : 0) * n + r) * O + o);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) sq[i][j] = *reinterpret_cast<const f32x4q *>(ssq + (size_t)r * n_ssq + (4 * j < n_ssq ? 4 * j : 0));
+    c[i] = *reinterpret_cast<const float2 *>(rope + (size_t)r * 128 + (dd >> 1));
+    s[i] = *reinterpret_cast<const float2 *>(rope + (size_t)r * 128 + 64 + (dd >> 1));
+  }
+  __builtin_amdgcn_sched_barrier(0); // all of them on their way before the first sum
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    const int row = row0 + 32 * i, pos = L + row;
+    if (row >= n) continue;
+    f32x4q v = p[i][0];
+#pragma unroll
+    for (int j = 1; j < GEMM_MAX_SPLITS; ++j)
+      if (j < n_part) v += p[i][j];
+    float ss = (sq[i][0][0] + sq[i][0][1]) + (sq[i][0][2] + sq[i][0][3]);
+    if (n_ssq > 4) ss += (sq[i][1][0] + sq[i][1][1]) + (sq[i][1][2] + sq[i][1][3]);
+    v *= 1.0f / sqrtf(ss / (float)norm_dim + eps);
+    if (rotated) {
+      const uint2 w = uint2{bf16_pair(v[0] * c[i].x - v[1] * s[i].x, v[1] * c[i].x + v[0] * s[i].x),
+                            bf16_pair(v[2] * c[i].y - v[3] * s[i].y, v[3] * c[i].y + v[2] * s[i].y)};
+      bf16_t *dst = head < H ? q + ((size_t)row * H + head) * 128 + dd
+                             : k_layer + (size_t)(head - H) * cap * 128 + kv_k_index(pos, dd);
+      *reinterpret_cast<uint2 *>(dst) = w;
+    } else {
+      const uint32_t w[2] = {bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])};
+      bf16_t *dst = v_layer + (size_t)(head - H - Hkv) * 128 * cap;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dst[kv_v_index(pos, dd + e)] = (bf16_t)(w[e >> 1] >> (16 * (e & 1)));
+    }
+  }
+}
+
 // row-major bf16 [n, K] -> fragment order (standalone linear op only)
 __global__ __launch_bounds__(256) void k_rows_to_frag(const bf16_t *__restrict__ a, int32_t n, int32_t K,
                                                       int32_t row_tiles, bf16_t *__restrict__ frag) {
@@ -423,15 +479,16 @@ static bool packed_supported(const tr_model &m) {
 }
 
 // One projection of a tree step by the faster of its two kernels; fills g.splits.  (tr_plan_step_projection says which.)
+static bool operands_on_16(const GemmArgs &g) { // what goes straight into LDS
+  bool on = starts_on_16(g.a_frag) && starts_on_16(g.w2);
+  for (int i = 0; i < g.n_seg; ++i) on = on && starts_on_16(g.seg[i].w);
+  return on;
+}
 static bool project_rows8(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan) {
   int32_t total = 0;
-  bool on = starts_on_16(g.a_frag) && starts_on_16(g.w2); // what goes straight into LDS
-  for (int i = 0; i < g.n_seg; ++i) {
-    total += g.seg[i].out_tiles;
-    on = on && starts_on_16(g.seg[i].w);
-  }
+  for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   const bool swiglu = g.mode == GEMM_SWIGLU, scaled = g.row_ssq != nullptr;
-  return on && g.rope.q == nullptr && (scaled ? g.n_ssq <= 8 : !swiglu) && rows8_plan(g.n, g.K, total, swiglu, swiglu || scaled ? 1 : max_splits, plan);
+  return operands_on_16(g) && g.rope.q == nullptr && (scaled ? g.n_ssq <= 8 : !swiglu) && rows8_plan(g.n, g.K, total, swiglu, swiglu || scaled ? 1 : max_splits, plan);
 }
 static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipStream_t st) {
   Rows8Plan plan;
@@ -504,7 +561,24 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
       // needs complete sums); wq and wk are packed with interleaved rows for that
       g.rope = GemmRope{q, (T *)kv.k + (size_t)l * lsz, (T *)kv.v + (size_t)l * lsz, rope, kv.d_len,
                         H, Hkv, hd, kv.capacity, kv.layout};
-      TR_TRY(project(g, 1, prof_next(prof, PC_QKV), st));
+      const int O = hq + 2 * hk;
+      Rows8Plan plan;
+      if (hd == 128 && kv.layout == TR_KV_TILED && n_ssq <= 8 && operands_on_16(g) && qkv_split_plan(n, d, O / 16, &plan) &&
+          (size_t)plan.splits * n * O + 8192 + 4 <= (size_t)(WIDE_PART_ROWS - GEMM_MAX_SPLITS * NP) * d) {
+        const GemmRope rp = g.rope;
+        float *const parts = ssq + 8192; // behind the sums of squares
+        g.rope = GemmRope{};
+        g.row_ssq = nullptr;
+        g.y = parts; g.ldy = O; g.split_stride = (size_t)n * O;
+        TR_TRY(launch_gemm_rows8(g, plan, st, prof_next(prof, PC_QKV)));
+        auto finish = [&](auto kernel) {
+          return launch(kernel, dim3(O / 32), dim3(256), 0, st, prof_next(prof, PC_QKV), parts, ssq, rope, kv.d_len, n, O, plan.splits,
+                        n_ssq, H, d, m.rms_eps, Hkv, kv.capacity, q, rp.k_layer, rp.v_layer);
+        };
+        TR_TRY(n <= 64 ? finish(k_qkv_finish<2>) : n <= 96 ? finish(k_qkv_finish<3>) : finish(k_qkv_finish<4>));
+      } else {
+        TR_TRY(project(g, 1, prof_next(prof, PC_QKV), st));
+      }
     }
     if (l == m.n_layers - 1 && logits_out == nullptr) break; // as in forward_wide
     TR_TRY(attention_dispatch<T>(kv, l, H, tree, n, q, attn, NT, (float *)(ws + w.part_ml), (float *)(ws + w.part_acc),

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(const bf16_t *a_f
       const int uu = MODE == GEMM_SWIGLU ? u >> 1 : u;
       int t = tile0 + (uu < n_valid ? uu : 0);
       const bf16_t *mat = MODE == GEMM_SWIGLU && (u & 1) ? w1 : w0;
-      if constexpr (ROPE) {
+      if constexpr (ROPE || MODE == GEMM_PARTS) {
         if (t >= g.seg[0].out_tiles + g.seg[1].out_tiles) {
           t -= g.seg[0].out_tiles + g.seg[1].out_tiles;
           mat = g.seg[2].w;
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(WIDE_WAVES * 64) void k_gemm_wide(const bf16_t *a_f
         const int u = MODE == GEMM_SWIGLU ? wc * NP2 + p2 : 2 * (wc * NP2 + p2) + half;
         if (u >= n_valid) continue;
         const int t = tile0 + u;
-        if constexpr (MODE == GEMM_STORE) {
+        if constexpr (MODE == GEMM_STORE || MODE == GEMM_PARTS) {
           if (row >= g.n) continue;
 #pragma unroll
           for (int q = 2 * half; q < 2 * half + 2; ++q) {
@@ -648,6 +648,23 @@ bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t 
   return false;
 }
 
+// Q/K/V: 8 out-tiles and as many shares of k as fill one round.  Whole, every workgroup of the decode kernel has 3 or 4 out-tiles and all
+// of the activations to load; in shares they load a half or a third of that, and the launch that adds the shares (6.4 us at 80 rows of
+// 70B width) is less than they save from where the activations are many.  us of the launches at 70B width, 80 rows: 48.5 / 35.5 + 6.4.  A
+// step, whole / in shares: 70B width (3 layers) 33 rows 1297 / 1284, 48 1315 / 1290, 64 1321 / 1301, 128 1438 / 1426, 80 rows on 8 layers
+// 3187 / 3151; 13B (10 layers) 64 rows 1509 / 1527, 81 1689 / 1687, 96 1829 / 1814, 100 2022 / 1999, 128 2139 / 2098.  At 7B width its two
+// shares of 96 groups do not fill the chip.  Chains of 16 k-steps, where a wave of the decode kernel has 20 at K = 5120 and 32 at 8192.
+bool qkv_split_plan(int32_t n, int32_t K, int32_t total_tiles, Rows8Plan *plan) {
+  const int NT = (n + 15) / 16, g8 = (total_tiles + 7) / 8;
+  if (n > NP || K < 5120 || K % 32 != 0 || NT < (K < 8192 ? 6 : 3)) return false;
+  for (int sp = 2; sp <= GEMM_MAX_SPLITS; ++sp)
+    if (g8 * sp >= 200 && g8 * sp <= 256) {
+      *plan = Rows8Plan{8, g8, sp};
+      return true;
+    }
+  return false;
+}
+
 hipError_t launch_gemm_rows8(const GemmArgs &args, const Rows8Plan &plan, hipStream_t st, KernelTimer tm) {
   GemmArgs g = args;
   g.total_tiles = 0;
@@ -664,6 +681,10 @@ hipError_t launch_gemm_rows8(const GemmArgs &args, const Rows8Plan &plan, hipStr
   // Chains of 16 k-steps: as long as a wave's in the decode kernel at K = 4096 in eight waves, or in shares of 128, and shorter than
   // all others there.  Its MFMA adds 32 products, these 16 twice, and the errors are the same: relative to float64 1.31e-7 with both for
   // 4096 -> 32064, 96 and 128 rows; where the decode kernel has four waves (80 rows) 1.81e-7 / 1.32e-7.
+  if (g.n_seg == 3) { // partial sums of Q/K/V
+    if (swiglu || scaled || plan.out_tiles != 8) return hipErrorInvalidValue;
+    return launch_ks<GEMM_PARTS, false, 1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
+  }
   if (plan.out_tiles == 6 && swiglu) return launch_ks<GEMM_SWIGLU, true, 1, 3, 4, 1, 5, 16, 2>(g, row_tiles, grid, st, tm);
   if (plan.out_tiles == 8 && swiglu) return launch_ks<GEMM_SWIGLU, true, 1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);
   if (plan.out_tiles == 8 && scaled) return launch_ks<GEMM_STORE, true, 1, 2, 4, 2, 5, 16>(g, row_tiles, grid, st, tm);

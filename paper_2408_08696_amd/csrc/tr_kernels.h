@@ -5,7 +5,8 @@
 namespace tr {
 
 enum GemmMode { GEMM_STORE = 0, GEMM_ROPE = 1 /* GEMM_STORE with GemmRope, picked by the launch */, GEMM_SWIGLU = 2,
-                GEMM_RESID = 3 /* GEMM_STORE with GemmResid, likewise */ };
+                GEMM_RESID = 3 /* GEMM_STORE with GemmResid, likewise */,
+                GEMM_PARTS = 4 /* GEMM_STORE over the three matrices of Q/K/V, by launch_gemm_rows8 */ };
 
 // Streaming store for activations that the next kernel reads once: written through as issued, so the
 // kernel does not end with dirty L2 lines to write back before its successor may start (the consumers
@@ -165,6 +166,8 @@ struct Rows8Plan {
 };
 bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, Rows8Plan *plan);
 hipError_t launch_gemm_rows8(const GemmArgs &g, const Rows8Plan &plan, hipStream_t st, KernelTimer tm = KernelTimer{});
+// Q/K/V of a step split over k, with a launch behind it that adds the shares, scales, rotates and writes (k_qkv_finish).
+bool qkv_split_plan(int32_t n, int32_t K, int32_t total_tiles, Rows8Plan *plan);
 hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t K, int32_t rope_hd, hipStream_t st);
 
 // Shape-generic projections on row-major weights with their prologue and epilogue (tr_rows.hip).

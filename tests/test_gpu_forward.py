@@ -840,6 +840,38 @@ def test_projections_that_update_the_residual_stream(d, F, groups):
     assert taken >= 4
 
 
+@pytest.mark.parametrize("d,heads,kv_heads,nodes", [(8192, 64, 8, (32, 33, 80, 128)), (8192, 40, 8, (49, 64, 65)),
+                                                    (5120, 40, 40, (80, 96, 97, 128)), (5152, 80, 16, (81, 113))])
+def test_qkv_in_shares_of_k(d, heads, kv_heads, nodes):
+    """Q/K/V in two, three and four shares of k, and the rows where it stays whole: keys and values of all nodes against float64 (one
+    bf16 rounding of at most 2^-9 and float32 sums), the queries through the logits of a step
+    against those with a query matrix off 16 bytes, which is never split."""
+    require_gpu()
+    shape = synth.ModelShape("qkv", 1, d, heads, kv_heads, 128, 256, 512, "bf16")
+    wo = _uniform(torch.Generator("cuda").manual_seed(3), d, heads * 128)
+    for n in nodes:
+        say("qkv in shares", d, heads, kv_heads, n)
+        eng, w, xe = _feed_forward_step(shape, n, 9, wo=wo)
+        whole, _, _ = _feed_forward_step(shape, n, 9, wo=wo, moved=("wq",))
+        lw, a = w["layers"][0], xe / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
+        parent, depth = synth.prefix_template(n).parent, np.zeros(n)
+        for i in range(1, n):
+            depth[i] = depth[parent[i]] + 1
+        angle = (150 + torch.from_numpy(depth).cuda())[:, None] * 10000.0 ** (-torch.arange(64, device="cuda").double() / 64)
+        k = (a @ lw["wk"].double().T).view(n, kv_heads, 128)
+        cos, sin = angle.cos()[:, None], angle.sin()[:, None]
+        k = torch.cat([k[..., :64] * cos - k[..., 64:] * sin, k[..., 64:] * cos + k[..., :64] * sin], -1)
+        v = (a @ lw["wv"].double().T).view(n, kv_heads, 128)
+        kp, vp = kv_plain_views(eng.kv, k_interleaved=True)
+        moved_rows = int(eng.kv.d_len.item()) - 150                # the accepted nodes lie there now
+        for got, ref in ((kp, k), (vp, v)):
+            got = got[0, :, 150:150 + n].permute(1, 0, 2).double()
+            over = (got - ref).abs() / (2.0 ** -8 * ref.abs() + 1e-5)
+            assert float(over[moved_rows:].max()) < 1.01 and float(over[0].max()) < 1.01, (n, float(over.max()))
+        rel = (eng.logits - whole.logits).norm() / whole.logits.norm()
+        assert float(rel) < 1e-2, (n, float(rel))
+
+
 @pytest.mark.parametrize("d,vocab,out_tiles,nodes", [
     # 201 workgroups of 8 and of 16 out-tiles, the last one partly filled, and several rounds of both
     (4096, 25632, 8, (65, 80, 97, 128)), (5152, 25632, 8, (33, 48)), (4096, 76832, 8, (81, 128)), (4096, 51232, 16, (33, 49, 128)),
