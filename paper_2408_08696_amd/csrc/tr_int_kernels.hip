@@ -426,124 +426,17 @@ hipError_t launch_matrix_update(const tr_ctx *c, const int32_t *d_S, const int32
 }
 
 // ---------------------------------------------------------------------------------------------
-// Greedy accept + matrix update in one workgroup (Section 3.3 with the chain rule of Section 2.2).
-// match bit i  = draft token i equals the model output at its parent (root: always)
-// node i is ok = every bit of its ancestor mask is a match bit
-// winner       = deepest ok node, smallest index among equals
-// host: the same result in pinned memory of the context, when the caller waits for it: a copy kernel and its staging on the
-// host less per step (whole request on the tiny model, 19 steps: 2.11 -> 1.70 ms).
-// The kernel also publishes the committed length before the step (step_L) and advances *d_len, so
-// the compaction kernel that follows works from step_L and needs no further bookkeeping launch.
-// Two waves; what bounds it is the chain load -> barrier -> match -> barrier -> winner -> stores.  Every thread
-// places its own node: a node on the winner's path is entry popcount(path bits below it) of the path, and repeated
-// tokens are compared four at a time.  With one thread walking the 80 nodes for the path and every thread walking them
-// for the repeats the launch took 15.6 us (21.9 at 128 nodes).
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(TR_MAX_NODES) void k_accept_update(const int32_t *__restrict__ S,
-                                                                const int32_t *__restrict__ topk,
-                                                                const int32_t *__restrict__ tokens,
-                                                                const uint64_t *__restrict__ anc,
-                                                                const int32_t *__restrict__ depth,
-                                                                const int32_t *__restrict__ parent, int32_t n_nodes, int32_t k,
-                                                                int32_t *__restrict__ d_len, int32_t V,
-                                                                int32_t *__restrict__ M, int32_t *__restrict__ step_L,
-                                                                tr_step_out *__restrict__ out,
-                                                                tr_step_out *__restrict__ host, int32_t mode) {
-  __shared__ __align__(16) int32_t sS[TR_MAX_NODES];
-  __shared__ int32_t sOut[TR_MAX_NODES];
-  __shared__ uint64_t sAnc[TR_MAX_NODES][2];
-  __shared__ uint64_t mbits[2];
-  __shared__ int32_t wkey[2];
-  const int i = threadIdx.x;
-  const bool live = i < n_nodes;
-  // everything that does not depend on the match is loaded up front, in one round trip
-  const uint64_t anc0 = live ? anc[2 * i] : 0, anc1 = live ? anc[2 * i + 1] : 0;
-  const int dep = live ? depth[i] : 0;
-  const int par = live && i > 0 ? parent[i] : 0;
-  const int L0 = i == 0 ? *d_len : 0;
-  int tk = -1;
-  if (live) {
-    tk = S[i];
-    // the token the model emits at node i: its argmax, or the caller's draw under temperature sampling
-    int ot = tokens != nullptr ? tokens[i] : topk[(size_t)i * k];
-    tk = tk < 0 ? 0 : (tk >= V ? V - 1 : tk);
-    sOut[i] = ot < 0 ? 0 : (ot >= V ? V - 1 : ot);
-  }
-  sS[i] = tk;
-  sAnc[i][0] = anc0;
-  sAnc[i][1] = anc1;
-  __syncthreads();
-  const bool match = live && (i == 0 || tk == sOut[par]);
-  const uint64_t ballot = __ballot(match);
-  if ((i & 63) == 0) mbits[i >> 6] = ballot;
-  __syncthreads();
-  const bool ok = live && ((mbits[0] & anc0) == anc0) && ((mbits[1] & anc1) == anc1);
-  int key = ok ? dep * 256 + (255 - i) : -1; // the root is always ok
-  for (int off = 32; off > 0; off >>= 1) {
-    const int o = __shfl_xor(key, off);
-    key = o > key ? o : key;
-  }
-  if ((i & 63) == 0) wkey[i >> 6] = key;
-  __syncthreads();
-  key = wkey[0] > wkey[1] ? wkey[0] : wkey[1];
-  const int w = 255 - (key & 255), a = key >> 8;
-  const uint64_t p0 = sAnc[w][0], p1 = sAnc[w][1];
-  // ancestors in increasing index order are the path root..winner (breadth-first numbering)
-  const bool on_path = ((i < 64 ? p0 >> i : p1 >> (i - 64)) & 1ull) != 0;
-  const int at = i < 64 ? __popcll(p0 & ((1ull << i) - 1)) : __popcll(p0) + __popcll(p1 & ((1ull << (i - 64)) - 1));
-  auto publish = [&](tr_step_out *o) {
-    if (on_path) {
-      o->path[at] = i;
-      if (at > 0) o->emitted[at - 1] = tk;
-    }
-    if (i > a && i < TR_MAX_LAYERS) {
-      o->path[i] = -1;
-      o->emitted[i] = -1;
-    }
-    if (i == 0) {
-      const int bonus = sOut[w];
-      o->emitted[a] = bonus;
-      o->n_accepted = a;
-      o->n_emitted = a + 1;
-      o->winner = w;
-      o->next_root = bonus;
-      o->kv_len = L0 + a + 1;
-    }
-  };
-  publish(out);
-  if (host != nullptr) publish(host);
-  if (i == 0) {
-    *step_L = L0;
-    *d_len = L0 + a + 1;
-  }
-  if ((mode & TR_UPDATE_ACCEPTED_ONLY) != 0) { // uniform
-    __syncthreads();
-    if (!on_path) sS[i] = -1;
-    __syncthreads();
-  }
-  scatter_rows(M, k, n_nodes, sS, topk, i, mode);
-}
-
-// ---------------------------------------------------------------------------------------------
 // KV compaction: the accepted path's keys/values (written by the forward at L + node index) move
-// to L + 0..a.  One workgroup per (layer, kv head); all sources are staged in LDS before any
+// to L + 0..a.  One workgroup of 256 threads per (layer, kv head); all sources are staged in LDS before any
 // destination is written, so overlapping source/destination positions are safe.
 //   K: [layers][Hkv][cap][hd]   V: [layers][Hkv][hd][cap]
 // ---------------------------------------------------------------------------------------------
+// blk = layer * Hkv + head; path in LDS; sk: LDS for 2 * TR_MAX_LAYERS * hd elements
 template <typename T>
-__global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__restrict__ Vt, int32_t cap, int32_t hd,
-                                                    int32_t tiled, const int32_t *__restrict__ step_L,
-                                                    const tr_step_out *__restrict__ out) {
-  extern __shared__ unsigned char smem_raw[];
-  T *sk = reinterpret_cast<T *>(smem_raw);          // [a+1][hd]
-  __shared__ int32_t path[TR_MAX_LAYERS];
+__device__ inline void compact_head(T *__restrict__ K, T *__restrict__ Vt, size_t blk, int32_t cap, int32_t hd, int32_t tiled, int L,
+                                    int a, const int32_t *path, T *sk) {
   const int tid = threadIdx.x;
-  const int a = out->n_accepted, L = *step_L;
-  if (tid < TR_MAX_LAYERS) path[tid] = out->path[tid]; // asked for together with the two scalars
-  if (a == 0) return;                                 // root already sits at L
-  __syncthreads();
-  T *sv = sk + (size_t)TR_MAX_LAYERS * hd;           // [a+1][hd]
-  const size_t blk = blockIdx.x;                     // layer * Hkv + head
+  T *sv = sk + (size_t)TR_MAX_LAYERS * hd;           // [a+1][hd] both
   T *Kb = K + blk * (size_t)cap * hd;
   T *Vb = Vt + blk * (size_t)hd * cap;
   const int total = (a + 1) * hd;
@@ -574,6 +467,139 @@ __global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__rest
     Kb[tiled ? kv_k_index(dst, d) : (size_t)dst * hd + d] = sk[e];
     Vb[tiled ? kv_v_index(dst, d) : (size_t)d * cap + dst] = sv[e];
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__restrict__ Vt, int32_t cap, int32_t hd,
+                                                    int32_t tiled, const int32_t *__restrict__ step_L,
+                                                    const tr_step_out *__restrict__ out) {
+  extern __shared__ unsigned char smem_raw[];
+  __shared__ int32_t path[TR_MAX_LAYERS];
+  const int a = out->n_accepted, L = *step_L;
+  if (threadIdx.x < TR_MAX_LAYERS) path[threadIdx.x] = out->path[threadIdx.x]; // asked for together with the two scalars
+  if (a == 0) return;                                                         // root already sits at L
+  __syncthreads();
+  compact_head<T>(K, Vt, blockIdx.x, cap, hd, tiled, L, a, path, reinterpret_cast<T *>(smem_raw));
+}
+
+// ---------------------------------------------------------------------------------------------
+// Greedy accept + matrix update in one workgroup (Section 3.3 with the chain rule of Section 2.2).
+// match bit i  = draft token i equals the model output at its parent (root: always)
+// node i is ok = every bit of its ancestor mask is a match bit
+// winner       = deepest ok node, smallest index among equals
+// host: the same result in pinned memory of the context, when the caller waits for it: a copy kernel and its staging on the
+// host less per step (whole request on the tiny model, 19 steps: 2.11 -> 1.70 ms).
+// The kernel also publishes the committed length before the step (step_L) and advances *d_len, so
+// the compaction kernel that follows works from step_L and needs no further bookkeeping launch.
+// Where the compaction has few workgroups they are blocks 1 .. of this launch: each finds the winner for itself, and the last of all
+// blocks to have read the length advances it (an atomic per block on one word, about 20 ns each; the count wraps to zero).
+// Two waves; what bounds it is the chain load -> barrier -> match -> barrier -> winner -> stores.  Every thread
+// places its own node: a node on the winner's path is entry popcount(path bits below it) of the path, and repeated
+// tokens are compared four at a time.  With one thread walking the 80 nodes for the path and every thread walking them
+// for the repeats the launch took 15.6 us (21.9 at 128 nodes).
+// ---------------------------------------------------------------------------------------------
+template <typename T, bool COMPACT>
+__global__ __launch_bounds__(COMPACT ? 256 : TR_MAX_NODES) void k_accept_update(const int32_t *__restrict__ S,
+                                                                const int32_t *__restrict__ topk,
+                                                                const int32_t *__restrict__ tokens,
+                                                                const uint64_t *__restrict__ anc,
+                                                                const int32_t *__restrict__ depth,
+                                                                const int32_t *__restrict__ parent, int32_t n_nodes, int32_t k,
+                                                                int32_t *__restrict__ d_len, int32_t V,
+                                                                int32_t *__restrict__ M, int32_t *__restrict__ step_L,
+                                                                tr_step_out *__restrict__ out,
+                                                                tr_step_out *__restrict__ host, int32_t mode,
+                                                                T *__restrict__ K, T *__restrict__ Vt, int32_t cap, int32_t hd,
+                                                                int32_t tiled) {
+  __shared__ __align__(16) int32_t sS[TR_MAX_NODES];
+  __shared__ int32_t sOut[TR_MAX_NODES];
+  __shared__ uint64_t sAnc[TR_MAX_NODES][2];
+  __shared__ uint64_t mbits[2];
+  __shared__ int32_t wkey[2];
+  __shared__ int32_t sL;
+  const int i = threadIdx.x;
+  const bool live = i < n_nodes;
+  // everything that does not depend on the match is loaded up front, in one round trip
+  const uint64_t anc0 = live ? anc[2 * i] : 0, anc1 = live ? anc[2 * i + 1] : 0;
+  const int dep = live ? depth[i] : 0;
+  const int par = live && i > 0 ? parent[i] : 0;
+  int L0 = i == 0 ? *d_len : 0;
+  int tk = -1;
+  if (live) {
+    tk = S[i];
+    // the token the model emits at node i: its argmax, or the caller's draw under temperature sampling
+    int ot = tokens != nullptr ? tokens[i] : topk[(size_t)i * k];
+    tk = tk < 0 ? 0 : (tk >= V ? V - 1 : tk);
+    sOut[i] = ot < 0 ? 0 : (ot >= V ? V - 1 : ot);
+  }
+  if (!COMPACT || i < TR_MAX_NODES) {
+    sS[i] = tk;
+    sAnc[i][0] = anc0;
+    sAnc[i][1] = anc1;
+  }
+  if (COMPACT && i == 0) sL = L0;
+  __syncthreads();
+  const bool match = live && (i == 0 || tk == sOut[par]);
+  const uint64_t ballot = __ballot(match);
+  if ((i & 63) == 0 && i < TR_MAX_NODES) mbits[i >> 6] = ballot;
+  __syncthreads();
+  const bool ok = live && ((mbits[0] & anc0) == anc0) && ((mbits[1] & anc1) == anc1);
+  int key = ok ? dep * 256 + (255 - i) : -1; // the root is always ok
+  for (int off = 32; off > 0; off >>= 1) {
+    const int o = __shfl_xor(key, off);
+    key = o > key ? o : key;
+  }
+  if ((i & 63) == 0 && i < TR_MAX_NODES) wkey[i >> 6] = key;
+  __syncthreads();
+  key = wkey[0] > wkey[1] ? wkey[0] : wkey[1];
+  const int w = 255 - (key & 255), a = key >> 8;
+  const uint64_t p0 = sAnc[w][0], p1 = sAnc[w][1];
+  // ancestors in increasing index order are the path root..winner (breadth-first numbering)
+  const bool on_path = live && ((i < 64 ? p0 >> i : p1 >> (i - 64)) & 1ull) != 0;
+  const int at = !live ? 0 : i < 64 ? __popcll(p0 & ((1ull << i) - 1)) : __popcll(p0) + __popcll(p1 & ((1ull << (i - 64)) - 1));
+  auto publish = [&](tr_step_out *o) {
+    if (on_path) {
+      o->path[at] = i;
+      if (at > 0) o->emitted[at - 1] = tk;
+    }
+    if (i > a && i < TR_MAX_LAYERS) {
+      o->path[i] = -1;
+      o->emitted[i] = -1;
+    }
+    if (i == 0) {
+      const int bonus = sOut[w];
+      o->emitted[a] = bonus;
+      o->n_accepted = a;
+      o->n_emitted = a + 1;
+      o->winner = w;
+      o->next_root = bonus;
+      o->kv_len = L0 + a + 1;
+    }
+  };
+  if constexpr (COMPACT) {
+    if (i == 0 && atomicInc(reinterpret_cast<uint32_t *>(step_L), gridDim.x - 1) == gridDim.x - 1) *d_len = L0 + a + 1;
+    if (blockIdx.x > 0) {
+      if (a == 0) return; // root already sits at L
+      extern __shared__ unsigned char smem_raw[];
+      __shared__ int32_t path[TR_MAX_LAYERS];
+      if (on_path) path[at] = i;
+      __syncthreads();
+      compact_head<T>(K, Vt, blockIdx.x - 1, cap, hd, tiled, sL, a, path, reinterpret_cast<T *>(smem_raw));
+      return;
+    }
+  }
+  publish(out);
+  if (host != nullptr) publish(host);
+  if (!COMPACT && i == 0) {
+    *step_L = L0;
+    *d_len = L0 + a + 1;
+  }
+  if ((mode & TR_UPDATE_ACCEPTED_ONLY) != 0) { // uniform
+    __syncthreads();
+    if (!on_path && i < TR_MAX_NODES) sS[i] = -1;
+    __syncthreads();
+  }
+  scatter_rows(M, k, n_nodes, sS, topk, i, mode);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -658,20 +684,30 @@ hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logit
                 c->V, pos0, noise_rows, inv_t, c->tree.depth, kv->d_len, d_tokens);
 }
 
+// Up to this many (layer, kv head) blocks are compacted by the accepting launch itself; more would queue at the atomic.  us a step of the
+// tiny model (8 blocks), two launches / one: 15 nodes 71.5 / 69.4, 80 nodes 85.2 / 81.8; a whole request 1749 / 1689.
+constexpr int ACCEPT_COMPACT_BLOCKS = 32;
+template <typename T>
+static hipError_t launch_accept_t(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk, const int32_t *d_tokens,
+                                  tr_step_out *d_out, tr_step_out *host_out, hipStream_t st) {
+  const int blocks = kv->n_layers * kv->n_kv_heads;
+  const size_t smem = 2 * (size_t)TR_MAX_LAYERS * kv->head_dim * sizeof(T);
+  auto accept = [&](auto kernel, int grid, int threads, size_t lds, int32_t *word) {
+    return launch(kernel, dim3(grid), dim3(threads), lds, st, c->prof.next(PC_ACCEPT), d_S, d_topk, d_tokens, c->tree.anc, c->tree.depth,
+                  c->tree.parent, c->tree.n_nodes, c->k, kv->d_len, c->V, c->d_M, word, d_out, host_out, c->update_mode, (T *)kv->k,
+                  (T *)kv->v, kv->capacity, kv->head_dim, kv->layout);
+  };
+  if (blocks <= ACCEPT_COMPACT_BLOCKS && smem <= 32768) return accept(k_accept_update<T, true>, 1 + blocks, 256, smem, c->d_step_L + 1);
+  const hipError_t e = accept(k_accept_update<T, false>, 1, TR_MAX_NODES, 0, c->d_step_L);
+  if (e != hipSuccess) return e;
+  return launch(k_compact_kv<T>, dim3(blocks), dim3(256), smem, st, c->prof.next(PC_COMPACT), (T *)kv->k, (T *)kv->v, kv->capacity,
+                kv->head_dim, kv->layout, c->d_step_L, d_out);
+}
+
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk,
                                 const int32_t *d_tokens, tr_step_out *d_out, tr_step_out *host_out, hipStream_t st) {
-  hipError_t e = launch(k_accept_update, dim3(1), dim3(TR_MAX_NODES), 0, st, c->prof.next(PC_ACCEPT), d_S, d_topk, d_tokens,
-                        c->tree.anc, c->tree.depth, c->tree.parent, c->tree.n_nodes, c->k, kv->d_len, c->V, c->d_M, c->d_step_L,
-                        d_out, host_out, c->update_mode);
-  if (e != hipSuccess) return e;
-  const int blocks = kv->n_layers * kv->n_kv_heads;
-  const size_t esz = dtype_size(kv->dtype);
-  const size_t smem = 2 * (size_t)TR_MAX_LAYERS * kv->head_dim * esz;
-  if (kv->dtype == TR_BF16)
-    return launch(k_compact_kv<bf16_t>, dim3(blocks), dim3(256), smem, st, c->prof.next(PC_COMPACT), (bf16_t *)kv->k,
-                  (bf16_t *)kv->v, kv->capacity, kv->head_dim, kv->layout, c->d_step_L, d_out);
-  return launch(k_compact_kv<float>, dim3(blocks), dim3(256), smem, st, c->prof.next(PC_COMPACT), (float *)kv->k,
-                (float *)kv->v, kv->capacity, kv->head_dim, kv->layout, c->d_step_L, d_out);
+  return kv->dtype == TR_BF16 ? launch_accept_t<bf16_t>(c, kv, d_S, d_topk, d_tokens, d_out, host_out, st)
+                              : launch_accept_t<float>(c, kv, d_S, d_topk, d_tokens, d_out, host_out, st);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -324,6 +324,39 @@ def test_accept_compacts_the_widest_heads(hd, dtype):
     ctx.close()
 
 
+@pytest.mark.parametrize("layers,heads", [(1, 1), (4, 8), (11, 3)])
+def test_accept_advances_the_length_once_a_call(layers, heads):
+    """One launch that accepts and compacts up to 32 (layer, head) blocks, two launches beyond: every call of many on the same context
+    and cache advances the committed length once, by what it accepted, and moves every block's rows."""
+    require_gpu()
+    t = synth.tree15()
+    tree = O.make_tree(t.parent, t.rank, K)
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    kv = tr.KVDesc(synth.ModelShape("t", layers, heads * 32, heads, heads, 32, 32, 64, "f32"), 160)
+    kp, vp = kv_plain_views(kv)
+    out = torch.zeros(tr.STEP_OUT_INTS, dtype=torch.int32, device="cuda")
+    rng, L = np.random.default_rng(5), 7
+    kv.reset(L)
+    for call in range(12):
+        say("accept in one launch", layers, heads, "call", call)
+        S = np.arange(t.n_nodes) + 1
+        topk = np.full((t.n_nodes, K), 63)
+        path = tree.paths[int(rng.integers(0, t.n_nodes))]
+        for i in range(1, len(path)):
+            topk[path[i - 1], 0] = S[path[i]]
+        rows = 100.0 * (call + 1) + torch.arange(t.n_nodes, device="cuda", dtype=torch.float32)
+        kp[:, :, L:L + t.n_nodes, :] = rows[None, None, :, None]
+        vp[:, :, L:L + t.n_nodes, :] = -rows[None, None, :, None]
+        h = ctx.accept_and_update(kv, torch.from_numpy(S.astype(np.int32)).cuda(), torch.from_numpy(topk.astype(np.int32)).cuda(), out,
+                                  sync=True)
+        assert list(h.path[:h.n_emitted]) == list(path)
+        assert h.kv_len == L + len(path) and int(kv.d_len.item()) == h.kv_len
+        for i, node in enumerate(path):
+            assert (kp[:, :, L + i] == 100.0 * (call + 1) + node).all() and (vp[:, :, L + i] == -100.0 * (call + 1) - node).all()
+        L = h.kv_len
+    ctx.close()
+
+
 @pytest.mark.parametrize("mode", [tr.TR_UPDATE_FIRST, tr.TR_UPDATE_ACCEPTED_ONLY,
                                   tr.TR_UPDATE_FIRST | tr.TR_UPDATE_ACCEPTED_ONLY])
 def test_update_variants_match_oracle(mode):
