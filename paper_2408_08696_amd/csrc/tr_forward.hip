@@ -319,12 +319,24 @@ __device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 
   }
 }
 
+// From this many row tiles on the eight rows that share the operand's 128-byte lines are on one XCD, whose L2 writes a line back once.  us of
+// a prompt, other order / this: 7B width, 16 layers, 511 tokens 3767 / 3723, 640 5471 / 5438; 13B, 8 layers, 700 3516 / 3490; 70B, 4
+// layers, 1000 4546 / 4507; but 300 and 400 at 7B width 3469 / 3502 and 3635 / 3659.
+constexpr int ADD_LINE_TILES = 32;
+
 template <int PARTS>
 __global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const float *__restrict__ part,
                                                   size_t part_stride, const bf16_t *__restrict__ g, int32_t n, int32_t d,
                                                   int32_t row_tiles, bf16_t *__restrict__ xg_frag,
                                                   float *__restrict__ ssq, int32_t ld_ssq) {
-  const int row = blockIdx.x, chunk = blockIdx.y;
+  int row = blockIdx.x, chunk = blockIdx.y;
+  if (row_tiles >= ADD_LINE_TILES) { // block id -> (eight rows, chunk) on XCD id % 8, row of the eight
+    const int groups = row_tiles * 2, n_chunks = (d + NORM_CHUNK - 1) / NORM_CHUNK, eighth = blockIdx.x >> 3;
+    const int at = (eighth >> 3) * 8 + (blockIdx.x & 7);
+    if (at >= groups * n_chunks) return;
+    chunk = at / groups;
+    row = (at - chunk * groups) * 8 + (eighth & 7);
+  }
   const int j = chunk * NORM_CHUNK + threadIdx.x * 8;
   const bool live = row < n && j < d;
   float v[8];
@@ -357,7 +369,8 @@ __global__ __launch_bounds__(128) void k_add_frag(float *__restrict__ x, const f
 static hipError_t launch_add_frag(int n_part, int chunks, float *x, const float *part, size_t part_stride, const bf16_t *g,
                                   int32_t n, int32_t d, int32_t row_tiles, bf16_t *xg_frag, float *ssq, int32_t ld_ssq,
                                   KernelTimer tm, hipStream_t st) {
-  const dim3 grid(row_tiles * 16, chunks), block(128);
+  const dim3 block(128);
+  const dim3 grid = row_tiles >= ADD_LINE_TILES ? dim3((row_tiles * 2 * chunks + 7) / 8 * 64) : dim3(row_tiles * 16, chunks);
   switch (n_part) {
   case 1: return launch(k_add_frag<1>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, ld_ssq);
   case 2: return launch(k_add_frag<2>, grid, block, 0, st, tm, x, part, part_stride, g, n, d, row_tiles, xg_frag, ssq, ld_ssq);

@@ -252,14 +252,16 @@ def test_packed_prefill_cache_matches_oracle(shape_name, plen, small):
     _cache_against_oracle(eng, kv, n)
 
 
-@pytest.mark.parametrize("d,F,plen", [(1056, 480, 150), (4128, 480, 300), (4096, 256, 2049), (6144, 256, 2049), (8160, 256, 2001)])
-def test_ingestion_that_updates_the_residual_stream(d, F, plen):
+@pytest.mark.parametrize("d,heads,F,plen", [(1056, 2, 480, 150), (4128, 2, 480, 300), (4096, 2, 256, 2049), (6144, 2, 256, 2049),
+                                            (8160, 2, 256, 2001), (1056, 8, 2048, 497), (1056, 8, 2048, 498), (1056, 8, 2048, 540)])
+def test_ingestion_that_updates_the_residual_stream(d, heads, F, plen):
     """o and down that are not split over k add to the residual stream in their own epilogue, in every workgroup shape, with out-tiles
-    missing in the last workgroup and rows in the last block; the second layer's keys and values carry what they leave, the operand and
+    missing in the last workgroup and rows in the last block; with 8 heads they are split, and the residual kernel takes its rows one by
+    one up to 31 row tiles and by eights from 32 on.  The second layer's keys and values carry what they leave, the operand and
     the sums of squares.  Gains are powers of two, so that they round nothing."""
     require_gpu()
-    say("ingestion with residual epilogue", d, F, plen)
-    sh = synth.ModelShape("resid", 2, d, 2, 1, 128, F, 512, "bf16")
+    say("ingestion with residual epilogue", d, heads, F, plen)
+    sh = synth.ModelShape("resid", 2, d, heads, 1, 128, F, 512, "bf16")
     w = synth.make_weights(sh, seed=8)
     gen = torch.Generator().manual_seed(d)
     for lw in w["layers"]:
