@@ -478,7 +478,7 @@ void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t
       if (hbm_kib / 6000.0 > t) t = hbm_kib / 6000.0;
       t = rounds * (t + 3.0) + 3.0;
       if (s > 1) t += 2.0 * (s - 1) * NT * total_tiles / 8000.0 + 0.5; // extra KiB of partials written and re-read
-      if (max_splits > 1 && !gemm_updates_residual(n, groups, s)) t += 2.5; // the residual kernel's launch
+      if (max_splits > 1 && !gemm_updates_residual(n, groups, s)) t += 2.5; // the residual kernel, less what its absence costs
       if (t < best) {
         best = t;
         bp = p;

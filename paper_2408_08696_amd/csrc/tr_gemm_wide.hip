@@ -25,7 +25,7 @@
 // 360, Q/K/V 108 / 97.
 //
 // Same packed weight layout, fragment-ordered activations and epilogues (plain store, RoPE + cache append,
-// SwiGLU) as the decode kernel.
+// SwiGLU, residual update) as the decode kernel.
 #include <type_traits>
 #include <utility>
 
