@@ -20,6 +20,8 @@
  *   - Work is enqueued on the given stream (a hipStream_t passed as void*; NULL = the
  *     default stream).  Nothing synchronises unless stated.
  *   - Calls on one tr_ctx must be issued from one thread at a time.
+ *     What they enqueue must not overlap on the device (matrix and top-k scratch are the context's), but for accepts into different
+ *     caches: a matrix row that both write then holds either's candidates.
  *   - Matrices are row-major.  Weight matrices are [out_features, in_features].
  */
 #ifndef TR_H

@@ -113,14 +113,13 @@ tr_status tr_create(int32_t V, int32_t k, const tr_tree_template *t, tr_ctx **ou
 
   // host image of both trees and of the context's scratch.  The 64-bit parts come first so that every
   // section is 8-byte aligned whatever the node count: anc u64 x 2(n + cn) (tree, then chain), the top-k
-  // candidate scratch (u64), then [parent | rank | depth] int32 x n of the tree and x cn of the chain, then
-  // the step's committed length.
+  // candidate scratch (u64), then [parent | rank | depth] int32 x n of the tree and x cn of the chain.
   const int n = t->n_nodes, cn = TR_MAX_NODES;
   const size_t ancs = 2 * (size_t)(n + cn) * sizeof(uint64_t);
   const size_t cand = topk_scratch_bytes();
   const size_t ints = 3 * (size_t)(n + cn) * sizeof(int32_t);
   static_assert(sizeof(uint64_t) == 8, "section offsets below assume 8-byte words");
-  const size_t blob = ancs + cand + ints + sizeof(int32_t) * 64;
+  const size_t blob = ancs + cand + ints;
   unsigned char *h = new (std::nothrow) unsigned char[blob];
   if (h == nullptr) {
     delete c;
@@ -163,7 +162,6 @@ tr_status tr_create(int32_t V, int32_t k, const tr_tree_template *t, tr_ctx **ou
   c->tree = TreeDev{n, t->n_layers, di, di + n, di + 2 * n, da};
   c->chain = TreeDev{cn, cn, di + 3 * n, di + 3 * n + cn, di + 3 * n + 2 * cn, da + 2 * n};
   c->d_topk_cand = d + ancs;
-  c->d_step_L = reinterpret_cast<int32_t *>(d + ancs + cand + ints);
   *out = c;
   return TR_OK;
 }

@@ -471,11 +471,10 @@ __device__ inline void compact_head(T *__restrict__ K, T *__restrict__ Vt, size_
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__restrict__ Vt, int32_t cap, int32_t hd,
-                                                    int32_t tiled, const int32_t *__restrict__ step_L,
-                                                    const tr_step_out *__restrict__ out) {
+                                                    int32_t tiled, const tr_step_out *__restrict__ out) {
   extern __shared__ unsigned char smem_raw[];
   __shared__ int32_t path[TR_MAX_LAYERS];
-  const int a = out->n_accepted, L = *step_L;
+  const int a = out->n_accepted, L = out->kv_len - a - 1; // the committed length before the step
   if (threadIdx.x < TR_MAX_LAYERS) path[threadIdx.x] = out->path[threadIdx.x]; // asked for together with the two scalars
   if (a == 0) return;                                                         // root already sits at L
   __syncthreads();
@@ -489,15 +488,16 @@ __global__ __launch_bounds__(256) void k_compact_kv(T *__restrict__ K, T *__rest
 // winner       = deepest ok node, smallest index among equals
 // host: the same result in pinned memory of the context, when the caller waits for it: a copy kernel and its staging on the
 // host less per step (whole request on the tiny model, 19 steps: 2.11 -> 1.70 ms).
-// The kernel also publishes the committed length before the step (step_L) and advances *d_len, so
-// the compaction kernel that follows works from step_L and needs no further bookkeeping launch.
-// Where the compaction has few workgroups they are blocks 1 .. of this launch: each finds the winner for itself, and the last of all
-// blocks to have read the length advances it (an atomic per block on one word, about 20 ns each; the count wraps to zero).
+// The kernel also advances *d_len; the compaction kernel that follows takes the length before the step from the published result.
+// Where the compaction has few workgroups they are blocks 1 .. of this launch: each finds the winner for itself and takes the length
+// with an atomic add that counts it in the bits above LEN_BITS, and the last to do so replaces the count by what was accepted
+// (about 20 ns a block).  Nothing of either form stays behind: accepts into different caches may overlap on the device.
 // Two waves; what bounds it is the chain load -> barrier -> match -> barrier -> winner -> stores.  Every thread
 // places its own node: a node on the winner's path is entry popcount(path bits below it) of the path, and repeated
 // tokens are compared four at a time.  With one thread walking the 80 nodes for the path and every thread walking them
 // for the repeats the launch took 15.6 us (21.9 at 128 nodes).
 // ---------------------------------------------------------------------------------------------
+constexpr int LEN_BITS = 25;
 template <typename T, bool COMPACT>
 __global__ __launch_bounds__(COMPACT ? 256 : TR_MAX_NODES) void k_accept_update(const int32_t *__restrict__ S,
                                                                 const int32_t *__restrict__ topk,
@@ -506,8 +506,7 @@ __global__ __launch_bounds__(COMPACT ? 256 : TR_MAX_NODES) void k_accept_update(
                                                                 const int32_t *__restrict__ depth,
                                                                 const int32_t *__restrict__ parent, int32_t n_nodes, int32_t k,
                                                                 int32_t *__restrict__ d_len, int32_t V,
-                                                                int32_t *__restrict__ M, int32_t *__restrict__ step_L,
-                                                                tr_step_out *__restrict__ out,
+                                                                int32_t *__restrict__ M, tr_step_out *__restrict__ out,
                                                                 tr_step_out *__restrict__ host, int32_t mode,
                                                                 T *__restrict__ K, T *__restrict__ Vt, int32_t cap, int32_t hd,
                                                                 int32_t tiled) {
@@ -523,7 +522,17 @@ __global__ __launch_bounds__(COMPACT ? 256 : TR_MAX_NODES) void k_accept_update(
   const uint64_t anc0 = live ? anc[2 * i] : 0, anc1 = live ? anc[2 * i + 1] : 0;
   const int dep = live ? depth[i] : 0;
   const int par = live && i > 0 ? parent[i] : 0;
-  int L0 = i == 0 ? *d_len : 0;
+  int L0 = 0;
+  uint32_t before = 0; // blocks that took the length before this one
+  if (i == 0) {
+    if constexpr (COMPACT) {
+      const uint32_t got = atomicAdd(reinterpret_cast<uint32_t *>(d_len), 1u << LEN_BITS);
+      L0 = (int)(got & ((1u << LEN_BITS) - 1));
+      before = got >> LEN_BITS;
+    } else {
+      L0 = *d_len;
+    }
+  }
   int tk = -1;
   if (live) {
     tk = S[i];
@@ -577,7 +586,7 @@ __global__ __launch_bounds__(COMPACT ? 256 : TR_MAX_NODES) void k_accept_update(
     }
   };
   if constexpr (COMPACT) {
-    if (i == 0 && atomicInc(reinterpret_cast<uint32_t *>(step_L), gridDim.x - 1) == gridDim.x - 1) *d_len = L0 + a + 1;
+    if (i == 0 && before == gridDim.x - 1) atomicAdd(reinterpret_cast<uint32_t *>(d_len), (uint32_t)(a + 1) - (gridDim.x << LEN_BITS));
     if (blockIdx.x > 0) {
       if (a == 0) return; // root already sits at L
       extern __shared__ unsigned char smem_raw[];
@@ -590,10 +599,7 @@ __global__ __launch_bounds__(COMPACT ? 256 : TR_MAX_NODES) void k_accept_update(
   }
   publish(out);
   if (host != nullptr) publish(host);
-  if (!COMPACT && i == 0) {
-    *step_L = L0;
-    *d_len = L0 + a + 1;
-  }
+  if (!COMPACT && i == 0) *d_len = L0 + a + 1;
   if ((mode & TR_UPDATE_ACCEPTED_ONLY) != 0) { // uniform
     __syncthreads();
     if (!on_path && i < TR_MAX_NODES) sS[i] = -1;
@@ -684,24 +690,28 @@ hipError_t launch_sample_tokens(tr_ctx *c, const tr_kv *kv, const float *d_logit
                 c->V, pos0, noise_rows, inv_t, c->tree.depth, kv->d_len, d_tokens);
 }
 
-// Up to this many (layer, kv head) blocks are compacted by the accepting launch itself; more would queue at the atomic.  us a step of the
-// tiny model (8 blocks), two launches / one: 15 nodes 71.5 / 69.4, 80 nodes 85.2 / 81.8; a whole request 1749 / 1689.
+// Up to this many (layer, kv head) blocks are compacted by the accepting launch itself.  us an accept of 5 drafts (80 nodes) or 3 (15) in a graph of 40, two
+// launches / one: 80 nodes, 8 blocks 8.2 / 4.7, 16 blocks 8.6 / 4.7, 32 blocks 8.7 / 4.8; 15 nodes, 8 and 32 blocks 7.0 / 4.0 and 7.4 / 4.5.  A
+// step of the tiny model (8 blocks): 15 nodes 71.5 / 69.4, 80 nodes 85.2 / 81.8.  One launch is the faster with 40, 64 and 96 blocks too (8.9 / 4.9,
+// 8.9 / 5.1, 9.0 / 5.5); more than 32 have not been compared in whole steps and stay.
 constexpr int ACCEPT_COMPACT_BLOCKS = 32;
 template <typename T>
 static hipError_t launch_accept_t(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk, const int32_t *d_tokens,
                                   tr_step_out *d_out, tr_step_out *host_out, hipStream_t st) {
   const int blocks = kv->n_layers * kv->n_kv_heads;
   const size_t smem = 2 * (size_t)TR_MAX_LAYERS * kv->head_dim * sizeof(T);
-  auto accept = [&](auto kernel, int grid, int threads, size_t lds, int32_t *word) {
+  auto accept = [&](auto kernel, int grid, int threads, size_t lds) {
     return launch(kernel, dim3(grid), dim3(threads), lds, st, c->prof.next(PC_ACCEPT), d_S, d_topk, d_tokens, c->tree.anc, c->tree.depth,
-                  c->tree.parent, c->tree.n_nodes, c->k, kv->d_len, c->V, c->d_M, word, d_out, host_out, c->update_mode, (T *)kv->k,
+                  c->tree.parent, c->tree.n_nodes, c->k, kv->d_len, c->V, c->d_M, d_out, host_out, c->update_mode, (T *)kv->k,
                   (T *)kv->v, kv->capacity, kv->head_dim, kv->layout);
   };
-  if (blocks <= ACCEPT_COMPACT_BLOCKS && smem <= 32768) return accept(k_accept_update<T, true>, 1 + blocks, 256, smem, c->d_step_L + 1);
-  const hipError_t e = accept(k_accept_update<T, false>, 1, TR_MAX_NODES, 0, c->d_step_L);
+  static_assert(ACCEPT_COMPACT_BLOCKS + 1 < 1 << (32 - LEN_BITS), "the count of blocks fits above the length");
+  if (blocks <= ACCEPT_COMPACT_BLOCKS && smem <= 32768 && kv->capacity < 1 << LEN_BITS)
+    return accept(k_accept_update<T, true>, 1 + blocks, 256, smem);
+  const hipError_t e = accept(k_accept_update<T, false>, 1, TR_MAX_NODES, 0);
   if (e != hipSuccess) return e;
   return launch(k_compact_kv<T>, dim3(blocks), dim3(256), smem, st, c->prof.next(PC_COMPACT), (T *)kv->k, (T *)kv->v, kv->capacity,
-                kv->head_dim, kv->layout, c->d_step_L, d_out);
+                kv->head_dim, kv->layout, d_out);
 }
 
 hipError_t launch_accept_update(tr_ctx *c, const tr_kv *kv, const int32_t *d_S, const int32_t *d_topk,

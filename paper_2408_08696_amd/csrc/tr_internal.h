@@ -142,7 +142,6 @@ struct tr_ctx {
   tr::TreeDev tree;      // the static draft tree
   tr::TreeDev chain;     // chain of TR_MAX_NODES nodes (prefill chunks)
   void *d_tree_blob;     // backing store of both trees
-  int32_t *d_step_L;     // committed length at the start of the current accept/update
   tr_step_out *h_step;   // pinned: the result of a step whose caller waits for it
   void *d_topk_cand;     // top-k candidates of rows longer than one segment
   int32_t update_mode;   // tr_update_mode bits

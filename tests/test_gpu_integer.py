@@ -357,6 +357,47 @@ def test_accept_advances_the_length_once_a_call(layers, heads):
     ctx.close()
 
 
+@pytest.mark.parametrize("layers,heads", [(1, 1), (4, 8), (11, 3)])
+def test_accepts_into_two_caches_may_overlap(layers, heads):
+    """Accepts of one context on two streams, into caches of their own: no call depends on what another left in the context, in one
+    launch (up to 32 blocks) or in two.  Both write the same candidates.  Position p of a cache starts out holding p."""
+    require_gpu()
+    t, calls = synth.tree15(), 40
+    tree = O.make_tree(t.parent, t.rank, K)
+    path = list(tree.paths[t.n_nodes - 1])
+    ctx = tr.Context(64, K, t.parent, t.rank, t.n_layers)
+    S = np.arange(t.n_nodes) + 1
+    topk = np.full((t.n_nodes, K), 63)
+    for i in range(1, len(path)):
+        topk[path[i - 1], 0] = S[path[i]]
+    S, topk = (torch.from_numpy(x.astype(np.int32)).cuda() for x in (S, topk))
+    sides = []
+    for L in (7, 300):
+        kv = tr.KVDesc(synth.ModelShape("t", layers, heads * 32, heads, heads, 32, 32, 64, "f32"), L + calls * t.n_layers + t.n_nodes)
+        kp, vp = kv_plain_views(kv)
+        at = torch.arange(kv.capacity, device="cuda", dtype=torch.float32)
+        kp[:] = at[None, None, :, None]
+        vp[:] = -at[None, None, :, None]
+        kv.reset(L)
+        want = np.arange(kv.capacity)
+        for call in range(calls):
+            here = L + call * len(path)
+            want[here:here + len(path)] = want[[here + p for p in path]]
+        sides.append((kv, kp, vp, L, want, torch.zeros(tr.STEP_OUT_INTS, dtype=torch.int32, device="cuda"), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    say("accepts on two streams", layers, heads)
+    for call in range(calls):
+        for kv, _, _, _, _, out, stream in sides:
+            with torch.cuda.stream(stream):
+                ctx.accept_and_update(kv, S, topk, out)
+    torch.cuda.synchronize()
+    for kv, kp, vp, L, want, out, _ in sides:
+        assert int(kv.d_len.item()) == L + calls * len(path) == int(out[4].item())
+        want = torch.from_numpy(want.astype(np.float32)).cuda()[None, None, :, None]
+        assert (kp == want).all() and (vp == -want).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("mode", [tr.TR_UPDATE_FIRST, tr.TR_UPDATE_ACCEPTED_ONLY,
                                   tr.TR_UPDATE_FIRST | tr.TR_UPDATE_ACCEPTED_ONLY])
 def test_update_variants_match_oracle(mode):
