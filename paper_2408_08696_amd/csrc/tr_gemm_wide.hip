@@ -560,8 +560,9 @@ bool wide_updates_residual(int32_t n, int32_t K, int32_t out_tiles, int32_t max_
 // squares per row that *out_splits receives.
 hipError_t launch_gemm_wide(const GemmArgs &args, int32_t max_splits, int32_t *out_splits, hipStream_t st, KernelTimer tm) {
   GemmArgs g = args;
-  if (g.n < 1 || g.n > WIDE_MAX_ROWS || g.K % 32 != 0 || g.K < 64 || (g.row_ssq != nullptr && g.n_ssq > 8 && g.n_ssq % 4 != 0))
-    return hipErrorInvalidValue;
+  if (g.n < 1 || g.n > WIDE_MAX_ROWS || g.K % 32 != 0 || g.K < 64) return hipErrorInvalidValue;
+  if (g.row_ssq != nullptr && g.n_ssq > 8 && (g.n_ssq % 4 != 0 || !starts_on_16(g.row_ssq))) return hipErrorInvalidValue;
+  if (g.n_seg != (g.rope.q != nullptr ? 3 : 1)) return hipErrorInvalidValue; // only Q/K/V walks several matrices
   int32_t total = 0;
   for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   if (total < 1 || (g.mode != GEMM_STORE && g.mode != GEMM_SWIGLU)) return hipErrorInvalidValue;
@@ -678,6 +679,7 @@ hipError_t launch_gemm_rows8(const GemmArgs &args, const Rows8Plan &plan, hipStr
   const unsigned grid = (unsigned)(((g.groups + 7) / 8) * 8 * g.splits);
   const bool swiglu = g.mode == GEMM_SWIGLU, scaled = g.row_ssq != nullptr;
   if (g.n < 1 || g.n > NP || (scaled ? g.n_ssq > 8 || g.splits != 1 : swiglu)) return hipErrorInvalidValue;
+  if (g.n_seg != 1 && g.n_seg != 3) return hipErrorInvalidValue;
   // Chains of 16 k-steps: as long as a wave's in the decode kernel at K = 4096 in eight waves, or in shares of 128, and shorter than
   // all others there.  Its MFMA adds 32 products, these 16 twice, and the errors are the same: relative to float64 1.31e-7 with both for
   // 4096 -> 32064, 96 and 128 rows; where the decode kernel has four waves (80 rows) 1.81e-7 / 1.32e-7.
