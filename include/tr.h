@@ -202,8 +202,9 @@ tr_status tr_pack_weight_rope(const void *d_src, void *d_dst, int32_t out_f, int
                               int32_t head_dim, void *stream);
 
 /*
- * Launch plan of one packed projection by the decode projection kernel (diagnostic; touches no GPU), which is the one
- * tr_op_linear takes for up to TR_MAX_NODES rows; tr_plan_step_projection says what a step launches.  For n_rows activation rows
+ * Launch plan of one packed projection by the decode projection kernel (diagnostic; touches no GPU); tr_plan_step_projection says
+ * which kernel a step launches.  With max_splits > 1 it is a projection that feeds the residual stream (o, down), behind which a plan
+ * may save a launch.  For n_rows activation rows
  * (tree nodes, Section 2.2: all nodes of the draft tree go through the model in one forward) and a
  * weight of [out_f, in_f]: plan[0] = most 16-row weight
  * tiles one workgroup owns (gate/up tile pairs when fused_pair != 0, where out_f counts one of the two
@@ -214,6 +215,13 @@ tr_status tr_pack_weight_rope(const void *d_src, void *d_dst, int32_t out_f, int
  */
 tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t fused_pair,
                              int32_t max_splits, int32_t *plan);
+
+/*
+ * Launch plan of tr_op_linear with packed weights and up to TR_MAX_NODES rows, by the same kernel (diagnostic; touches no GPU): plan[0],
+ * plan[1] as in tr_plan_projection, in the given splits of the input dimension.  plan is [host], 2 values.  TR_EINVAL for null plan, splits
+ * outside 1..4, or a shape the packed kernels do not take.
+ */
+tr_status tr_plan_linear(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t splits, int32_t *plan);
 
 /*
  * What tr_verify_forward launches for one packed projection of a step (diagnostic; touches no GPU): plan[0..2] as in

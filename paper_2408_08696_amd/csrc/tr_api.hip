@@ -208,7 +208,14 @@ tr_status tr_plan_projection(int32_t n_rows, int32_t in_f, int32_t out_f, int32_
                              int32_t *plan) {
   if (plan == nullptr || max_splits < 1 || !gemm_mfma_supported(n_rows, in_f, out_f)) return TR_EINVAL;
   const int32_t tiles = out_f / 16;
-  gemm_choose(n_rows, in_f, tiles, fused_pair != 0, fused_pair != 0 ? 1 : max_splits, &plan[0], &plan[1], &plan[2]);
+  gemm_choose(n_rows, in_f, tiles, fused_pair != 0, fused_pair != 0 ? 1 : max_splits, fused_pair == 0 && max_splits > 1, &plan[0], &plan[1], &plan[2]);
+  return TR_OK;
+}
+
+tr_status tr_plan_linear(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t splits, int32_t *plan) {
+  if (plan == nullptr || splits < 1 || splits > GEMM_MAX_SPLITS || !gemm_mfma_supported(n_rows, in_f, out_f)) return TR_EINVAL;
+  int32_t fewer;
+  gemm_choose(n_rows, in_f, out_f / 16, false, splits, false, &plan[0], &plan[1], &fewer);
   return TR_OK;
 }
 
@@ -225,7 +232,7 @@ tr_status tr_plan_step_projection(int32_t projection, int32_t n_rows, int32_t in
     plan[3] = 1;
     return TR_OK;
   }
-  gemm_choose(n_rows, in_f, out_f / 16, pair, max_splits, &plan[0], &plan[1], &plan[2]);
+  gemm_choose(n_rows, in_f, out_f / 16, pair, max_splits, max_splits > 1, &plan[0], &plan[1], &plan[2]);
   plan[3] = 0;
   return TR_OK;
 }

@@ -509,7 +509,7 @@ static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipSt
     g.splits = plan.splits;
     return launch_gemm_rows8(g, plan, st, tm);
   }
-  gemm_plan(g, max_splits);
+  gemm_plan(g, max_splits, max_splits > 1); // o and down alone may be split
   return launch_gemm_mfma(g, st, tm);
 }
 
@@ -550,7 +550,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
     next.row_ssq = ssq; next.n_ssq = n_ssq; next.norm_dim = d; next.eps = m.rms_eps;
     Rows8Plan r8;
     if (!project_rows8(g, GEMM_MAX_SPLITS, &r8) && !project_rows8(next, 1, &r8)) {
-      gemm_plan(g, GEMM_MAX_SPLITS);
+      gemm_plan(g, GEMM_MAX_SPLITS, true);
       if (gemm_updates_residual(n, g.groups, g.splits)) {
         next.n_ssq = n_ssq = (g.groups + 3) & ~3;
         g.resid = GemmResid{x, (const T *)gain, xn, ssq, n_ssq};
@@ -764,7 +764,7 @@ hipError_t run_linear(const void *x, const void *w, int32_t dtype, int32_t layou
     if (n > NP) { // the prompt-ingestion kernel; it may use fewer splits than allowed
       TR_TRY(launch_gemm_wide(g, splits, &splits, st));
     } else {
-      gemm_plan(g, splits);
+      gemm_plan(g, splits, false);
       g.splits = splits; // the caller's split count is used as given
       TR_TRY(launch_gemm_mfma(g, st));
     }

@@ -454,7 +454,7 @@ static bool variant_ok(int NT, int p, bool swiglu) {
 // per-CU rate, or the round's weight stream at the HBM rate if that is slower, plus a fixed cost per
 // round and what the consumer pays to re-read K-split partial sums.  Rates in KiB/us, fitted to
 // measurements on MI355X.
-void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, int32_t *out_p,
+void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, bool feeds_x, int32_t *out_p,
                  int32_t *out_groups, int32_t *out_splits) {
   const int NT = (n + 15) / 16, KT = K / 32;
   const double wmul = swiglu ? 2.0 : 1.0;
@@ -478,7 +478,7 @@ void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t
       if (hbm_kib / 6000.0 > t) t = hbm_kib / 6000.0;
       t = rounds * (t + 3.0) + 3.0;
       if (s > 1) t += 2.0 * (s - 1) * NT * total_tiles / 8000.0 + 0.5; // extra KiB of partials written and re-read
-      if (max_splits > 1 && !gemm_updates_residual(n, groups, s)) t += 2.5; // the residual kernel, less what its absence costs
+      if (feeds_x && !gemm_updates_residual(n, groups, s)) t += 2.5; // the residual kernel, less what its absence costs
       if (t < best) {
         best = t;
         bp = p;

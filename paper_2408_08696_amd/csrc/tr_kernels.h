@@ -120,14 +120,15 @@ struct GemmArgs {
   GemmResid resid;          // residual epilogue (see above), off when resid.x == nullptr
 };
 
-// Fills g.total_tiles, g.tiles_per_wg, g.groups and g.splits (<= max_splits; 1 for GEMM_SWIGLU).
-void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, int32_t *out_pmax,
+// Fills g.total_tiles, g.tiles_per_wg, g.groups and g.splits (<= max_splits; 1 for GEMM_SWIGLU).  feeds_x: o and down of a step, behind
+// which a residual kernel is launched unless they update the residual stream themselves.
+void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, bool feeds_x, int32_t *out_pmax,
                  int32_t *out_groups, int32_t *out_splits);
-inline void gemm_plan(GemmArgs &g, int32_t max_splits) {
+inline void gemm_plan(GemmArgs &g, int32_t max_splits, bool feeds_x) {
   int32_t total = 0;
   for (int i = 0; i < g.n_seg; ++i) total += g.seg[i].out_tiles;
   g.total_tiles = total;
-  gemm_choose(g.n, g.K, total, g.mode == GEMM_SWIGLU, g.mode == GEMM_SWIGLU ? 1 : max_splits, &g.tiles_per_wg,
+  gemm_choose(g.n, g.K, total, g.mode == GEMM_SWIGLU, g.mode == GEMM_SWIGLU ? 1 : max_splits, feeds_x, &g.tiles_per_wg,
               &g.groups, &g.splits);
 }
 

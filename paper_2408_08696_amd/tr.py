@@ -69,6 +69,7 @@ _SIGS = {
     "tr_build_tree": [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p],
     "tr_workspace_bytes": [C.c_void_p, C.POINTER(Model), C.POINTER(C.c_size_t)],
     "tr_plan_projection": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
+    "tr_plan_linear": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_step_projection": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_attention": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_attention_form": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
@@ -245,9 +246,17 @@ class Context:
 
 
 def plan_projection(n_rows: int, in_f: int, out_f: int, fused_pair: bool = False, max_splits: int = 4):
-    """(weight tiles per workgroup, workgroups per split, splits) of one packed projection by the decode kernel."""
+    """(weight tiles per workgroup, workgroups per split, splits) of one packed projection by the decode kernel; with max_splits > 1
+    one that feeds the residual stream."""
     plan = (C.c_int32 * 3)()
     _check(lib().tr_plan_projection(n_rows, in_f, out_f, int(fused_pair), max_splits, plan), "tr_plan_projection")
+    return tuple(plan)
+
+
+def plan_linear(n_rows: int, in_f: int, out_f: int, splits: int = 1):
+    """(weight tiles per workgroup, workgroups per split) of op_linear with packed weights and up to TR_MAX_NODES rows."""
+    plan = (C.c_int32 * 2)()
+    _check(lib().tr_plan_linear(n_rows, in_f, out_f, splits, plan), "tr_plan_linear")
     return tuple(plan)
 
 

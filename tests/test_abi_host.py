@@ -124,6 +124,23 @@ def test_projection_plan_rejects_bad_shapes(lib):
     assert lib.tr_plan_projection(80, 4096, 4096, 0, 0, plan) == tr.TR_EINVAL
 
 
+@pytest.mark.parametrize("n,in_f,out_f,splits,plan", [
+    # op_linear stores its sums: that a step's o could save a launch by staying whole is no reason for it to take more workgroups.  One round
+    (20, 4096, 4096, 2, (2, 128)), (1, 3200, 3200, 2, (2, 100)), (32, 3200, 3200, 4, (4, 50)), (20, 6656, 6656, 2, (4, 104)),
+    (20, 4096, 4096, 1, (1, 256)), (80, 4096, 4096, 4, (4, 64))])
+def test_linear_plans(lib, n, in_f, out_f, splits, plan):
+    assert tr.plan_linear(n, in_f, out_f, splits) == plan and plan[1] * splits <= 256
+
+
+def test_linear_plan_rejects_bad_shapes(lib):
+    plan = (C.c_int32 * 2)()
+    f = lib.tr_plan_linear
+    assert f(80, 4096, 4096, 2, None) == tr.TR_EINVAL and f(0, 4096, 4096, 2, plan) == tr.TR_EINVAL
+    assert f(129, 4096, 4096, 2, plan) == tr.TR_EINVAL and f(80, 4100, 4096, 2, plan) == tr.TR_EINVAL
+    assert f(80, 4096, 4100, 2, plan) == tr.TR_EINVAL and f(80, 4096, 4096, 0, plan) == tr.TR_EINVAL
+    assert f(80, 4096, 4096, 5, plan) == tr.TR_EINVAL
+
+
 def test_projection_plans_of_the_7b_step_fill_the_chip(lib):
     # the five projections of a 7B layer at the 80-node tree: every plan puts work on >= 230 of 256 CUs
     for in_f, out_f, fused, ms in ((4096, 12288, False, 1), (4096, 4096, False, 4), (4096, 11008, True, 1),

@@ -1007,7 +1007,7 @@ def test_linear_row_limits():
 
 
 def test_linear_packed_every_planned_variant():
-    """Every (row tiles, weight tiles per workgroup) pair the launch planner can choose over a grid of shapes,
+    """Every (row tiles, weight tiles per workgroup) pair the operation's planner can choose over a grid of shapes,
     with 1, 2 and 4 K-splits, is run once at the cheapest shape that selects it, against a float64 matrix
     product."""
     require_gpu()
@@ -1018,7 +1018,7 @@ def test_linear_packed_every_planned_variant():
                 if K_ * O_ > 140e6:
                     continue
                 for ms in (1, 2, 4):
-                    p, _, _ = tr.plan_projection(n, K_, O_, False, ms)
+                    p, _ = tr.plan_linear(n, K_, O_, ms)
                     key, cost = ((n + 15) // 16, p, ms), n * K_ * O_   # the op runs exactly ms K-splits
                     if key not in chosen or cost < chosen[key][0]:
                         chosen[key] = (cost, (n, K_, O_, ms))
