@@ -478,7 +478,9 @@ void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t
       if (hbm_kib / 6000.0 > t) t = hbm_kib / 6000.0;
       t = rounds * (t + 3.0) + 3.0;
       if (s > 1) t += 2.0 * (s - 1) * NT * total_tiles / 8000.0 + 0.5; // extra KiB of partials written and re-read
-      if (feeds_x && !gemm_updates_residual(n, groups, s)) t += 2.5; // the residual kernel, less what its absence costs
+      // the residual kernel, less what its absence costs.  Not two out-tiles for its sake (6432 .. 7744 outputs, o of 17 to 32 rows): us a step
+      // of six layers of 6656 with 17, 20, 32 nodes, o as 4 x 104 x 2 and k_add_frag / as 2 x 208 and fused 1334 / 1379, 1346 / 1384, 1359 / 1366
+      if (feeds_x && !(tpw == 1 && gemm_updates_residual(n, groups, s))) t += 2.5;
       if (t < best) {
         best = t;
         bp = p;

@@ -219,6 +219,16 @@ def test_projections_in_shares_of_k(lib, in_f, out_f, shared, decode):
         assert tr.plan_step_projection("o_down", n, in_f, out_f)[3] == 0, n
 
 
+def test_whole_o_and_down_of_few_rows(lib):
+    # kept whole so that they update the residual stream themselves: with one out-tile a workgroup, not with two for its sake
+    for n in (17, 20, 32):
+        assert tr.plan_step_projection("o_down", n, 4096, 4096) == (1, 256, 1, 0), n
+        assert tr.plan_step_projection("o_down", n, 3200, 3200) == (1, 200, 1, 0), n
+        for d in (6432, 6656, 7168, 7744):
+            assert tr.plan_step_projection("o_down", n, d, d)[2:] == (2, 0), (n, d)
+        assert tr.plan_step_projection("o_down", n, 8192, 8192) == (2, 256, 1, 0), n    # the faster plan in any case
+
+
 def test_step_projections_of_the_7b_step_fill_the_chip(lib):
     # what 80- and 128-node steps of the 7B shape launch: with 128 nodes gate/up and the LM head share operands in LDS
     for projection, in_f, out_f, kernel in (("qkv", 4096, 12288, 0), ("o_down", 4096, 4096, 0), ("gate_up", 4096, 11008, 1),
