@@ -224,7 +224,7 @@ def test_whole_o_and_down_of_few_rows(lib):
     for n in (17, 20, 32):
         assert tr.plan_step_projection("o_down", n, 4096, 4096) == (1, 256, 1, 0), n
         assert tr.plan_step_projection("o_down", n, 3200, 3200) == (1, 200, 1, 0), n
-        for d in (6432, 6656, 7168, 7744):
+        for d in (6432, 6656, 7168, 7552):
             assert tr.plan_step_projection("o_down", n, d, d)[2:] == (2, 0), (n, d)
         assert tr.plan_step_projection("o_down", n, 8192, 8192) == (2, 256, 1, 0), n    # the faster plan in any case
 
