@@ -299,13 +299,17 @@ __device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 
     }
     pk = uint4{o[0], o[1], o[2], o[3]};
   }
-  // Written through up to 1 MiB.  us a step, plain / through: 7B width, 80 nodes (640 KiB) 3713 / 3641, 13B (20 layers, 800 KiB) 3362 /
-  // 3344, 7B, 128 nodes (1 MiB) 4821 / 4805, 70B (6 layers, 80 nodes, 1.3 MiB) 2411 / 2419; prompt of 511 tokens at 7B width (16 layers)
-  // 3913 / 3986.  7B, 80 nodes, without the streaming hint 3685, with that alone 3727; with the rows of a line on one XCD 3726 plain,
-  // 3668 through.  No gain in the partial sums, x, the queries or SwiGLU's output.
+  // Written through in steps of four row tiles and more, from 2560 columns on and up to 1 MiB: the stores then reach memory before the
+  // launch ends, which costs small operands more than the lines left dirty.  us a step, plain / through, on the same buffers: 7B
+  // width, 80 nodes (640 KiB) 3714 / 3641, 13B (20 layers, 800 KiB) 3170 / 3115, 10 layers of 7B width, 64, 96, 128 nodes 1152 / 1115, 1377 / 1365,
+  // 1542 / 1538, 12 layers of 2560, 3072, 3200, 80 nodes 934 / 918, 1016 / 1013, 1199 / 1163, but two of 512 (80 KiB) 81.9 / 83.3, 16 of 1024 650 / 658, of
+  // 2048 1019 / 1020, and 15 nodes at 1024, 2560, 3072 523 / 526, 658 / 663, 756 / 761, 33 and 48 at 4096 1069 / 1072, 1082 / 1087.  70B (6 layers, 80 nodes, 1.3 MiB)
+  // 2411 / 2419; prompts: 511 tokens at 7B width (16 layers) 3913 / 3986, 300 tokens of the two layers of 512 92.1 / 96.2.  7B, 80 nodes, without the streaming
+  // hint 3685, with that alone 3727; with the rows of a line on one XCD 3726 plain, 3668 through.  No gain in the partial sums, x, the
+  // queries or SwiGLU's output.
   const size_t at = act_frag_index(row, j, row_tiles);
   if (j < d) {
-    if (row_tiles * 16 * d <= (1 << 20) / 2) store_through(xg_frag, (uint32_t)at * 2, pk);
+    if (row_tiles >= 4 && row_tiles <= NP / 16 && d >= 2560 && row_tiles * 16 * d <= (1 << 20) / 2) store_through(xg_frag, (uint32_t)at * 2, pk);
     else *reinterpret_cast<uint4 *>(xg_frag + at) = pk;
   }
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
