@@ -227,14 +227,31 @@ tr_status tr_plan_linear(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t sp
  * What tr_verify_forward launches for one packed projection of a step (diagnostic; touches no GPU): plan[0..2] as in
  * tr_plan_projection, plan[3] = 0 for the decode projection kernel, 1 for the kernel that shares operands in LDS, which
  * matrices of very many rows take (with weights and workspace on 16 bytes, else the decode kernel's plan holds).  out_f is the sum
- * over the three matrices of the Q/K/V projection, one of the two of gate/up.  plan is [host], 4 values.  Q/K/V is reported as
- * launched with a plain cache; into a tiled one wide models (in_f from 5120 on) write it from 33 or 81 rows on by the other kernel in
- * 2 to 4 splits of the input dimension and a launch that adds them.
+ * over the three matrices of the Q/K/V projection, one of the two of gate/up.  plan is [host], 4 values.  Q/K/V is reported
+ * as launched where it is not split over the input dimension, which tr_plan_step_qkv says.
  * TR_EINVAL for null plan, an unknown projection, or a shape the packed kernels do not take.
  */
 typedef enum { TR_PROJ_QKV = 0, TR_PROJ_O_DOWN = 1, TR_PROJ_GATE_UP = 2, TR_PROJ_LM_HEAD = 3 } tr_projection;
 tr_status tr_plan_step_projection(int32_t projection, int32_t n_rows, int32_t in_f, int32_t out_f,
                                   int32_t *plan);
+
+/*
+ * The same for the Q/K/V projection of n_heads query heads and n_kv_heads key / value heads into a cache of this layout
+ * (diagnostic; touches no GPU): plan[2] = 1 and plan[3] = 0 where the decode projection kernel writes queries, keys and values, or
+ * plan[2] = 2 to 4 splits and plan[3] = 1 where the other kernel leaves partial sums to a launch of its own that adds them, rotates
+ * and writes (tiled cache, weights and workspace on 16 bytes).  plan is [host], 4 values.  TR_EINVAL for null plan, heads or
+ * layout that no model has, or a shape the packed kernels do not take.
+ */
+tr_status tr_plan_step_qkv(int32_t n_rows, int32_t in_f, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim, int32_t kv_layout,
+                           int32_t *plan);
+
+/*
+ * How a prompt-ingestion pass of n_rows > TR_MAX_NODES tokens takes o or down (diagnostic; touches no GPU): plan[0], plan[1] = 16-row
+ * tiles of activations and of weights a workgroup owns, plan[2] = groups of out-tiles, plan[3] = splits of the input dimension.  Where
+ * neither o nor down of a pass is split both update the residual stream in their own epilogue, else a residual kernel follows each.  plan
+ * is [host], 4 values.  TR_EINVAL for null plan, n_rows outside TR_MAX_NODES + 1 .. 2048, or a shape the kernel does not take.
+ */
+tr_status tr_plan_ingestion(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t *plan);
 
 /*
  * Launch plan of the tree-attention kernel (Section 2.2 "Tree Attention") for n_heads query heads over

@@ -237,6 +237,34 @@ tr_status tr_plan_step_projection(int32_t projection, int32_t n_rows, int32_t in
   return TR_OK;
 }
 
+tr_status tr_plan_step_qkv(int32_t n_rows, int32_t in_f, int32_t n_heads, int32_t n_kv_heads, int32_t head_dim, int32_t kv_layout,
+                           int32_t *plan) {
+  if (plan == nullptr || n_kv_heads < 1 || n_heads < n_kv_heads || n_heads % n_kv_heads != 0 || head_dim < 2 || head_dim % 2 != 0 ||
+      head_dim > 256 || (kv_layout != TR_KV_PLAIN && kv_layout != TR_KV_TILED) || n_heads > (1 << 20))
+    return TR_EINVAL;
+  const int32_t out_f = (n_heads + 2 * n_kv_heads) * head_dim;
+  Rows8Plan p;
+  if (!gemm_mfma_supported(n_rows, in_f, out_f)) return TR_EINVAL;
+  if (!step_qkv_plan(n_rows, in_f, n_heads, n_kv_heads, head_dim, kv_layout, &p))
+    return tr_plan_step_projection(TR_PROJ_QKV, n_rows, in_f, out_f, plan);
+  plan[0] = p.out_tiles;
+  plan[1] = p.groups;
+  plan[2] = p.splits;
+  plan[3] = 1;
+  return TR_OK;
+}
+
+tr_status tr_plan_ingestion(int32_t n_rows, int32_t in_f, int32_t out_f, int32_t *plan) {
+  if (plan == nullptr || n_rows <= TR_MAX_NODES || n_rows > NPW_MOST || out_f < 1 || !gemm_wide_supported(n_rows, in_f, out_f))
+    return TR_EINVAL;
+  const WideProjection p = wide_plan(n_rows, in_f, out_f / 16);
+  plan[0] = p.row_tiles;
+  plan[1] = p.out_tiles;
+  plan[2] = p.groups;
+  plan[3] = p.splits;
+  return TR_OK;
+}
+
 tr_status tr_plan_attention(int32_t n_heads, int32_t n_kv_heads, int32_t n_nodes, int32_t len_bound, int32_t *plan) {
   if (plan == nullptr || n_kv_heads < 1 || n_heads < n_kv_heads || n_heads % n_kv_heads != 0 || n_nodes < 1 ||
       n_nodes > TR_MAX_NODES || len_bound < 1)

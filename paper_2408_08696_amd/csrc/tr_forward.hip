@@ -495,7 +495,6 @@ static bool packed_supported(const tr_model &m) {
          hk % 32 == 0 && m.vocab % 32 == 0;
 }
 
-// One projection of a tree step by the faster of its two kernels; fills g.splits.  (tr_plan_step_projection says which.)
 static bool operands_on_16(const GemmArgs &g) { // what goes straight into LDS
   bool on = starts_on_16(g.a_frag) && starts_on_16(g.w2);
   for (int i = 0; i < g.n_seg; ++i) on = on && starts_on_16(g.seg[i].w);
@@ -507,6 +506,7 @@ static bool project_rows8(const GemmArgs &g, int32_t max_splits, Rows8Plan *plan
   const bool swiglu = g.mode == GEMM_SWIGLU, scaled = g.row_ssq != nullptr;
   return operands_on_16(g) && g.rope.q == nullptr && (scaled ? g.n_ssq <= 8 : !swiglu) && rows8_plan(g.n, g.K, total, swiglu, swiglu || scaled ? 1 : max_splits, plan);
 }
+// One projection of a tree step by the faster of its two kernels; fills g.splits.  (tr_plan_step_projection says which.)
 static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipStream_t st) {
   Rows8Plan plan;
   if (project_rows8(g, max_splits, &plan)) {
@@ -515,6 +515,13 @@ static hipError_t project(GemmArgs &g, int32_t max_splits, KernelTimer tm, hipSt
   }
   gemm_plan(g, max_splits, max_splits > 1); // o and down alone may be split
   return launch_gemm_mfma(g, st, tm);
+}
+
+// Q/K/V in shares of k, whose sums lie in ypart behind a step's other partial sums and the sums of squares.
+bool step_qkv_plan(int32_t n, int32_t d, int32_t H, int32_t Hkv, int32_t hd, int32_t layout, Rows8Plan *plan) {
+  const int O = (H + 2 * Hkv) * hd;
+  return hd == 128 && layout == TR_KV_TILED && qkv_split_plan(n, d, O / 16, plan) &&
+         (size_t)plan->splits * n * O + 8192 + 4 <= (size_t)(WIDE_PART_ROWS - GEMM_MAX_SPLITS * NP) * d;
 }
 
 static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeDev &tree, int32_t n, const int32_t *tok,
@@ -580,8 +587,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
                         H, Hkv, hd, kv.capacity, kv.layout};
       const int O = hq + 2 * hk;
       Rows8Plan plan;
-      if (hd == 128 && kv.layout == TR_KV_TILED && n_ssq <= 8 && operands_on_16(g) && qkv_split_plan(n, d, O / 16, &plan) &&
-          (size_t)plan.splits * n * O + 8192 + 4 <= (size_t)(WIDE_PART_ROWS - GEMM_MAX_SPLITS * NP) * d) {
+      if (n_ssq <= 8 && operands_on_16(g) && step_qkv_plan(n, d, H, Hkv, hd, kv.layout, &plan)) {
         const GemmRope rp = g.rope;
         float *const parts = ssq + 8192; // behind the sums of squares
         g.rope = GemmRope{};
@@ -606,7 +612,7 @@ static hipError_t forward_packed(const tr_model &m, const tr_kv &kv, const TreeD
     up.n_seg = 1; up.w2 = (const T *)lw.w_up; up.h_frag = hbuf; up.mode = GEMM_SWIGLU;
     TR_TRY(residual(attn, hq, lw.wo, lw.ffn_norm, up, PC_OPROJ));
     TR_TRY(project(up, 1, prof_next(prof, PC_GATEUP), st));
-    GemmArgs next{}; // the LM head, or a Q/K/V projection, which the decode kernel takes always
+    GemmArgs next{}; // the LM head, or nothing for Q/K/V: of the up to two row tiles that count here the decode kernel takes it always
     if (l == m.n_layers - 1) {
       next.a_frag = xn; next.n = n; next.K = d;
       next.seg[0] = GemmSeg{(const T *)m.lm_head, m.vocab / 16};
@@ -642,13 +648,13 @@ static hipError_t forward_wide(const tr_model &m, const tr_kv &kv, int32_t n, in
   const int nch = (d + NORM_CHUNK - 1) / NORM_CHUNK;
   const KernelTimer no_timer{};
   const size_t ystride = (size_t)RT * 16 * d; // the fewer rows a pass has, the more partial sums fit ypart
-  const int max_splits = WIDE_PART_ROWS / (RT * 16) < WIDE_MAX_SPLITS ? WIDE_PART_ROWS / (RT * 16) : WIDE_MAX_SPLITS;
+  const int max_splits = wide_max_splits(n);
 
   TR_TRY(launch(k_embed_frag, dim3(RT * 16, nch + 1), dim3(128), 0, st, no_timer, (const T *)m.embed, m.vocab, tok,
                 (const int32_t *)nullptr, kv.d_len, hd, m.rope_theta, x, rope, (const T *)m.layers[0].attn_norm, n, d, RT,
                 xn, ssq, nch));
   // Without partial sums of either o or down, ypart holds the sums of squares they leave (a row of x is as long as its sums at least).
-  const bool fused = wide_updates_residual(n, hq, d / 16, max_splits) && wide_updates_residual(n, F, d / 16, max_splits);
+  const bool fused = wide_plan(n, hq, d / 16).splits == 1 && wide_plan(n, F, d / 16).splits == 1;
   float *const fused_ssq = (float *)(((uintptr_t)ypart + 15) & ~(uintptr_t)15);
   int n_ssq = nch;
   auto residual = [&](const T *a, int K, const void *wt, const void *gain) { // x += a * wt^T and the next operand

@@ -549,8 +549,10 @@ static WidePlan wide_choose(int n, int K, int total, int unit, int max_splits) {
   }
   return plan;
 }
-bool wide_updates_residual(int32_t n, int32_t K, int32_t out_tiles, int32_t max_splits) {
-  return wide_choose(n, K, out_tiles, 1, max_splits).splits == 1;
+WideProjection wide_plan(int32_t n, int32_t K, int32_t out_tiles) {
+  const WidePlan p = wide_choose(n, K, out_tiles, 1, wide_max_splits(n));
+  const WideShape &s = WIDE_SHAPES[p.shape];
+  return WideProjection{s.rb, s.nw, wide_groups(out_tiles, s.nw, 1), p.splits};
 }
 
 // Fills the plan and the tile assignment and launches.  g.n is the total row count

@@ -159,9 +159,16 @@ constexpr int WIDE_MAX_SPLITS = 4;
 bool gemm_wide_supported(int32_t n, int32_t K, int32_t O);
 hipError_t launch_gemm_wide(const GemmArgs &g, int32_t max_splits, int32_t *out_splits, hipStream_t st,
                             KernelTimer tm = KernelTimer{});
-// Whether o and down of an ingestion pass are best not split over k: then they update the residual stream themselves (GemmResid; ld_ssq
-// is filled by the launch).
-bool wide_updates_residual(int32_t n, int32_t K, int32_t out_tiles, int32_t max_splits);
+// How an ingestion pass of n rows takes o or down: workgroup shape (row tiles x out-tiles), groups of out-tiles, k-splits.  Where neither is
+// split they update the residual stream themselves (GemmResid; ld_ssq is filled by the launch).
+struct WideProjection {
+  int32_t row_tiles, out_tiles, groups, splits;
+};
+WideProjection wide_plan(int32_t n, int32_t K, int32_t out_tiles);
+inline int32_t wide_max_splits(int32_t n) { // as many partial sums of all row tiles as ypart has room for
+  const int fit = WIDE_PART_ROWS / ((n + 15) / 16 * 16);
+  return fit < WIDE_MAX_SPLITS ? fit : WIDE_MAX_SPLITS;
+}
 // The same kernel for a tree step's rows (n <= TR_MAX_NODES), where it is the faster one: true and the plan, else
 // launch_gemm_mfma is.  Operands have to start on 16 bytes.  max_splits > 1: a plain store without an RMS scale.
 struct Rows8Plan {
@@ -169,8 +176,10 @@ struct Rows8Plan {
 };
 bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t max_splits, Rows8Plan *plan);
 hipError_t launch_gemm_rows8(const GemmArgs &g, const Rows8Plan &plan, hipStream_t st, KernelTimer tm = KernelTimer{});
-// Q/K/V of a step split over k, with a launch behind it that adds the shares, scales, rotates and writes (k_qkv_finish).
+// Q/K/V of a step split over k, with a launch behind it that adds the shares, scales, rotates and writes (k_qkv_finish): by size, and
+// (operands on 16 bytes) whether a step with this cache and workspace takes it.
 bool qkv_split_plan(int32_t n, int32_t K, int32_t total_tiles, Rows8Plan *plan);
+bool step_qkv_plan(int32_t n, int32_t d, int32_t H, int32_t Hkv, int32_t hd, int32_t layout, Rows8Plan *plan);
 hipError_t launch_pack_weight(const bf16_t *src, bf16_t *dst, int32_t O, int32_t K, int32_t rope_hd, hipStream_t st);
 
 // Shape-generic projections on row-major weights with their prologue and epilogue (tr_rows.hip).

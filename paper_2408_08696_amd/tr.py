@@ -69,6 +69,8 @@ _SIGS = {
     "tr_build_tree": [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p],
     "tr_workspace_bytes": [C.c_void_p, C.POINTER(Model), C.POINTER(C.c_size_t)],
     "tr_plan_projection": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
+    "tr_plan_step_qkv": [C.c_int32] * 6 + [C.POINTER(C.c_int32)],
+    "tr_plan_ingestion": [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_linear": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_step_projection": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
     "tr_plan_attention": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)],
@@ -266,9 +268,24 @@ ATTENTION_FORMS = ("few_rows", "one_launch", "short_shares", "long_shares")
 
 def plan_step_projection(projection: str, n_rows: int, in_f: int, out_f: int):
     """(weight tiles per workgroup, workgroups per split, splits, kernel) of what a step launches; kernel 0 is the decode
-    projection kernel, 1 the one that shares operands in LDS."""
+    projection kernel, 1 the one that shares operands in LDS.  "qkv": where plan_step_qkv does not split it."""
     plan = (C.c_int32 * 4)()
     _check(lib().tr_plan_step_projection(PROJECTIONS.index(projection), n_rows, in_f, out_f, plan), "tr_plan_step_projection")
+    return tuple(plan)
+
+
+def plan_step_qkv(n_rows: int, in_f: int, n_heads: int, n_kv_heads: int, head_dim: int = 128, tiled: bool = True):
+    """(weight tiles per workgroup, workgroups per split, splits, kernel) of a step's Q/K/V projection."""
+    plan = (C.c_int32 * 4)()
+    _check(lib().tr_plan_step_qkv(n_rows, in_f, n_heads, n_kv_heads, head_dim, int(tiled), plan), "tr_plan_step_qkv")
+    return tuple(plan)
+
+
+def plan_ingestion(n_rows: int, in_f: int, out_f: int):
+    """(row tiles, out-tiles per workgroup, groups, splits) of o or down in an ingestion pass; the residual stream is updated in their
+    epilogue where neither of the two is split."""
+    plan = (C.c_int32 * 4)()
+    _check(lib().tr_plan_ingestion(n_rows, in_f, out_f, plan), "tr_plan_ingestion")
     return tuple(plan)
 
 

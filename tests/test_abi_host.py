@@ -206,6 +206,52 @@ def test_projections_that_share_operands(lib, projection, in_f, out_f, out_tiles
         assert tr.plan_step_projection(projection, n, in_f, out_f)[3] == 0, n
 
 
+@pytest.mark.parametrize("in_f,heads,kv_heads,splits,split,whole", [
+    # rows for which Q/K/V is taken in shares of k: as many as make 200 to 256 workgroups of 8 out-tiles, and for which it stays whole
+    (8192, 64, 8, 3, (33, 48, 80, 128), (1, 16, 32)), (8192, 40, 8, 4, (33, 49, 65, 128), (1, 32)), (5120, 40, 40, 2, (97, 128), (1, 33, 80)),
+    (5120, 40, 8, 4, (81, 128), (1, 80)), (6144, 48, 8, 4, (81, 128), (33, 80)), (4096, 32, 32, 0, (), (1, 80, 128)),
+    (5152, 40, 40, 2, (113, 128), (80,)), (6144, 48, 48, 0, (), (80, 128)), (8192, 64, 64, 0, (), (33, 128))])
+def test_qkv_in_shares_of_k(lib, in_f, heads, kv_heads, splits, split, whole):
+    tiles = (heads + 2 * kv_heads) * 8
+    for n in split:
+        p, groups, s, kernel = tr.plan_step_qkv(n, in_f, heads, kv_heads)
+        assert (p, groups, s, kernel) == (8, -(-tiles // 8), splits, 1) and 200 <= groups * s <= 256, n
+        per_k = -(-(in_f // 32) // s)
+        assert (s - 1) * per_k < in_f // 32                                       # no share of k is empty
+        assert tr.plan_step_qkv(n, in_f, heads, kv_heads, tiled=False)[2:] == (1, 0), n
+    for n in whole:
+        assert tr.plan_step_qkv(n, in_f, heads, kv_heads) == tr.plan_step_projection("qkv", n, in_f, tiles * 16), n
+        assert tr.plan_step_qkv(n, in_f, heads, kv_heads)[2:] == (1, 0), n
+    assert tr.plan_step_qkv(128, in_f, heads, kv_heads, head_dim=64)[2:] == (1, 0)   # the kernel behind is for head dimension 128
+
+
+def test_step_qkv_plan_rejects_bad_shapes(lib):
+    plan = (C.c_int32 * 4)()
+    f = lib.tr_plan_step_qkv
+    assert f(80, 4096, 32, 32, 128, 1, None) == tr.TR_EINVAL and f(0, 4096, 32, 32, 128, 1, plan) == tr.TR_EINVAL
+    assert f(129, 4096, 32, 32, 128, 1, plan) == tr.TR_EINVAL and f(80, 4100, 32, 32, 128, 1, plan) == tr.TR_EINVAL
+    assert f(80, 4096, 32, 5, 128, 1, plan) == tr.TR_EINVAL and f(80, 4096, 32, 0, 128, 1, plan) == tr.TR_EINVAL
+    assert f(80, 4096, 32, 32, 0, 1, plan) == tr.TR_EINVAL and f(80, 4096, 32, 32, 258, 1, plan) == tr.TR_EINVAL
+    assert f(80, 4096, 32, 32, 128, 2, plan) == tr.TR_EINVAL
+
+
+def test_ingestion_plans_cover_every_tile_and_k_step_once(lib):
+    for n in (129, 144, 300, 512, 513, 700, 1024, 1025, 2047, 2048):
+        for in_f in (64, 256, 4096, 5120, 8192, 28672):
+            for out_f in (32, 1056, 4096, 5120, 6656, 8192):
+                rows, p, groups, splits = tr.plan_ingestion(n, in_f, out_f)
+                assert (rows, p) in ((8, 8), (8, 12), (16, 8), (16, 12), (16, 16))
+                assert groups == -(-(out_f // 16) // p) and 1 <= splits <= 4
+                assert splits * -(-n // 16) * 16 <= 2048                              # room for partial sums
+                assert splits == 1 or (splits - 1) * -(-(in_f // 32) // splits) < in_f // 32
+    plan = (C.c_int32 * 4)()
+    f = lib.tr_plan_ingestion
+    assert f(512, 4096, 4096, None) == tr.TR_EINVAL and f(128, 4096, 4096, plan) == tr.TR_EINVAL
+    assert f(2049, 4096, 4096, plan) == tr.TR_EINVAL and f(512, 32, 4096, plan) == tr.TR_EINVAL
+    assert f(512, 4100, 4096, plan) == tr.TR_EINVAL and f(512, 4096, 4100, plan) == tr.TR_EINVAL
+    assert f(512, 4096, 0, plan) == tr.TR_EINVAL
+
+
 @pytest.mark.parametrize("in_f,out_f,shared,decode", [
     # rows for which o and down share operands in LDS, in four shares of k, and for which they do not: never where a wave of the decode
     # kernel has shorter chains of sums (an eighth of a share, against 16 k-steps), nor where it is the faster one

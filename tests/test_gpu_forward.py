@@ -252,15 +252,22 @@ def test_packed_prefill_cache_matches_oracle(shape_name, plen, small):
     _cache_against_oracle(eng, kv, n)
 
 
-@pytest.mark.parametrize("d,heads,F,plen", [(1056, 2, 480, 150), (4128, 2, 480, 300), (4096, 2, 256, 2049), (6144, 2, 256, 2049),
-                                            (8160, 2, 256, 2001), (1056, 8, 2048, 497), (1056, 8, 2048, 498), (1056, 8, 2048, 540)])
-def test_ingestion_that_updates_the_residual_stream(d, heads, F, plen):
+@pytest.mark.parametrize("d,heads,F,plen,tiles", [
+    (1056, 2, 480, 150, (8, 8)), (4128, 2, 480, 300, (8, 8)), (6560, 2, 480, 522, (8, 12)), (4096, 2, 256, 2049, (16, 8)),
+    (6144, 2, 256, 2049, (16, 12)), (8160, 2, 256, 2001, (16, 16)), (1056, 8, 2048, 497, None), (1056, 8, 2048, 498, None),
+    (1056, 8, 2048, 540, None)])
+def test_ingestion_that_updates_the_residual_stream(d, heads, F, plen, tiles):
     """o and down that are not split over k add to the residual stream in their own epilogue, in every workgroup shape, with out-tiles
     missing in the last workgroup and rows in the last block; with 8 heads they are split, and the residual kernel takes its rows one by
     one up to 31 row tiles and by eights from 32 on.  The second layer's keys and values carry what they leave, the operand and
     the sums of squares.  Gains are powers of two, so that they round nothing."""
     require_gpu()
     say("ingestion with residual epilogue", d, heads, F, plen)
+    plans = [tr.plan_ingestion(plen - 1, in_f, d) for in_f in (heads * 128, F)]             # o and down
+    if tiles is not None:
+        assert all(p[:2] == tiles and p[3] == 1 for p in plans), plans
+    else:
+        assert all(p[3] > 1 for p in plans), plans
     sh = synth.ModelShape("resid", 2, d, heads, 1, 128, F, 512, "bf16")
     w = synth.make_weights(sh, seed=8)
     gen = torch.Generator().manual_seed(d)
@@ -719,9 +726,9 @@ def _uniform(gen, out_f, in_f, std=1.0):
     return torch.empty(out_f, in_f, dtype=torch.bfloat16, device="cuda").uniform_(-s, s, generator=gen)
 
 
-def _feed_forward_step(shape, n, seed, moved=(), **given):
+def _feed_forward_step(shape, n, seed, moved=(), counted=False, **given):
     """One step of one layer whose attention adds nothing (wo = 0); `given` replaces weights, `moved` names those that start off 16
-    bytes.  Returns the engine behind the step, its weights and the embeddings of its tokens in float64."""
+    bytes.  With `counted`, eng.launches holds how often the step launched each kind of kernel.  Returns the engine behind the step, its weights and the embeddings of its tokens in float64."""
     d, F, gen = shape.d_model, shape.d_ffn, torch.Generator("cuda").manual_seed(seed)
     hq, hk = shape.n_heads * shape.head_dim, shape.n_kv_heads * shape.head_dim
     ones = torch.ones(d, dtype=torch.bfloat16, device="cuda")
@@ -738,8 +745,12 @@ def _feed_forward_step(shape, n, seed, moved=(), **given):
     eng.kv.reset(150)
     eng.ctx.matrix_load(np.random.default_rng(n).integers(0, shape.vocab, (shape.vocab, K), dtype=np.int32))
     eng.root.fill_(7)
+    if counted:
+        eng.ctx.profile_enable(True)
     eng.step()
     torch.cuda.synchronize()
+    if counted:
+        eng.launches = {kind: launches for kind, (launches, _) in eng.ctx.profile_read().items()}
     return eng, w, w["embed"][eng.S.long()].double()
 
 
@@ -826,9 +837,11 @@ def test_projections_that_update_the_residual_stream(d, F, groups):
     taken = 0
     for n in (1, 2, 15, 16, 17, 31, 32, 33):
         say("residual epilogue", d, F, n)
-        _, g, splits, kernel = tr.plan_step_projection("o_down", n, F, d)
-        taken += (g, splits, kernel) == (groups, 1, 0) and n <= 32
-        eng, w, xe = _feed_forward_step(shape, n, 6, lm_head=eye, ffn_norm=gains[0], final_norm=gains[1])
+        plans = [tr.plan_step_projection("o_down", n, in_f, d) for in_f in (256, F)]       # o and down
+        fused = [200 <= g <= 256 and (splits, kernel) == (1, 0) and n <= 32 for _, g, splits, kernel in plans]
+        taken += all(fused) and plans[1][1] == groups
+        eng, w, xe = _feed_forward_step(shape, n, 6, counted=True, lm_head=eye, ffn_norm=gains[0], final_norm=gains[1])
+        assert eng.launches.get("residual_norm", 0) == 2 - sum(fused), (n, eng.launches)
         a = xe * gains[0].double() / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
         lw = w["layers"][0]
         gate, up = a @ lw["w_gate"].double().T, a @ lw["w_up"].double().T
@@ -842,9 +855,10 @@ def test_projections_that_update_the_residual_stream(d, F, groups):
     assert taken >= 4
 
 
-@pytest.mark.parametrize("d,heads,kv_heads,nodes", [(8192, 64, 8, (32, 33, 80, 128)), (8192, 40, 8, (49, 64, 65)),
-                                                    (5120, 40, 40, (80, 96, 97, 128)), (5152, 80, 16, (81, 113))])
-def test_qkv_in_shares_of_k(d, heads, kv_heads, nodes):
+@pytest.mark.parametrize("d,heads,kv_heads,nodes,shares", [
+    (8192, 64, 8, (32, 33, 80, 128), (33, 80, 128)), (8192, 40, 8, (49, 64, 65), (49, 64, 65)),
+    (5120, 40, 40, (80, 96, 97, 128), (96, 97, 128)), (5152, 80, 16, (81, 113), (81, 113))])
+def test_qkv_in_shares_of_k(d, heads, kv_heads, nodes, shares):
     """Q/K/V in two, three and four shares of k, and the rows where it stays whole: keys and values of all nodes against float64 (one
     bf16 rounding of at most 2^-9 and float32 sums), the queries through the logits of a step
     against those with a query matrix off 16 bytes, which is never split."""
@@ -853,8 +867,11 @@ def test_qkv_in_shares_of_k(d, heads, kv_heads, nodes):
     wo = _uniform(torch.Generator("cuda").manual_seed(3), d, heads * 128)
     for n in nodes:
         say("qkv in shares", d, heads, kv_heads, n)
-        eng, w, xe = _feed_forward_step(shape, n, 9, wo=wo)
-        whole, _, _ = _feed_forward_step(shape, n, 9, wo=wo, moved=("wq",))
+        split = tr.plan_step_qkv(n, d, heads, kv_heads)[2] > 1
+        eng, w, xe = _feed_forward_step(shape, n, 9, counted=True, wo=wo)
+        whole, _, _ = _feed_forward_step(shape, n, 9, moved=("wq",), counted=True, wo=wo)
+        assert (eng.launches["qkv_proj"], whole.launches["qkv_proj"]) == (1 + split, 1), n
+        assert split == (n in shares), n
         lw, a = w["layers"][0], xe / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
         parent, depth = synth.prefix_template(n).parent, np.zeros(n)
         for i in range(1, n):
