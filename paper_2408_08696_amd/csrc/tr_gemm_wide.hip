@@ -654,14 +654,20 @@ bool rows8_plan(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t 
 // Q/K/V: 8 out-tiles and as many shares of k as fill one round.  Whole, every workgroup of the decode kernel has 3 or 4 out-tiles and all
 // of the activations to load; in shares they load a half or a third of that, and the launch that adds the shares (6.4 us at 80 rows of
 // 70B width) is less than they save from where the activations are many.  us of the launches at 70B width, 80 rows: 48.5 / 35.5 + 6.4.  A
-// step, whole / in shares: 70B width (3 layers) 33 rows 1297 / 1284, 48 1315 / 1290, 64 1321 / 1301, 128 1438 / 1426, 80 rows on 8 layers
-// 3187 / 3151; 13B (10 layers) 64 rows 1509 / 1527, 81 1689 / 1687, 96 1829 / 1814, 100 2022 / 1999, 128 2139 / 2098.  At 7B width its two
-// shares of 96 groups do not fill the chip.  Chains of 16 k-steps, where a wave of the decode kernel has 20 at K = 5120 and 32 at 8192.
+// step on the same buffers, whole / in shares:
+//   three shares   K = 8192 (3 layers) 33 rows 1288 / 1276, 48 1320 / 1311, 64 1350 / 1342, 80 1384 / 1363, 128 1480 / 1443;
+//                  7168 (5) 81 rows 1462 / 1426, 96 1482 / 1450, 128 1655 / 1614
+//   four           8192 (3) 33 rows 848 / 836, 64 906 / 897, 96 1031 / 1006; 5120 (8) 81 rows 1356 / 1326, 128 1545 / 1526; 6144 (6) 96 rows 1285 / 1276
+//   two            5120 (20) 81 rows 3294 / 3337, 96 3388 / 3418, 97 3801 / 3766, (8) 128 rows 1685 / 1653; 7168 (4) 81 rows 1323 / 1301; 8192 (3)
+//                  33 rows 1060 / 1074, 64 1109 / 1123, 80 1164 / 1164, 81 1212 / 1195
+// Three and four shares of K < 8192 and fewer rows were not measured and stay whole.  At 7B width two shares of 96 groups do not
+// fill the chip.  Chains of 16 k-steps, where a wave of the decode kernel has 20 at K = 5120 and 32 at 8192.
 bool qkv_split_plan(int32_t n, int32_t K, int32_t total_tiles, Rows8Plan *plan) {
   const int NT = (n + 15) / 16, g8 = (total_tiles + 7) / 8;
-  if (n > NP || K < 5120 || K % 32 != 0 || NT < (K < 8192 ? 6 : 3)) return false;
+  if (n > NP || K < 5120 || K % 32 != 0) return false;
   for (int sp = 2; sp <= GEMM_MAX_SPLITS; ++sp)
     if (g8 * sp >= 200 && g8 * sp <= 256) {
+      if (NT < (sp == 2 ? (K < 7168 ? 7 : 6) : (K < 8192 ? 6 : 3))) return false;
       *plan = Rows8Plan{8, g8, sp};
       return true;
     }

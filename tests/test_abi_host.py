@@ -208,9 +208,11 @@ def test_projections_that_share_operands(lib, projection, in_f, out_f, out_tiles
 
 @pytest.mark.parametrize("in_f,heads,kv_heads,splits,split,whole", [
     # rows for which Q/K/V is taken in shares of k: as many as make 200 to 256 workgroups of 8 out-tiles, and for which it stays whole
-    (8192, 64, 8, 3, (33, 48, 80, 128), (1, 16, 32)), (8192, 40, 8, 4, (33, 49, 65, 128), (1, 32)), (5120, 40, 40, 2, (97, 128), (1, 33, 80)),
+    (8192, 64, 8, 3, (33, 48, 80, 128), (1, 16, 32)), (8192, 40, 8, 4, (33, 49, 65, 128), (1, 32)), (5120, 40, 40, 2, (97, 128), (1, 33, 80, 81, 96)),
+    # (two shares from one row tile later on than three and four, and with fewer rows never)
+    (7168, 56, 28, 2, (81, 128), (80,)), (8192, 64, 32, 2, (81, 128), (33, 64, 80)), (7168, 56, 8, 3, (81, 128), (80,)),
     (5120, 40, 8, 4, (81, 128), (1, 80)), (6144, 48, 8, 4, (81, 128), (33, 80)), (4096, 32, 32, 0, (), (1, 80, 128)),
-    (5152, 40, 40, 2, (113, 128), (80,)), (6144, 48, 48, 0, (), (80, 128)), (8192, 64, 64, 0, (), (33, 128))])
+    (5152, 40, 40, 2, (97, 128), (80, 81, 96)), (6144, 48, 48, 0, (), (80, 128)), (8192, 64, 64, 0, (), (33, 128))])
 def test_qkv_in_shares_of_k(lib, in_f, heads, kv_heads, splits, split, whole):
     tiles = (heads + 2 * kv_heads) * 8
     for n in split:

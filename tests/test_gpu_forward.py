@@ -857,7 +857,7 @@ def test_projections_that_update_the_residual_stream(d, F, groups):
 
 @pytest.mark.parametrize("d,heads,kv_heads,nodes,shares", [
     (8192, 64, 8, (32, 33, 80, 128), (33, 80, 128)), (8192, 40, 8, (49, 64, 65), (49, 64, 65)),
-    (5120, 40, 40, (80, 96, 97, 128), (96, 97, 128)), (5152, 80, 16, (81, 113), (81, 113))])
+    (5120, 40, 40, (80, 96, 97, 128), (97, 128)), (5152, 80, 16, (81, 97, 113), (97, 113))])
 def test_qkv_in_shares_of_k(d, heads, kv_heads, nodes, shares):
     """Q/K/V in two, three and four shares of k, and the rows where it stays whole: keys and values of all nodes against float64 (one
     bf16 rounding of at most 2^-9 and float32 sums), the queries through the logits of a step
