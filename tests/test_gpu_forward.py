@@ -726,9 +726,10 @@ def _uniform(gen, out_f, in_f, std=1.0):
     return torch.empty(out_f, in_f, dtype=torch.bfloat16, device="cuda").uniform_(-s, s, generator=gen)
 
 
-def _feed_forward_step(shape, n, seed, moved=(), counted=False, **given):
+def _feed_forward_step(shape, n, seed, moved=(), counted=False, past=None, **given):
     """One step of one layer whose attention adds nothing (wo = 0); `given` replaces weights, `moved` names those that start off 16
-    bytes.  With `counted`, eng.launches holds how often the step launched each kind of kernel.  Returns the engine behind the step, its weights and the embeddings of its tokens in float64."""
+    bytes, `past` are the keys and values of the cache (zeros).  With `counted`, eng.launches holds how often the step launched each kind
+    of kernel.  Returns the engine behind the step, its weights and the embeddings of its tokens in float64."""
     d, F, gen = shape.d_model, shape.d_ffn, torch.Generator("cuda").manual_seed(seed)
     hq, hk = shape.n_heads * shape.head_dim, shape.n_kv_heads * shape.head_dim
     ones = torch.ones(d, dtype=torch.bfloat16, device="cuda")
@@ -743,6 +744,8 @@ def _feed_forward_step(shape, n, seed, moved=(), counted=False, **given):
     for m, x in eng.moved.items():
         setattr(eng.model.c if m == "lm_head" else eng.model._layers[0], m, x.data_ptr())
     eng.kv.reset(150)
+    if past is not None:
+        kv_fill(eng.kv, *past, k_interleaved=True)
     eng.ctx.matrix_load(np.random.default_rng(n).integers(0, shape.vocab, (shape.vocab, K), dtype=np.int32))
     eng.root.fill_(7)
     if counted:
@@ -859,36 +862,71 @@ def test_projections_that_update_the_residual_stream(d, F, groups):
     (8192, 64, 8, (32, 33, 80, 128), (33, 80, 128)), (8192, 40, 8, (49, 64, 65), (49, 64, 65)),
     (5120, 40, 40, (80, 96, 97, 128), (97, 128)), (5152, 80, 16, (81, 97, 113), (97, 113))])
 def test_qkv_in_shares_of_k(d, heads, kv_heads, nodes, shares):
-    """Q/K/V in two, three and four shares of k, and the rows where it stays whole: keys and values of all nodes against float64 (one
-    bf16 rounding of at most 2^-9 and float32 sums), the queries through the logits of a step
-    against those with a query matrix off 16 bytes, which is never split."""
+    """Q/K/V in two, three and four shares of k, and the rows where it stays whole or a matrix off 16 bytes keeps it whole: keys and values
+    of all nodes against float64 (one bf16 rounding of at most 2^-9 and float32 sums), the queries through what the attention makes of
+    them.  It runs behind 150 random positions with scores of standard deviation 3, and wo and the LM head hand its output on feature by
+    feature, so that every 32 features of a row are compared with float64 behind queries, keys and values in bf16.  Probabilities, output and
+    stream are rounded by up to 2^-9 each, the first against sum p |v|, up to four times the output: 6 * 2^-9.  The reference with the
+    queries of one row, of one head or of a pair of a head's features left out has to be further away."""
     require_gpu()
-    shape = synth.ModelShape("qkv", 1, d, heads, kv_heads, 128, 256, 512, "bf16")
-    wo = _uniform(torch.Generator("cuda").manual_seed(3), d, heads * 128)
+    hq, P = heads * 128, 150
+    shape = synth.ModelShape("qkv", 1, d, heads, kv_heads, 128, 256, d, "bf16")
+    gen, eye = torch.Generator("cuda").manual_seed(3), torch.eye(d, dtype=torch.bfloat16, device="cuda")
+    f = torch.arange(hq, device="cuda")
+    wo = torch.zeros(d, hq, dtype=torch.bfloat16, device="cuda")            # more heads than features: features f and f + d meet
+    wo[f % d, f] = ((1 + (f // d) / 8) * (1 - 2 * (f // d % 2))).to(torch.bfloat16)
+    given = dict(wo=wo, lm_head=eye, embed=_uniform(gen, d, d, d ** 0.5 / 64), wq=_uniform(gen, hq, d, 3.0),
+                 w_down=torch.zeros(d, 256, dtype=torch.bfloat16, device="cuda"))
+    past = [torch.randn(1, kv_heads, 320, 128, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2)]
     for n in nodes:
         say("qkv in shares", d, heads, kv_heads, n)
-        split = tr.plan_step_qkv(n, d, heads, kv_heads)[2] > 1
-        eng, w, xe = _feed_forward_step(shape, n, 9, counted=True, wo=wo)
-        whole, _, _ = _feed_forward_step(shape, n, 9, moved=("wq",), counted=True, wo=wo)
-        assert (eng.launches["qkv_proj"], whole.launches["qkv_proj"]) == (1 + split, 1), n
-        assert split == (n in shares), n
-        lw, a = w["layers"][0], xe / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
-        parent, depth = synth.prefix_template(n).parent, np.zeros(n)
+        parent, depth, anc = synth.prefix_template(n).parent, np.zeros(n), np.eye(n, dtype=bool)
         for i in range(1, n):
             depth[i] = depth[parent[i]] + 1
-        angle = (150 + torch.from_numpy(depth).cuda())[:, None] * 10000.0 ** (-torch.arange(64, device="cuda").double() / 64)
-        k = (a @ lw["wk"].double().T).view(n, kv_heads, 128)
+            anc[i] |= anc[parent[i]]
+        seen = torch.from_numpy(np.concatenate([np.ones((n, P), bool), anc], 1))
+        angle = (P + torch.from_numpy(depth).cuda())[:, None] * 10000.0 ** (-torch.arange(64, device="cuda").double() / 64)
         cos, sin = angle.cos()[:, None], angle.sin()[:, None]
-        k = torch.cat([k[..., :64] * cos - k[..., 64:] * sin, k[..., 64:] * cos + k[..., :64] * sin], -1)
-        v = (a @ lw["wv"].double().T).view(n, kv_heads, 128)
-        kp, vp = kv_plain_views(eng.kv, k_interleaved=True)
-        moved_rows = int(eng.kv.d_len.item()) - 150                # the accepted nodes lie there now
-        for got, ref in ((kp, k), (vp, v)):
-            got = got[0, :, 150:150 + n].permute(1, 0, 2).double()
-            over = (got - ref).abs() / (2.0 ** -8 * ref.abs() + 1e-5)
-            assert float(over[moved_rows:].max()) < 1.01 and float(over[0].max()) < 1.01, (n, float(over.max()))
-        rel = (eng.logits - whole.logits).norm() / whole.logits.norm()
-        assert float(rel) < 1e-2, (n, float(rel))
+
+        def rotated(x):
+            return torch.cat([x[..., :64] * cos - x[..., 64:] * sin, x[..., 64:] * cos + x[..., :64] * sin], -1)
+
+        split = tr.plan_step_qkv(n, d, heads, kv_heads)[2] > 1
+        assert split == (n in shares), n
+        for moved, launches in (((), 1 + split), (("wq",), 1)):
+            eng, w, xe = _feed_forward_step(shape, n, 9, moved=moved, counted=True, past=past, **given)
+            assert eng.launches["qkv_proj"] == launches, n
+            lw, a = w["layers"][0], xe / (xe.square().mean(1, keepdim=True) + shape.rms_eps).sqrt()
+            q = rotated((a @ lw["wq"].double().T).view(n, heads, 128)).cpu()
+            k = rotated((a @ lw["wk"].double().T).view(n, kv_heads, 128))
+            v = (a @ lw["wv"].double().T).view(n, kv_heads, 128)
+            kp, vp = kv_plain_views(eng.kv, k_interleaved=True)
+            moved_rows = int(eng.kv.d_len.item()) - P                  # the accepted nodes lie there now
+            for got, ref in ((kp, k), (vp, v)):
+                got = got[0, :, P:P + n].permute(1, 0, 2).double()
+                over = (got - ref).abs() / (2.0 ** -8 * ref.abs() + 1e-5)
+                assert float(over[moved_rows:].max()) < 1.01 and float(over[0].max()) < 1.01, (n, float(over.max()))
+            keys, values = (torch.cat([c[0, :, :P], x.permute(1, 0, 2).to(torch.bfloat16)], 1).double().cpu() for c, x in zip(past, (k, v)))
+            got, xe, out = eng.logits.double().cpu(), xe.cpu(), wo.double().cpu()
+
+            def worst(q):
+                """Largest relative error of 32 features of a row, with these queries in the reference."""
+                o = torch.empty(n, heads, 128, dtype=torch.float64)
+                for h in range(heads):
+                    s = (q[:, h].to(torch.bfloat16).double() @ keys[h * kv_heads // heads].T) / 128 ** 0.5
+                    o[:, h] = torch.softmax(s.masked_fill(~seen, -np.inf), 1) @ values[h * kv_heads // heads]
+                ref = xe + o.view(n, hq) @ out.T
+                scale = (got * ref).sum(1) / (ref * ref).sum(1)
+                err, size = ((x.view(n, -1, 32)).norm(dim=2) for x in (got / scale[:, None] - ref, ref))
+                return float((err / size).max())
+
+            error = worst(q)
+            say("largest relative error of 32 features", error)
+            assert error < 6 * 2.0 ** -9, (n, error)
+            for rows, hs, feats in ((n - 1, slice(None), slice(None)), (slice(None), heads - 1, slice(None)), (slice(None), 0, [5, 69])):
+                wrong = q.clone()
+                wrong[rows, hs, feats] = 0
+                assert worst(wrong) > 5e-2, (rows, hs, feats)          # the comparison tells
 
 
 @pytest.mark.parametrize("d,vocab,out_tiles,nodes", [
