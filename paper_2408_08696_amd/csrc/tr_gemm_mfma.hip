@@ -478,9 +478,13 @@ void gemm_choose(int32_t n, int32_t K, int32_t total_tiles, bool swiglu, int32_t
       if (hbm_kib / 6000.0 > t) t = hbm_kib / 6000.0;
       t = rounds * (t + 3.0) + 3.0;
       if (s > 1) t += 2.0 * (s - 1) * NT * total_tiles / 8000.0 + 0.5; // extra KiB of partials written and re-read
-      // the residual kernel, less what its absence costs.  Not two out-tiles for its sake (6432 .. 7744 outputs, o of 17 to 32 rows): us a step
-      // of six layers of 6656 with 17, 20, 32 nodes, o as 4 x 104 x 2 and k_add_frag / as 2 x 208 and fused 1334 / 1379, 1346 / 1384, 1359 / 1366
-      if (feeds_x && !(tpw == 1 && gemm_updates_residual(n, groups, s))) t += 2.5;
+      // What a whole projection that updates the residual stream saves against another plan and k_add_frag.  us a step, the plan without / with it:
+      //   two out-tiles a workgroup (6432 .. 7744 outputs, o of 17 to 32 rows): six layers of 6656, 17, 20, 32 nodes 1334 / 1379, 1346 / 1384, 1359 / 1366
+      //   one, up to 16 rows: 12 layers of 3328, 3456, 3712, 16 nodes 912 / 907, 910 / 892, 1023 / 958; but with 2.5 us instead of 1.5 3200 too, 862 / 867 with one
+      //     node, and down from 18944 features to 3584 (10 layers), 1 and 15 nodes 1087 / 1092, 1106 / 1117
+      //   one, 17 to 32 rows (o): 10 layers of 4096, 17, 24, 32 nodes 1221 / 1199, 1196 / 1178, 1234 / 1213; 12 of 3840 1095 / 1079, 1104 / 1082, 1110 / 1080; but
+      //     fewer workgroups, or waves with unequal numbers of k-steps: 3328 958 / 967, 963 / 975, 973 / 986, 3968 1150 / 1158, 1157 / 1167, 1163 / 1176
+      if (feeds_x && tpw == 1 && gemm_updates_residual(n, groups, s)) t -= NT == 1 ? 1.5 : (groups >= 240 && KT % GEMM_WAVES == 0 ? 2.5 : 0.0);
       if (t < best) {
         best = t;
         bp = p;

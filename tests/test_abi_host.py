@@ -268,12 +268,17 @@ def test_projections_in_shares_of_k(lib, in_f, out_f, shared, decode):
 
 
 def test_whole_o_and_down_of_few_rows(lib):
-    # kept whole so that they update the residual stream themselves: with one out-tile a workgroup, not with two for its sake
+    # kept whole so that they update the residual stream themselves: with one out-tile a workgroup, not with two for its sake ...
     for n in (17, 20, 32):
-        assert tr.plan_step_projection("o_down", n, 4096, 4096) == (1, 256, 1, 0), n
-        assert tr.plan_step_projection("o_down", n, 3200, 3200) == (1, 200, 1, 0), n
+        for d, whole in ((4096, True), (3840, True), (3968, False), (3584, False), (3200, False)):
+            assert (tr.plan_step_projection("o_down", n, d, d)[1:] == (d // 16, 1, 0)) == whole, (n, d)
         for d in (6432, 6656, 7168, 7552):
             assert tr.plan_step_projection("o_down", n, d, d)[2:] == (2, 0), (n, d)
+        # ... and not where shares of many features are that much faster
+    for n in (1, 15, 16):
+        for in_f, d, whole in ((9568, 3584, True), (18944, 3584, False), (9888, 3712, True), (8864, 3328, True), (8640, 3200, False)):
+            assert (tr.plan_step_projection("o_down", n, in_f, d)[1:] == (d // 16, 1, 0)) == whole, (n, in_f, d)
+    for n in (17, 20, 32):
         assert tr.plan_step_projection("o_down", n, 8192, 8192) == (2, 256, 1, 0), n    # the faster plan in any case
 
 
