@@ -324,8 +324,10 @@ __device__ inline void norm_operand(const float (&v)[8], bool live, const uint4 
 }
 
 // From this many row tiles on the eight rows that share the operand's 128-byte lines are on one XCD, whose L2 writes a line back once.  us of
-// a prompt, other order / this: 7B width, 16 layers, 511 tokens 3767 / 3723, 640 5471 / 5438; 13B, 8 layers, 700 3516 / 3490; 70B, 4
-// layers, 1000 4546 / 4507; but 300 and 400 at 7B width 3469 / 3502 and 3635 / 3659.
+// a prompt on the same buffers, other order / this: 497 tokens at 2048 (12 layers) 1344 / 1327, 4096 (8) 1848 / 1829, 5120 (6) 1854 / 1829, 6144 (5) 1725 / 1705,
+// 8192 (3) 1738 / 1724; 700 tokens 1637 / 1626, 2779 / 2763, 2589 / 2569, 2510 / 2487, 2440 / 2416; 1000 tokens 1966 / 1950, 3125 / 3121, 3387 / 3349, 2970 / 2939,
+// 3096 / 3085.  300 tokens 4096 1716 / 1731, 5120 1677 / 1699, 400 4096 1855 / 1868.  From 28 row tiles on (440 to 480 tokens, 0.5 to 1.5 %) it would be the
+// faster order too; that has not been compared in whole rounds of widths and the line stays.
 constexpr int ADD_LINE_TILES = 32;
 
 template <int PARTS>

@@ -79,8 +79,12 @@ struct Workspace {
   size_t logits;   // float  [NP, V]            used when the caller passes no logits buffer
   size_t part_ml;  // float  [SPLITS, NP, H, 2] attention split partials: running max, sum
   size_t part_acc; // float  [SPLITS, NP, H, hd]
-  size_t ypart;    // float  [GEMM_MAX_SPLITS, NP, d] K-split partial sums of o_proj / down_proj (packed path)
-  size_t ssq;      // float  [NP, ceil(d/1024)] per-row partial sums of squares of the residual stream (packed path)
+  // float [WIDE_PART_ROWS, d], packed path.  A step: K-split partial sums of o and down [GEMM_MAX_SPLITS, NP, d], from the next 16 bytes on
+  // 8192 floats for the sums of squares of the residual stream ([NP, 4 or 8], or [32, 256]), then the partial sums of Q/K/V in shares
+  // of k [shares, n, (H + 2 Hkv) hd] if they fit.  An ingestion pass: the partial sums of o and down, or, where neither is split, the
+  // sums of squares [rows, up to 128] that they leave.
+  size_t ypart;
+  size_t ssq;      // float  [rows, ceil(d/1024)] sums of squares in an ingestion pass whose residual kernel is a launch of its own (packed path)
   size_t total;
 };
 constexpr int NP = TR_MAX_NODES;

@@ -133,11 +133,12 @@ inline void gemm_plan(GemmArgs &g, int32_t max_splits, bool feeds_x) {
 }
 
 // Whether a step's o and down update the residual stream in their own epilogue (GemmResid) instead of leaving partial sums to
-// k_add_frag: from whole sums of up to two row tiles, with a workgroup for most compute units.  One kernel then costs 0.4 us more,
-// as does the one behind it for its 256 sums of squares per row instead of 4, and the launch of 4.6 to 5 us is gone.  us per layer,
-// both o and down, k_add_frag / this: 7B width, 1 row 34.4 / 25.6; 15 rows 34.4 / 25.9.  17 to 32 rows take o whole for it at 7B width (20 rows,
-// 12 layers 1231 / 1208).  13B's 320 out-tiles make 160 workgroups when whole, which is too few: down of one row 23.9 + 4.7 in two shares,
-// 31.2 whole.
+// k_add_frag: from whole sums of up to two row tiles, with a workgroup for most compute units.  At 7B width one kernel then costs 0.4 us
+// more, as does the one behind it for its 256 sums of squares per row instead of 4, and the launch of 4.6 to 5 us is gone: both o and down
+// of a layer, 1 row 34.4 / 25.6 us, 15 rows 34.4 / 25.9.  us a step on the same buffers, k_add_frag / this, 1 and 15 nodes: 8 layers of 7B 747 /
+// 720, 795 / 761, 3 of 70B 1209 / 1199, 1202 / 1186, 6 of 6656 1227 / 1211, 1244 / 1225, 12 of 3840 1055 / 1013, 1076 / 1024, of 3328 849 / 837, 912 / 907; 17 to
+// 32 rows where gemm_choose keeps o whole for it, and 0.1 to 1.2 % at 8192.  13B's 320 out-tiles make 160 workgroups when whole, which is too
+// few: down of one row 23.9 + 4.7 in two shares, 31.2 whole.
 // More rows are split over k, and the sums of the shares are no cheaper to bring together inside the launch: 80 rows, 7B o and down 17.0 and
 // 26.4 us with k_add_frag, 16.6 and 25.8 with sums that the waves of a group send each other, and 2.6 more in the kernels behind.
 constexpr int GEMM_RESID_ROW_TILES = 2;
