@@ -304,7 +304,8 @@ tr_status tr_verify_forward(tr_ctx *ctx, const tr_model *model, tr_kv *kv, const
  *   - M[S[i], :] = d_topk[i, :] for ALL N nodes (accepted, rejected and the root); a token that
  *     occurs several times keeps the candidates of its last occurrence (Appendix A.5 "Last",
  *     one of the outcomes the paper's unordered update can produce);
- *   - the path nodes' keys/values move to cache positions L..L+a and *kv->d_len becomes L+a+1.
+ *   - the path nodes' keys/values move to cache positions L..L+a and *kv->d_len becomes L+a+1 (to be read behind
+ *     the call on its stream: while it runs the word may hold more than a length).
  * d_out [device] receives the result.  If h_out is not NULL ([host]) the result is also copied
  * there and the stream is synchronised; kv->len_bound then becomes exact, otherwise it grows
  * by the tree depth.  Errors: TR_EINVAL, TR_ECAPACITY, TR_EHIP.
